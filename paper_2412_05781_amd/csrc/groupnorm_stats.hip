@@ -1,48 +1,137 @@
 // Mean and 1/sqrt(var + eps) per (image, channel group): the statistics that the activation
 // transform needs to apply GroupNorm + SiLU while it loads x (the operators next to the 3x3
 // convolution inside a residual block; the paper's Section "Techniques" argues for keeping such
-// dependent steps local).  Two launches: partial (sum, sum of squares) per slice of a group, fp32
-// per lane and fp64 from the block reduction on; then one lane per group merges the slices.
-// Deterministic (fixed reduction trees, no atomics).  Bound by reading x once from HBM.
+// dependent steps local).  Partial (sum, sum of squares) per slice of a group, fp32 per lane and
+// fp64 from the block reduction on; then one wave per group merges the slices.  Where a group is
+// small enough for one workgroup (NCHW, at most kWholeGroupBytes) that workgroup writes the
+// statistics itself and the second launch is saved.
+// Deterministic (fixed reduction trees, no atomics).  Bound by reading x once from HBM, and for the
+// small tensors of the UNet by the latency of the launches.
 #include "wino_internal.h"
 
 namespace wino {
 
-constexpr int kMaxSplit = 32;
+constexpr int kMaxSplit = 256;
+// A second launch costs 2-3 us and as much again on the host: a group of up to 128 KB is read as fast by one workgroup (fp16, 64
+// groups: 82 KB each 5.4 us against 5.8 in two launches, 128 KB 5.5 against 7.0; 184 KB stay with slices, 6.5 us).
+constexpr size_t kWholeGroupBytes = (size_t)128 << 10;
 
 size_t groupnorm_stats_bytes(int N, int groups) {
     const size_t ng = (size_t)N * groups;
     return ((ng * 2 * sizeof(float) + 255) / 256) * 256 + ng * kMaxSplit * 2 * sizeof(double);
 }
 
-// block reduction of (s, q): fp32 inside a wave (shuffles), fp64 across the four waves
-__device__ __forceinline__ void block_reduce_store(float s, float q, double* dst) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) { s += __shfl_down(s, off, 64); q += __shfl_down(q, off, 64); }
-    __shared__ double ws[4], wq[4];
-    if ((threadIdx.x & 63) == 0) { ws[threadIdx.x >> 6] = (double)s; wq[threadIdx.x >> 6] = (double)q; }
-    __syncthreads();
-    if (threadIdx.x == 0) { dst[0] = ws[0] + ws[1] + ws[2] + ws[3]; dst[1] = wq[0] + wq[1] + wq[2] + wq[3]; }
+__device__ __forceinline__ void write_stats(float* stats, int ng, double s, double q, double inv_count, float eps) {
+    const double mean = s * inv_count;
+    double var = q * inv_count - mean * mean;
+    var = var > 0.0 ? var : 0.0;
+    stats[(size_t)ng * 2 + 0] = (float)mean;
+    stats[(size_t)ng * 2 + 1] = (float)(1.0 / sqrt(var + (double)eps));
 }
 
-// NCHW fast path: a group is one contiguous run of cpg*H*W elements; 16-byte loads.
-template <typename E>
-__global__ void __launch_bounds__(256)
-groupnorm_partial_vec_kernel(const E* __restrict__ x, double* __restrict__ partial, size_t group_elems, int split,
-                             size_t per_slice) {
+// block reduction of (s, q): fp32 inside a wave (shuffles), fp64 across the waves; the total is valid in thread 0
+template <int WAVES>
+__device__ __forceinline__ void block_reduce(float s, float q, double& ts, double& tq) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) { s += __shfl_down(s, off, 64); q += __shfl_down(q, off, 64); }
+    __shared__ double ws[WAVES], wq[WAVES];
+    if ((threadIdx.x & 63) == 0) { ws[threadIdx.x >> 6] = (double)s; wq[threadIdx.x >> 6] = (double)q; }
+    __syncthreads();
+    ts = 0.0; tq = 0.0;
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) { ts += ws[w]; tq += wq[w]; }
+    }
+}
+
+// NCHW fast path: a group is one contiguous run of cpg*H*W elements; 16-byte loads, four in flight per lane
+// (512 channels at 256x256: 18.4 -> 16.2 us = 4.1 TB/s; 320 channels at 128x128, N=2: 11.2 -> 8.6).
+// WHOLE: one workgroup per group (split = 1), which writes the statistics; otherwise one per slice, which writes partial sums.
+template <typename E, int THREADS, bool WHOLE>
+__global__ void __launch_bounds__(THREADS)
+groupnorm_vec_kernel(const E* __restrict__ x, double* __restrict__ partial, float* __restrict__ stats, size_t group_elems, int split,
+                     size_t per_slice, double inv_count, float eps) {
     constexpr int EPC = 16 / (int)sizeof(E);
     const int ng = blockIdx.x, sl = blockIdx.y;
     const E* base = x + (size_t)ng * group_elems;          // groups of all images are laid end to end
     const size_t lo = (size_t)sl * per_slice;
     size_t hi = lo + per_slice; hi = hi < group_elems ? hi : group_elems;
     float s = 0.f, q = 0.f;
-    for (size_t e = lo + (size_t)threadIdx.x * EPC; e < hi; e += 256 * EPC) {
-        const uint4 raw = *reinterpret_cast<const uint4*>(base + e);
-        const E* v = reinterpret_cast<const E*>(&raw);
+    for (size_t e0 = lo + (size_t)threadIdx.x * EPC; e0 < hi; e0 += (size_t)4 * THREADS * EPC) {
+        uint4 raw[4];
 #pragma unroll
-        for (int u = 0; u < EPC; ++u) { const float f = to_f32<E>(v[u]); s += f; q = fmaf(f, f, q); }
+        for (int u = 0; u < 4; ++u) {
+            const size_t e = e0 + (size_t)u * THREADS * EPC;
+            raw[u] = *reinterpret_cast<const uint4*>(base + (e < hi ? e : e0));      // clamped, so that the four loads stay together
+            const uint32_t m = e < hi ? 0xffffffffu : 0u;
+            raw[u].x &= m; raw[u].y &= m; raw[u].z &= m; raw[u].w &= m;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const E* v = reinterpret_cast<const E*>(&raw[u]);
+#pragma unroll
+            for (int i = 0; i < EPC; ++i) { const float f = to_f32<E>(v[i]); s += f; q = fmaf(f, f, q); }
+        }
     }
-    block_reduce_store(s, q, partial + ((size_t)ng * split + sl) * 2);
+    double ts, tq;
+    block_reduce<THREADS / 64>(s, q, ts, tq);
+    if (threadIdx.x == 0) {
+        if (WHOLE) write_stats(stats, ng, ts, tq, inv_count, eps);
+        else { double* dst = partial + ((size_t)ng * split + sl) * 2; dst[0] = ts; dst[1] = tq; }
+    }
+}
+
+// Channel-last, C a multiple of 8: a workgroup reads all channels of a slab of pixels, a lane the same eight channels of every
+// PX-th pixel (16-byte loads that run along the channels).  Lane sums are added per channel over the pixel lanes and then per
+// group in fp64.  Read group by group instead, a group of 10...40 channels is a 20...80-byte piece of every pixel
+// (N=2, 1280 channels at 16x16: 10.7 -> 6.8 us; 512 channels at 256x256: 66 -> 17 us = 3.9 TB/s).
+template <typename E, int THREADS>
+__global__ void __launch_bounds__(THREADS)
+groupnorm_partial_nhwc_vec_kernel(const E* __restrict__ x, double* __restrict__ partial, int C, int HW, int groups, int cpg,
+                                  int split, int pixels_per_slab) {
+    constexpr int EPC = 16 / (int)sizeof(E);
+    __shared__ float ls[THREADS * EPC], lq[THREADS * EPC];
+    const int n = blockIdx.x, sl = blockIdx.y;
+    const int octs = C / EPC, px = THREADS / octs;          // pixel lanes; lanes beyond px * octs are idle
+    const int oct = threadIdx.x % octs, pl = threadIdx.x / octs;
+    float s[EPC], q[EPC];
+#pragma unroll
+    for (int i = 0; i < EPC; ++i) { s[i] = 0.f; q[i] = 0.f; }
+    const int p0 = sl * pixels_per_slab, p1 = min(p0 + pixels_per_slab, HW);
+    if (pl < px) {
+        const E* base = x + (size_t)n * HW * C + (size_t)oct * EPC;
+        for (int p = p0 + pl; p < p1; p += 4 * px) {
+            uint4 raw[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int pu = p + u * px;
+                raw[u] = *reinterpret_cast<const uint4*>(base + (size_t)(pu < p1 ? pu : p) * C);
+                const uint32_t m = pu < p1 ? 0xffffffffu : 0u;
+                raw[u].x &= m; raw[u].y &= m; raw[u].z &= m; raw[u].w &= m;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const E* v = reinterpret_cast<const E*>(&raw[u]);
+#pragma unroll
+                for (int i = 0; i < EPC; ++i) { const float f = to_f32<E>(v[i]); s[i] += f; q[i] = fmaf(f, f, q[i]); }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < EPC; ++i) { ls[pl * C + oct * EPC + i] = s[i]; lq[pl * C + oct * EPC + i] = q[i]; }
+    }
+    __syncthreads();
+    for (int c = threadIdx.x; c < C; c += THREADS) {        // over the pixel lanes, fixed order
+        float a = ls[c], b = lq[c];
+        for (int k = 1; k < px; ++k) { a += ls[k * C + c]; b += lq[k * C + c]; }
+        ls[c] = a; lq[c] = b;                               // only this lane touches column c
+    }
+    __syncthreads();
+    for (int g = threadIdx.x; g < groups; g += THREADS) {
+        double a = 0.0, b = 0.0;
+        for (int j = 0; j < cpg; ++j) { a += (double)ls[g * cpg + j]; b += (double)lq[g * cpg + j]; }
+        double* dst = partial + (((size_t)n * groups + g) * split + sl) * 2;
+        dst[0] = a; dst[1] = b;
+    }
 }
 
 template <typename E, bool NHWC>
@@ -62,20 +151,21 @@ groupnorm_partial_kernel(const E* __restrict__ x, double* __restrict__ partial, 
         const float v = to_f32<E>(x[idx]);
         s += v; q = fmaf(v, v, q);
     }
-    block_reduce_store(s, q, partial + ((size_t)ng * split + sl) * 2);
+    double ts, tq;
+    block_reduce<4>(s, q, ts, tq);
+    if (threadIdx.x == 0) { double* dst = partial + ((size_t)ng * split + sl) * 2; dst[0] = ts; dst[1] = tq; }
 }
 
-__global__ void groupnorm_finalize_kernel(const double* __restrict__ partial, float* __restrict__ stats, int total,
-                                          int split, double inv_count, float eps) {
-    const int ng = blockIdx.x * blockDim.x + threadIdx.x;
-    if (ng >= total) return;
+// One wave per group: the slices are loaded side by side and added in a fixed shuffle tree.
+__global__ void __launch_bounds__(64)
+groupnorm_finalize_kernel(const double* __restrict__ partial, float* __restrict__ stats, int split, double inv_count, float eps) {
+    const int ng = blockIdx.x, lane = threadIdx.x;
+    const double2* src = reinterpret_cast<const double2*>(partial) + (size_t)ng * split;
     double s = 0.0, q = 0.0;
-    for (int i = 0; i < split; ++i) { s += partial[((size_t)ng * split + i) * 2]; q += partial[((size_t)ng * split + i) * 2 + 1]; }
-    const double mean = s * inv_count;
-    double var = q * inv_count - mean * mean;
-    var = var > 0.0 ? var : 0.0;
-    stats[(size_t)ng * 2 + 0] = (float)mean;
-    stats[(size_t)ng * 2 + 1] = (float)(1.0 / sqrt(var + (double)eps));
+    for (int i = lane; i < split; i += 64) { const double2 v = src[i]; s += v.x; q += v.y; }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) { s += __shfl_down(s, off, 64); q += __shfl_down(q, off, 64); }
+    if (lane == 0) write_stats(stats, ng, s, q, inv_count, eps);
 }
 
 hipError_t launch_groupnorm_stats(const void* x, float* stats, int N, int C, int H, int W, int groups, float eps,
@@ -83,27 +173,60 @@ hipError_t launch_groupnorm_stats(const void* x, float* stats, int N, int C, int
     const int cpg = C / groups, HW = H * W, total = N * groups;
     const size_t elems = (size_t)cpg * HW;
     const size_t esz = two_byte(dt) ? 2 : 4, epc = 16 / esz;
-    // slices are whole numbers of block-wide 16-byte loads (256 lanes x 16 bytes)
-    const size_t quantum = 256 * epc;
-    int split = (int)((elems + 2 * quantum - 1) / (2 * quantum));
-    split = split < 1 ? 1 : (split > kMaxSplit ? kMaxSplit : split);
-    size_t per_slice = (elems + split - 1) / split;
-    per_slice = (per_slice + quantum - 1) / quantum * quantum;
+    const double inv_count = 1.0 / (double)elems;
     double* partial = reinterpret_cast<double*>(reinterpret_cast<unsigned char*>(stats) +
                                                 (((size_t)total * 2 * sizeof(float) + 255) / 256) * 256);
+    const bool x16 = (reinterpret_cast<uintptr_t>(x) & 15u) == 0;
+    const bool vec = !nhwc && (elems * esz) % 16 == 0 && x16;
+    if (vec && elems * esz <= kWholeGroupBytes) {
+        (void)with_dtype(dt, [&](auto* tag) {
+            using E = std::remove_pointer_t<decltype(tag)>;
+            hipLaunchKernelGGL((groupnorm_vec_kernel<E, 1024, true>), dim3((unsigned)total, 1), dim3(1024), 0, s,
+                               (const E*)x, partial, stats, elems, 1, elems, inv_count, eps);
+            return hipSuccess;
+        });
+        return hipGetLastError();
+    }
+    // channel-last with whole 16-byte channel octets, all of them within one workgroup's lanes
+    constexpr int NT = 512;
+    if (nhwc && C % (int)epc == 0 && C / (int)epc <= NT && x16) {
+        // about 16 KB per slab, and enough slabs for two rounds of workgroups on large tensors
+        const size_t bytes = (size_t)HW * C * esz;
+        int split = (int)((bytes + (16 << 10) - 1) / (16 << 10));
+        split = split > kMaxSplit ? kMaxSplit : split;
+        split = split > HW ? HW : split;
+        const int pps = (HW + split - 1) / split;
+        split = (HW + pps - 1) / pps;
+        (void)with_dtype(dt, [&](auto* tag) {
+            using E = std::remove_pointer_t<decltype(tag)>;
+            hipLaunchKernelGGL((groupnorm_partial_nhwc_vec_kernel<E, NT>), dim3((unsigned)N, (unsigned)split), dim3(NT), 0, s,
+                               (const E*)x, partial, C, HW, groups, cpg, split, pps);
+            return hipSuccess;
+        });
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(groupnorm_finalize_kernel, dim3((unsigned)total), dim3(64), 0, s, (const double*)partial, stats, split, inv_count, eps);
+        return hipGetLastError();
+    }
+    // slices are whole numbers of block-wide 16-byte loads (256 lanes x 16 bytes), eight of them per slice with 16-byte loads, two with single elements
+    const size_t quantum = 256 * epc;
+    const size_t per = (vec ? 8 : 2) * quantum;
+    const size_t want = (elems + per - 1) / per;
+    const int split0 = want < 1 ? 1 : (want > (size_t)kMaxSplit ? kMaxSplit : (int)want);
+    size_t per_slice = (elems + split0 - 1) / split0;
+    per_slice = (per_slice + quantum - 1) / quantum * quantum;
+    const int split = (int)((elems + per_slice - 1) / per_slice);
     dim3 grid((unsigned)total, (unsigned)split), block(256);
-    const bool vec = !nhwc && (elems * esz) % 16 == 0 && (reinterpret_cast<uintptr_t>(x) & 15u) == 0;
     (void)with_dtype(dt, [&](auto* tag) {
         using E = std::remove_pointer_t<decltype(tag)>;
-        if (vec)       hipLaunchKernelGGL((groupnorm_partial_vec_kernel<E>), grid, block, 0, s, (const E*)x, partial, elems, split, per_slice);
+        if (vec)       hipLaunchKernelGGL((groupnorm_vec_kernel<E, 256, false>), grid, block, 0, s, (const E*)x, partial, stats, elems, split, per_slice, inv_count, eps);
         else if (nhwc) hipLaunchKernelGGL((groupnorm_partial_kernel<E, true>), grid, block, 0, s, (const E*)x, partial, C, HW, groups, cpg, split, per_slice);
         else           hipLaunchKernelGGL((groupnorm_partial_kernel<E, false>), grid, block, 0, s, (const E*)x, partial, C, HW, groups, cpg, split, per_slice);
         return hipSuccess;
     });
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(groupnorm_finalize_kernel, dim3((unsigned)((total + 63) / 64)), dim3(64), 0, s,
-                       (const double*)partial, stats, total, split, 1.0 / (double)elems, eps);
+    hipLaunchKernelGGL(groupnorm_finalize_kernel, dim3((unsigned)total), dim3(64), 0, s, (const double*)partial, stats, split, inv_count, eps);
     return hipGetLastError();
 }
 

@@ -41,6 +41,21 @@ def test_groupnorm_stats(dtype, groups):
             assert np.abs(st[:, :, 1] / rstd - 1).max() <= 5e-6
 
 
+@pytest.mark.parametrize("layout", [B.WINO_NCHW, B.WINO_NHWC])
+@pytest.mark.parametrize("shape", [(2, 64, 37, 53, 32), (1, 8, 256, 256, 8), (1, 8, 256, 264, 8), (2, 16, 300, 300, 2), (1, 320, 9, 7, 32),
+                                   (1, 4104, 3, 3, 8)])
+def test_groupnorm_stats_routes(shape, layout):
+    """One workgroup per group up to 128 KB and slices beyond, channel octets straddling groups, channel counts beyond one
+    workgroup; the sums are fp32 over at most 128 elements per lane and fp64 from there on: a few fp32 roundings."""
+    N, C, H, W, G = shape
+    x = (torch.randn(N, C, H, W, generator=torch.Generator().manual_seed(C + W)) * 0.7 - 0.3).half()
+    xd = (x.permute(0, 2, 3, 1).contiguous() if layout == B.WINO_NHWC else x).to(DEV)
+    st = B.stats_view(B.wino_groupnorm_stats(xd, G, 1e-5, layout), N, G).cpu().numpy().astype(np.float64)
+    mean, rstd = fo.groupnorm_stats(_np(x), G, 1e-5)
+    assert np.abs(st[:, :, 0] - mean).max() <= 2e-6 * (1 + np.abs(mean).max())
+    assert np.abs(st[:, :, 1] / rstd - 1).max() <= 5e-6
+
+
 # the last two have rows long enough for the sliding-window activation kernel (C padded to 64, ragged last step)
 CASES = [(1, 8, 8, 4, 4, 4), (2, 24, 40, 9, 13, 4), (1, 64, 130, 17, 30, 32), (2, 96, 40, 16, 16, 32), (1, 40, 33, 33, 6, 8),
          (2, 60, 8, 7, 216, 4), (1, 128, 6, 5, 108, 32)]
