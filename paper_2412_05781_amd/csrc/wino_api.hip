@@ -87,6 +87,8 @@ int run_chain(const void* x, const wino_filter* w_t, const float* bias, void* y,
     const Workspace ws = workspace_layout(g, w_t->dtype, w_t->variant);
     void* V = workspace;
     float* M = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + ws.v_bytes);
+    if (fewc_conv_ok(g, dt, pre))
+        return launch_fewc_conv(x, w_t->data, bias, y, g, nhwc, pre, post, s) == hipSuccess ? WINO_OK : WINO_ERR_HIP;
     if (launch_input_transform(x, V, g, dt, nhwc, pre, s) != hipSuccess) return WINO_ERR_HIP;
     if (w_t->variant == WINO_FUSED_F2)
         return launch_fused_gemm_output(w_t->data, V, bias, y, g, dt, nhwc, post, -1, s) == hipSuccess ? WINO_OK : WINO_ERR_HIP;

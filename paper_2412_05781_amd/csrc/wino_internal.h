@@ -116,6 +116,12 @@ __device__ __forceinline__ float pre_apply(float x, const PreLane& l, bool in_im
 bool fewk_conv_ok(const void* x, int N, int C, int H, int W, int K, int R, int st, int dt, bool nhwc, int up, bool pre, bool post);
 hipError_t launch_fewk_conv3x3(const void* x, const void* Wr, const float* bias, void* y, int N, int C, int H, int W, int K, bool nhwc, hipStream_t s);
 
+// All three steps in one kernel for F(4x4) in fp32 with few input channels (wino_fewc.hip): whether it applies, and the launch.
+// U as for the F(4x4) chain; no workspace.
+bool fewc_conv_ok(const Geom& g, int dt, const PreOp* pre);
+hipError_t launch_fewc_conv(const void* x, const void* U, const float* bias, void* y, const Geom& g, bool nhwc, const PreOp* pre,
+                            const PostOp* post, hipStream_t s);
+
 // launchers (each enqueues on `s`, returns the launch status)
 hipError_t launch_filter_transform(const void* w, void* U, int K, int C, int Cp, int m, int dt, hipStream_t s);
 hipError_t launch_input_transform(const void* x, void* V, const Geom& g, int dt, bool nhwc, const PreOp* pre, hipStream_t s);

@@ -1,0 +1,61 @@
+"""The one-kernel F(4x4) path for few input channels in fp32 (csrc/wino_fewc.hip), against the fp64 oracle.
+
+Tolerance: relative L2 1e-5 as for every fp32 path (measured 5e-7...8e-7), and element by element the bound of
+tests/parity_util.py, which catches one wrong tile."""
+import os
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import fused_ops as fo
+from paper_2412_05781_amd import binding as B
+from paper_2412_05781_amd import synth
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+import parity_util  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _np(t):
+    return None if t is None else t.float().numpy().astype(np.float64)
+
+
+# tile counts around the 16 of a wave, rows of tiles shorter and longer than 16, sizes off the tile edge, channels around
+# the chunk of 8 and the limit of 16 (17 runs the chain), output channels off 16 and off 4
+CASES = [(1, 4, 320, 64, 64), (2, 9, 33, 5, 7), (1, 1, 1, 1, 1), (3, 16, 18, 4, 60), (1, 8, 16, 68, 68), (2, 15, 21, 9, 66), (1, 17, 16, 8, 64),
+         (1, 5, 20, 6, 130)]
+
+
+@pytest.mark.parametrize("layout", [B.WINO_NCHW, B.WINO_NHWC])
+@pytest.mark.parametrize("post", [False, True])
+@pytest.mark.parametrize("case", CASES)
+def test_few_channels(case, post, layout):
+    N, C, K, H, W = case
+    x, w, b = synth.make_inputs(N, C, K, H, W, "f32", seed=500 + sum(case))
+    g = torch.Generator().manual_seed(sum(case))
+    addvec = torch.randn(N, K, generator=g) if post else None
+    residual = torch.randn(N, K, H, W, generator=g) if post else None
+    perm = (lambda t: t.permute(0, 2, 3, 1).contiguous()) if layout == B.WINO_NHWC else (lambda t: t)
+    dev = lambda t: None if t is None else t.to(DEV)
+    y = B.conv2d_fused(perm(x).to(DEV), w.to(DEV), b.to(DEV), B.WINO_F4, layout, addvec=dev(addvec),
+                       residual=dev(perm(residual)) if post else None)
+    torch.cuda.synchronize()
+    y = y.cpu()
+    y = (y.permute(0, 3, 1, 2) if layout == B.WINO_NHWC else y).numpy().astype(np.float64)
+    ref = fo.conv2d_fused(_np(x), _np(w), _np(b), addvec=_np(addvec), residual=_np(residual))
+    parity_util.check(y, ref, 1e-5, 4, "f32", what=(case, post, layout), channels=C)
+
+
+@pytest.mark.parametrize("layout", [B.WINO_NCHW, B.WINO_NHWC])
+def test_few_channels_upsampled(layout):
+    N, C, K, h, w_ = 2, 6, 20, 9, 17
+    x, w, b = synth.make_inputs(N, C, K, h, w_, "f32", seed=77)
+    up = x.repeat_interleave(2, 2).repeat_interleave(2, 3).contiguous()
+    perm = (lambda t: t.permute(0, 2, 3, 1).contiguous()) if layout == B.WINO_NHWC else (lambda t: t)
+    a = B.conv2d_fused(perm(x).to(DEV), w.to(DEV), b.to(DEV), B.WINO_F4, layout, upsample=True)
+    c = B.conv2d(perm(up).to(DEV), w.to(DEV), b.to(DEV), B.WINO_F4, layout)
+    assert torch.equal(a, c)
