@@ -122,6 +122,12 @@ bool fewc_conv_ok(const Geom& g, int dt, const PreOp* pre);
 hipError_t launch_fewc_conv(const void* x, const void* U, const float* bias, void* y, const Geom& g, bool nhwc, const PreOp* pre,
                             const PostOp* post, hipStream_t s);
 
+// All three steps in one kernel for F(2x2), two-byte storage types (wino_onepass.hip): whether it applies and pays, and the launch.
+// U as for the F(2x2) chain; no workspace.
+bool onepass_conv_ok(const void* x, const Geom& g, int dt, bool nhwc, bool fused_variant, const PreOp* pre);
+hipError_t launch_onepass_conv(const void* x, const void* U, const float* bias, void* y, const Geom& g, int dt, bool nhwc,
+                               const PreOp* pre, const PostOp* post, hipStream_t s);
+
 // launchers (each enqueues on `s`, returns the launch status)
 hipError_t launch_filter_transform(const void* w, void* U, int K, int C, int Cp, int m, int dt, hipStream_t s);
 hipError_t launch_input_transform(const void* x, void* V, const Geom& g, int dt, bool nhwc, const PreOp* pre, hipStream_t s);
