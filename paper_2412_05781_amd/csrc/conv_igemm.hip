@@ -19,20 +19,9 @@
 // even a channel-last input is copied once.  The optional 2x upsampling is pure address arithmetic.
 #include "wino_internal.h"
 #include "wino_mma.h"
+#include "conv_igemm.h"
 
 namespace wino {
-
-struct ConvGeom {
-    int N, C, Cp, H, W, K, R, st, pad, Ho, Wo, T;      // T = N*Ho*Wo output pixels
-    int up, Hs, Ws;                                    // up = 1: x is stored at Hs x Ws = H/2 x W/2 and read upsampled
-};
-// Optional additions in the epilogue (fp32, before the one rounding): a per-(image, channel) vector and a
-// tensor of y's shape and layout.
-struct IgemmPost {
-    const float* addvec = nullptr;    // [N][K]
-    const void* residual = nullptr;   // like y
-    float scale = 1.f;                // the accumulated sum is multiplied by this first (quantised operands: 1 / (sx * sw))
-};
 
 // PIX_A: the pixel operand supplies the rows of the block (outputs [t][k], channel-last y);
 // otherwise the filter does (outputs [k][t], NCHW y).
@@ -256,32 +245,47 @@ conv_igemm_kernel(const E* __restrict__ xh, const E* __restrict__ Wr, const E* _
 
 // Sum of the nsplit partial products (fixed order), bias, one rounding, y in its layout.
 // part is [nsplit][rowsA][rowsB]; PIX_A: (t, k) -> y[t][k]; otherwise (k, t) -> y[n][k][p].
-template <typename E, bool PIX_A>
+// EPL adjacent outputs per lane (4: the contiguous dimension of y is a multiple of four, so they share an image and a channel or pixel).
+// All partial sums of a lane are loaded before the first is added (2048 x 320 outputs in two ranges: 4.6 -> 3.5 us).
+template <typename E, bool PIX_A, int EPL>
 __global__ void __launch_bounds__(256)
 igemm_reduce_kernel(const float* __restrict__ part, const float* __restrict__ bias, E* __restrict__ y,
                     int K, int T, int HoWo, int nsplit, IgemmPost post) {
     const size_t total = (size_t)K * T;
-    const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const size_t e = ((size_t)blockIdx.x * 256 + threadIdx.x) * EPL;
     if (e >= total) return;
-    float acc = 0.f;
-    for (int sp = 0; sp < nsplit; ++sp) acc += part[(size_t)sp * total + e];
-    acc *= post.scale;
-    const E* res = static_cast<const E*>(post.residual);
-    if (PIX_A) {
-        const int k = (int)(e % K), t = (int)(e / K);
-        acc += bias ? bias[k] : 0.f;
-        if (post.addvec) acc += post.addvec[(size_t)(t / HoWo) * K + k];
-        if (res) acc += to_f32<E>(res[e]);
-        y[e] = from_f32<E>(acc);
-    } else {
-        const int t = (int)(e % T), k = (int)(e / T);
-        const int n = t / HoWo, p = t - n * HoWo;
-        const size_t o = ((size_t)n * K + k) * HoWo + p;
-        acc += bias ? bias[k] : 0.f;
-        if (post.addvec) acc += post.addvec[(size_t)n * K + k];
-        if (res) acc += to_f32<E>(res[o]);
-        y[o] = from_f32<E>(acc);
+    float acc[EPL];
+    typedef float vec_t __attribute__((ext_vector_type(EPL)));
+#pragma unroll
+    for (int u = 0; u < EPL; ++u) acc[u] = 0.f;
+    for (int s0 = 0; s0 < nsplit; s0 += 4) {
+        vec_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const vec_t*>(part + (size_t)min(s0 + u, nsplit - 1) * total + e);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (s0 + u < nsplit) {
+#pragma unroll
+                for (int i = 0; i < EPL; ++i) acc[i] += EPL == 1 ? *reinterpret_cast<const float*>(&v[u]) : reinterpret_cast<const float*>(&v[u])[i];
+            }
     }
+    const E* res = static_cast<const E*>(post.residual);
+    const int fast = (int)(e % (PIX_A ? K : T)), slow = (int)(e / (PIX_A ? K : T));
+    const int t = PIX_A ? slow : fast, k = PIX_A ? fast : slow;
+    const int n = t / HoWo, p = t - n * HoWo;
+    const size_t o = PIX_A ? e : ((size_t)n * K + k) * HoWo + p;
+    union { E e[EPL]; unsigned char b[EPL * sizeof(E)]; } out;
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) {
+        const int ki = PIX_A ? k + i : k;
+        float f = acc[i] * post.scale + (bias ? bias[ki] : 0.f);
+        if (post.addvec) f += post.addvec[(size_t)n * K + ki];
+        if (res) f += to_f32<E>(res[o + i]);
+        out.e[i] = from_f32<E>(f);
+    }
+    if constexpr (EPL * sizeof(E) == 8) *reinterpret_cast<uint2*>(y + o) = *reinterpret_cast<const uint2*>(&out);
+    else if constexpr (EPL * sizeof(E) == 16) *reinterpret_cast<uint4*>(y + o) = *reinterpret_cast<const uint4*>(&out);
+    else y[o] = out.e[0];
 }
 
 // w[K][C][R][R] -> Wr[R*R][K][Cp] (channel index contiguous, zero-filled to Cp), followed by one row
@@ -391,6 +395,22 @@ igemm_pad_nhwc_kernel(const E* __restrict__ x, E* __restrict__ xh, size_t pixels
     xh[e] = v;
 }
 
+// the kernel that adds the partial sums of a split reduction
+template <typename EO>
+static hipError_t launch_igemm_reduce(const float* part, const float* bias, EO* y, int nsplit, const ConvGeom& g, const IgemmPost& post, bool nhwc,
+                                      hipStream_t s) {
+    const int run = nhwc ? g.K : g.Ho * g.Wo;              // the contiguous dimension of y
+    const bool quad = run % 4 == 0 && ((reinterpret_cast<uintptr_t>(y) | reinterpret_cast<uintptr_t>(post.residual)) & 15u) == 0;
+    const size_t blocks = ((size_t)g.K * g.T / (quad ? 4 : 1) + 255) / 256;
+    if (blocks > 0x7fffffffULL) return hipErrorInvalidValue;
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, s, part, bias, y, g.K, g.T, g.Ho * g.Wo, nsplit, post);
+        return hipGetLastError();
+    };
+    if (quad) return nhwc ? go(igemm_reduce_kernel<EO, true, 4>) : go(igemm_reduce_kernel<EO, false, 4>);
+    return nhwc ? go(igemm_reduce_kernel<EO, true, 1>) : go(igemm_reduce_kernel<EO, false, 1>);
+}
+
 template <typename E, typename EO, int BM, int BN, int NST, bool PIX_A, int WGM = 2, int WGN = 2>
 static hipError_t launch_igemm_cfg(const E* xh, const E* Wr, const float* bias, EO* y, float* part, int nsplit,
                                    const ConvGeom& g, const IgemmPost& post, hipStream_t s) {
@@ -409,11 +429,7 @@ static hipError_t launch_igemm_cfg(const E* xh, const E* Wr, const float* bias, 
     hipLaunchKernelGGL(kern, dim3((unsigned)(per_xcd * 8)), dim3(WGM * WGN * 64), lds_bytes, s,
                        xh, Wr, zero_row, bias, y, part, g, post, tiles_m, tiles_n, (int)total, per_xcd, nsplit);
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-    if (nsplit > 1) {
-        const size_t blocks = ((size_t)g.K * g.T + 255) / 256;
-        if (blocks > 0x7fffffffULL) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((igemm_reduce_kernel<EO, PIX_A>), dim3((unsigned)blocks), dim3(256), 0, s, part, bias, y, g.K, g.T, g.Ho * g.Wo, nsplit, post);
-    }
+    if (nsplit > 1) return launch_igemm_reduce<EO>(part, bias, y, nsplit, g, post, PIX_A, s);
     return hipGetLastError();
 }
 
@@ -435,7 +451,11 @@ static IgemmShape igemm_shape(int T, int K) {
 // Few blocks and a long reduction (deep down-sampling layers: 8x8 outputs, 9 x 1280 channels): cut the
 // reduction so that about two workgroups per compute unit are in flight, at least eight stages each
 // (the second kernel costs ~3 us, more than a short reduction gains).
-int igemm_split(int T, int K, int Cp, int R, int dt) {
+int igemm_split(int T, int K, int Cp, int R, int dt, bool nhwc) {
+    if (dt >= 0) {
+        const IgemmTilePlan plan = igemm_tile_plan(T, K, Cp, R, dt, nhwc);
+        if (plan.id >= 0) return plan.split;
+    }
     // dt < 0: 8-bit operands, 128 reduction elements per stage
     const bool f16 = two_byte(dt);
     if (dt < 0) Cp = (Cp + 1) / 2;                        // same stage count as 64-element stages over half the channels
@@ -482,7 +502,8 @@ template <typename E>
 static hipError_t igemm_conv_t(const void* x, const void* Wr, const float* bias, void* y, const ConvGeom& g, const IgemmPost& post,
                                const PreOp& pre, bool nhwc, void* workspace, size_t xh_bytes, hipStream_t s) {
     const E* xh = static_cast<const E*>(x);
-    const int nsplit = igemm_split(g.T, g.K, g.Cp, g.R, sizeof(E) == 2 ? DT_F16 : DT_F32);
+    const int dt = std::is_same_v<E, float> ? DT_F32 : (std::is_same_v<E, __half> ? DT_F16 : DT_BF16);
+    const int nsplit = igemm_split(g.T, g.K, g.Cp, g.R, dt, nhwc);
     float* part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + xh_bytes);   // only used when nsplit > 1
     if (!nhwc) {
         constexpr int EPC = 16 / (int)sizeof(E);
@@ -506,6 +527,11 @@ static hipError_t igemm_conv_t(const void* x, const void* Wr, const float* bias,
         hipLaunchKernelGGL(igemm_pad_nhwc_kernel<E>, dim3((unsigned)blocks), dim3(256), 0, s, (const E*)x, (E*)workspace, pixels, (size_t)g.Hs * g.Ws, g.C, g.Cp, pre);
         if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
         xh = static_cast<const E*>(workspace);
+    }
+    const IgemmTilePlan plan = igemm_tile_plan(g.T, g.K, g.Cp, g.R, dt, nhwc);
+    if (plan.id >= 0) {
+        const hipError_t e = launch_igemm_tile(xh, Wr, bias, y, part, plan, g, post, dt, nhwc, s);
+        return e == hipSuccess && plan.split > 1 ? launch_igemm_reduce<E>(part, bias, (E*)y, plan.split, g, post, nhwc, s) : e;
     }
     return nhwc ? launch_igemm_t<E, E, true>(xh, (const E*)Wr, bias, (E*)y, part, nsplit, g, post, s)
                 : launch_igemm_t<E, E, false>(xh, (const E*)Wr, bias, (E*)y, part, nsplit, g, post, s);
@@ -744,7 +770,7 @@ hipError_t launch_igemm_fp8_conv2d(const void* x, const void* Wq, const float* b
                                    (const EO*)x, (uint32_t*)workspace, g.N, g.C, g.Cp, g.Hs, g.Ws, wtiles, sx, pre);
         }
         if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-        const int nsplit = igemm_split(g.T, g.K, g.Cp, g.R, -1);
+        const int nsplit = igemm_split(g.T, g.K, g.Cp, g.R, -1, nhwc);
         float* part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + xq_bytes);
         const fp8_t* xq = static_cast<const fp8_t*>(workspace);
         return nhwc ? launch_igemm_t<fp8_t, EO, true>(xq, (const fp8_t*)Wq, bias, (EO*)y, part, nsplit, g, post, s)

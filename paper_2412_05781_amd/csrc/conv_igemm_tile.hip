@@ -1,0 +1,351 @@
+// Implicit-GEMM convolution, two-byte storage types: same operands and same staging as conv_igemm.hip (128-byte reduction stages,
+// global -> LDS transfers into a ring, XOR-swizzled chunks), but built from 16x16 MFMA tiles with four waves, blocks small enough that
+// two or three workgroups share a compute unit, and the fragments of the next step requested before the current one is multiplied.
+//
+// The layers of a UNet (1x1 shortcuts, stride 2, 8x8 ... 64x64 outputs) are bound by the latency of a stage - transfer, barrier, LDS
+// read, MFMA - and what hides it is another workgroup on the same unit, not a deeper ring (64x64 blocks with 2, 3, 4 and 9 slots: within
+// 3 %).  On large images the 128x128 block reaches 0.95 PFLOP/s (512 channels at 256x256 in 323 us).
+//
+// Rows of the block are the dimension that is contiguous in y - output channels for a channel-last y, pixels for NCHW - because a lane
+// of a 16x16 accumulator holds four consecutive rows: they leave as one 8-byte store.  NCHW images with an odd number of
+// pixels (no such store, nor pairs) keep the channels as rows: 16 lanes then write 16 neighbouring pixels.
+#include "wino_internal.h"
+#include "wino_mma.h"
+#include "conv_igemm.h"
+
+namespace wino {
+
+namespace {
+
+template <typename E> struct Mma16;
+template <> struct Mma16<__half> {
+    static __device__ __forceinline__ void run(const u32x4_t& a, const u32x4_t& b, f32x4_t& c) {
+        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
+    }
+};
+template <> struct Mma16<bf16_t> {
+    static __device__ __forceinline__ void run(const u32x4_t& a, const u32x4_t& b, f32x4_t& c) {
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+    }
+};
+
+template <typename E> __device__ __forceinline__ uint32_t pack2(float a, float b) {
+    const E ea = from_f32<E>(a), eb = from_f32<E>(b);
+    return (uint32_t)*reinterpret_cast<const uint16_t*>(&ea) | ((uint32_t)*reinterpret_cast<const uint16_t*>(&eb) << 16);
+}
+template <typename E> __device__ __forceinline__ float lo16(uint32_t w) { const uint16_t h = (uint16_t)(w & 0xffffu); return to_f32<E>(*reinterpret_cast<const E*>(&h)); }
+template <typename E> __device__ __forceinline__ float hi16(uint32_t w) { const uint16_t h = (uint16_t)(w >> 16); return to_f32<E>(*reinterpret_cast<const E*>(&h)); }
+
+}  // namespace
+
+// BP pixels x BK output channels per workgroup, WP x WK waves.  PIX_A: pixels are the rows (NCHW y), else output channels (channel-last y).
+template <typename E, int BP, int BK, int WP, int WK, int NST, bool PIX_A>
+__global__ void __launch_bounds__(WP * WK * 64)
+conv_igemm_tile_kernel(const E* __restrict__ xh, const E* __restrict__ Wr, const E* __restrict__ zero_row, const float* __restrict__ bias,
+                       E* __restrict__ y, float* __restrict__ part, ConvGeom g, IgemmPost post, int tiles_p, int tiles_k,
+                       int total_blocks, int blocks_per_xcd, int nsplit, int vec_ok, int planes) {
+    constexpr int RB = 128, CPR = RB / 16, BKE = RB / 2;  // stage: bytes, 16-byte chunks and reduction elements per row
+    constexpr int BM = PIX_A ? BP : BK, BN = PIX_A ? BK : BP, WGM = PIX_A ? WP : WK, WGN = PIX_A ? WK : WP;
+    constexpr int ROWS = BM + BN, NW = WP * WK;
+    constexpr int LOADS = ROWS / 8, LPW = (LOADS + NW - 1) / NW;       // 1 KB transfers (8 rows) per stage, and per wave
+    constexpr int WTM = BM / WGM, WTN = BN / WGN, FM = WTM / 16, FN = WTN / 16;
+    constexpr int STAGE_BYTES = ROWS * RB;
+    static_assert(WTM % 16 == 0 && WTN % 16 == 0 && LOADS >= NW, "tile shape");
+    static_assert(NST >= 2 && LPW * (NST - 1) < 64, "ring depth / vmcnt range");
+
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+
+    const int logical = (int)(blockIdx.x % 8) * blocks_per_xcd + (int)(blockIdx.x / 8);   // one contiguous range per XCD
+    if (logical >= total_blocks) return;                        // uniform, before any barrier
+    const int split = logical % nsplit, tile = logical / nsplit;
+    int tp, tk;
+    if (tiles_k <= tiles_p) { tk = tile % tiles_k; tp = tile / tiles_k; }
+    else { tp = tile % tiles_p; tk = tile / tiles_p; }
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WGN, wn = wave % WGN;
+    const int p0 = tp * BP, k0 = tk * BK;
+    const int row_a0 = PIX_A ? p0 : k0, row_b0 = PIX_A ? k0 : p0;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte_t*)lds;
+
+    // Per-lane description of its transfers.  Filter rows: a pointer that advances with the tap.  Pixel rows: the first pixel of the image
+    // and the top-left input coordinate of the output pixel.  Where the transfers do not divide by the waves the last ones
+    // repeat a transfer of the same wave.
+    const int lrow = lane / CPR, lchunk = lane % CPR;
+    const int HoWo = g.Ho * g.Wo;
+    const E* fptr[LPW];
+    int pn[LPW], pi0[LPW], pj0[LPW], chunk_of[LPW];
+    uint32_t dst_of[LPW];
+    bool is_pix[LPW];
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+        int load = wave + NW * i;
+        if (load >= LOADS) load -= NW;
+        const int row = load * 8 + lrow;                    // row inside the stage, A rows first
+        const int chunk = lchunk ^ ((row >> 1) & (CPR - 1));
+        chunk_of[i] = chunk * 8;
+        dst_of[i] = lds0 + (uint32_t)load * 1024u;
+        const bool in_a = load * 8 < BM;
+        is_pix[i] = in_a == PIX_A;                          // wave-uniform: BM is a multiple of 8
+        int gr = in_a ? row_a0 + row : row_b0 + (row - BM);
+        const int lim = is_pix[i] ? g.T : g.K;
+        gr = gr < lim ? gr : lim - 1;                       // rows beyond the end repeat the last one; never stored
+        fptr[i] = Wr + (size_t)gr * g.Cp + chunk_of[i];
+        const int n = gr / HoWo, p = gr - n * HoWo;
+        const int oi = p / g.Wo, oj = p - oi * g.Wo;
+        pn[i] = n * g.Hs * g.Ws; pi0[i] = oi * g.st - g.pad; pj0[i] = oj * g.st - g.pad;
+    }
+
+    const int nkc = g.Cp / BKE;                             // whole stages per tap on this path
+    const int nstage_all = g.R * g.R * nkc;
+    const int q0 = (int)((long long)split * nstage_all / nsplit), q1 = (int)((long long)(split + 1) * nstage_all / nsplit);
+    const int total = q1 - q0;
+
+    int itap = q0 / nkc, ikc = q0 - (q0 / nkc) * nkc;
+    const unsigned char* src[LPW];
+    auto set_tap = [&]() __attribute__((always_inline)) {
+        const int r = itap / g.R, s = itap - r * g.R;
+#pragma unroll
+        for (int i = 0; i < LPW; ++i) {
+            const E* p;
+            if (is_pix[i]) {
+                const int ii = pi0[i] + r, jj = pj0[i] + s;
+                const bool in = ii >= 0 && ii < g.H && jj >= 0 && jj < g.W;
+                p = in ? xh + ((size_t)pn[i] + (size_t)(ii >> g.up) * g.Ws + (jj >> g.up)) * g.Cp + chunk_of[i] : zero_row + chunk_of[i];
+            } else {
+                p = fptr[i] + (size_t)itap * g.K * g.Cp;
+            }
+            src[i] = reinterpret_cast<const unsigned char*>(p + ikc * BKE);
+        }
+    };
+    set_tap();
+    auto issue = [&](int slot) __attribute__((always_inline)) {          // the next stage in order
+#pragma unroll
+        for (int i = 0; i < LPW; ++i) {
+            dma_load_1k_v(src[i], dst_of[i] + (uint32_t)slot * STAGE_BYTES);
+            src[i] += RB;
+        }
+        if (++ikc == nkc) { ikc = 0; if (++itap < g.R * g.R) set_tap(); }
+    };
+
+    f32x4_t acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+    // A stage holds two MFMA steps of 32 reduction elements.  The fragments of a step are requested one step ahead, across the
+    // stage barrier, and waited for explicitly (as in the batched GEMM kernel).
+    constexpr int NREAD = FM + FN;
+    u32x4_t fa[2][FM], fb[2][FN];
+    const int frow = lane & 15, fq = lane >> 4;
+    const int rowA = wm * WTM + frow, rowB = BM + wn * WTN + frow;
+    const uint32_t abase = lds0 + (uint32_t)rowA * RB + (uint32_t)((fq ^ ((rowA >> 1) & (CPR - 1))) << 4);
+    const uint32_t bbase = lds0 + (uint32_t)rowB * RB + (uint32_t)((fq ^ ((rowB >> 1) & (CPR - 1))) << 4);
+    auto read_step = [&](int slot, auto hc) __attribute__((always_inline)) {
+        constexpr int h = decltype(hc)::value;
+        const uint32_t a = (abase + (uint32_t)slot * STAGE_BYTES) ^ (uint32_t)(h * 64), b = (bbase + (uint32_t)slot * STAGE_BYTES) ^ (uint32_t)(h * 64);
+        static_for<FM>([&](auto ic) { constexpr int i = decltype(ic)::value; lds_read16_async<i * 16 * RB>(fa[h][i], a); });
+        static_for<FN>([&](auto jc) { constexpr int j = decltype(jc)::value; lds_read16_async<j * 16 * RB>(fb[h][j], b); });
+    };
+    auto await = [&](auto hc, auto newerc) __attribute__((always_inline)) {
+        constexpr int h = decltype(hc)::value;
+        lds_wait<decltype(newerc)::value>();
+#pragma unroll
+        for (int i = 0; i < FM; ++i) pin(fa[h][i]);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) pin(fb[h][j]);
+    };
+    auto mma = [&](auto hc) __attribute__((always_inline)) {
+        constexpr int h = decltype(hc)::value;
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) Mma16<E>::run(fa[h][i], fb[h][j], acc[i][j]);
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using NR = std::integral_constant<int, NREAD>;
+    static_assert(STAGE_BYTES % 128 == 0 && NREAD <= 15, "swizzle period; lgkmcnt range");
+
+#pragma unroll
+    for (int s = 0; s < NST; ++s)
+        if (s < total) issue(s);
+    if (NST - 1 >= total) wait_vmcnt<0>();
+    else wait_vmcnt<(NST - 1) * LPW>();
+    __syncthreads();
+    read_step(0, I0());
+    int slot = 0;
+    for (int s = 0; s < total - 1; ++s) {
+        const int next = slot + 1 == NST ? 0 : slot + 1;
+        read_step(slot, I1());
+        await(I0(), NR());
+        __builtin_amdgcn_sched_barrier(0);
+        mma(I0());
+        __builtin_amdgcn_sched_barrier(0);
+        if (s + NST >= total) wait_vmcnt<0>();              // stage s+1 has landed
+        else wait_vmcnt<(NST - 2) * LPW>();
+        await(I1(), I0());                                  // this wave has read all of stage s
+        __syncthreads();
+        if (s + NST < total) issue(slot);                   // stage s+NST, into the slot of stage s
+        read_step(next, I0());
+        __builtin_amdgcn_sched_barrier(0);
+        mma(I1());
+        __builtin_amdgcn_sched_barrier(0);
+        slot = next;
+    }
+    read_step(slot, I1());
+    await(I0(), NR());
+    mma(I0());
+    await(I1(), I0());
+    mma(I1());
+
+    // 16x16 accumulator layout: register r of lane l holds row 4*(l/16) + r, column l%16.  Outputs are numbered in y's own
+    // order, [pixel][channel] or [channel][pixel]; partial sums are stored in that order.
+    const int rowsA = PIX_A ? g.T : g.K, rowsB = PIX_A ? g.K : g.T;
+    const bool vec_pair = HoWo % 2 == 0;                    // y and the residual are 16-byte aligned
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+        const int cb = row_b0 + wn * WTN + j * 16 + frow;
+        if (cb >= rowsB) continue;
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+            const int ra = row_a0 + wm * WTM + i * 16 + 4 * fq;          // four rows ra .. ra+3
+            if (ra >= rowsA) continue;
+            f32x4_t v = acc[i][j];
+            if (nsplit > 1) {
+                float* dst = part + (size_t)split * rowsA * rowsB + (size_t)cb * rowsA + ra;
+                if (rowsA % 4 == 0) *reinterpret_cast<f32x4_t*>(dst) = v;
+                else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) if (ra + r < rowsA) dst[r] = v[r];
+                }
+                continue;
+            }
+            if (vec_ok) {                                   // the four outputs are adjacent and 8-byte aligned
+                size_t o;
+                if constexpr (PIX_A) {
+                    const int n = ra / HoWo, k = cb;
+                    o = ((size_t)n * g.K + k) * HoWo + (ra - n * HoWo);
+                    v = v * post.scale + ((bias ? bias[k] : 0.f) + (post.addvec ? post.addvec[(size_t)n * g.K + k] : 0.f));
+                } else {
+                    const int n = cb / HoWo;
+                    o = (size_t)cb * g.K + ra;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        v[r] = v[r] * post.scale + ((bias ? bias[ra + r] : 0.f) + (post.addvec ? post.addvec[(size_t)n * g.K + ra + r] : 0.f));
+                }
+                if (post.residual) {
+                    const uint2 w = *reinterpret_cast<const uint2*>(static_cast<const E*>(post.residual) + o);
+                    v[0] += lo16<E>(w.x); v[1] += hi16<E>(w.x); v[2] += lo16<E>(w.y); v[3] += hi16<E>(w.y);
+                }
+                *reinterpret_cast<uint2*>(y + o) = make_uint2(pack2<E>(v[0], v[1]), pack2<E>(v[2], v[3]));
+            } else if (PIX_A && vec_pair) {                 // an even number of pixels per image: pairs are adjacent and aligned
+#pragma unroll
+                for (int r = 0; r < 4; r += 2) {
+                    const int t = ra + r, k = cb;
+                    if (t >= rowsA) continue;
+                    const int n = t / HoWo;
+                    const size_t o = ((size_t)n * g.K + k) * HoWo + (t - n * HoWo);
+                    const float bb = (bias ? bias[k] : 0.f) + (post.addvec ? post.addvec[(size_t)n * g.K + k] : 0.f);
+                    float f0 = v[r] * post.scale + bb, f1 = v[r + 1] * post.scale + bb;
+                    if (post.residual) {
+                        const uint32_t w = *reinterpret_cast<const uint32_t*>(static_cast<const E*>(post.residual) + o);
+                        f0 += lo16<E>(w); f1 += hi16<E>(w);
+                    }
+                    *reinterpret_cast<uint32_t*>(y + o) = pack2<E>(f0, f1);
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    if (ra + r >= rowsA) continue;
+                    const int t = PIX_A ? ra + r : cb, k = PIX_A ? cb : ra + r;
+                    const int n = t / HoWo;
+                    const size_t o = PIX_A || planes ? ((size_t)n * g.K + k) * HoWo + (t - n * HoWo) : (size_t)t * g.K + k;
+                    float f = v[r] * post.scale + (bias ? bias[k] : 0.f);
+                    if (post.addvec) f += post.addvec[(size_t)n * g.K + k];
+                    if (post.residual) f += to_f32<E>(static_cast<const E*>(post.residual)[o]);
+                    y[o] = from_f32<E>(f);
+                }
+            }
+        }
+    }
+}
+
+template <typename E, int BP, int BK, int WP, int WK, int NST, bool PIX_A>
+static hipError_t launch_tile_cfg(const E* xh, const E* Wr, const float* bias, E* y, float* part, int nsplit, const ConvGeom& g,
+                                  const IgemmPost& post, bool planes, hipStream_t s) {
+    const int tiles_p = (g.T + BP - 1) / BP, tiles_k = (g.K + BK - 1) / BK;
+    const long long total = (long long)tiles_p * tiles_k * nsplit;
+    if (total > 0x3fffffffLL) return hipErrorInvalidValue;
+    const int per_xcd = (int)((total + 7) / 8);
+    constexpr int lds_bytes = (BP + BK) * 128 * NST;
+    static_assert(lds_bytes <= 160 * 1024, "LDS budget");
+    auto kern = conv_igemm_tile_kernel<E, BP, BK, WP, WK, NST, PIX_A>;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    if (attr != hipSuccess) return attr;
+    const E* zero_row = Wr + (size_t)g.R * g.R * g.K * g.Cp;
+    const int run = PIX_A ? g.Ho * g.Wo : g.K;              // the contiguous dimension of y
+    const int vec_ok = run % 4 == 0 && !planes && ((reinterpret_cast<uintptr_t>(y) | reinterpret_cast<uintptr_t>(post.residual)) & 7u) == 0;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(per_xcd * 8)), dim3(WP * WK * 64), lds_bytes, s, xh, Wr, zero_row, bias, y, part, g, post,
+                       tiles_p, tiles_k, (int)total, per_xcd, nsplit, vec_ok, planes ? 1 : 0);
+    return hipGetLastError();
+}
+
+// Blocks on offer, pixels x output channels, with the time of a reduction stage: `alone` where a compute unit holds one workgroup,
+// `each` per workgroup where it holds several (us, measured).  Three workgroups of 64x64 or two of the others share a unit's LDS; rings
+// deeper than that and fewer workgroups were slower on every shape (128x128 with three slots, one workgroup per unit, 1.3x).
+struct TileShape { int bp, bk; double alone, each; };
+static const TileShape kTiles[3] = {{64, 64, 0.27, 0.20}, {64, 80, 0.35, 0.295}, {128, 128, 0.65, 0.57}};
+
+// The block and the number of reduction ranges with the least time by these figures, plus 6 us for launch, start and end and, with a
+// split reduction, 3 us and the traffic of the partial sums for the second kernel.  Measured, channel-last, us, against the kernels of
+// conv_igemm.hip: 1x1 960 -> 320 at 64x64 (N=2) 15.4 / 18.2, 1920 -> 640 at 64x64 36 / 45, stride 2 320 channels at 64x64 18.2 / 22.1, at
+// 97x121 23.8 / 32.7, 512 channels at 256x256 88 / 110, 3x3 128 channels at 256x256 34 / 39, 512 at 256x256 323 / 338.
+// Left to conv_igemm.hip: 256 output channels and 65536 pixels or more channel-last, where its 256x256 block reads x once instead of
+// twice (3x3 256 channels at 512x512 368 / 355, stride 2 103 / 91).
+IgemmTilePlan igemm_tile_plan(int T, int K, int Cp, int R, int dt, bool nhwc) {
+    IgemmTilePlan best{-1, 1};
+    if (!(dt == DT_F16 || dt == DT_BF16) || Cp % 64 != 0) return best;
+    if (nhwc && K == 256 && T >= 65536) return best;
+    const int stages = R * R * (Cp / 64);
+    double cost = 1e300;
+    for (int id = 0; id < 3; ++id) {
+        const TileShape& sh = kTiles[id];
+        const long long blocks = (long long)((T + sh.bp - 1) / sh.bp) * ((K + sh.bk - 1) / sh.bk);
+        for (int sp = 1; sp <= 16 && (sp == 1 || sp * 8 <= stages); ++sp) {
+            const double share = (double)(blocks * sp) / 256.0;            // workgroups per compute unit
+            const double most = (double)((blocks * sp + 255) / 256), n = share < 2.0 ? 0.5 * (share + most) : most;
+            const double stage = n * sh.each > sh.alone ? n * sh.each : sh.alone;
+            double c = 6.0 + (double)((stages + sp - 1) / sp) * stage;
+            if (sp > 1) c += 3.0 + (double)sp * K * T * 8.0 / 3e6;
+            if (c < cost) { cost = c; best = {id, sp}; }
+        }
+    }
+    return best;
+}
+
+template <typename E, bool PIX_A>
+static hipError_t launch_tile_t(const E* xh, const E* Wr, const float* bias, E* y, float* part, const IgemmTilePlan& plan, const ConvGeom& g,
+                                const IgemmPost& post, bool planes, hipStream_t s) {
+    switch (plan.id) {
+        case 0: return launch_tile_cfg<E, 64, 64, 2, 2, 3, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
+        case 1: return launch_tile_cfg<E, 64, 80, 4, 1, 4, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
+        case 2: return launch_tile_cfg<E, 128, 128, 2, 2, 2, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_igemm_tile(const void* xh, const void* Wr, const float* bias, void* y, float* part, const IgemmTilePlan& plan,
+                             const ConvGeom& g, const IgemmPost& post, int dt, bool nhwc, hipStream_t s) {
+    auto run = [&](auto* tag) {
+        using E = std::remove_pointer_t<decltype(tag)>;
+        const bool planes = !nhwc && plan.split == 1 && g.Ho * g.Wo % 2 != 0;
+        return nhwc || planes ? launch_tile_t<E, false>((const E*)xh, (const E*)Wr, bias, (E*)y, part, plan, g, post, planes, s)
+                              : launch_tile_t<E, true>((const E*)xh, (const E*)Wr, bias, (E*)y, part, plan, g, post, false, s);
+    };
+    return dt == DT_F16 ? run(static_cast<__half*>(nullptr)) : run(static_cast<bf16_t*>(nullptr));
+}
+
+}  // namespace wino

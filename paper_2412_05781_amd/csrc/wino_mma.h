@@ -108,6 +108,11 @@ __device__ __forceinline__ void dma_load_1k_s(const void* base, uint32_t lane_of
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :: "s"(lds_addr), "v"(lane_off), "s"(base) : "memory", "m0");
 }
+// Per-lane 64-bit source addresses, wave-uniform LDS byte address.
+__device__ __forceinline__ void dma_load_1k_v(const void* src, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 :: "s"(lds_addr), "v"(src) : "memory", "m0");
+}
 #pragma clang diagnostic pop
 
 // Fragment reads under explicit control.  The read is issued from inline assembly, so the compiler does not track it

@@ -87,6 +87,27 @@ def test_igemm_split_reduction(dtype, shape, R, stride, layout):
     assert err <= (6e-4 if dtype == "f16" else 1e-5), (shape, R, stride, layout, dtype, err)
 
 
+# Cp a whole number of 64-channel stages (the 16x16-tile kernel): every block it has (64x64, 64x80, 128x128), tails in pixels and channels,
+# split reductions, outputs with 4k, 2k and an odd number of pixels, and the shapes left to the other kernels
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("layout", [B.WINO_NCHW, B.WINO_NHWC])
+@pytest.mark.parametrize("shape,R,stride", [((1, 64, 16, 5, 5), 1, 1), ((2, 128, 70, 9, 10), 3, 1), ((2, 192, 320, 64, 63), 1, 1), ((2, 320, 320, 64, 64), 1, 1),
+                                            ((1, 64, 130, 190, 131), 3, 2), ((1, 1280, 72, 9, 6), 3, 2), ((1, 640, 33, 7, 9), 1, 2),
+                                            ((1, 64, 256, 256, 257), 1, 1)])
+def test_igemm_tile_kernel(shape, R, stride, layout, dtype):
+    N, C, K, H, W = shape
+    x, w, b = _inputs(N, C, K, H, W, R, dtype, seed=8800 + sum(shape))
+    ref = oracle.conv2d_general(_np(x), _np(w), _np(b), stride)
+    xd = (x.permute(0, 2, 3, 1).contiguous() if layout == B.WINO_NHWC else x).to(DEV)
+    y = B.conv2d_igemm(xd, w.to(DEV), b.to(DEV), stride, layout)
+    torch.cuda.synchronize()
+    y = y.float().cpu()
+    y = (y.permute(0, 3, 1, 2) if layout == B.WINO_NHWC else y).numpy().astype(np.float64)
+    # only the output is rounded: element-wise half a unit in the last place, plus fp32 sums of up to 11520 products
+    half_ulp = 2.0 ** -11 if dtype == "f16" else 2.0 ** -8
+    assert np.all(np.abs(y - ref) <= 1.001 * half_ulp * np.abs(ref) + 3e-5), np.abs(y - ref).max()
+
+
 def test_igemm_matches_winograd_and_direct_kernels():
     """3x3 / stride 1: the same operator as the Winograd path and the checking kernel."""
     N, C, K, H, W = 1, 48, 56, 20, 24
