@@ -321,7 +321,7 @@ igemm_relayout_nchw_kernel(const E* __restrict__ x, E* __restrict__ xh, int N, i
     for (int k = 0; k < 8; ++k) {
         const int c = c0 + ty + 8 * k, wq = w0 + tx;
         E v = (c < C && wq < W) ? x[(((size_t)n * C + c) * H + h) * W + wq] : from_f32<E>(0.f);
-        if (pre.stats && c < C) v = from_f32<E>(pre_apply(to_f32<E>(v), pre_lane(pre, n, c, C), true));   // SiLU(GroupNorm(x)), rounded once
+        if (pre.stats && c < C) v = from_f32<E>(pre_apply_as<E>(to_f32<E>(v), pre_lane(pre, n, c, C), true));   // SiLU(GroupNorm(x)), rounded once
         tile[ty + 8 * k][tx] = v;
     }
     __syncthreads();
@@ -362,7 +362,7 @@ igemm_relayout_nchw_vec_kernel(const E* __restrict__ x, E* __restrict__ xh, int 
             if (pre.stats) {                                  // SiLU(GroupNorm(x)), rounded once to the storage type
                 const PreLane pl = pre_lane(pre, n, c, C);
 #pragma unroll
-                for (int i = 0; i < EPC; ++i) v.e[i] = from_f32<E>(pre_apply(to_f32<E>(v.e[i]), pl, true));
+                for (int i = 0; i < EPC; ++i) v.e[i] = from_f32<E>(pre_apply_as<E>(to_f32<E>(v.e[i]), pl, true));
             }
         }
         uint32_t* d = tile + cl * PITCHW + ch * 4;
@@ -391,7 +391,7 @@ igemm_pad_nhwc_kernel(const E* __restrict__ x, E* __restrict__ xh, size_t pixels
     const int c = (int)(e % Cp);
     const size_t p = e / Cp;
     E v = c < C ? x[p * C + c] : from_f32<E>(0.f);
-    if (pre.stats && c < C) v = from_f32<E>(pre_apply(to_f32<E>(v), pre_lane(pre, (int)(p / pixels_per_image), c, C), true));
+    if (pre.stats && c < C) v = from_f32<E>(pre_apply_as<E>(to_f32<E>(v), pre_lane(pre, (int)(p / pixels_per_image), c, C), true));
     xh[e] = v;
 }
 

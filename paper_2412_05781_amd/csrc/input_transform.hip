@@ -17,6 +17,43 @@
 
 namespace wino {
 
+// These kernels are bound by the vector ALU and by LDS reads as much as by memory: windows are read from LDS as 32-bit words, shared
+// columns of neighbouring tiles are read, normalised and transformed once, and SiLU takes the hardware's exponential and reciprocal.
+// 512 channels at 256x256 with GroupNorm 87 -> 71 us, 1280 at 16x16 channel-last 9.0 -> 5.7, 320 at 64x64 11.4 -> 10.2.
+//
+// The transforms of NT neighbouring tiles of a tile row for one channel.  get(a, b): element (a, b) of the (m+2) x (m*NT+2) window;
+// put(u, xi, nu, value): position (xi, nu) of tile u.  Columns that two windows share are transformed once.
+template <int M, int NT, typename Get, typename Put>
+__device__ __forceinline__ void transform_tiles(Get&& get, Put&& put) {
+    constexpr int A = M + 2, NC = M * NT + 2;
+    float tmp[A][NC];                                    // tmp[:, b] = B^T d[:, b]
+#pragma unroll
+    for (int b = 0; b < NC; ++b) {
+        float in[A], out[A];
+#pragma unroll
+        for (int a = 0; a < A; ++a) in[a] = get(a, b);
+        bt_1d<M>(in, out);
+#pragma unroll
+        for (int a = 0; a < A; ++a) tmp[a][b] = out[a];
+    }
+#pragma unroll
+    for (int u = 0; u < NT; ++u)
+#pragma unroll
+        for (int xi = 0; xi < A; ++xi) {
+            float out[A];
+            bt_1d<M>(tmp[xi] + M * u, out);              // rows: (B^T d) B = (B^T (B^T d)^T)^T
+#pragma unroll
+            for (int nu = 0; nu < A; ++nu) put(u, xi, nu, out[nu]);
+        }
+}
+
+// element h (0 or 1) of a 32-bit word of storage elements; fp32: the word itself
+template <typename E> __device__ __forceinline__ float unpack(uint32_t w, int h) {
+    if constexpr (sizeof(E) == 4) return __uint_as_float(w);
+    const uint16_t e = (uint16_t)(h ? w >> 16 : w & 0xffffu);
+    return to_f32<E>(*reinterpret_cast<const E*>(&e));
+}
+
 template <int M, typename E, int CB, int TJ, bool PRE>
 __global__ void __launch_bounds__(256)
 input_transform_nchw_kernel(const E* __restrict__ x, E* __restrict__ V,
@@ -26,9 +63,9 @@ input_transform_nchw_kernel(const E* __restrict__ x, E* __restrict__ V,
     // channel stride: odd number of 32-bit words so lanes (= channels) hit distinct banks
     constexpr int RAW = A * PW;
     constexpr int EPW = 4 / (int)sizeof(E);              // elements per 32-bit word
-    constexpr int WORDS = (RAW + EPW - 1) / EPW;
-    constexpr int CS = ((WORDS % 2 == 0) ? WORDS + 1 : WORDS) * EPW;
-    __shared__ E patch[CB * CS];
+    constexpr int CSW = (RAW / EPW) | 1;
+    static_assert(PW % EPW == 0 && M % EPW == 0 && CB == 64, "windows start on a word; lane = channel");
+    __shared__ uint32_t patch[CB * CSW];
 
     const int tid = threadIdx.x;
     int sidx = blockIdx.x;
@@ -40,62 +77,57 @@ input_transform_nchw_kernel(const E* __restrict__ x, E* __restrict__ V,
     const int row0 = M * ti - 1;
     const int col0 = M * tj0 - 1;
 
-    // ---- stage the patch: consecutive lanes walk along W -------------------------------
-    for (int e = tid; e < CB * RAW; e += 256) {
-        const int cc = e / RAW;
-        const int rem = e - cc * RAW;
-        const int a = rem / PW;
-        const int b = rem - a * PW;
-        const int r = row0 + a, q = col0 + b, c = c0 + cc;
-        E v = from_f32<E>(0.f);
-        if (c < C && r >= 0 && r < H && q >= 0 && q < W)
-            v = x[(((size_t)n * C + c) * (H >> pre.up) + (r >> pre.up)) * (W >> pre.up) + (q >> pre.up)];
-        patch[cc * CS + rem] = v;
+    const int cc = tid & 63;
+    const int c = c0 + cc;
+    PreLane pl = {0.f, 0.f, false};
+    if (PRE) pl = pre_lane(pre, n, c, C);
+
+    // ---- stage the patch: a lane owns one patch position and walks the channels, so its address and its bounds test are found once;
+    // consecutive lanes walk along W.  Loads are issued from clamped addresses and masked: all of a lane's are in flight together.
+    // (Element by element over [channel][row][column], each index divided out and tested: 20.2 us against 11.9 for 640 channels, N=2,
+    // 52x78 upsampled.)
+    constexpr int G = 256 / RAW;                         // channels in hand at a time
+    constexpr int LOADS = (CB + G - 1) / G;
+    const int Hs = H >> pre.up, Ws = W >> pre.up;
+    const int rem = tid % RAW, cg = tid / RAW;
+    const int pr = row0 + rem / PW, pq = col0 + rem % PW;
+    const bool in = pr >= 0 && pr < H && pq >= 0 && pq < W;
+    const size_t img = (size_t)Hs * Ws;
+    const E* xp = x + ((size_t)n * C + c0) * img + (size_t)(min(max(pr, 0), H - 1) >> pre.up) * Ws + (min(max(pq, 0), W - 1) >> pre.up);
+    E v[LOADS];
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) v[i] = xp[(size_t)min(cg + G * i, C - 1 - c0) * img];
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+        const int ch = cg + G * i;
+        if (cg < G && ch < CB) reinterpret_cast<E*>(patch + ch * CSW)[rem] = in && c0 + ch < C ? v[i] : from_f32<E>(0.f);
     }
     __syncthreads();
 
     // ---- transform: lane = channel, one tile per wave per iteration ----------------------
-    const int cc = tid % CB;
-    const int c = c0 + cc;
-    constexpr int TILES_PER_ITER = 256 / CB;
+    if (c >= Cp) return;                                 // no barrier follows
     const size_t plane = (size_t)T * Cp;
-    for (int tl = tid / CB; tl < TJ; tl += TILES_PER_ITER) {
+    for (int tl = __builtin_amdgcn_readfirstlane(tid >> 6); tl < TJ; tl += 4) {
         const int tj = tj0 + tl;
-        if (tj >= tw || c >= Cp) continue;
-        const E* p = patch + cc * CS + M * tl;
-        float d[A][A];
-        PreLane pl = {0.f, 0.f, false};
-        if (PRE) pl = pre_lane(pre, n, c, C);
+        if (tj >= tw) break;                             // wave-uniform
+        const uint32_t* p = patch + cc * CSW + M * tl / EPW;
+        uint32_t w[A][A / EPW];
 #pragma unroll
         for (int a = 0; a < A; ++a)
 #pragma unroll
-            for (int b = 0; b < A; ++b) {
-                d[a][b] = to_f32<E>(p[a * PW + b]);
-                if (PRE) {
-                    const int r = M * ti - 1 + a, q = M * tj - 1 + b;
-                    d[a][b] = pre_apply(d[a][b], pl, r >= 0 && r < H && q >= 0 && q < W);
-                }
-            }
-        // columns: tmp[:, b] = B^T d[:, b]
-        float tmp[A][A];
-#pragma unroll
-        for (int b = 0; b < A; ++b) {
-            float in[A], out[A];
-#pragma unroll
-            for (int a = 0; a < A; ++a) in[a] = d[a][b];
-            bt_1d<M>(in, out);
-#pragma unroll
-            for (int a = 0; a < A; ++a) tmp[a][b] = out[a];
-        }
+            for (int b = 0; b < A / EPW; ++b) w[a][b] = p[a * (PW / EPW) + b];
         const size_t t = ((size_t)n * th + ti) * tw + tj;
         E* dst = V + t * Cp + c;
-#pragma unroll
-        for (int xi = 0; xi < A; ++xi) {
-            float out[A];
-            bt_1d<M>(tmp[xi], out);                      // rows: (B^T d) B = (B^T (B^T d)^T)^T
-#pragma unroll
-            for (int nu = 0; nu < A; ++nu) dst[(size_t)(xi * A + nu) * plane] = from_f32<E>(out[nu]);
-        }
+        transform_tiles<M, 1>(
+            [&](int a, int b) __attribute__((always_inline)) {
+                float d = unpack<E>(w[a][b / EPW], b % EPW);
+                if (PRE) {
+                    const int r = M * ti - 1 + a, q = M * tj - 1 + b;
+                    d = pre_apply_as<E>(d, pl, r >= 0 && r < H && q >= 0 && q < W);
+                }
+                return d;
+            },
+            [&](int, int xi, int nu, float o) __attribute__((always_inline)) { dst[(size_t)(xi * A + nu) * plane] = from_f32<E>(o); });
     }
 }
 
@@ -129,6 +161,11 @@ input_transform_nchw_vec_kernel(const E* __restrict__ x, E* __restrict__ V,
     const int tj0 = js * TJ;
     const int row0 = M * ti - 1;
     const int col0 = M * tj0 - EPC;
+    static_assert(CB == 64, "lane = channel");
+    const int cc = tid & 63;                              // of the transform
+    const int c = c0 + cc;
+    PreLane pl = {0.f, 0.f, false};                       // requested here, with the pixels
+    if (PRE) pl = pre_lane(pre, n, c, C);
 
     // 32-bit lane offsets against wave-uniform 64-bit bases keep the address arithmetic off the
     // vector ALU (the transform itself is only ~200 operations per tile and channel).
@@ -174,55 +211,35 @@ input_transform_nchw_vec_kernel(const E* __restrict__ x, E* __restrict__ V,
     __syncthreads();
 
     // one tile per wave per iteration (lane = channel), so the tile index is wave-uniform
-    static_assert(CB == 64, "lane = channel");
-    const int cc = tid & 63;
-    const int c = c0 + cc;
     const size_t plane = (size_t)T * Cp;
-    const E* pch = reinterpret_cast<const E*>(patch + cc * CSW);
+    constexpr int EPW = 4 / (int)sizeof(E);
+    constexpr int W0 = EPC - EPW, NWD = (A - 1 + EPW - 1) / EPW + 1;       // first word of tile 0's window (its last element), words per row
+    if (c >= Cp) return;                                  // no barrier follows
     for (int tl = __builtin_amdgcn_readfirstlane(tid >> 6); tl < TJ; tl += 4) {
         const int tj = tj0 + tl;
         if (tj >= tw) break;                              // wave-uniform
-        const E* p = pch + (EPC - 1) + M * tl;
-        float d[A][A];
-        PreLane pl = {0.f, 0.f, false};
-        if (PRE) pl = pre_lane(pre, n, c, C);
+        const uint32_t* p = patch + cc * CSW + (W0 + M * tl) / EPW;
+        uint32_t w[A][NWD];
 #pragma unroll
         for (int a = 0; a < A; ++a)
 #pragma unroll
-            for (int b = 0; b < A; ++b) {
-                d[a][b] = to_f32<E>(p[a * (NCH * EPC) + b]);
+            for (int b = 0; b < NWD; ++b) w[a][b] = p[a * ROWW + b];
+        const size_t t = ((size_t)n * th + ti) * tw + tj;  // wave-uniform
+        unsigned char* base = reinterpret_cast<unsigned char*>(V + t * Cp);      // wave-uniform; the lane's offset is just c
+        const unsigned coff = (unsigned)c * (unsigned)sizeof(E);
+        const size_t plane_bytes = plane * sizeof(E);
+        transform_tiles<M, 1>(
+            [&](int a, int b) __attribute__((always_inline)) {
+                float d = unpack<E>(w[a][(b + EPW - 1) / EPW], (b + EPW - 1) % EPW);
                 if (PRE) {
                     const int r = M * ti - 1 + a, q = M * tj - 1 + b;
-                    d[a][b] = pre_apply(d[a][b], pl, r >= 0 && r < H && q >= 0 && q < W);
+                    d = pre_apply_as<E>(d, pl, r >= 0 && r < H && q >= 0 && q < W);
                 }
-            }
-        float tmp[A][A];
-#pragma unroll
-        for (int b = 0; b < A; ++b) {
-            float in[A], out[A];
-#pragma unroll
-            for (int a = 0; a < A; ++a) in[a] = d[a][b];
-            bt_1d<M>(in, out);
-#pragma unroll
-            for (int a = 0; a < A; ++a) tmp[a][b] = out[a];
-        }
-        const size_t t = ((size_t)n * th + ti) * tw + tj;  // wave-uniform
-        E* rowp = V + t * Cp;                              // wave-uniform base; lane offset is just c
-        const unsigned coff = (unsigned)c * (unsigned)sizeof(E);
-        if (c < Cp) {
-            unsigned char* pp = reinterpret_cast<unsigned char*>(rowp);     // walks the alpha^2 planes
-            const size_t plane_bytes = plane * sizeof(E);
-#pragma unroll
-            for (int xi = 0; xi < A; ++xi) {
-                float out[A];
-                bt_1d<M>(tmp[xi], out);
-#pragma unroll
-                for (int nu = 0; nu < A; ++nu) {
-                    *reinterpret_cast<E*>(pp + coff) = from_f32<E>(out[nu]);
-                    pp += plane_bytes;
-                }
-            }
-        }
+                return d;
+            },
+            [&](int, int xi, int nu, float o) __attribute__((always_inline)) {
+                *reinterpret_cast<E*>(base + (size_t)(xi * A + nu) * plane_bytes + coff) = from_f32<E>(o);
+            });
     }
 }
 
@@ -247,6 +264,8 @@ input_transform_nchw_slide_kernel(const E* __restrict__ x, E* __restrict__ V,
     static_assert(TJ * M == BODYE && TJ % 4 == 0, "a body is TJ tiles wide, TJ/4 tiles per wave");
     constexpr int ROWW = 32;                             // words per patch row: two bodies
     constexpr int CSW = (A * ROWW) | 1;                  // words per channel, odd: lanes = channels hit distinct banks
+    constexpr int NT = TJ / 4;                           // tiles per wave and step
+    constexpr int NWD = (M * NT + 2 - 1 + EPW - 1) / EPW + 1;      // words per row under their windows, the first from its last element on
     __shared__ uint32_t patch[64 * CSW];
 
     const int tid = threadIdx.x;
@@ -299,7 +318,7 @@ input_transform_nchw_slide_kernel(const E* __restrict__ x, E* __restrict__ V,
     const int c = c0 + cc;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const size_t plane_bytes = (size_t)T * Cp * sizeof(E);
-    const E* pch = reinterpret_cast<const E*>(patch + cc * CSW);
+    const uint32_t* pch = patch + cc * CSW;
     const unsigned coff = (unsigned)c * (unsigned)sizeof(E);
     PreLane pl = {0.f, 0.f, false};
     if (PRE) pl = pre_lane(pre, n, c, C);
@@ -311,48 +330,32 @@ input_transform_nchw_slide_kernel(const E* __restrict__ x, E* __restrict__ V,
     __syncthreads();
     for (int s = s0; s < s1; ++s) {
         if (s + 1 < s1) fetch(s + 1);                     // in flight while this step is transformed
+        // the wave's tiles, neighbours (wave-uniform); moved inside the row as a group, the duplicates write identical values
+        const int tj = min(max(TJ * s - TJ / 2 + wave * NT, 0), tw - NT);
+        const int g0 = M * tj - 1;                        // first window column (global), -1 for the left border
+        const int w0 = (g0 + 1 - EPW) / EPW;              // its word
+        uint32_t w[A][NWD];
 #pragma unroll
-        for (int i = 0; i < TJ / 4; ++i) {
-            int tj = TJ * s - TJ / 2 + wave + 4 * i;
-            tj = min(max(tj, 0), tw - 1);                 // wave-uniform; duplicates write identical values
-            const int g0 = M * tj - 1;                    // first window column (global), -1 for the left border
-            int colofs[A];
+        for (int b = 0; b < NWD; ++b) {
+            const uint32_t* p = pch + ((w0 + b) & (ROWW - 1));
 #pragma unroll
-            for (int b = 0; b < A; ++b) colofs[b] = (g0 + b) & (2 * BODYE - 1);
-            float d[A][A];
-#pragma unroll
-            for (int a = 0; a < A; ++a)
-#pragma unroll
-                for (int b = 0; b < A; ++b) {
-                    d[a][b] = to_f32<E>(pch[a * (ROWW * EPW) + colofs[b]]);
-                    if (PRE) {
-                        const int r = M * ti - 1 + a, q = g0 + b;
-                        d[a][b] = pre_apply(d[a][b], pl, r >= 0 && r < H && q >= 0 && q < W);
-                    }
-                }
-            float tmp[A][A];
-#pragma unroll
-            for (int b = 0; b < A; ++b) {
-                float in[A], out[A];
-#pragma unroll
-                for (int a = 0; a < A; ++a) in[a] = d[a][b];
-                bt_1d<M>(in, out);
-#pragma unroll
-                for (int a = 0; a < A; ++a) tmp[a][b] = out[a];
-            }
-            const size_t t = ((size_t)n * th + ti) * tw + tj;                  // wave-uniform
-            unsigned char* pp = reinterpret_cast<unsigned char*>(V + t * Cp);  // walks the alpha^2 planes
-#pragma unroll
-            for (int xi = 0; xi < A; ++xi) {
-                float out[A];
-                bt_1d<M>(tmp[xi], out);
-#pragma unroll
-                for (int nu = 0; nu < A; ++nu) {
-                    *reinterpret_cast<E*>(pp + coff) = from_f32<E>(out[nu]);
-                    pp += plane_bytes;
-                }
-            }
+            for (int a = 0; a < A; ++a) w[a][b] = p[a * ROWW];
         }
+        const size_t t = ((size_t)n * th + ti) * tw + tj;                      // wave-uniform
+        unsigned char* base = reinterpret_cast<unsigned char*>(V + t * Cp);
+        const size_t row_bytes = (size_t)Cp * sizeof(E);
+        transform_tiles<M, NT>(
+            [&](int a, int b) __attribute__((always_inline)) {
+                float d = unpack<E>(w[a][(b + EPW - 1) / EPW], (b + EPW - 1) % EPW);
+                if (PRE) {
+                    const int r = M * ti - 1 + a, q = g0 + b;
+                    d = pre_apply_as<E>(d, pl, r >= 0 && r < H && q >= 0 && q < W);
+                }
+                return d;
+            },
+            [&](int u, int xi, int nu, float o) __attribute__((always_inline)) {
+                *reinterpret_cast<E*>(base + (size_t)u * row_bytes + (size_t)(xi * A + nu) * plane_bytes + coff) = from_f32<E>(o);
+            });
         if (s + 1 < s1) {
             __syncthreads();                              // everyone is done with body s-1
             stash(s + 1);                                 // overwrites it
@@ -420,7 +423,7 @@ input_transform_nhwc_kernel(const E* __restrict__ x, E* __restrict__ V,
 #pragma unroll
             for (int u = 0; u < CPT; ++u) {
                 d[u][a][b] = to_f32<E>(v.e[u]);
-                if (PRE) d[u][a][b] = pre_apply(d[u][a][b], pl[u], msk != 0u);
+                if (PRE) d[u][a][b] = pre_apply_as<E>(d[u][a][b], pl[u], msk != 0u);
             }
         }
     }

@@ -110,6 +110,14 @@ __device__ __forceinline__ float pre_apply(float x, const PreLane& l, bool in_im
     const float v = fmaf(x, l.sc, l.sh);
     return __fdividef(v, 1.f + __expf(-v));
 }
+// The same for values that are rounded to a two-byte type afterwards: hardware exponential and reciprocal (one unit in the last place
+// of fp32 each) instead of the full division's refinement steps, and a select instead of a branch.  fp32 storage keeps pre_apply.
+template <typename E> __device__ __forceinline__ float pre_apply_as(float x, const PreLane& l, bool in_image) {
+    if constexpr (sizeof(E) == 4) return pre_apply(x, l, in_image);
+    const float v = fmaf(x, l.sc, l.sh);
+    const float r = v * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(v * -1.44269504f));
+    return l.on && in_image ? r : 0.f;
+}
 
 // Direct 3x3 / stride 1 kernel for K <= 4 output channels on large images (fp16, conv_fewk.hip): whether it applies, and the launch.
 // Wr is the tap-major filter of the implicit-GEMM path.

@@ -85,6 +85,26 @@ def test_fused_full_tensor(case, layout, variant, dtype):
     assert err <= TOL[dtype], (case, layout, variant, dtype, err)
 
 
+# edges of the activation kernels: a last step of 2, 6 and 4 of the wave's tile groups (rows of 58, 54 and 20 tiles), a second slab of
+# eight channels, strips of one tile, a single row
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("variant", [B.WINO_F2, B.WINO_F4])
+@pytest.mark.parametrize("case", [(1, 64, 8, 6, 232, 32), (1, 64, 8, 3, 216, 32), (1, 64, 8, 6, 40, 32), (2, 72, 8, 5, 18, 8), (1, 72, 8, 6, 24, 8),
+                                  (2, 65, 8, 1, 17, 5)])
+def test_activation_windows(case, variant, dtype):
+    N, C, K, H, W, G = case
+    x, w, b = synth.make_inputs(N, C, K, H, W, dtype, seed=3100 + sum(case))
+    gamma, beta, _, _ = _extras(N, C, K, H, W, dtype, 78 + sum(case))
+    for gn in (False, True):
+        ga, be = (gamma, beta) if gn else (None, None)
+        ref = fo.conv2d_fused(_np(x), _np(w), _np(b), _np(ga), _np(be), G)
+        y = B.conv2d_fused(x.to(DEV), w.to(DEV), b.to(DEV), variant, B.WINO_NCHW, None if ga is None else ga.to(DEV),
+                           None if be is None else be.to(DEV), G)
+        err = oracle.rel_l2(y.float().cpu().numpy(), ref)
+        # bf16 carries three bits less than fp16, F(4x4) near 2.5e-2
+        assert err <= (TOL[dtype] if dtype != "bf16" else 4e-2), (case, variant, dtype, gn, err)
+
+
 def test_each_part_alone_and_in_place_residual():
     N, C, K, H, W, G = 2, 32, 32, 12, 12, 8
     x, w, b = synth.make_inputs(N, C, K, H, W, "f16", seed=11)
