@@ -1,6 +1,7 @@
 // Declarations shared by the implicit-GEMM convolution sources (conv_igemm.hip, conv_igemm_tile.hip).
 #pragma once
 #include "wino_internal.h"
+#include "wino_mma.h"
 
 namespace wino {
 
@@ -22,5 +23,79 @@ struct IgemmTilePlan { int id, split; };
 IgemmTilePlan igemm_tile_plan(int T, int K, int Cp, int R, int dt, bool nhwc);
 hipError_t launch_igemm_tile(const void* xh, const void* Wr, const float* bias, void* y, float* part, const IgemmTilePlan& plan,
                              const ConvGeom& g, const IgemmPost& post, int dt, bool nhwc, hipStream_t s);
+
+// Shared by the kernels with two-byte outputs whose block rows are the contiguous dimension of y: four consecutive rows ra .. ra+3 of
+// column cb.  PIX_A: rows are pixels (NCHW y), else output channels (channel-last y; `planes`: an NCHW y with an odd number of pixels,
+// whose outputs are stored one by one).  Additions in fp32, one rounding.
+template <typename E> __device__ __forceinline__ uint32_t pack2(float a, float b) {
+    const E ea = from_f32<E>(a), eb = from_f32<E>(b);
+    return (uint32_t)*reinterpret_cast<const uint16_t*>(&ea) | ((uint32_t)*reinterpret_cast<const uint16_t*>(&eb) << 16);
+}
+template <typename E> __device__ __forceinline__ float lo16(uint32_t w) { const uint16_t h = (uint16_t)(w & 0xffffu); return to_f32<E>(*reinterpret_cast<const E*>(&h)); }
+template <typename E> __device__ __forceinline__ float hi16(uint32_t w) { const uint16_t h = (uint16_t)(w >> 16); return to_f32<E>(*reinterpret_cast<const E*>(&h)); }
+
+template <typename E, bool PIX_A>
+__device__ __forceinline__ void igemm_store4(f32x4_t v, int ra, int cb, E* __restrict__ y, const float* __restrict__ bias, const ConvGeom& g,
+                                             const IgemmPost& post, int vec_ok, int planes) {
+    const int howo = g.Ho * g.Wo, rows_a = PIX_A ? g.T : g.K;
+    if (ra >= rows_a || cb >= (PIX_A ? g.K : g.T)) return;
+    if (vec_ok) {                                   // the four outputs are adjacent and 8-byte aligned
+        size_t o;
+        if constexpr (PIX_A) {
+            const int n = ra / howo, k = cb;
+            o = ((size_t)n * g.K + k) * howo + (ra - n * howo);
+            v = v * post.scale + ((bias ? bias[k] : 0.f) + (post.addvec ? post.addvec[(size_t)n * g.K + k] : 0.f));
+        } else {
+            const int n = post.addvec ? cb / howo : 0;
+            o = (size_t)cb * g.K + ra;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                v[r] = v[r] * post.scale + ((bias ? bias[ra + r] : 0.f) + (post.addvec ? post.addvec[(size_t)n * g.K + ra + r] : 0.f));
+        }
+        if (post.residual) {
+            const uint2 w = *reinterpret_cast<const uint2*>(static_cast<const E*>(post.residual) + o);
+            v[0] += lo16<E>(w.x); v[1] += hi16<E>(w.x); v[2] += lo16<E>(w.y); v[3] += hi16<E>(w.y);
+        }
+        *reinterpret_cast<uint2*>(y + o) = make_uint2(pack2<E>(v[0], v[1]), pack2<E>(v[2], v[3]));
+    } else if (PIX_A && howo % 2 == 0) {                 // an even number of pixels per image: pairs are adjacent and aligned
+#pragma unroll
+        for (int r = 0; r < 4; r += 2) {
+            const int t = ra + r, k = cb;
+            if (t >= rows_a) continue;
+            const int n = t / howo;
+            const size_t o = ((size_t)n * g.K + k) * howo + (t - n * howo);
+            const float bb = (bias ? bias[k] : 0.f) + (post.addvec ? post.addvec[(size_t)n * g.K + k] : 0.f);
+            float f0 = v[r] * post.scale + bb, f1 = v[r + 1] * post.scale + bb;
+            if (post.residual) {
+                const uint32_t w = *reinterpret_cast<const uint32_t*>(static_cast<const E*>(post.residual) + o);
+                f0 += lo16<E>(w); f1 += hi16<E>(w);
+            }
+            *reinterpret_cast<uint32_t*>(y + o) = pack2<E>(f0, f1);
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (ra + r >= rows_a) continue;
+            const int t = PIX_A ? ra + r : cb, k = PIX_A ? cb : ra + r;
+            const int n = t / howo;
+            const size_t o = PIX_A || planes ? ((size_t)n * g.K + k) * howo + (t - n * howo) : (size_t)t * g.K + k;
+            float f = v[r] * post.scale + (bias ? bias[k] : 0.f);
+            if (post.addvec) f += post.addvec[(size_t)n * g.K + k];
+            if (post.residual) f += to_f32<E>(static_cast<const E*>(post.residual)[o]);
+            y[o] = from_f32<E>(f);
+        }
+    }
+}
+
+// four adjacent outputs share an image and are 8-byte aligned
+template <bool PIX_A, typename E> inline int igemm_vec_ok(const ConvGeom& g, const E* y, const IgemmPost& post, bool planes) {
+    const int run = PIX_A ? g.Ho * g.Wo : g.K;            // the contiguous dimension of y
+    return run % 4 == 0 && !planes && ((reinterpret_cast<uintptr_t>(y) | reinterpret_cast<uintptr_t>(post.residual)) & 7u) == 0;
+}
+
+// The kernel for 8-bit operands (conv_igemm_fp8.hip), two-byte y: whether it applies, and the launch.
+bool igemm_fp8_tile_ok(const ConvGeom& g, int dt, bool nhwc, int nsplit);
+hipError_t launch_igemm_fp8_tile(const void* xq, const void* Wq, const float* bias, void* y, const ConvGeom& g, const IgemmPost& post, int dt,
+                                 bool nhwc, hipStream_t s);
 
 }  // namespace wino

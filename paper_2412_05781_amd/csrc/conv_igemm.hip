@@ -667,55 +667,62 @@ igemm_quant_nchw_kernel(const E* __restrict__ x, uint32_t* __restrict__ xq, int 
     }
 }
 
-// The same with 16-byte accesses on both sides, for rows of whole 16-byte chunks: a tile of 64 channels x TW pixels;
-// a lane quantises one chunk along w into LDS bytes and later writes 16 adjacent channels of one pixel.
-template <typename E>
+// The same with 16-byte accesses on both sides, for planes of whole 16-byte chunks (rows play no part): a tile of 64 channels x TP
+// pixels.  All loads of a lane are in flight together; codes go to LDS four pixels to a word, and a lane then takes 4 pixels x 16
+// channels as sixteen words, transposes them with byte permutes and writes 16 channels of each pixel.  (One byte at a time out of LDS,
+// two loads per lane and tile, 256 channels at 512x512: 56 us against 43.)
+template <typename E, int TP>
 __global__ void __launch_bounds__(256)
-igemm_quant_nchw_vec_kernel(const E* __restrict__ x, uint4* __restrict__ xq, int N, int C, int Cq, int H, int W, int wtiles,
-                            float sx, PreOp pre) {
-    constexpr int EPC = 16 / (int)sizeof(E);
-    constexpr int TW = 8 * EPC;                            // pixels per tile
-    constexpr int PITCH = TW + 4;                          // bytes per channel row (a multiple of 4, an odd number of words)
-    __shared__ __attribute__((aligned(16))) uint8_t tile[64 * PITCH];
-    int b = blockIdx.x;
-    const int wt = b % wtiles; b /= wtiles;
-    const int h = b % H; const int n = b / H;
-    const int c0 = blockIdx.y * 64, w0 = wt * TW;
+igemm_quant_nchw_vec_kernel(const E* __restrict__ x, uint4* __restrict__ xq, int C, int Cq, int P, int ptiles, float sx, PreOp pre) {
+    constexpr int EPC = 16 / (int)sizeof(E), CHUNKS = TP / EPC;
+    constexpr int LOADS = 64 * CHUNKS / 256;
+    __shared__ uint32_t tile[64][TP / 4 + 1];
+    const int n = blockIdx.x / ptiles, p0 = (blockIdx.x % ptiles) * TP;
+    const int c0 = blockIdx.y * 64, tid = threadIdx.x;
+    union chunk_t { uint4 q; E e[EPC]; };
+    chunk_t v[LOADS];
+    PreLane pl[LOADS];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const int item = threadIdx.x + 256 * k;            // 64 channels x 8 chunks
-        const int cl = item >> 3, ch = item & 7;
-        const int c = c0 + cl, wq = w0 + ch * EPC;
+    for (int k = 0; k < LOADS; ++k) {
+        const int item = tid + 256 * k;
+        const int c = min(c0 + item / CHUNKS, C - 1), p = min(p0 + item % CHUNKS * EPC, P - EPC);
+        v[k].q = *reinterpret_cast<const uint4*>(x + ((size_t)n * C + c) * P + p);
+        pl[k] = PreLane{0.f, 0.f, false};
+        if (pre.stats) pl[k] = pre_lane(pre, n, c, C);
+    }
+#pragma unroll
+    for (int k = 0; k < LOADS; ++k) {
+        const int item = tid + 256 * k;
+        const int cl = item / CHUNKS, ch = item % CHUNKS;
         uint32_t out[EPC / 4];
 #pragma unroll
         for (int i = 0; i < EPC / 4; ++i) out[i] = 0u;
-        if (c < C && wq < W) {
-            union { uint4 q; E e[EPC]; } v;
-            v.q = *reinterpret_cast<const uint4*>(x + (((size_t)n * C + c) * H + h) * W + wq);
-            PreLane pl = {0.f, 0.f, false};
-            if (pre.stats) pl = pre_lane(pre, n, c, C);
 #pragma unroll
-            for (int i = 0; i < EPC; ++i) {
-                float f = to_f32<E>(v.e[i]);
-                if (pre.stats) f = pre_apply(f, pl, true);
-                out[i >> 2] |= quant_e4m3(f * sx) << (8 * (i & 3));
-            }
+        for (int i = 0; i < EPC; ++i) {
+            float f = to_f32<E>(v[k].e[i]);
+            if (pre.stats) f = pre_apply(f, pl[k], true);
+            out[i >> 2] |= quant_e4m3(f * sx) << (8 * (i & 3));
         }
-        uint32_t* d = reinterpret_cast<uint32_t*>(tile + cl * PITCH + ch * EPC);
 #pragma unroll
-        for (int i = 0; i < EPC / 4; ++i) d[i] = out[i];
+        for (int i = 0; i < EPC / 4; ++i) tile[cl][ch * (EPC / 4) + i] = c0 + cl < C ? out[i] : 0u;
     }
     __syncthreads();
-    // out: TW pixels x 4 groups of 16 channels
-    for (int item = threadIdx.x; item < TW * 4; item += 256) {
-        const int wl = item % TW, cg = item / TW;
-        const int wq = w0 + wl, c = c0 + cg * 16;
-        if (wq >= W || c >= Cq) continue;
-        uint32_t o[4] = {0u, 0u, 0u, 0u};
+    if (tid >= TP) return;                                 // TP / 4 pixel quads x 4 groups of 16 channels
+    const int cg = tid & 3, pq = tid >> 2;
+    const int p = p0 + 4 * pq, c = c0 + 16 * cg;
+    if (p >= P || c >= Cq) return;                         // P is a multiple of four, Cq of sixteen
+    uint32_t o[4][4];                                      // [pixel][word]
 #pragma unroll
-        for (int i = 0; i < 16; ++i) o[i >> 2] |= (uint32_t)tile[(cg * 16 + i) * PITCH + wl] << (8 * (i & 3));
-        xq[((((size_t)n * H + h) * W + wq) * Cq + c) / 16] = make_uint4(o[0], o[1], o[2], o[3]);
+    for (int g = 0; g < 4; ++g) {
+        const uint32_t w0 = tile[16 * cg + 4 * g][pq], w1 = tile[16 * cg + 4 * g + 1][pq];
+        const uint32_t w2 = tile[16 * cg + 4 * g + 2][pq], w3 = tile[16 * cg + 4 * g + 3][pq];
+        const uint32_t a = __builtin_amdgcn_perm(w1, w0, 0x05010400u), b = __builtin_amdgcn_perm(w3, w2, 0x05010400u);
+        const uint32_t e = __builtin_amdgcn_perm(w1, w0, 0x07030602u), f = __builtin_amdgcn_perm(w3, w2, 0x07030602u);
+        o[0][g] = __builtin_amdgcn_perm(b, a, 0x05040100u); o[1][g] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+        o[2][g] = __builtin_amdgcn_perm(f, e, 0x05040100u); o[3][g] = __builtin_amdgcn_perm(f, e, 0x07060302u);
     }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) xq[(((size_t)n * P + p + j) * Cq + c) / 16] = make_uint4(o[j][0], o[j][1], o[j][2], o[j][3]);
 }
 
 hipError_t launch_igemm_fp8_filter_quant(const void* w, void* Wq, int K, int C, int R, int dt, float sw, hipStream_t s) {
@@ -757,22 +764,27 @@ hipError_t launch_igemm_fp8_conv2d(const void* x, const void* Wq, const float* b
                                pixels, (size_t)g.Hs * g.Ws, g.C, g.Cp, sx, pre);
         } else {
             constexpr int EPC = 16 / (int)sizeof(EO);
-            const bool chunks = g.Ws % EPC == 0;            // x is 16-byte aligned, so every row then is
-            const int tw = chunks ? 8 * EPC : 32;
-            const int wtiles = (g.Ws + tw - 1) / tw;
-            const long long bx = (long long)g.N * g.Hs * wtiles;
-            if (bx > 0x7fffffffLL || (g.Cp + 63) / 64 > 65535) return hipErrorInvalidValue;
-            if (chunks)
-                hipLaunchKernelGGL(igemm_quant_nchw_vec_kernel<EO>, dim3((unsigned)bx, (unsigned)((g.Cp + 63) / 64)), dim3(256), 0, s,
-                                   (const EO*)x, (uint4*)workspace, g.N, g.C, g.Cp, g.Hs, g.Ws, wtiles, sx, pre);
+            const bool chunks = g.Ws % EPC == 0;            // x is 16-byte aligned, so every row and plane then is
+            const int P = g.Hs * g.Ws, cb = (g.Cp + 63) / 64;
+            // 256 pixels per workgroup, 64 where that would leave compute units idle
+            const int tp = (long long)g.N * ((P + 255) / 256) * cb >= 1024 ? 256 : 64;
+            const int wtiles = chunks ? (P + tp - 1) / tp : (g.Ws + 31) / 32;
+            const long long bx = chunks ? (long long)g.N * wtiles : (long long)g.N * g.Hs * wtiles;
+            if (bx > 0x7fffffffLL || cb > 65535) return hipErrorInvalidValue;
+            const dim3 grid((unsigned)bx, (unsigned)cb);
+            if (chunks && tp == 256)
+                hipLaunchKernelGGL((igemm_quant_nchw_vec_kernel<EO, 256>), grid, dim3(256), 0, s, (const EO*)x, (uint4*)workspace, g.C, g.Cp, P, wtiles, sx, pre);
+            else if (chunks)
+                hipLaunchKernelGGL((igemm_quant_nchw_vec_kernel<EO, 64>), grid, dim3(256), 0, s, (const EO*)x, (uint4*)workspace, g.C, g.Cp, P, wtiles, sx, pre);
             else
-                hipLaunchKernelGGL(igemm_quant_nchw_kernel<EO>, dim3((unsigned)bx, (unsigned)((g.Cp + 63) / 64)), dim3(256), 0, s,
+                hipLaunchKernelGGL(igemm_quant_nchw_kernel<EO>, grid, dim3(256), 0, s,
                                    (const EO*)x, (uint32_t*)workspace, g.N, g.C, g.Cp, g.Hs, g.Ws, wtiles, sx, pre);
         }
         if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
         const int nsplit = igemm_split(g.T, g.K, g.Cp, g.R, -1, nhwc);
         float* part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + xq_bytes);
         const fp8_t* xq = static_cast<const fp8_t*>(workspace);
+        if (igemm_fp8_tile_ok(g, dt, nhwc, nsplit)) return launch_igemm_fp8_tile(xq, Wq, bias, y, g, post, dt, nhwc, s);
         return nhwc ? launch_igemm_t<fp8_t, EO, true>(xq, (const fp8_t*)Wq, bias, (EO*)y, part, nsplit, g, post, s)
                     : launch_igemm_t<fp8_t, EO, false>(xq, (const fp8_t*)Wq, bias, (EO*)y, part, nsplit, g, post, s);
     });

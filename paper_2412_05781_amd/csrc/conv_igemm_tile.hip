@@ -29,13 +29,6 @@ template <> struct Mma16<bf16_t> {
     }
 };
 
-template <typename E> __device__ __forceinline__ uint32_t pack2(float a, float b) {
-    const E ea = from_f32<E>(a), eb = from_f32<E>(b);
-    return (uint32_t)*reinterpret_cast<const uint16_t*>(&ea) | ((uint32_t)*reinterpret_cast<const uint16_t*>(&eb) << 16);
-}
-template <typename E> __device__ __forceinline__ float lo16(uint32_t w) { const uint16_t h = (uint16_t)(w & 0xffffu); return to_f32<E>(*reinterpret_cast<const E*>(&h)); }
-template <typename E> __device__ __forceinline__ float hi16(uint32_t w) { const uint16_t h = (uint16_t)(w >> 16); return to_f32<E>(*reinterpret_cast<const E*>(&h)); }
-
 }  // namespace
 
 // BP pixels x BK output channels per workgroup, WP x WK waves.  PIX_A: pixels are the rows (NCHW y), else output channels (channel-last y).
@@ -204,7 +197,6 @@ conv_igemm_tile_kernel(const E* __restrict__ xh, const E* __restrict__ Wr, const
     // 16x16 accumulator layout: register r of lane l holds row 4*(l/16) + r, column l%16.  Outputs are numbered in y's own
     // order, [pixel][channel] or [channel][pixel]; partial sums are stored in that order.
     const int rowsA = PIX_A ? g.T : g.K, rowsB = PIX_A ? g.K : g.T;
-    const bool vec_pair = HoWo % 2 == 0;                    // y and the residual are 16-byte aligned
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
         const int cb = row_b0 + wn * WTN + j * 16 + frow;
@@ -223,52 +215,7 @@ conv_igemm_tile_kernel(const E* __restrict__ xh, const E* __restrict__ Wr, const
                 }
                 continue;
             }
-            if (vec_ok) {                                   // the four outputs are adjacent and 8-byte aligned
-                size_t o;
-                if constexpr (PIX_A) {
-                    const int n = ra / HoWo, k = cb;
-                    o = ((size_t)n * g.K + k) * HoWo + (ra - n * HoWo);
-                    v = v * post.scale + ((bias ? bias[k] : 0.f) + (post.addvec ? post.addvec[(size_t)n * g.K + k] : 0.f));
-                } else {
-                    const int n = cb / HoWo;
-                    o = (size_t)cb * g.K + ra;
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        v[r] = v[r] * post.scale + ((bias ? bias[ra + r] : 0.f) + (post.addvec ? post.addvec[(size_t)n * g.K + ra + r] : 0.f));
-                }
-                if (post.residual) {
-                    const uint2 w = *reinterpret_cast<const uint2*>(static_cast<const E*>(post.residual) + o);
-                    v[0] += lo16<E>(w.x); v[1] += hi16<E>(w.x); v[2] += lo16<E>(w.y); v[3] += hi16<E>(w.y);
-                }
-                *reinterpret_cast<uint2*>(y + o) = make_uint2(pack2<E>(v[0], v[1]), pack2<E>(v[2], v[3]));
-            } else if (PIX_A && vec_pair) {                 // an even number of pixels per image: pairs are adjacent and aligned
-#pragma unroll
-                for (int r = 0; r < 4; r += 2) {
-                    const int t = ra + r, k = cb;
-                    if (t >= rowsA) continue;
-                    const int n = t / HoWo;
-                    const size_t o = ((size_t)n * g.K + k) * HoWo + (t - n * HoWo);
-                    const float bb = (bias ? bias[k] : 0.f) + (post.addvec ? post.addvec[(size_t)n * g.K + k] : 0.f);
-                    float f0 = v[r] * post.scale + bb, f1 = v[r + 1] * post.scale + bb;
-                    if (post.residual) {
-                        const uint32_t w = *reinterpret_cast<const uint32_t*>(static_cast<const E*>(post.residual) + o);
-                        f0 += lo16<E>(w); f1 += hi16<E>(w);
-                    }
-                    *reinterpret_cast<uint32_t*>(y + o) = pack2<E>(f0, f1);
-                }
-            } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    if (ra + r >= rowsA) continue;
-                    const int t = PIX_A ? ra + r : cb, k = PIX_A ? cb : ra + r;
-                    const int n = t / HoWo;
-                    const size_t o = PIX_A || planes ? ((size_t)n * g.K + k) * HoWo + (t - n * HoWo) : (size_t)t * g.K + k;
-                    float f = v[r] * post.scale + (bias ? bias[k] : 0.f);
-                    if (post.addvec) f += post.addvec[(size_t)n * g.K + k];
-                    if (post.residual) f += to_f32<E>(static_cast<const E*>(post.residual)[o]);
-                    y[o] = from_f32<E>(f);
-                }
-            }
+            igemm_store4<E, PIX_A>(v, ra, cb, y, bias, g, post, vec_ok, planes);
         }
     }
 }
@@ -286,8 +233,7 @@ static hipError_t launch_tile_cfg(const E* xh, const E* Wr, const float* bias, E
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
     if (attr != hipSuccess) return attr;
     const E* zero_row = Wr + (size_t)g.R * g.R * g.K * g.Cp;
-    const int run = PIX_A ? g.Ho * g.Wo : g.K;              // the contiguous dimension of y
-    const int vec_ok = run % 4 == 0 && !planes && ((reinterpret_cast<uintptr_t>(y) | reinterpret_cast<uintptr_t>(post.residual)) & 7u) == 0;
+    const int vec_ok = igemm_vec_ok<PIX_A>(g, y, post, planes);
     hipLaunchKernelGGL(kern, dim3((unsigned)(per_xcd * 8)), dim3(WP * WK * 64), lds_bytes, s, xh, Wr, zero_row, bias, y, part, g, post,
                        tiles_p, tiles_k, (int)total, per_xcd, nsplit, vec_ok, planes ? 1 : 0);
     return hipGetLastError();

@@ -100,9 +100,29 @@ def test_fp8_fused_operators(dtype, layout):
     assert oracle.rel_l2(y.numpy(), exact) <= 6e-2
 
 
+# the kernel for whole reductions: blocks of 256x256 with one and several stages, the last one partial, blocks that straddle two images,
+# planes that are and are not whole 16-byte pieces; blocks of 128x128 off the edge in both dimensions; additions at the end
+@pytest.mark.parametrize("layout", [B.WINO_NCHW, B.WINO_NHWC])
+@pytest.mark.parametrize("case", [(2, 272, 256, 180, 184, 1), (2, 80, 256, 181, 182, 1), (1, 384, 256, 255, 259, 1), (1, 112, 200, 24, 40, 3),
+                                  (2, 48, 136, 25, 40, 3), (3, 112, 72, 9, 11, 3)])
+def test_fp8_whole_reductions(case, layout):
+    N, C, K, H, W, R = case
+    x, w, b = _inputs(N, C, K, H, W, R, "f16", seed=400 + sum(case))
+    g = torch.Generator().manual_seed(sum(case))
+    addvec, residual = torch.randn(N, K, generator=g), torch.randn(N, K, H, W, generator=g).half()
+    sx, sw = f8.power_of_two_scale(_np(x)), f8.power_of_two_scale(_np(w))
+    model = f8.conv2d_fp8(_np(x), _np(w), _np(b), sx, sw, 1) + _np(addvec)[:, :, None, None] + _np(residual)
+    perm = (lambda t: t.permute(0, 2, 3, 1).contiguous()) if layout == B.WINO_NHWC else (lambda t: t)
+    y = B.conv2d_fp8(perm(x).to(DEV), w.to(DEV), b.to(DEV), sx, sw, 1, layout, addvec=addvec.to(DEV), residual=perm(residual).to(DEV))
+    y = y.float().cpu()
+    y = (y.permute(0, 3, 1, 2) if layout == B.WINO_NHWC else y).numpy()
+    assert oracle.rel_l2(y, model) <= OUT_TOL["f16"], (case, layout)
+    assert np.abs(y - model).max() <= 4e-3 * np.abs(model).max(), (case, layout)       # two roundings of the largest output and the accumulation
+
+
 @pytest.mark.parametrize("name,layout", [("E2_vae", B.WINO_NHWC), ("E3_vae", B.WINO_NCHW), ("C6_unet", B.WINO_NCHW)])
 def test_fp8_full_size_layers_sampled(name, layout):
-    """Full-size layers (256x256 blocks of 16 waves; a split reduction on the 8x8 one): 4096 sampled outputs and the
+    """Full-size layers (256x256 blocks of 16 and of eight waves; a split reduction on the 8x8 one): 4096 sampled outputs and the
     image corners against the quantisation model, evaluated one output at a time."""
     layer = synth.LAYERS[name]
     x, w, b = synth.make_layer_inputs(layer)
