@@ -15,7 +15,7 @@
 // most 256 channels, where the unfused path is bound by writing and re-reading M.  Two-byte storage types only.
 //
 // Operand staging is that of the batched GEMM kernel: 128-byte stages per row, global -> LDS directly into a ring,
-// XOR-swizzled 16-byte chunks, one barrier per stage, explicit vmcnt waits.
+// XOR-swizzled 16-byte chunks, explicit vmcnt waits; one barrier per pair of stages.
 // ROWS_K = true : rows of the block are output channels (U), columns are tiles (V); y is NCHW.
 // ROWS_K = false: operands swapped, rows are tiles, columns output channels; y is channel-last.
 #include "wino_internal.h"
@@ -77,7 +77,7 @@ wino_fused_f4_kernel(const E* __restrict__ Aop, const E* __restrict__ Bop, const
     constexpr int LA = BM / (RPL * NW);                   // ... of which from the row operand
     constexpr int STAGE_BYTES = ROWS * RB;
     static_assert(ROWS % (RPL * NW) == 0 && BM % (RPL * NW) == 0, "load i of every wave lies in the same operand");
-    static_assert(NST >= 2 && (NST & (NST - 1)) == 0 && LPW * (NST - 1) < 64, "ring depth: a power of two, within the vmcnt range");
+    static_assert(NST >= 4 && NST % 2 == 0 && LPW * (NST - 1) < 64, "ring depth: pairs of stages, within the vmcnt range");
 
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
 
@@ -177,9 +177,10 @@ wino_fused_f4_kernel(const E* __restrict__ Aop, const E* __restrict__ Bop, const
         lds_read16_async<0>(fb[set][1][0], b0 ^ 64u);
         lds_read16_async<16 * RB>(fb[set][1][1], b0 ^ 64u);
     };
-    auto await_stage = [&](auto setc) __attribute__((always_inline)) {                   // every fragment read issued so far has arrived
+    // every fragment read but the `newer` youngest has arrived
+    auto await_stage = [&](auto setc, auto newerc) __attribute__((always_inline)) {
         constexpr int set = decltype(setc)::value;
-        lds_wait<0>();
+        lds_wait<decltype(newerc)::value>();
 #pragma unroll
         for (int h = 0; h < 2; ++h) { pin(fa[set][h]); pin(fb[set][h][0]); pin(fb[set][h][1]); }
     };
@@ -197,8 +198,8 @@ wino_fused_f4_kernel(const E* __restrict__ Aop, const E* __restrict__ Bop, const
 #pragma unroll
     for (int s = 0; s < NST; ++s)
         if (s < total) issue_stage(s);
-    if (NST - 1 >= total) wait_vmcnt<0>();
-    else wait_vmcnt<(NST - 1) * LPW>();
+    if (NST - 2 >= total) wait_vmcnt<0>();
+    else wait_vmcnt<(NST - 2) * LPW>();                    // the first pair has landed
     __syncthreads();
     read_stage(0, I0());
 
@@ -241,29 +242,38 @@ wino_fused_f4_kernel(const E* __restrict__ Aop, const E* __restrict__ Bop, const
         ++xi;
     };
 
-    // stage s (fragment set s % 2, requested one stage earlier): make stage s+1 visible, refill the slot of stage s, request
-    // the fragments of stage s+1, multiply stage s
-    auto stage = [&](int s, auto setc, auto nextc) __attribute__((always_inline)) {
-        const int slot = s & (NST - 1), next_slot = (s + 1) & (NST - 1);
-        // stage s+1 has landed once no more transfers are outstanding than were issued after it
-        if (s + NST >= total) wait_vmcnt<0>();
-        else wait_vmcnt<(NST - 2) * LPW>();
-        await_stage(setc);              // this wave has read all of stage s
-        __syncthreads();                // stage s+1 visible to all waves; every wave has read all of stage s
-        if (s + NST < total) issue_stage(slot);                  // stage s+NST, into the slot stage s used
-        read_stage(next_slot, nextc);
+    // Stages are taken in pairs (36 * nk is even), one barrier per pair: on entry the pair is visible and the fragments of its first stage
+    // have been requested.  The transfers bound the kernel, so this gains little over a barrier per stage and half the ring (whole calls:
+    // 256 channels at 512x512 334 -> 327 us, 512 at 256x256 channel-last 238 -> 236, 128 at 1024x1024 channel-last 494 -> 491).  Blocks
+    // of 32 tiles x 128 channels, which fetch V half as often and U twice, are slower (349, 268 and 530).
+    const int pairs = total / 2;
+    auto first_half = [&](int slot) __attribute__((always_inline)) {
+        read_stage(slot + 1, I1());
+        await_stage(I0(), std::integral_constant<int, 6>());
         __builtin_amdgcn_sched_barrier(0);
-        mma_stage(setc);
+        mma_stage(I0());
         __builtin_amdgcn_sched_barrier(0);
         end_of_stage();
     };
-    // total = 36 * nk is even: stages are taken in pairs so that the fragment sets are compile-time; the last stage is peeled
-    for (int s = 0; s < total - 2; s += 2) {
-        stage(s, I0(), I1());
-        stage(s + 1, I1(), I0());
+    int slot = 0;
+    for (int p = 0; p < pairs - 1; ++p) {
+        const int next = slot + 2 == NST ? 0 : slot + 2;
+        first_half(slot);
+        // the next pair has landed once no more transfers are outstanding than were issued after it
+        if (p + NST / 2 >= pairs) wait_vmcnt<0>();
+        else wait_vmcnt<(NST - 4) * LPW>();
+        await_stage(I1(), I0());        // this wave has read all of the pair
+        __syncthreads();                // the next pair visible to all waves; every wave has read all of this one
+        if (p + NST / 2 < pairs) { issue_stage(slot); issue_stage(slot + 1); }
+        read_stage(next, I0());
+        __builtin_amdgcn_sched_barrier(0);
+        mma_stage(I1());
+        __builtin_amdgcn_sched_barrier(0);
+        end_of_stage();
+        slot = next;
     }
-    stage(total - 2, I0(), I1());
-    await_stage(I1());
+    first_half(slot);
+    await_stage(I1(), I0());
     mma_stage(I1());
     end_of_stage();
 
@@ -399,10 +409,10 @@ template <typename E, bool ROWS_K>
 static hipError_t launch_fused4_t(const void* Aop, const void* Bop, int rowsA, int rowsB, const float* bias, void* y,
                                   const Geom& g, const PostOp& post, int shape, hipStream_t s) {
     if (g.Cp % 64 != 0)       // a reduction length that is not a whole number of stages: the zero-filling last stage
-        return launch_fused4_cfg<E, 4, 2, 2, ROWS_K, true>(Aop, Bop, rowsA, rowsB, bias, y, g, post, s);
+        return launch_fused4_cfg<E, 8, 2, 2, ROWS_K, true>(Aop, Bop, rowsA, rowsB, bias, y, g, post, s);
     switch (shape) {
-        case 0: return launch_fused4_cfg<E, 4, 4, 2, ROWS_K>(Aop, Bop, rowsA, rowsB, bias, y, g, post, s);
-        case 1: return launch_fused4_cfg<E, 4, 2, 2, ROWS_K>(Aop, Bop, rowsA, rowsB, bias, y, g, post, s);
+        case 0: return launch_fused4_cfg<E, 8, 4, 2, ROWS_K>(Aop, Bop, rowsA, rowsB, bias, y, g, post, s);
+        case 1: return launch_fused4_cfg<E, 8, 2, 2, ROWS_K>(Aop, Bop, rowsA, rowsB, bias, y, g, post, s);
         default: return hipErrorInvalidValue;
     }
 }
