@@ -39,6 +39,7 @@ template <> struct Mma16<bf16_t> {
     }
 };
 
+typedef f32x4_t f32x4_word_t __attribute__((aligned(4)));           // bias and vector need only be aligned to their elements
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -430,8 +431,8 @@ wino_onepass_f2_kernel(const E* __restrict__ x, const E* __restrict__ U, const f
                     const f32x4_t s0 = *reinterpret_cast<const f32x4_t*>(zp), s1 = *reinterpret_cast<const f32x4_t*>(zp + ZN);
                     const f32x4_t s2 = *reinterpret_cast<const f32x4_t*>(zp + 2 * ZN), s3 = *reinterpret_cast<const f32x4_t*>(zp + 3 * ZN);
                     f32x4_t bb = {0.f, 0.f, 0.f, 0.f};
-                    if (bias) bb = *reinterpret_cast<const f32x4_t*>(bias + k + 4 * h);
-                    if (post.addvec) bb += *reinterpret_cast<const f32x4_t*>(post.addvec + (size_t)n * K + k + 4 * h);
+                    if (bias) bb = *reinterpret_cast<const f32x4_word_t*>(bias + k + 4 * h);
+                    if (post.addvec) bb += *reinterpret_cast<const f32x4_word_t*>(post.addvec + (size_t)n * K + k + 4 * h);
                     *reinterpret_cast<f32x4_t*>(o0 + 4 * h) = s0 + s1 + s2 + bb;
                     *reinterpret_cast<f32x4_t*>(o1 + 4 * h) = s1 - s2 - s3 + bb;
                 }
