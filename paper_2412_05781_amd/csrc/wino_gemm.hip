@@ -469,11 +469,29 @@ static int pick_shape(int K, int T, int nbatch, bool f16) {
     return best;
 }
 
+// Shape 7 with blocks of 96 in one dimension (9: rows, 10: columns) where they still fit in one round of compute units: units that would
+// stay idle take a share, and a workgroup moves 7/8 of the bytes into LDS, which is what it waits for.  From 20 stages on; with fewer the
+// larger number of workgroups costs what the shorter stages gain.  Whole calls, us, 128 / 96: 1280 channels at 16x16 (N=2, 16 products
+// of 1280 x 128, 20 stages) 24.2 / 22.9, 2560 -> 1280 (40 stages) 48.3 / 44.1, 1920 -> 640 at 32x32 (36 products of 640 x 128, 30 stages)
+// 42.9 / 41.2, but 640 -> 640 at 32x32 (10 stages) 20.9 / 21.9.
+static int one_round_shape(int K, int T, int nbatch, int stages) {
+    const long long tm = (K + 127) / 128, tn = (T + 127) / 128, b7 = tm * tn * nbatch;
+    const long long b9 = (long long)((K + 95) / 96) * tn * nbatch, b10 = tm * ((T + 95) / 96) * nbatch;
+    if (stages < 20) return 7;
+    if (b10 <= 256 && b10 > b7 && (b9 > 256 || b10 >= b9)) return 10;
+    return b9 <= 256 && b9 > b7 ? 9 : 7;
+}
+
 template <typename E, typename MT>
 static hipError_t launch_gemm_t(const void* U, const void* V, void* M, int K, int Cp, int T, int nbatch, int nsplit, int shape, hipStream_t s,
                                 const float* rs = nullptr, const float* cs = nullptr) {
-    const int sh = shape < 0 ? pick_shape(K, T, nbatch, sizeof(E) == 2) : shape;
+    int sh = shape < 0 ? pick_shape(K, T, nbatch, sizeof(E) == 2) : shape;
     if (Cp % (128 / (int)sizeof(E)) == 0) {               // whole stages: the lean kernel, same block shapes
+        if constexpr (sizeof(E) == 2) {
+            if (shape < 0 && sh == 7 && nsplit == 1) sh = one_round_shape(K, T, nbatch, Cp / 64);
+            if (sh == 9) return launch_gemm_lean<E, MT, 96, 128, 3, 1, 4>(U, V, M, K, Cp, T, nbatch, nsplit, s, rs, cs);
+            if (sh == 10) return launch_gemm_lean<E, MT, 128, 96, 3, 4, 1>(U, V, M, K, Cp, T, nbatch, nsplit, s, rs, cs);
+        }
         switch (sh) {
             case 0: return launch_gemm_lean<E, MT, 128, 128, 2, 2, 2>(U, V, M, K, Cp, T, nbatch, nsplit, s, rs, cs);
             case 1: return launch_gemm_lean<E, MT, 128, 64, 2, 2, 2>(U, V, M, K, Cp, T, nbatch, nsplit, s, rs, cs);

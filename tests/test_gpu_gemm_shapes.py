@@ -39,6 +39,21 @@ def test_named_block_shape_against_fp64_product(dims, block_shape, variant, dtyp
     assert np.abs(got - M_auto.cpu().numpy().astype(np.float64)).max() <= tol
 
 
+# the library's own choice where blocks of 96 rows or columns fill one round of compute units (long reductions, one operand of
+# about 128 rows), with the last block partial in both dimensions
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("variant,dims", [(B.WINO_F2, (127, 1280, 1270)), (B.WINO_F2, (1270, 1280, 127)), (B.WINO_F4, (127, 1344, 630)),
+                                          (B.WINO_F4, (630, 1280, 126))])
+def test_one_round_blocks_against_fp64_product(variant, dims, dtype):
+    K, C, T = dims
+    a2 = (variant + 2) ** 2
+    g = torch.Generator().manual_seed(sum(dims))
+    U, V = torch.randn(a2, K, C, generator=g).to(dtype), torch.randn(a2, T, C, generator=g).to(dtype)
+    got = B.wino_batched_gemm(U.to(DEV), V.to(DEV), K, C, T, variant).cpu().double()
+    ref = U.double() @ V.double().transpose(1, 2).contiguous()
+    assert (got - ref).abs().max() <= 2e-5 * np.sqrt(C) * 4       # as above
+
+
 def test_block_shape_out_of_range_is_rejected():
     U = torch.zeros(16 * 8 * 8, dtype=torch.float16, device=DEV)
     for bad in (-1, 9, 100):
