@@ -451,11 +451,7 @@ static IgemmShape igemm_shape(int T, int K) {
 // Few blocks and a long reduction (deep down-sampling layers: 8x8 outputs, 9 x 1280 channels): cut the
 // reduction so that about two workgroups per compute unit are in flight, at least eight stages each
 // (the second kernel costs ~3 us, more than a short reduction gains).
-int igemm_split(int T, int K, int Cp, int R, int dt, bool nhwc) {
-    if (dt >= 0) {
-        const IgemmTilePlan plan = igemm_tile_plan(T, K, Cp, R, dt, nhwc);
-        if (plan.id >= 0) return plan.split;
-    }
+int igemm_split_rule(int T, int K, int Cp, int R, int dt) {
     // dt < 0: 8-bit operands, 128 reduction elements per stage
     const bool f16 = two_byte(dt);
     if (dt < 0) Cp = (Cp + 1) / 2;                        // same stage count as 64-element stages over half the channels
@@ -471,6 +467,13 @@ int igemm_split(int T, int K, int Cp, int R, int dt, bool nhwc) {
     }
     if (sp > nstage) sp = nstage;
     return sp < 1 ? 1 : sp;
+}
+int igemm_split(int T, int K, int Cp, int R, int dt, bool nhwc) {
+    if (dt >= 0) {
+        const IgemmTilePlan plan = igemm_tile_plan(T, K, Cp, R, dt, nhwc);
+        if (plan.id >= 0) return plan.split;
+    }
+    return igemm_split_rule(T, K, Cp, R, dt);
 }
 
 template <typename E, typename EO, bool PIX_A>

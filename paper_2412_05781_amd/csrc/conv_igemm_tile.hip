@@ -256,11 +256,14 @@ IgemmTilePlan igemm_tile_plan(int T, int K, int Cp, int R, int dt, bool nhwc) {
     if (!(dt == DT_F16 || dt == DT_BF16) || Cp % 64 != 0) return best;
     if (nhwc && K == 256 && T >= 65536) return best;
     const int stages = R * R * (Cp / 64);
+    // never more ranges than the other kernel takes: the workspace of a call, and with it what fits the library's static scratch, stays
+    // what it is there
+    const int most_sp = igemm_split_rule(T, K, Cp, R, dt);
     double cost = 1e300;
     for (int id = 0; id < 3; ++id) {
         const TileShape& sh = kTiles[id];
         const long long blocks = (long long)((T + sh.bp - 1) / sh.bp) * ((K + sh.bk - 1) / sh.bk);
-        for (int sp = 1; sp <= 16 && (sp == 1 || sp * 8 <= stages); ++sp) {
+        for (int sp = 1; sp <= most_sp && (sp == 1 || sp * 8 <= stages); ++sp) {
             const double share = (double)(blocks * sp) / 256.0;            // workgroups per compute unit
             const double most = (double)((blocks * sp + 255) / 256), n = share < 2.0 ? 0.5 * (share + most) : most;
             const double stage = n * sh.each > sh.alone ? n * sh.each : sh.alone;

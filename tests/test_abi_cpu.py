@@ -213,3 +213,12 @@ def test_fused_variant_sizes_and_the_entry_points_added_for_it(L):
     assert L.wino_conv2d_static(x, ctypes.byref(f), None, y, 1, 512, 128, 128, 500, B.WINO_NCHW, None) == B.WINO_ERR_DIM
     assert L.wino_conv2d_static(x, ctypes.byref(f), None, y, 1, 512, 8, 8, 512, 7, None) == B.WINO_ERR_LAYOUT
     assert L.wino_conv2d_static(x, ctypes.byref(f), None, x, 1, 512, 8, 8, 512, B.WINO_NCHW, None) == B.WINO_ERR_ALIAS
+
+
+# shapes at which the 16x16-tile kernel would like a split reduction and the rule of the other kernel has fewer ranges: the workspace stays
+# what that rule needs (0, or two ranges and the re-laid x), so calls that fit the static scratch keep fitting
+@pytest.mark.parametrize("args,most", [((1, 1792, 172, 190, 1120, 3, 2, B.WINO_F16, B.WINO_NHWC), 0), ((2, 2496, 43, 126, 896, 3, 1, B.WINO_F16, B.WINO_NHWC), 0),
+                                       ((1, 2304, 112, 77, 1112, 3, 1, B.WINO_BF16, B.WINO_NCHW), 39739392),
+                                       ((1, 1728, 134, 106, 959, 3, 2, B.WINO_BF16, B.WINO_NCHW), 49089024)])
+def test_direct_path_workspace_is_bounded_by_the_split_rule(L, args, most):
+    assert B.wino_igemm_workspace_bytes(*args) <= most <= B.wino_static_scratch_bytes()
