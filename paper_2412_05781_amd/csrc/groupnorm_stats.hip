@@ -11,10 +11,16 @@
 
 namespace wino {
 
-constexpr int kMaxSplit = 256;
+// Slices per group.  The buffer's size follows from it and the call is not told that size: 32 is what the buffer has always held, and a
+// caller may have kept the number of bytes.
+constexpr int kMaxSplit = 32;
 // A second launch costs 2-3 us and as much again on the host: a group of up to 128 KB is read as fast by one workgroup (fp16, 64
 // groups: 82 KB each 5.4 us against 5.8 in two launches, 128 KB 5.5 against 7.0; 184 KB stay with slices, 6.5 us).
 constexpr size_t kWholeGroupBytes = (size_t)128 << 10;
+// Channel-last: the least bytes of a pixel that a workgroup reads.  Pieces shorter than a 128-byte line fetch the line several times out
+// of L2, longer ones leave compute units idle (fp16, 32 groups, us: 128 channels at 1024x1024, pieces of 32 / 64 / 128 bytes = 256 / 128 /
+// 64 workgroups: 55 / 63 / 84; 512 channels at 256x256 16.6 with any of them).
+constexpr size_t kMinPiece = 32;
 
 size_t groupnorm_stats_bytes(int N, int groups) {
     const size_t ng = (size_t)N * groups;
@@ -81,25 +87,30 @@ groupnorm_vec_kernel(const E* __restrict__ x, double* __restrict__ partial, floa
     }
 }
 
-// Channel-last, C a multiple of 8: a workgroup reads all channels of a slab of pixels, a lane the same eight channels of every
-// PX-th pixel (16-byte loads that run along the channels).  Lane sums are added per channel over the pixel lanes and then per
+// Channel-last, C a multiple of 8: a workgroup reads the channels of `gpb` groups of a slab of pixels, a lane the same eight channels of
+// every PX-th pixel (16-byte loads that run along the channels).  Lane sums are added per channel over the pixel lanes and then per
 // group in fp64.  Read group by group instead, a group of 10...40 channels is a 20...80-byte piece of every pixel
 // (N=2, 1280 channels at 16x16: 10.7 -> 6.8 us; 512 channels at 256x256: 66 -> 17 us = 3.9 TB/s).
+// The workgroups of a slab, which share the lines of its pixels, are neighbours in one XCD's range.  (All channels to a workgroup and 256
+// slabs would take eight times the buffer; 128 channels at 1024x1024 in 43 us instead of 55, 320 at 64x64 in 8.6 instead of 7.7.)
 template <typename E, int THREADS>
 __global__ void __launch_bounds__(THREADS)
 groupnorm_partial_nhwc_vec_kernel(const E* __restrict__ x, double* __restrict__ partial, int C, int HW, int groups, int cpg,
-                                  int split, int pixels_per_slab) {
+                                  int split, int pixels_per_slab, int gpb, int gblocks, int total_blocks, int blocks_per_xcd) {
     constexpr int EPC = 16 / (int)sizeof(E);
     __shared__ float ls[THREADS * EPC], lq[THREADS * EPC];
-    const int n = blockIdx.x, sl = blockIdx.y;
-    const int octs = C / EPC, px = THREADS / octs;          // pixel lanes; lanes beyond px * octs are idle
+    const int logical = (int)(blockIdx.x % 8) * blocks_per_xcd + (int)(blockIdx.x / 8);
+    if (logical >= total_blocks) return;                    // uniform, before any barrier
+    const int gb = logical % gblocks, sl = logical / gblocks % split, n = logical / gblocks / split;
+    const int g0 = gb * gpb, ng = min(gpb, groups - g0), c0 = g0 * cpg, CW = ng * cpg;      // groups and channels of the workgroup
+    const int octs = CW / EPC, px = THREADS / octs;         // pixel lanes; lanes beyond px * octs are idle
     const int oct = threadIdx.x % octs, pl = threadIdx.x / octs;
     float s[EPC], q[EPC];
 #pragma unroll
     for (int i = 0; i < EPC; ++i) { s[i] = 0.f; q[i] = 0.f; }
     const int p0 = sl * pixels_per_slab, p1 = min(p0 + pixels_per_slab, HW);
     if (pl < px) {
-        const E* base = x + (size_t)n * HW * C + (size_t)oct * EPC;
+        const E* base = x + (size_t)n * HW * C + c0 + (size_t)oct * EPC;
         for (int p = p0 + pl; p < p1; p += 4 * px) {
             uint4 raw[4];
 #pragma unroll
@@ -117,19 +128,19 @@ groupnorm_partial_nhwc_vec_kernel(const E* __restrict__ x, double* __restrict__ 
             }
         }
 #pragma unroll
-        for (int i = 0; i < EPC; ++i) { ls[pl * C + oct * EPC + i] = s[i]; lq[pl * C + oct * EPC + i] = q[i]; }
+        for (int i = 0; i < EPC; ++i) { ls[pl * CW + oct * EPC + i] = s[i]; lq[pl * CW + oct * EPC + i] = q[i]; }
     }
     __syncthreads();
-    for (int c = threadIdx.x; c < C; c += THREADS) {        // over the pixel lanes, fixed order
+    for (int c = threadIdx.x; c < CW; c += THREADS) {       // over the pixel lanes, fixed order
         float a = ls[c], b = lq[c];
-        for (int k = 1; k < px; ++k) { a += ls[k * C + c]; b += lq[k * C + c]; }
+        for (int k = 1; k < px; ++k) { a += ls[k * CW + c]; b += lq[k * CW + c]; }
         ls[c] = a; lq[c] = b;                               // only this lane touches column c
     }
     __syncthreads();
-    for (int g = threadIdx.x; g < groups; g += THREADS) {
+    for (int g = threadIdx.x; g < ng; g += THREADS) {
         double a = 0.0, b = 0.0;
         for (int j = 0; j < cpg; ++j) { a += (double)ls[g * cpg + j]; b += (double)lq[g * cpg + j]; }
-        double* dst = partial + (((size_t)n * groups + g) * split + sl) * 2;
+        double* dst = partial + (((size_t)n * groups + g0 + g) * split + sl) * 2;
         dst[0] = a; dst[1] = b;
     }
 }
@@ -190,17 +201,26 @@ hipError_t launch_groupnorm_stats(const void* x, float* stats, int N, int C, int
     // channel-last with whole 16-byte channel octets, all of them within one workgroup's lanes
     constexpr int NT = 512;
     if (nhwc && C % (int)epc == 0 && C / (int)epc <= NT && x16) {
-        // about 16 KB per slab, and enough slabs for two rounds of workgroups on large tensors
+        // about 16 KB per workgroup and at most 256 per image: 32 slabs of pixels, then blocks of groups, of whole 16-byte pieces and at
+        // least kMinPiece bytes of a pixel
         const size_t bytes = (size_t)HW * C * esz;
-        int split = (int)((bytes + (16 << 10) - 1) / (16 << 10));
-        split = split > kMaxSplit ? kMaxSplit : split;
+        const int want = (int)(bytes / (16 << 10) < 1 ? 1 : (bytes / (16 << 10) > 256 ? 256 : bytes / (16 << 10)));
+        int split = want > kMaxSplit ? kMaxSplit : want;
         split = split > HW ? HW : split;
         const int pps = (HW + split - 1) / split;
         split = (HW + pps - 1) / pps;
+        int unit = 1;                                                                     // groups
+        while ((unit * cpg) % (int)epc != 0 || ((size_t)unit * cpg * esz < kMinPiece && unit < groups)) ++unit;
+        const int units = (groups + unit - 1) / unit, blocks = want / split < units ? (want / split < 1 ? 1 : want / split) : units;
+        const int gpb = (units + blocks - 1) / blocks * unit;
+        const int gblocks = (groups + gpb - 1) / gpb;
+        const long long all = (long long)N * split * gblocks;
+        if (all > 0x3fffffffLL) return hipErrorInvalidValue;
+        const int per_xcd = (int)((all + 7) / 8);
         (void)with_dtype(dt, [&](auto* tag) {
             using E = std::remove_pointer_t<decltype(tag)>;
-            hipLaunchKernelGGL((groupnorm_partial_nhwc_vec_kernel<E, NT>), dim3((unsigned)N, (unsigned)split), dim3(NT), 0, s,
-                               (const E*)x, partial, C, HW, groups, cpg, split, pps);
+            hipLaunchKernelGGL((groupnorm_partial_nhwc_vec_kernel<E, NT>), dim3((unsigned)(per_xcd * 8)), dim3(NT), 0, s,
+                               (const E*)x, partial, C, HW, groups, cpg, split, pps, gpb, gblocks, (int)all, per_xcd);
             return hipSuccess;
         });
         hipError_t e = hipGetLastError();
@@ -216,10 +236,13 @@ hipError_t launch_groupnorm_stats(const void* x, float* stats, int N, int C, int
     size_t per_slice = (elems + split0 - 1) / split0;
     per_slice = (per_slice + quantum - 1) / quantum * quantum;
     const int split = (int)((elems + per_slice - 1) / per_slice);
+    // few groups and long slices: four times the lanes (512x512, 128 channels, 4 groups: 46 -> 15.4 us)
+    const bool tall = (long long)total * split < 512 && per_slice >= 16 * quantum;
     dim3 grid((unsigned)total, (unsigned)split), block(256);
     (void)with_dtype(dt, [&](auto* tag) {
         using E = std::remove_pointer_t<decltype(tag)>;
-        if (vec)       hipLaunchKernelGGL((groupnorm_vec_kernel<E, 256, false>), grid, block, 0, s, (const E*)x, partial, stats, elems, split, per_slice, inv_count, eps);
+        if (vec && tall) hipLaunchKernelGGL((groupnorm_vec_kernel<E, 1024, false>), grid, dim3(1024), 0, s, (const E*)x, partial, stats, elems, split, per_slice, inv_count, eps);
+        else if (vec)  hipLaunchKernelGGL((groupnorm_vec_kernel<E, 256, false>), grid, block, 0, s, (const E*)x, partial, stats, elems, split, per_slice, inv_count, eps);
         else if (nhwc) hipLaunchKernelGGL((groupnorm_partial_kernel<E, true>), grid, block, 0, s, (const E*)x, partial, C, HW, groups, cpg, split, per_slice);
         else           hipLaunchKernelGGL((groupnorm_partial_kernel<E, false>), grid, block, 0, s, (const E*)x, partial, C, HW, groups, cpg, split, per_slice);
         return hipSuccess;

@@ -222,3 +222,10 @@ def test_fused_variant_sizes_and_the_entry_points_added_for_it(L):
                                        ((1, 1728, 134, 106, 959, 3, 2, B.WINO_BF16, B.WINO_NCHW), 49089024)])
 def test_direct_path_workspace_is_bounded_by_the_split_rule(L, args, most):
     assert B.wino_igemm_workspace_bytes(*args) <= most <= B.wino_static_scratch_bytes()
+
+
+# wino_groupnorm_stats is not told the size of its buffer, so the size that a caller may have kept has to stay: (mean, 1/std) per group in
+# fp32, and 32 partial (sum, sum of squares) in fp64
+@pytest.mark.parametrize("N,groups", [(1, 1), (1, 32), (2, 32), (3, 33), (16, 32), (1, 4096)])
+def test_groupnorm_stats_buffer_keeps_its_size(L, N, groups):
+    assert B.wino_groupnorm_stats_bytes(N, groups) == (8 * N * groups + 255) // 256 * 256 + 32 * 16 * N * groups

@@ -56,6 +56,22 @@ def test_groupnorm_stats_routes(shape, layout):
     assert np.abs(st[:, :, 1] / rstd - 1).max() <= 5e-6
 
 
+@pytest.mark.parametrize("layout", [B.WINO_NCHW, B.WINO_NHWC])
+@pytest.mark.parametrize("shape", [(1, 64, 256, 256, 32), (2, 128, 128, 128, 2), (1, 512, 64, 64, 512), (1, 66, 128, 128, 33), (3, 320, 40, 40, 32)])
+def test_groupnorm_stats_stays_inside_its_buffer(shape, layout):
+    """32 slices per group whatever the tensor: nothing is written behind the number of bytes that the buffer has always had."""
+    N, C, H, W, G = shape
+    x = torch.randn((N, H, W, C) if layout == B.WINO_NHWC else (N, C, H, W), generator=torch.Generator().manual_seed(C)).half().to(DEV)
+    size = (8 * N * G + 255) // 256 * 256 + 32 * 16 * N * G
+    buf = torch.full((size + 65536,), 0x5a, dtype=torch.uint8, device=DEV)
+    st = B.stats_view(B.wino_groupnorm_stats(x, G, 1e-5, layout, out=buf), N, G).cpu().numpy().astype(np.float64)
+    assert bool((buf[size:] == 0x5a).all())
+    xn = _np(x.cpu().permute(0, 3, 1, 2) if layout == B.WINO_NHWC else x.cpu())
+    mean, rstd = fo.groupnorm_stats(xn, G, 1e-5)
+    assert np.abs(st[:, :, 0] - mean).max() <= 2e-6 * (1 + np.abs(mean).max())
+    assert np.abs(st[:, :, 1] / rstd - 1).max() <= 5e-6
+
+
 # the last two have rows long enough for the sliding-window activation kernel (C padded to 64, ragged last step)
 CASES = [(1, 8, 8, 4, 4, 4), (2, 24, 40, 9, 13, 4), (1, 64, 130, 17, 30, 32), (2, 96, 40, 16, 16, 32), (1, 40, 33, 33, 6, 8),
          (2, 60, 8, 7, 216, 4), (1, 128, 6, 5, 108, 32)]
