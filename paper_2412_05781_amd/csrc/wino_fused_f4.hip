@@ -54,11 +54,12 @@ template <typename E> __device__ __forceinline__ float hi16(uint32_t w) { const 
 
 struct Fused4Geom { int N, K, H, W, th, tw, T; };
 
+__device__ const uint4 zero_chunk = {0u, 0u, 0u, 0u};     // source of the chunks beyond Cp
+
 }  // namespace
 
 // Block = (WGM * 16) rows x (WGN * 32) columns, one 16 x 32 piece per wave.
-// RAGGED = true: Cp is not a multiple of the stage (64 elements); the last stage of every position then goes through
-// registers with zero fill.
+// RAGGED = true: Cp is not a multiple of the stage (64 elements); the chunks beyond Cp of the last stage of every position are zeros.
 template <typename E, int NST, int WGM, int WGN, bool ROWS_K, bool RAGGED>
 __global__ void __launch_bounds__(WGM * WGN * 64)
 wino_fused_f4_kernel(const E* __restrict__ Aop, const E* __restrict__ Bop, const float* __restrict__ bias, E* __restrict__ y,
@@ -120,14 +121,14 @@ wino_fused_f4_kernel(const E* __restrict__ Aop, const E* __restrict__ Bop, const
     int issue_kt = 0;
     auto issue_stage = [&](int slot) __attribute__((always_inline)) {                    // the next stage in order, into ring slot `slot`
         const uint32_t dst = wave_dst + (uint32_t)slot * STAGE_BYTES;
-        if (RAGGED && issue_kt == nk - 1) {
+        if (RAGGED && issue_kt == nk - 1) {               // chunks beyond Cp come from the line of zeros
+            const unsigned char* zero = reinterpret_cast<const unsigned char*>(&zero_chunk);
 #pragma unroll
             for (int i = 0; i < LPW; ++i) {
                 const int row = (wave + NW * i) * RPL + lrow;
                 const int chunk = lchunk ^ ((row >> 1) & (CPR - 1));
-                uint4 v = make_uint4(0, 0, 0, 0);
-                if ((size_t)issue_kt * RB + (size_t)chunk * 16 < row_bytes) v = *reinterpret_cast<const uint4*>((i < LA ? sA : sB) + goff[i]);
-                *reinterpret_cast<uint4*>(lds + (size_t)slot * STAGE_BYTES + (size_t)(wave + NW * i) * 1024 + lane * 16) = v;
+                const bool past = (size_t)issue_kt * RB + (size_t)chunk * 16 >= row_bytes;
+                dma_load_1k_v(past ? zero : (i < LA ? sA : sB) + goff[i], dst + (uint32_t)(NW * i) * 1024u);
             }
         } else {
 #pragma unroll
@@ -245,7 +246,8 @@ wino_fused_f4_kernel(const E* __restrict__ Aop, const E* __restrict__ Bop, const
     // Stages are taken in pairs (36 * nk is even), one barrier per pair: on entry the pair is visible and the fragments of its first stage
     // have been requested.  The transfers bound the kernel, so this gains little over a barrier per stage and half the ring (whole calls:
     // 256 channels at 512x512 334 -> 327 us, 512 at 256x256 channel-last 238 -> 236, 128 at 1024x1024 channel-last 494 -> 491).  Blocks
-    // of 32 tiles x 128 channels, which fetch V half as often and U twice, are slower (349, 268 and 530).
+    // of 32 tiles x 128 channels, which fetch V half as often and U twice, are slower (349, 268 and 530).  The figures are of the 64x64
+    // block, one workgroup to a compute unit with either ring; for the 32x64 block see launch_fused4_t.
     const int pairs = total / 2;
     auto first_half = [&](int slot) __attribute__((always_inline)) {
         read_stage(slot + 1, I1());
@@ -405,14 +407,19 @@ int fused4_pick_shape(int rows, int cols) {
     return big >= 200 ? 0 : 1;
 }
 
+// The ring of the 32x64 block has six slots, 72 KB, because two workgroups then share a compute unit; with eight only one fits, with four
+// the next pair is waited for as soon as it is requested.  Whole calls, us, four / six / eight slots: 352 channels at 160x160 (N=4) 336 /
+// 323 / 453, 96 -> 128 at 512x512 131 / 128 / 199, 64 -> 896 at 49x234 48 / 48 / 76, 512 -> 256 at 64x64 97 / 89 / 89.
+// The chunks beyond Cp come by the same transfers as the rest, from a line of zeros: filled in through registers, the stage waits for
+// every transfer in front of it (352 channels 390 us instead of 323, 96 -> 128 159 instead of 128).
 template <typename E, bool ROWS_K>
 static hipError_t launch_fused4_t(const void* Aop, const void* Bop, int rowsA, int rowsB, const float* bias, void* y,
                                   const Geom& g, const PostOp& post, int shape, hipStream_t s) {
-    if (g.Cp % 64 != 0)       // a reduction length that is not a whole number of stages: the zero-filling last stage
-        return launch_fused4_cfg<E, 8, 2, 2, ROWS_K, true>(Aop, Bop, rowsA, rowsB, bias, y, g, post, s);
+    if (g.Cp % 64 != 0)       // a reduction length that is not a whole number of stages
+        return launch_fused4_cfg<E, 6, 2, 2, ROWS_K, true>(Aop, Bop, rowsA, rowsB, bias, y, g, post, s);
     switch (shape) {
         case 0: return launch_fused4_cfg<E, 8, 4, 2, ROWS_K>(Aop, Bop, rowsA, rowsB, bias, y, g, post, s);
-        case 1: return launch_fused4_cfg<E, 8, 2, 2, ROWS_K>(Aop, Bop, rowsA, rowsB, bias, y, g, post, s);
+        case 1: return launch_fused4_cfg<E, 6, 2, 2, ROWS_K>(Aop, Bop, rowsA, rowsB, bias, y, g, post, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -188,3 +188,26 @@ def test_f4_fused_is_for_two_byte_storage_only():
     with pytest.raises(B.WinoError) as e:
         B.wino_fused_gemm_output(Uh, Uh, None, 1, 8, 4, 4, 8, block_shape=2, m=4)
     assert e.value.status == B.WINO_ERR_VARIANT
+
+
+@pytest.mark.parametrize("layout", [B.WINO_NCHW, B.WINO_NHWC])
+@pytest.mark.parametrize("C", [8, 40, 96, 120, 136, 352])
+def test_f4_ragged_stage_multiplies_zeros_only(C, layout):
+    """Cp off the stage: the chunks beyond Cp are zeros, not the start of the next row of V or U.  A NaN in one tile (its pixel lies in that
+    tile's window only) and one in the filter of one output channel stay there; everything else keeps its bits.  One, two and
+    several stages per position, odd and even."""
+    N, K, H, W = 1, 72, 16, 24
+    x, w, b = synth.make_inputs(N, C, K, H, W, "f16", seed=7300 + C)
+    perm = (lambda t: t.permute(0, 2, 3, 1).contiguous()) if layout == B.WINO_NHWC else (lambda t: t)
+    run = lambda a, f: _nchw(B.conv2d(perm(a).to(DEV), f.to(DEV), b.to(DEV), B.WINO_FUSED_F4, layout=layout), layout)
+    clean = run(x, w)
+    pu.check(clean, oracle.conv2d_direct(_np(x), _np(w), _np(b)), TOL["f16"], 4, "f16", what=(C, layout), channels=C)
+    xn, wn = x.clone(), w.clone()
+    xn[0, 0, 9, 10] = float("nan")               # tile (2, 2)
+    wn[33, 0, 1, 1] = float("nan")
+    y = run(xn, w)
+    hit = np.zeros((H, W), bool); hit[8:12, 8:12] = True
+    assert np.isnan(y[:, :, hit]).all() and np.array_equal(y[:, :, ~hit], clean[:, :, ~hit])
+    y = run(x, wn)
+    rest = np.arange(K) != 33
+    assert np.isnan(y[:, 33]).all() and np.array_equal(y[:, rest], clean[:, rest])
