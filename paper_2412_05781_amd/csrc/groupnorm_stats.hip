@@ -1,8 +1,9 @@
 // Mean and 1/sqrt(var + eps) per (image, channel group): the statistics that the activation
 // transform needs to apply GroupNorm + SiLU while it loads x (the operators next to the 3x3
 // convolution inside a residual block; the paper's Section "Techniques" argues for keeping such
-// dependent steps local).  Partial (sum, sum of squares) per slice of a group, fp32 per lane and
-// fp64 from the block reduction on; then one wave per group merges the slices.  Where a group is
+// dependent steps local).  Partial (sum, sum of squares) per slice of a group: fp32 over at most 32
+// elements of a lane, fp64 from there on; then one wave per group merges the slices.  (Channel-last a
+// lane adds all its pixels of a slab in fp32, see there.)  Where a group is
 // small enough for one workgroup (NCHW, at most kWholeGroupBytes) that workgroup writes the
 // statistics itself and the second launch is saved.
 // Deterministic (fixed reduction trees, no atomics).  Bound by reading x once from HBM, and for the
@@ -35,13 +36,25 @@ __device__ __forceinline__ void write_stats(float* stats, int ng, double s, doub
     stats[(size_t)ng * 2 + 1] = (float)(1.0 / sqrt(var + (double)eps));
 }
 
-// block reduction of (s, q): fp32 inside a wave (shuffles), fp64 across the waves; the total is valid in thread 0
+// Sum over the wave, valid in its last lane: four shifts inside the rows of 16 lanes, then rows 0 and 2 to rows 1 and 3, then the lower
+// half to the upper.  Shuffles through LDS take 0.1-0.4 us more.
+template <int CTRL, int ROWS> __device__ __forceinline__ double add_lanes(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0u, (uint32_t)u, CTRL, ROWS, 0xf, false), hi = __builtin_amdgcn_update_dpp(0u, (uint32_t)(u >> 32), CTRL, ROWS, 0xf, false);
+    return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+    v = add_lanes<0x111, 0xf>(v); v = add_lanes<0x112, 0xf>(v); v = add_lanes<0x114, 0xf>(v); v = add_lanes<0x118, 0xf>(v);
+    v = add_lanes<0x142, 0xa>(v);
+    return add_lanes<0x143, 0xc>(v);
+}
+
+// block reduction of (s, q); the total is valid in thread 0
 template <int WAVES>
-__device__ __forceinline__ void block_reduce(float s, float q, double& ts, double& tq) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) { s += __shfl_down(s, off, 64); q += __shfl_down(q, off, 64); }
+__device__ __forceinline__ void block_reduce(double s, double q, double& ts, double& tq) {
+    s = wave_sum(s); q = wave_sum(q);
     __shared__ double ws[WAVES], wq[WAVES];
-    if ((threadIdx.x & 63) == 0) { ws[threadIdx.x >> 6] = (double)s; wq[threadIdx.x >> 6] = (double)q; }
+    if ((threadIdx.x & 63) == 63) { ws[threadIdx.x >> 6] = s; wq[threadIdx.x >> 6] = q; }
     __syncthreads();
     ts = 0.0; tq = 0.0;
     if (threadIdx.x == 0) {
@@ -62,8 +75,9 @@ groupnorm_vec_kernel(const E* __restrict__ x, double* __restrict__ partial, floa
     const E* base = x + (size_t)ng * group_elems;          // groups of all images are laid end to end
     const size_t lo = (size_t)sl * per_slice;
     size_t hi = lo + per_slice; hi = hi < group_elems ? hi : group_elems;
-    float s = 0.f, q = 0.f;
+    double ds = 0.0, dq = 0.0;
     for (size_t e0 = lo + (size_t)threadIdx.x * EPC; e0 < hi; e0 += (size_t)4 * THREADS * EPC) {
+        float s = 0.f, q = 0.f;
         uint4 raw[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -78,9 +92,10 @@ groupnorm_vec_kernel(const E* __restrict__ x, double* __restrict__ partial, floa
 #pragma unroll
             for (int i = 0; i < EPC; ++i) { const float f = to_f32<E>(v[i]); s += f; q = fmaf(f, f, q); }
         }
+        ds += (double)s; dq += (double)q;
     }
     double ts, tq;
-    block_reduce<THREADS / 64>(s, q, ts, tq);
+    block_reduce<THREADS / 64>(ds, dq, ts, tq);
     if (threadIdx.x == 0) {
         if (WHOLE) write_stats(stats, ng, ts, tq, inv_count, eps);
         else { double* dst = partial + ((size_t)ng * split + sl) * 2; dst[0] = ts; dst[1] = tq; }
@@ -88,8 +103,10 @@ groupnorm_vec_kernel(const E* __restrict__ x, double* __restrict__ partial, floa
 }
 
 // Channel-last, C a multiple of 8: a workgroup reads the channels of `gpb` groups of a slab of pixels, a lane the same eight channels of
-// every PX-th pixel (16-byte loads that run along the channels).  Lane sums are added per channel over the pixel lanes and then per
-// group in fp64.  Read group by group instead, a group of 10...40 channels is a 20...80-byte piece of every pixel
+// every PX-th pixel (16-byte loads that run along the channels), added in fp32: 1/32 of the pixels over 4096 / (channels of the workgroup)
+// lanes, 128 elements for 128 channels at 1024x1024.  (fp64 after 32 of them costs 20 % of the time, 16.6 -> 19.9 us for 512 channels at
+// 256x256, and changes the largest error of a standard deviation from 6.0e-8 to 6.0e-8.)  Lane sums are added per channel over the pixel
+// lanes, rounded to fp32, and added per group, both in fp64.  Read group by group instead, a group of 10...40 channels is a 20...80-byte piece of every pixel
 // (N=2, 1280 channels at 16x16: 10.7 -> 6.8 us; 512 channels at 256x256: 66 -> 17 us = 3.9 TB/s).
 // The workgroups of a slab, which share the lines of its pixels, are neighbours in one XCD's range.  (All channels to a workgroup and 256
 // slabs would take eight times the buffer; 128 channels at 1024x1024 in 43 us instead of 55, 320 at 64x64 in 8.6 instead of 7.7.)
@@ -132,9 +149,9 @@ groupnorm_partial_nhwc_vec_kernel(const E* __restrict__ x, double* __restrict__ 
     }
     __syncthreads();
     for (int c = threadIdx.x; c < CW; c += THREADS) {       // over the pixel lanes, fixed order
-        float a = ls[c], b = lq[c];
-        for (int k = 1; k < px; ++k) { a += ls[k * CW + c]; b += lq[k * CW + c]; }
-        ls[c] = a; lq[c] = b;                               // only this lane touches column c
+        double a = 0.0, b = 0.0;
+        for (int k = 0; k < px; ++k) { a += (double)ls[k * CW + c]; b += (double)lq[k * CW + c]; }
+        ls[c] = (float)a; lq[c] = (float)b;                 // only this lane touches column c
     }
     __syncthreads();
     for (int g = threadIdx.x; g < ng; g += THREADS) {
@@ -154,29 +171,32 @@ groupnorm_partial_kernel(const E* __restrict__ x, double* __restrict__ partial, 
     const size_t elems = (size_t)cpg * HW;
     const size_t lo = (size_t)sl * per_slice;
     size_t hi = lo + per_slice; hi = hi < elems ? hi : elems;
-    float s = 0.f, q = 0.f;
-    for (size_t e = lo + threadIdx.x; e < hi; e += 256) {
-        size_t idx;
-        if (NHWC) { const size_t p = e / cpg; const int j = (int)(e - p * cpg); idx = ((size_t)n * HW + p) * C + (size_t)g * cpg + j; }
-        else idx = ((size_t)n * C + (size_t)g * cpg) * HW + e;
-        const float v = to_f32<E>(x[idx]);
-        s += v; q = fmaf(v, v, q);
+    double ds = 0.0, dq = 0.0;
+    for (size_t eb = lo + threadIdx.x; eb < hi; eb += 32 * 256) {
+        float s = 0.f, q = 0.f;
+        for (size_t e = eb; e < hi && e < eb + 32 * 256; e += 256) {
+            size_t idx;
+            if (NHWC) { const size_t p = e / cpg; const int j = (int)(e - p * cpg); idx = ((size_t)n * HW + p) * C + (size_t)g * cpg + j; }
+            else idx = ((size_t)n * C + (size_t)g * cpg) * HW + e;
+            const float v = to_f32<E>(x[idx]);
+            s += v; q = fmaf(v, v, q);
+        }
+        ds += (double)s; dq += (double)q;
     }
     double ts, tq;
-    block_reduce<4>(s, q, ts, tq);
+    block_reduce<4>(ds, dq, ts, tq);
     if (threadIdx.x == 0) { double* dst = partial + ((size_t)ng * split + sl) * 2; dst[0] = ts; dst[1] = tq; }
 }
 
-// One wave per group: the slices are loaded side by side and added in a fixed shuffle tree.
+// One wave per group: the slices are loaded side by side and added in a fixed tree.
 __global__ void __launch_bounds__(64)
 groupnorm_finalize_kernel(const double* __restrict__ partial, float* __restrict__ stats, int split, double inv_count, float eps) {
     const int ng = blockIdx.x, lane = threadIdx.x;
     const double2* src = reinterpret_cast<const double2*>(partial) + (size_t)ng * split;
     double s = 0.0, q = 0.0;
     for (int i = lane; i < split; i += 64) { const double2 v = src[i]; s += v.x; q += v.y; }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) { s += __shfl_down(s, off, 64); q += __shfl_down(q, off, 64); }
-    if (lane == 0) write_stats(stats, ng, s, q, inv_count, eps);
+    s = wave_sum(s); q = wave_sum(q);
+    if (lane == 63) write_stats(stats, ng, s, q, inv_count, eps);
 }
 
 hipError_t launch_groupnorm_stats(const void* x, float* stats, int N, int C, int H, int W, int groups, float eps,

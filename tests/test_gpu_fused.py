@@ -43,10 +43,10 @@ def test_groupnorm_stats(dtype, groups):
 
 @pytest.mark.parametrize("layout", [B.WINO_NCHW, B.WINO_NHWC])
 @pytest.mark.parametrize("shape", [(2, 64, 37, 53, 32), (1, 8, 256, 256, 8), (1, 8, 256, 264, 8), (2, 16, 300, 300, 2), (1, 320, 9, 7, 32),
-                                   (1, 4104, 3, 3, 8)])
+                                   (1, 4104, 3, 3, 8), (2, 1280, 16, 16, 1), (1, 200, 30, 31, 2), (2, 520, 20, 9, 8), (1, 96, 700, 400, 3)])
 def test_groupnorm_stats_routes(shape, layout):
-    """One workgroup per group up to 128 KB and slices beyond, channel octets straddling groups, channel counts beyond one
-    workgroup; the sums are fp32 over at most 128 elements per lane and fp64 from there on: a few fp32 roundings."""
+    """One workgroup per group up to 128 KB and slices beyond, channel octets straddling groups, channel counts beyond one workgroup, few
+    groups of many channels; at most 32 elements of a lane (a slab's pixels channel-last) are added in fp32: a few fp32 roundings."""
     N, C, H, W, G = shape
     x = (torch.randn(N, C, H, W, generator=torch.Generator().manual_seed(C + W)) * 0.7 - 0.3).half()
     xd = (x.permute(0, 2, 3, 1).contiguous() if layout == B.WINO_NHWC else x).to(DEV)
@@ -54,6 +54,24 @@ def test_groupnorm_stats_routes(shape, layout):
     mean, rstd = fo.groupnorm_stats(_np(x), G, 1e-5)
     assert np.abs(st[:, :, 0] - mean).max() <= 2e-6 * (1 + np.abs(mean).max())
     assert np.abs(st[:, :, 1] / rstd - 1).max() <= 5e-6
+
+
+@pytest.mark.parametrize("layout,chain", [(B.WINO_NCHW, 32), (B.WINO_NHWC, 128)])
+def test_groupnorm_stats_length_of_the_fp32_sums(layout, chain):
+    """One constant per group of 16 million elements: the sum of fp16 constants is exact in fp32 up to 2^13 of them, so the variance that is
+    left is the rounding of the sum of squares.  A sum of n equal terms is off by at most n/2 * 2^-24 of itself (every addition by 2^-24 of
+    the sum so far); `chain` terms are added in fp32 (channel-last, then one rounding of the lane's sum), the rest in fp64."""
+    consts = [0.1, 0.7, 1.3, 2.9]
+    x = torch.empty(1, 64, 1024, 1024, dtype=torch.float16, device=DEV)
+    for g, c in enumerate(consts):
+        x[:, 16 * g:16 * g + 16] = c
+    x = x.permute(0, 2, 3, 1).contiguous() if layout == B.WINO_NHWC else x
+    st = B.stats_view(B.wino_groupnorm_stats(x, 4, 1e-5, layout), 1, 4).cpu().numpy().astype(np.float64)[0]
+    c = np.float16(consts).astype(np.float64)
+    assert np.array_equal(st[:, 0], c)
+    # the stored standard deviation is itself rounded to fp32: 2^-23 of (variance + eps)
+    bound = (chain / 2 + (1 if layout == B.WINO_NHWC else 0)) * 2.0 ** -24 * c * c + 2.0 ** -23 * 2e-5
+    assert np.all(st[:, 1] ** -2 - 1e-5 <= bound), (st[:, 1] ** -2 - 1e-5, bound)
 
 
 @pytest.mark.parametrize("layout", [B.WINO_NCHW, B.WINO_NHWC])
