@@ -110,12 +110,18 @@ __device__ __forceinline__ float pre_apply(float x, const PreLane& l, bool in_im
     const float v = fmaf(x, l.sc, l.sh);
     return __fdividef(v, 1.f + __expf(-v));
 }
-// The same for values that are rounded to a two-byte type afterwards: hardware exponential and reciprocal (one unit in the last place
-// of fp32 each) instead of the full division's refinement steps, and a select instead of a branch.  fp32 storage keeps pre_apply.
+// The same quotient in fewer instructions and without a branch, for two-byte storage: reciprocal, product and one correction instead of
+// the division's scaling and second correction.  The denominator is at least 1, so there is nothing to scale at that end; above 2^126
+// (v < -87.3) its reciprocal would be flushed to zero, which bf16 could tell from the result (1e-36), so there a quarter of it is inverted.
+// The fixup keeps v / infinity, infinities and NaN as the division has them.  Compared with pre_apply over all 2^32 values of v: the bf16
+// form is equal bit for bit, the fp16 form after rounding to fp16.  10 and 8 vector instructions against 14 (whole calls with GroupNorm,
+// us: 512 channels at 256x256 fp16 324 with the division's kernel, 305 here; 320 at 128x128 bf16 97.2 with the division, 94.6 here; the
+// bare reciprocal, 5 instructions, 301 and 90.9, has twice the error).
 template <typename E> __device__ __forceinline__ float pre_apply_as(float x, const PreLane& l, bool in_image) {
     if constexpr (sizeof(E) == 4) return pre_apply(x, l, in_image);
-    const float v = fmaf(x, l.sc, l.sh);
-    const float r = v * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(v * -1.44269504f));
+    const float v = fmaf(x, l.sc, l.sh), e = __expf(-v), d = 1.f + e;
+    const float i = std::is_same_v<E, bf16_t> ? 0.25f * __builtin_amdgcn_rcpf(fmaf(e, 0.25f, 0.25f)) : __builtin_amdgcn_rcpf(d);
+    const float q = v * i, r = __builtin_amdgcn_div_fixupf(fmaf(fmaf(-d, q, v), i, q), d, v);
     return l.on && in_image ? r : 0.f;
 }
 

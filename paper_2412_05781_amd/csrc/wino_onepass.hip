@@ -162,12 +162,7 @@ wino_onepass_f2_kernel(const E* __restrict__ x, const E* __restrict__ U, const f
     auto put_constants = [&]() __attribute__((always_inline)) {          // same arithmetic as pre_lane
         if (has_pre && tid < 64) { const float sc = cg * cr; csc[tid] = sc; csh[tid] = cb - cm * sc; }
     };
-    // v / (1 + e^-v) on the hardware's exponential and reciprocal (one unit in the last place each); the library forms of the two
-    // spend eight more instructions on subnormal results, which are rounded away here
-    auto silu = [&](float v, float sc, float sh) __attribute__((always_inline)) {
-        v = fmaf(v, sc, sh);
-        return v * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(v * -1.44269504f));
-    };
+    auto silu = [&](float v, float sc, float sh) __attribute__((always_inline)) { return pre_apply_as<E>(v, PreLane{sc, sh, true}, true); };
     auto convert = [&](int j) __attribute__((always_inline)) {
         const int tid = here(threadIdx.x);
         if constexpr (XM == XM_NHWC) {

@@ -90,6 +90,39 @@ def test_groupnorm_stats_stays_inside_its_buffer(shape, layout):
     assert np.abs(st[:, :, 1] / rstd - 1).max() <= 5e-6
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("variant", [B.WINO_DIRECT, B.WINO_F2])
+def test_silu_is_a_division(dtype, variant):
+    """Images of one pixel and a filter that is 1 in the middle: y is SiLU(x), rounded to the storage type, over its whole range: down to
+    1e-36 (x = -88), where the reciprocal of 1 + e^-x is subnormal, the products with infinity, and NaN.  e^-x carries a relative error of
+    |x| 2^-24 from the rounding of its argument (and as much again from that of log2 e), hence 2^-17 at x = -88, far below bf16's 2^-9; the
+    F(2x2) path multiplies by powers of two only."""
+    td = {"f16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    vals = [0.0, -0.0, 1e-7, -1e-7, 0.3, -0.3, 1.0, -1.0, 5.5, -5.5, 30.0, -16.5, -60.0, -80.0, -87.0, -87.5, -88.0, -88.5, -90.0, -200.0, -3e4, 3e4]
+    if variant == B.WINO_DIRECT:
+        vals += [float("inf"), float("-inf"), float("nan")]
+    x = torch.tensor(vals, dtype=torch.float32).to(td).view(-1, 1, 1, 1)
+    N = len(vals)
+    w = torch.zeros(1, 1, 3, 3, dtype=td); w[0, 0, 1, 1] = 1.0
+    f = B.wino_filter_transform(w.to(DEV), variant)
+    stats = torch.tensor([0.0, 1.0]).repeat(N).view(torch.uint8).to(DEV)          # mean 0, 1/std 1
+    one, zero = torch.ones(1, device=DEV), torch.zeros(1, device=DEV)
+    y = torch.empty(N, 1, 1, 1, dtype=td, device=DEV)
+    ws = torch.empty(max(1 << 16, B.wino_workspace_bytes(N, 1, 1, 1, 1, B.DTYPE_OF[td], variant)), dtype=torch.uint8, device=DEV)
+    B.wino_conv2d_fused(x.to(DEV), f, None, y, ws, B.WINO_NCHW, gn_stats=stats, gn_gamma=one, gn_beta=zero, gn_groups=1)
+    got, xd = y.cpu().double().flatten(), x.double().flatten()
+    d = 1 + torch.exp(-xd)
+    ref = xd / torch.where(d > torch.finfo(torch.float32).max, float("inf"), d)         # an fp32 e^-x: infinite below x = -88.7
+    half_ulp, smallest = (2.0 ** -11, 2.0 ** -25) if dtype == "f16" else (2.0 ** -8, 0.0)
+    for v, a, r in zip(vals, got.tolist(), ref.tolist()):
+        if v == float("-inf") or v != v:
+            assert a != a, (v, a)
+        elif v == float("inf"):
+            assert a == v
+        else:                                          # F(2x2) rounds V and y, the direct path x' and y: equal values, one rounding
+            assert abs(a - r) <= 1.02 * half_ulp * abs(r) + smallest + 1.2e-38, (v, a, r)
+
+
 # the last two have rows long enough for the sliding-window activation kernel (C padded to 64, ragged last step)
 CASES = [(1, 8, 8, 4, 4, 4), (2, 24, 40, 9, 13, 4), (1, 64, 130, 17, 30, 32), (2, 96, 40, 16, 16, 32), (1, 40, 33, 33, 6, 8),
          (2, 60, 8, 7, 216, 4), (1, 128, 6, 5, 108, 32)]
