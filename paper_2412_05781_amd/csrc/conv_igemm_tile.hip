@@ -249,13 +249,22 @@ static const TileShape kTiles[3] = {{64, 64, 0.27, 0.20}, {64, 80, 0.35, 0.295},
 // split reduction, 3 us and the traffic of the partial sums for the second kernel.  Measured, channel-last, us, against the kernels of
 // conv_igemm.hip: 1x1 960 -> 320 at 64x64 (N=2) 15.4 / 18.2, 1920 -> 640 at 64x64 36 / 45, stride 2 320 channels at 64x64 18.2 / 22.1, at
 // 97x121 23.8 / 32.7, 512 channels at 256x256 88 / 110, 3x3 128 channels at 256x256 34 / 39, 512 at 256x256 323 / 338.
-// Left to conv_igemm.hip: 256 output channels and 65536 pixels or more channel-last, where its 256x256 block reads x once instead of
-// twice (3x3 256 channels at 512x512 368 / 355, stride 2 103 / 91).
+// Left to conv_igemm.hip: at least one round of its 256x256 blocks, of a number of channels that they divide, where that is the shorter time.
+// That block fetches half as much per product, and its start and end cost less than those of four small ones; the stages themselves are
+// 5 % longer, so a long reduction prefers the small blocks, and so does a last round that is not full.  Channel-last, us, here / there:
+// 1x1 at 256x256 128 -> 512 53 / 40, 512 -> 512 75 / 63, 1024 -> 1024 203 / 180; 3x3 128 -> 512 121 / 101, 512 -> 512 313 / 307; at 128x128
+// 1024 -> 1024 287 / 295; one and a half rounds (768 channels at 180x180) 1x1 128 in 39.7 / 36.5, 3x3 128 in 85 / 90, 1024 in 77 / 86 (1x1).
+// NCHW, where its stores are the narrower ones: 1x1 at 256x256 64 -> 512 52 / 48, 1024 -> 1024 261 / 246; 3x3 64 -> 512 89 / 81, 320 -> 512 234 / 233.
 IgemmTilePlan igemm_tile_plan(int T, int K, int Cp, int R, int dt, bool nhwc) {
     IgemmTilePlan best{-1, 1};
     if (!(dt == DT_F16 || dt == DT_BF16) || Cp % 64 != 0) return best;
-    if (nhwc && K == 256 && T >= 65536) return best;
     const int stages = R * R * (Cp / 64);
+    const long long wide_blocks = (long long)((T + 255) / 256) * (K / 256);
+    if (K % 256 == 0 && wide_blocks >= 256) {               // one of them, or one of its 128x128 quarters, to a compute unit (us)
+        const double share = (double)wide_blocks / 256.0, rounds = 0.4 * share + 0.6 * (double)((wide_blocks + 255) / 256);
+        const double quarters = (double)((T + 127) / 128) * (double)(K / 128) / 256.0;
+        if (rounds * (15.5 + 1.9 * stages) <= quarters * (nhwc ? 6.3 + 0.4425 * stages : 5.0 + 0.4525 * stages)) return best;
+    }
     // never more ranges than the other kernel takes: the workspace of a call, and with it what fits the library's static scratch, stays
     // what it is there
     const int most_sp = igemm_split_rule(T, K, Cp, R, dt);

@@ -1,0 +1,55 @@
+"""Asks libwino which kernel it takes for a call: the rules themselves (C++ functions of the library, by their mangled names), without a GPU.
+
+Tests use it to state which kernel they run, so that a change of a constant in a rule cannot quietly send them elsewhere."""
+import ctypes
+
+from paper_2412_05781_amd import binding as B
+
+ADDRESS = 0x10000                  # stands for a 16-byte aligned tensor; the rules look at the alignment only
+
+
+class Geom(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in "N C H W K m alpha th tw T Cp".split()]
+
+
+class ConvGeom(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in "N C Cp H W K R st pad Ho Wo T up Hs Ws".split()]
+
+
+class PreOp(ctypes.Structure):
+    _fields_ = [("stats", ctypes.c_void_p), ("gamma", ctypes.c_void_p), ("beta", ctypes.c_void_p), ("groups", ctypes.c_int), ("cpg", ctypes.c_int),
+                ("up", ctypes.c_int)]
+
+
+class Pair(ctypes.Structure):
+    _fields_ = [("a", ctypes.c_int), ("b", ctypes.c_int)]
+
+
+DT = {"f32": B.WINO_F32, "f16": B.WINO_F16, "bf16": B.WINO_BF16}
+INT, BOOL, PTR = ctypes.c_int, ctypes.c_bool, ctypes.c_void_p
+
+
+def _fn(name, restype, *argtypes):
+    f = getattr(B.lib(), name)
+    f.restype, f.argtypes = restype, list(argtypes)
+    return f
+
+
+def _out(n, R, st):
+    return (n + 2 * ((R - 1) // 2) - R) // st + 1
+
+
+def winograd_geom(N, C, K, H, W, m):
+    th, tw = -(-H // m), -(-W // m)
+    return Geom(N, C, H, W, K, m, m + 2, th, tw, N * th * tw, -(-C // 8) * 8)
+
+
+def pre_op(norm=False, up=False, C=1):
+    return PreOp(ADDRESS if norm else None, ADDRESS, ADDRESS, 1, C, int(up))
+
+
+def igemm_tile(N, C, K, H, W, R, st, dtype, nhwc):
+    """(block id, reduction ranges) of the 16x16-tile kernel: 0 = 64x64, 1 = 64x80, 2 = 128x128; id < 0: the kernels of conv_igemm.hip."""
+    f = _fn("_ZN4wino15igemm_tile_planEiiiiib", Pair, INT, INT, INT, INT, INT, BOOL)
+    p = f(N * _out(H, R, st) * _out(W, R, st), K, -(-C // 8) * 8, R, DT[dtype], nhwc)
+    return p.a, p.b
