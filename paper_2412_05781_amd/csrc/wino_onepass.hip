@@ -67,6 +67,7 @@ __device__ __forceinline__ const unsigned char* uniform(const unsigned char* p) 
 }
 
 constexpr int XM_NHWC = 0, XM_NCHW_ROWS = 1, XM_NCHW_ANY = 2;
+constexpr int onepass_most(int xm) { return xm == XM_NCHW_ANY ? 4 : 5; }        // element-wise pixel loads leave no registers for five sub-tiles
 
 }  // namespace
 
@@ -489,57 +490,64 @@ static hipError_t launch_onepass_cfg(const void* x, const void* U, const float* 
 }
 
 // Microseconds of the kernel with NS sub-tiles per wave, as measured (fp16 / bf16): workgroups come in rounds of 256; a chunk of 64
-// channels takes 2.0 (pixels, transform, barriers; NCHW 2.7) plus 0.74 per sub-tile, a workgroup's start and end 4, the launch 3.
-// 320 -> 320 channels, N=2, 128x128, channel-last: 67 predicted, 69 measured; 640 -> 640 at 64x64: 64 and 64; 960 -> 320 at 64x64: 70 and 66.
-static double onepass_us(const Geom& g, bool nhwc, int ns) {
+// channels takes a time for pixels, transform and barriers plus one per sub-tile, more of both where SiLU competes for the vector unit; a
+// workgroup's start and end take 4 and the launch 3.  Element by element, the pixels of a chunk take 4.4 to 6 and those of the first, which
+// nothing hides, 9 more.  Predicted / measured: 320 -> 320 channels, N=2, 128x128, channel-last 67 / 70, NCHW with GroupNorm 88 / 86;
+// 512 at 128x128 NCHW with GroupNorm 116 / 118; element by element 128 -> 128 at 300x300 86 / 91, with GroupNorm 96 / 99, 320 -> 320 at
+// 52x78 (N=2) 53 / 57, with GroupNorm 61 / 63.
+static double onepass_us(const Geom& g, int xm, bool gn, int ns) {
+    static const double pixels[3][2] = {{2.0, 1.2}, {2.7, 2.1}, {4.4, 6.0}}, subtile[3][2] = {{0.74, 1.10}, {0.74, 1.12}, {0.74, 0.74}};     // [xm][gn]
     const long long wgs = (long long)g.N * ((g.th + 3) / 4) * ((g.tw + 7) / 8) * ((g.K + 32 * ns - 1) / (32 * ns));
-    return 3.0 + (double)((wgs + 255) / 256) * (4.0 + (g.C / 64) * ((nhwc ? 2.0 : 2.7) + 0.74 * ns));
+    return 3.0 + (double)((wgs + 255) / 256) * ((xm == XM_NCHW_ANY ? 13.0 : 4.0) + (g.C / 64) * (pixels[xm][gn] + subtile[xm][gn] * ns));
 }
-static int onepass_subtiles(const Geom& g, bool nhwc, int most) {
-    int best = 2;
-    for (int ns = 3; ns <= most; ++ns)
-        if (onepass_us(g, nhwc, ns) < onepass_us(g, nhwc, best)) best = ns;
-    return best;
-}
-static bool onepass_rows(const void* x, const Geom& g, int up) { return g.W % 8 == 0 && !up && (reinterpret_cast<uintptr_t>(x) & 15u) == 0; }
 
-// It applies to whole 128-byte reduction stages and whole 16-channel sub-tiles, and is taken where it is faster than the paths that
-// store V.  Those move V (and the three-kernel chain M) through memory: 8 us + T * (1.26e-5 C + 2.1e-5 K + 2e-8 C K) us for the chain
-// (N=2: 320 channels at 64x64 34 us, 640 at 64x64 70, 960 -> 320 at 64x64 61, 1280 at 32x32 57), 6e-6 T C more with GroupNorm, which
-// costs this kernel next to nothing; 0.8 of that for the fused variant, and 0.62 where its 128-wide blocks have no padding.  One kernel, measured against them (us, NCHW / channel-last): 320 channels at
-// 128x128 81 / 69 against 98 / 98, at 64x64 30 / 25 against 36 / 33, 640 channels at 64x64 73 / 64 against 72 / 69; it loses with more
-// channels on fewer tiles, where the repeated transform and the filter dominate (1280 at 32x32 99 / 83 against 59 / 55).
-bool onepass_conv_ok(const void* x, const Geom& g, int dt, bool nhwc, bool fused_variant, const PreOp* pre) {
-    if (!(two_byte(dt) && dt != DT_I8 && g.m == 2 && g.C % 64 == 0 && g.K % 16 == 0)) return false;
-    if ((size_t)g.C * g.H * g.W >= ((size_t)1 << 31)) return false;            // byte offsets inside an image are 32-bit
-    if ((size_t)g.K * g.C * 2 >= ((size_t)1 << 31)) return false;              // byte offsets inside a position of U too
-    const bool any = !nhwc && !onepass_rows(x, g, pre ? pre->up : 0);
-    const double one = onepass_us(g, nhwc, onepass_subtiles(g, nhwc, any ? 4 : 5));
-    const double stored = 8.0 + (double)g.T * ((pre && pre->stats ? 1.86e-5 : 1.26e-5) * g.C + 2.1e-5 * g.K + 2e-8 * g.C * g.K);
-    return one < 0.95 * stored * (!fused_variant ? 1.0 : (g.K % 128 == 0 ? 0.62 : 0.8));
+// Whether it applies and is taken, and how.  It applies to whole 128-byte reduction stages and whole 16-channel sub-tiles, and is taken
+// where it is faster than the paths that store V.  Those move V (and the three-kernel chain M) through memory: 8 us + T * (1.26e-5 C +
+// 2.1e-5 K + 2e-8 C K) us for the chain (N=2: 320 channels at 64x64 34 us, 640 at 64x64 70, 960 -> 320 at 64x64 61, 1280 at 32x32 57),
+// 6e-6 T C more with GroupNorm; 0.8 of that for the fused variant, and 0.62 where its 128-wide blocks have no padding.  One kernel / the
+// other path (us; chain, and with (f) the fused variant): NCHW 320 channels at 128x128 80 / 111, with GroupNorm 92 / 128, (f) 92 / 103; at 64x64 30
+// / 35, 640 channels at 64x64 with GroupNorm 93 / 88, 256 at 256x256 with GroupNorm (f) 134 / 119; channel-last 320 at 64x64 25 / 34, 512
+// at 256x256 337 / 389; element by element 64 -> 128 at 250x250 47 / 62, (f) 46 / 33, 128 -> 128 at 300x300 93 / 121, (f) 91 / 80, 256 -> 256
+// at 250x250 with GroupNorm 226 / 204, (f) 227 / 126, 320 -> 320 at 52x78 (N=2) with GroupNorm 69 / 46.
+OnepassPlan onepass_plan(const void* x, const Geom& g, int dt, bool nhwc, bool fused_variant, const PreOp* pre) {
+    const OnepassPlan none{0, 0};
+    if (!(two_byte(dt) && dt != DT_I8 && g.m == 2 && g.C % 64 == 0 && g.K % 16 == 0)) return none;
+    if ((size_t)g.C * g.H * g.W >= ((size_t)1 << 31)) return none;             // byte offsets inside an image are 32-bit
+    if ((size_t)g.K * g.C * 2 >= ((size_t)1 << 31)) return none;               // byte offsets inside a position of U too
+    const bool gn = pre && pre->stats, rows = g.W % 8 == 0 && !(pre && pre->up) && (reinterpret_cast<uintptr_t>(x) & 15u) == 0;
+    const int xm = nhwc ? XM_NHWC : (rows ? XM_NCHW_ROWS : XM_NCHW_ANY);
+    OnepassPlan plan{2, xm};
+    for (int ns = 3; ns <= onepass_most(xm); ++ns)
+        if (onepass_us(g, xm, gn, ns) < onepass_us(g, xm, gn, plan.ns)) plan.ns = ns;
+    const double stored = 8.0 + (double)g.T * ((gn ? 1.86e-5 : 1.26e-5) * g.C + 2.1e-5 * g.K + 2e-8 * g.C * g.K);
+    return onepass_us(g, xm, gn, plan.ns) < 0.95 * stored * (!fused_variant ? 1.0 : (g.K % 128 == 0 ? 0.62 : 0.8)) ? plan : none;
 }
 
 template <typename E, int XM>
 static hipError_t launch_onepass_t(const void* x, const void* U, const float* bias, void* y, const Geom& g, const PreOp& pre,
-                                   const PostOp& post, hipStream_t s) {
-    constexpr int MOST = XM == XM_NCHW_ANY ? 4 : 5;       // element-wise pixel loads leave no registers for five
-    switch (onepass_subtiles(g, XM == XM_NHWC, MOST)) {
+                                   const PostOp& post, int ns, hipStream_t s) {
+    switch (ns) {
         case 2: return launch_onepass_cfg<E, 2, XM>(x, U, bias, y, g, pre, post, s);
         case 3: return launch_onepass_cfg<E, 3, XM>(x, U, bias, y, g, pre, post, s);
         case 4: return launch_onepass_cfg<E, 4, XM>(x, U, bias, y, g, pre, post, s);
-        default: return launch_onepass_cfg<E, MOST, XM>(x, U, bias, y, g, pre, post, s);
+        default: break;
     }
+    if constexpr (onepass_most(XM) == 5)
+        if (ns == 5) return launch_onepass_cfg<E, 5, XM>(x, U, bias, y, g, pre, post, s);
+    return hipErrorInvalidValue;
 }
 
-hipError_t launch_onepass_conv(const void* x, const void* U, const float* bias, void* y, const Geom& g, int dt, bool nhwc,
+hipError_t launch_onepass_conv(const void* x, const void* U, const float* bias, void* y, const Geom& g, int dt, const OnepassPlan& plan,
                                const PreOp* prep, const PostOp* postp, hipStream_t s) {
     const PreOp pre = prep ? *prep : PreOp();
     const PostOp post = postp ? *postp : PostOp();
     auto run = [&](auto* tag) {
         using E = std::remove_pointer_t<decltype(tag)>;
-        if (nhwc) return launch_onepass_t<E, XM_NHWC>(x, U, bias, y, g, pre, post, s);
-        return onepass_rows(x, g, pre.up) ? launch_onepass_t<E, XM_NCHW_ROWS>(x, U, bias, y, g, pre, post, s)
-                                          : launch_onepass_t<E, XM_NCHW_ANY>(x, U, bias, y, g, pre, post, s);
+        switch (plan.xm) {
+            case XM_NHWC: return launch_onepass_t<E, XM_NHWC>(x, U, bias, y, g, pre, post, plan.ns, s);
+            case XM_NCHW_ROWS: return launch_onepass_t<E, XM_NCHW_ROWS>(x, U, bias, y, g, pre, post, plan.ns, s);
+            default: return launch_onepass_t<E, XM_NCHW_ANY>(x, U, bias, y, g, pre, post, plan.ns, s);
+        }
     };
     return dt == DT_F16 ? run(static_cast<__half*>(nullptr)) : run(static_cast<bf16_t*>(nullptr));
 }
