@@ -61,3 +61,17 @@ def onepass(N, C, K, H, W, dtype, nhwc, fused_variant=False, norm=False, up=Fals
     f = _fn("_ZN4wino12onepass_planEPKvRKNS_4GeomEibbPKNS_5PreOpE", Pair, PTR, ctypes.POINTER(Geom), INT, BOOL, BOOL, ctypes.POINTER(PreOp))
     p = f(address, ctypes.byref(winograd_geom(N, C, K, H, W, 2)), DT[dtype], nhwc, fused_variant, ctypes.byref(pre_op(norm, up, C)))
     return p.a, p.b
+
+
+def fp8_tile(N, C, K, H, W, R, st, dtype, nhwc, nsplit=1):
+    """Whether the pipelined kernel takes an 8-bit direct call with an unsplit reduction."""
+    f = _fn("_ZN4wino17igemm_fp8_tile_okERKNS_8ConvGeomEibi", BOOL, ctypes.POINTER(ConvGeom), INT, BOOL, INT)
+    Ho, Wo = _out(H, R, st), _out(W, R, st)
+    g = ConvGeom(N, C, -(-C // 16) * 16, H, W, K, R, st, (R - 1) // 2, Ho, Wo, N * Ho * Wo, 0, H, W)
+    return f(ctypes.byref(g), DT[dtype], nhwc, nsplit)
+
+
+def fewc(N, C, K, H, W, dtype, nhwc, norm=False, up=False):
+    """Whether the one-kernel fp32 F(4x4) path for few input channels takes a call."""
+    f = _fn("_ZN4wino12fewc_conv_okERKNS_4GeomEibPKNS_5PreOpE", BOOL, ctypes.POINTER(Geom), INT, BOOL, ctypes.POINTER(PreOp))
+    return f(ctypes.byref(winograd_geom(N, C, K, H, W, 4)), DT[dtype], nhwc, ctypes.byref(pre_op(norm, up, C)))

@@ -43,3 +43,15 @@ def test_one_kernel_f2_does_not_apply():
         assert routes.onepass(**{**dict(N=1, C=128, K=128, H=512, W=512, dtype="bf16", nhwc=True), **bad})[0] == 0
     assert routes.onepass(1, 128, 128, 512, 512, "bf16", False) [1] == 1
     assert routes.onepass(1, 128, 128, 512, 512, "bf16", False, address=routes.ADDRESS + 2)[1] == 2
+
+
+# 8-bit direct path, unsplit reductions: the pipelined kernel from one 128x128 block to a compute unit on, and in NCHW for short reductions
+@pytest.mark.parametrize("N,C,K,H,W,R,st,nhwc,taken", [
+    (1, 64, 128, 32, 32, 1, 1, True, False), (1, 256, 256, 64, 64, 3, 1, True, False), (1, 640, 640, 64, 64, 3, 1, True, False), (1, 128, 128, 57, 175, 3, 2, True, False),
+    (1, 256, 256, 128, 128, 3, 1, True, True), (1, 64, 512, 96, 96, 1, 1, True, True), (1, 128, 128, 1024, 1024, 3, 1, True, True), (1, 256, 256, 512, 512, 3, 1, True, False),
+    (1, 256, 256, 64, 64, 3, 1, False, False), (1, 1280, 320, 64, 64, 3, 1, False, False), (1, 1280, 128, 180, 180, 3, 1, False, False), (1, 64, 256, 64, 64, 3, 1, False, True),
+    (1, 1280, 128, 64, 64, 1, 1, False, True), (1, 256, 256, 128, 128, 3, 1, False, True), (1, 256, 256, 512, 512, 3, 1, False, True)])
+def test_fp8_kernel(N, C, K, H, W, R, st, nhwc, taken):
+    for dtype in ("f16", "bf16"):
+        assert routes.fp8_tile(N, C, K, H, W, R, st, dtype, nhwc) == taken
+    assert not routes.fp8_tile(N, C, K, H, W, R, st, "f32", nhwc) and not routes.fp8_tile(N, C, K, H, W, R, st, "f16", nhwc, nsplit=2)
