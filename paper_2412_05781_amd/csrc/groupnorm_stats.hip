@@ -20,7 +20,7 @@ constexpr int kMaxSplit = 32;
 constexpr size_t kWholeGroupBytes = (size_t)128 << 10;
 // Channel-last: the least bytes of a pixel that a workgroup reads.  Pieces shorter than a 128-byte line fetch the line several times out
 // of L2, longer ones leave compute units idle (fp16, 32 groups, us: 128 channels at 1024x1024, pieces of 32 / 64 / 128 bytes = 256 / 128 /
-// 64 workgroups: 55 / 63 / 84; 512 channels at 256x256 16.6 with any of them).
+// 64 workgroups: 53 / 63 / 84; 512 channels at 256x256 16.6 with any of them).
 constexpr size_t kMinPiece = 32;
 
 size_t groupnorm_stats_bytes(int N, int groups) {
@@ -106,10 +106,10 @@ groupnorm_vec_kernel(const E* __restrict__ x, double* __restrict__ partial, floa
 // every PX-th pixel (16-byte loads that run along the channels), added in fp32: 1/32 of the pixels over 4096 / (channels of the workgroup)
 // lanes, 128 elements for 128 channels at 1024x1024.  (fp64 after 32 of them costs 20 % of the time, 16.6 -> 19.9 us for 512 channels at
 // 256x256, and changes the largest error of a standard deviation from 6.0e-8 to 6.0e-8.)  Lane sums are added per channel over the pixel
-// lanes, rounded to fp32, and added per group, both in fp64.  Read group by group instead, a group of 10...40 channels is a 20...80-byte piece of every pixel
+// lanes and then per group in fp64, rounded to fp32 in between.  Read group by group instead, a group of 10...40 channels is a 20...80-byte piece of every pixel
 // (N=2, 1280 channels at 16x16: 10.7 -> 6.8 us; 512 channels at 256x256: 66 -> 17 us = 3.9 TB/s).
 // The workgroups of a slab, which share the lines of its pixels, are neighbours in one XCD's range.  (All channels to a workgroup and 256
-// slabs would take eight times the buffer; 128 channels at 1024x1024 in 43 us instead of 55, 320 at 64x64 in 8.6 instead of 7.7.)
+// slabs would take eight times the buffer; 128 channels at 1024x1024 in 43 us instead of 53, 320 at 64x64 in 8.7 instead of 7.7.)
 template <typename E, int THREADS>
 __global__ void __launch_bounds__(THREADS)
 groupnorm_partial_nhwc_vec_kernel(const E* __restrict__ x, double* __restrict__ partial, int C, int HW, int groups, int cpg,
@@ -148,9 +148,22 @@ groupnorm_partial_nhwc_vec_kernel(const E* __restrict__ x, double* __restrict__ 
         for (int i = 0; i < EPC; ++i) { ls[pl * CW + oct * EPC + i] = s[i]; lq[pl * CW + oct * EPC + i] = q[i]; }
     }
     __syncthreads();
-    for (int c = threadIdx.x; c < CW; c += THREADS) {       // over the pixel lanes, fixed order
+    // over the pixel lanes, fixed order; many of them in two steps (256 pixel lanes over 16 channels left 16 lanes with 256 pairs of LDS reads each:
+    // 64 channels at 256x256 12.6 -> 9.3 us)
+    int rows = px;
+    if (px > 16) {
+        rows = min(16, THREADS / CW);
+        const int part = threadIdx.x / CW, c = threadIdx.x - part * CW;
+        if (part < rows) {
+            double a = 0.0, b = 0.0;
+            for (int k = part; k < px; k += rows) { a += (double)ls[k * CW + c]; b += (double)lq[k * CW + c]; }
+            ls[part * CW + c] = (float)a; lq[part * CW + c] = (float)b;     // only this lane touches rows part, part + rows, ... of column c
+        }
+        __syncthreads();
+    }
+    for (int c = threadIdx.x; c < CW; c += THREADS) {
         double a = 0.0, b = 0.0;
-        for (int k = 0; k < px; ++k) { a += (double)ls[k * CW + c]; b += (double)lq[k * CW + c]; }
+        for (int k = 0; k < rows; ++k) { a += (double)ls[k * CW + c]; b += (double)lq[k * CW + c]; }
         ls[c] = (float)a; lq[c] = (float)b;                 // only this lane touches column c
     }
     __syncthreads();
