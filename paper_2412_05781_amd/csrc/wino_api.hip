@@ -89,7 +89,7 @@ int run_chain(const void* x, const wino_filter* w_t, const float* bias, void* y,
     const Workspace ws = workspace_layout(g, w_t->dtype, w_t->variant);
     void* V = workspace;
     float* M = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + ws.v_bytes);
-    if (fewc_conv_ok(g, dt, pre))
+    if (fewc_conv_ok(g, dt, nhwc, pre))
         return launch_fewc_conv(x, w_t->data, bias, y, g, nhwc, pre, post, s) == hipSuccess ? WINO_OK : WINO_ERR_HIP;
     // (a caller that asks for the fp16 product gets the chain that has one)
     if (!(half_product && w_t->variant == WINO_F2 && dt == WINO_F16)) {

@@ -132,7 +132,7 @@ hipError_t launch_fewk_conv3x3(const void* x, const void* Wr, const float* bias,
 
 // All three steps in one kernel for F(4x4) in fp32 with few input channels (wino_fewc.hip): whether it applies, and the launch.
 // U as for the F(4x4) chain; no workspace.
-bool fewc_conv_ok(const Geom& g, int dt, const PreOp* pre);
+bool fewc_conv_ok(const Geom& g, int dt, bool nhwc, const PreOp* pre);
 hipError_t launch_fewc_conv(const void* x, const void* U, const float* bias, void* y, const Geom& g, bool nhwc, const PreOp* pre,
                             const PostOp* post, hipStream_t s);
 
