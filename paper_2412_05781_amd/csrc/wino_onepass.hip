@@ -504,10 +504,11 @@ static double onepass_us(const Geom& g, int xm, bool gn, int ns) {
 // Whether it applies and is taken, and how.  It applies to whole 128-byte reduction stages and whole 16-channel sub-tiles, and is taken
 // where it is faster than the paths that store V.  Those move V (and the three-kernel chain M) through memory: 8 us + T * (1.26e-5 C +
 // 2.1e-5 K + 2e-8 C K) us for the chain (N=2: 320 channels at 64x64 34 us, 640 at 64x64 70, 960 -> 320 at 64x64 61, 1280 at 32x32 57),
-// 6e-6 T C more with GroupNorm; 0.8 of that for the fused variant, and 0.62 where its 128-wide blocks have no padding.  One kernel / the
-// other path (us; chain, and with (f) the fused variant): NCHW 320 channels at 128x128 80 / 111, with GroupNorm 92 / 128, (f) 92 / 103; at 64x64 30
-// / 35, 640 channels at 64x64 with GroupNorm 93 / 88, 256 at 256x256 with GroupNorm (f) 134 / 119; channel-last 320 at 64x64 25 / 34, 512
-// at 256x256 337 / 389; element by element 64 -> 128 at 250x250 47 / 62, (f) 46 / 33, 128 -> 128 at 300x300 93 / 121, (f) 91 / 80, 256 -> 256
+// 6e-6 T C more with GroupNorm and a twelfth more element by element, for at least 128 output channels; 0.84 of that for the fused
+// variant, and 0.62 where its 128-wide blocks have no padding, but at least the serial chain of its 16 positions, 14 us + 0.075 C.  One
+// kernel / the other path (us; chain, and with (f) the fused variant): NCHW 320 channels at 128x128 80 / 111, with GroupNorm 92 / 128, (f) 92 / 103; at 64x64 30
+// / 35, 640 channels at 64x64 with GroupNorm 93 / 88, 256 at 256x256 with GroupNorm (f) 134 / 119; channel-last 320 at 64x64 25 / 34, with
+// GroupNorm (f) 36 / 51, 512 at 256x256 337 / 389; element by element 64 -> 128 at 250x250 47 / 62, (f) 46 / 33, 128 -> 128 at 300x300 93 / 121, (f) 91 / 80, 192 -> 96 at 500x300 (f) 164 / 198, 256 -> 256
 // at 250x250 with GroupNorm 226 / 204, (f) 227 / 126, 320 -> 320 at 52x78 (N=2) with GroupNorm 69 / 46.
 OnepassPlan onepass_plan(const void* x, const Geom& g, int dt, bool nhwc, bool fused_variant, const PreOp* pre) {
     const OnepassPlan none{0, 0};
@@ -519,8 +520,15 @@ OnepassPlan onepass_plan(const void* x, const Geom& g, int dt, bool nhwc, bool f
     OnepassPlan plan{2, xm};
     for (int ns = 3; ns <= onepass_most(xm); ++ns)
         if (onepass_us(g, xm, gn, ns) < onepass_us(g, xm, gn, plan.ns)) plan.ns = ns;
-    const double stored = 8.0 + (double)g.T * ((gn ? 1.86e-5 : 1.26e-5) * g.C + 2.1e-5 * g.K + 2e-8 * g.C * g.K);
-    return onepass_us(g, xm, gn, plan.ns) < 0.95 * stored * (!fused_variant ? 1.0 : (g.K % 128 == 0 ? 0.62 : 0.8)) ? plan : none;
+    const double K = g.K < 128 ? 128.0 : (double)g.K, C = (double)g.C, norm = gn ? 6e-6 * g.T * C : 0.0;
+    double other = 8.0 + (double)g.T * (1.26e-5 * C + 2.1e-5 * K + 2e-8 * C * K) + norm;
+    if (xm == XM_NCHW_ANY && !(pre && pre->up)) other *= 1.08;
+    if (fused_variant) {
+        const double chain = 14.0 + 0.075 * C + norm;
+        other *= g.K % 128 == 0 ? 0.62 : 0.84;
+        other = other > chain ? other : chain;
+    }
+    return onepass_us(g, xm, gn, plan.ns) < 0.95 * other ? plan : none;
 }
 
 template <typename E, int XM>

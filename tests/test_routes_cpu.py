@@ -26,13 +26,15 @@ def test_direct_path_wide_blocks(N, C, K, H, W, R, st, nhwc, wide, dtype):
 @pytest.mark.parametrize("N,C,K,H,W,nhwc,fused,norm,up,taken", [
     # element by element: rows of no whole 16-byte pieces, and upsampling
     (2, 320, 320, 52, 78, False, False, True, False, False), (1, 256, 256, 250, 250, False, True, True, False, False), (1, 256, 256, 250, 250, False, False, True, False, False),
-    (1, 128, 256, 200, 204, False, True, False, False, False), (1, 128, 256, 200, 204, False, True, False, True, False), (1, 64, 128, 250, 250, False, True, False, False, False),
+    (1, 128, 256, 200, 204, False, True, False, False, False), (1, 128, 256, 200, 204, False, True, False, True, False), (1, 192, 96, 500, 300, False, True, False, False, True),
+    (1, 64, 128, 250, 250, False, True, False, False, False),
     (1, 128, 128, 300, 300, False, True, True, False, False), (1, 64, 320, 140, 142, False, True, True, False, False),
     (1, 64, 128, 250, 250, False, False, True, False, True), (1, 128, 128, 300, 300, False, False, False, True, True), (1, 192, 96, 500, 300, False, False, True, False, True),
     # whole pieces, channel-last
     (2, 640, 640, 64, 64, False, False, True, False, False), (1, 512, 512, 128, 128, False, False, True, False, False), (1, 512, 512, 256, 256, False, False, True, False, False),
     (1, 256, 256, 256, 256, False, True, True, False, False), (2, 320, 320, 64, 64, False, False, True, False, True), (2, 320, 320, 128, 128, False, True, True, False, True),
-    (1, 256, 256, 256, 256, True, True, True, False, True), (2, 192, 192, 104, 152, False, False, True, False, True), (2, 1280, 1280, 32, 32, True, False, False, False, False)])
+    (1, 256, 256, 256, 256, True, True, True, False, True), (2, 320, 320, 64, 64, True, True, True, False, True), (1, 512, 256, 128, 128, True, True, True, False, True),
+    (4, 320, 320, 64, 96, True, True, True, False, True), (1, 512, 512, 128, 128, False, True, False, False, False), (2, 192, 192, 104, 152, False, False, True, False, True), (2, 1280, 1280, 32, 32, True, False, False, False, False)])
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_one_kernel_f2(N, C, K, H, W, nhwc, fused, norm, up, taken, dtype):
     assert (routes.onepass(N, C, K, H, W, dtype, nhwc, fused, norm, up)[0] > 0) == taken
