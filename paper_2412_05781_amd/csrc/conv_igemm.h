@@ -19,9 +19,10 @@ struct IgemmPost {
 
 // The 16x16-tile kernel (conv_igemm_tile.hip): two-byte storage types, Cp a whole number of 128-byte stages.
 // Its choice of block and of the number of reduction ranges; id < 0: it does not apply or another block of conv_igemm.hip is better.
+// plain: nothing but a bias is added to the sums.
 struct IgemmTilePlan { int id, split; };
 int igemm_split_rule(int T, int K, int Cp, int R, int dt);             // ranges where the 16x16-tile kernel does not apply (conv_igemm.hip)
-IgemmTilePlan igemm_tile_plan(int T, int K, int Cp, int R, int dt, bool nhwc);
+IgemmTilePlan igemm_tile_plan(int T, int HoWo, int K, int Cp, int R, int dt, bool nhwc, bool plain);
 hipError_t launch_igemm_tile(const void* xh, const void* Wr, const float* bias, void* y, float* part, const IgemmTilePlan& plan,
                              const ConvGeom& g, const IgemmPost& post, int dt, bool nhwc, hipStream_t s);
 

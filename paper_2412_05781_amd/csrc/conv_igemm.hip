@@ -468,9 +468,9 @@ int igemm_split_rule(int T, int K, int Cp, int R, int dt) {
     if (sp > nstage) sp = nstage;
     return sp < 1 ? 1 : sp;
 }
-int igemm_split(int T, int K, int Cp, int R, int dt, bool nhwc) {
+int igemm_split(int T, int HoWo, int K, int Cp, int R, int dt, bool nhwc) {
     if (dt >= 0) {
-        const IgemmTilePlan plan = igemm_tile_plan(T, K, Cp, R, dt, nhwc);
+        const IgemmTilePlan plan = igemm_tile_plan(T, HoWo, K, Cp, R, dt, nhwc, true);
         if (plan.id >= 0) return plan.split;
     }
     return igemm_split_rule(T, K, Cp, R, dt);
@@ -506,7 +506,7 @@ static hipError_t igemm_conv_t(const void* x, const void* Wr, const float* bias,
                                const PreOp& pre, bool nhwc, void* workspace, size_t xh_bytes, hipStream_t s) {
     const E* xh = static_cast<const E*>(x);
     const int dt = std::is_same_v<E, float> ? DT_F32 : (std::is_same_v<E, __half> ? DT_F16 : DT_BF16);
-    const int nsplit = igemm_split(g.T, g.K, g.Cp, g.R, dt, nhwc);
+    const int nsplit = igemm_split(g.T, g.Ho * g.Wo, g.K, g.Cp, g.R, dt, nhwc);
     float* part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + xh_bytes);   // only used when nsplit > 1
     if (!nhwc) {
         constexpr int EPC = 16 / (int)sizeof(E);
@@ -531,7 +531,7 @@ static hipError_t igemm_conv_t(const void* x, const void* Wr, const float* bias,
         if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
         xh = static_cast<const E*>(workspace);
     }
-    const IgemmTilePlan plan = igemm_tile_plan(g.T, g.K, g.Cp, g.R, dt, nhwc);
+    const IgemmTilePlan plan = igemm_tile_plan(g.T, g.Ho * g.Wo, g.K, g.Cp, g.R, dt, nhwc, !post.addvec && !post.residual);
     if (plan.id >= 0) {
         const hipError_t e = launch_igemm_tile(xh, Wr, bias, y, part, plan, g, post, dt, nhwc, s);
         return e == hipSuccess && plan.split > 1 ? launch_igemm_reduce<E>(part, bias, (E*)y, plan.split, g, post, nhwc, s) : e;
@@ -784,7 +784,7 @@ hipError_t launch_igemm_fp8_conv2d(const void* x, const void* Wq, const float* b
                                    (const EO*)x, (uint32_t*)workspace, g.N, g.C, g.Cp, g.Hs, g.Ws, wtiles, sx, pre);
         }
         if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-        const int nsplit = igemm_split(g.T, g.K, g.Cp, g.R, -1, nhwc);
+        const int nsplit = igemm_split(g.T, g.Ho * g.Wo, g.K, g.Cp, g.R, -1, nhwc);
         float* part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + xq_bytes);
         const fp8_t* xq = static_cast<const fp8_t*>(workspace);
         if (igemm_fp8_tile_ok(g, dt, nhwc, nsplit)) return launch_igemm_fp8_tile(xq, Wq, bias, y, g, post, dt, nhwc, s);

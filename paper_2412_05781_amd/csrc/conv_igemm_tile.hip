@@ -240,13 +240,14 @@ static hipError_t launch_tile_cfg(const E* xh, const E* Wr, const float* bias, E
 }
 
 // Blocks on offer, pixels x output channels, with the time of a reduction stage: `alone` where a compute unit holds one workgroup,
-// `each` per workgroup where it holds several (us, measured).  Three workgroups of 64x64 or two of the others share a unit's LDS; rings
+// `each` per workgroup where it holds several, and `ends` for a workgroup's start and stores, which overlap a little (us, measured; without the last, 1x1 and other
+// short reductions took the 128x128 block too often: 256 -> 560 1x1 at 144x51, N=2, 25.4 with it, 19.9 with 64x64).  Three workgroups of 64x64 or two of the others share a unit's LDS; rings
 // deeper than that and fewer workgroups were slower on every shape (128x128 with three slots, one workgroup per unit, 1.3x).
-struct TileShape { int bp, bk; double alone, each; };
-static const TileShape kTiles[3] = {{64, 64, 0.27, 0.20}, {64, 80, 0.35, 0.295}, {128, 128, 0.65, 0.57}};
+struct TileShape { int bp, bk; double alone, each, ends; };
+static const TileShape kTiles[3] = {{64, 64, 0.27, 0.20, 1.3}, {64, 80, 0.35, 0.295, 1.6}, {128, 128, 0.65, 0.57, 4.6}};
 
-// The block and the number of reduction ranges with the least time by these figures, plus 6 us for launch, start and end and, with a
-// split reduction, 3 us and the traffic of the partial sums for the second kernel.  Measured, channel-last, us, against the kernels of
+// The block and the number of reduction ranges with the least time by these figures, plus 6 us for the launch and, with a split reduction,
+// 1.5 us and the traffic of the partial sums for the second kernel (3x3 128 channels at 17x13, N=2, NCHW: 15.5 us whole, 13.0 in two ranges).  Measured, channel-last, us, against the kernels of
 // conv_igemm.hip: 1x1 960 -> 320 at 64x64 (N=2) 15.4 / 18.2, 1920 -> 640 at 64x64 36 / 45, stride 2 320 channels at 64x64 18.2 / 22.1, at
 // 97x121 23.8 / 32.7, 512 channels at 256x256 88 / 110, 3x3 128 channels at 256x256 34 / 39, 512 at 256x256 323 / 338.
 // Left to conv_igemm.hip: at least one round of its 256x256 blocks, of a number of channels that they divide, where that is the shorter time.
@@ -254,15 +255,20 @@ static const TileShape kTiles[3] = {{64, 64, 0.27, 0.20}, {64, 80, 0.35, 0.295},
 // 5 % longer, so a long reduction prefers the small blocks, and so does a last round that is not full.  Channel-last, us, here / there:
 // 1x1 at 256x256 128 -> 512 53 / 40, 512 -> 512 75 / 63, 1024 -> 1024 203 / 180; 3x3 128 -> 512 121 / 101, 512 -> 512 313 / 307; at 128x128
 // 1024 -> 1024 287 / 295; one and a half rounds (768 channels at 180x180) 1x1 128 in 39.7 / 36.5, 3x3 128 in 85 / 90, 1024 in 77 / 86 (1x1).
+// An image of an odd number of pixels, NCHW (see below), 1x1: 192 -> 320 at 311x201 82 / 75, 256 at 181x181 41 / 38; 1856 -> 1184 at 23x57 (N=2)
+// 45 / 40; but 3x3 256 at 181x181 72 / 74, 320 at 97x121 (N=2) 86 / 118.
+// With a residual or a vector to add it loses: it reads them element by element (bf16 3x3, 256 -> 512 at 360x360: vector 355 / 378 NCHW, 338
+// / 355 channel-last, residual 407 / 524, 380 / 439).  The number of reduction ranges is one either way.
 // NCHW, where its stores are the narrower ones: 1x1 at 256x256 64 -> 512 52 / 48, 1024 -> 1024 261 / 246; 3x3 64 -> 512 89 / 81, 320 -> 512 234 / 233.
-IgemmTilePlan igemm_tile_plan(int T, int K, int Cp, int R, int dt, bool nhwc) {
+IgemmTilePlan igemm_tile_plan(int T, int HoWo, int K, int Cp, int R, int dt, bool nhwc, bool plain) {
     IgemmTilePlan best{-1, 1};
     if (!(dt == DT_F16 || dt == DT_BF16) || Cp % 64 != 0) return best;
     const int stages = R * R * (Cp / 64);
     const long long wide_blocks = (long long)((T + 255) / 256) * (K / 256);
-    if (K % 256 == 0 && wide_blocks >= 256) {               // one of them, or one of its 128x128 quarters, to a compute unit (us)
+    if (plain && K % 256 == 0 && wide_blocks >= 256) {      // one of them, or one of its 128x128 quarters, to a compute unit (us)
         const double share = (double)wide_blocks / 256.0, rounds = 0.4 * share + 0.6 * (double)((wide_blocks + 255) / 256);
-        const double quarters = (double)((T + 127) / 128) * (double)(K / 128) / 256.0;
+        const long long small = (long long)((T + 127) / 128) * (K / 128);
+        const double quarters = 0.5 * ((double)small / 256.0 + (double)((small + 255) / 256));
         if (rounds * (15.5 + 1.9 * stages) <= quarters * (nhwc ? 6.3 + 0.4425 * stages : 5.0 + 0.4525 * stages)) return best;
     }
     // never more ranges than the other kernel takes: the workspace of a call, and with it what fits the library's static scratch, stays
@@ -276,11 +282,20 @@ IgemmTilePlan igemm_tile_plan(int T, int K, int Cp, int R, int dt, bool nhwc) {
             const double share = (double)(blocks * sp) / 256.0;            // workgroups per compute unit
             const double most = (double)((blocks * sp + 255) / 256), n = share < 2.0 ? 0.5 * (share + most) : most;
             const double stage = n * sh.each > sh.alone ? n * sh.each : sh.alone;
-            double c = 6.0 + (double)((stages + sp - 1) / sp) * stage;
-            if (sp > 1) c += 3.0 + (double)sp * K * T * 8.0 / 3e6;
+            double c = 6.0 + (double)((stages + sp - 1) / sp) * stage + (n > 1.0 ? 0.3 + 0.7 * n : 1.0) * sh.ends;
+            if (sp > 1) c += 1.5 + (double)sp * K * T * 8.0 / 3e6;
             if (c < cost) { cost = c; best = {id, sp}; }
         }
     }
+    // NCHW images that are no multiple of four pixels are stored one by one or in pairs, 16 lanes to 32 bytes, where the other kernel's
+    // 32x32 tiles make runs of 64; with a short reduction that costs more than the stages gain, most of all with the 128x128 block
+    if (plain && !nhwc && HoWo % 4 != 0) {
+        const long long blocks2 = (long long)((T + 127) / 128) * ((K + 127) / 128);
+        if (HoWo % 2 != 0 && stages <= 2) return {-1, 1};
+        if (best.id == 2 && ((blocks2 < 256 && stages <= 32) || (HoWo % 2 != 0 && stages <= 8))) return {-1, 1};
+    }
+    // channel-last, a number of channels that is no multiple of four: 16 lanes to as many lines (63 -> 799 1x1 at 249x7, N=8, 54 / 33)
+    if (nhwc && K % 4 != 0 && K >= 64 && best.split == 1) return {-1, 1};
     return best;
 }
 

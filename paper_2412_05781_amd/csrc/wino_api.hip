@@ -62,9 +62,10 @@ size_t igemm_xh_bytes(int N, int C, int H, int W, int dtype, int layout) {
 }
 size_t igemm_part_bytes(int N, int C, int H, int W, int K, int R, int stride, int dtype) {
     const int pad = (R - 1) / 2;
-    const long long T = (long long)N * ((H + 2 * pad - R) / stride + 1) * ((W + 2 * pad - R) / stride + 1);
+    const int HoWo = ((H + 2 * pad - R) / stride + 1) * ((W + 2 * pad - R) / stride + 1);
+    const long long T = (long long)N * HoWo;
     // the larger of the two layouts' choices: wino_workspace_bytes does not know the layout
-    const int sa = igemm_split((int)T, K, round_up(C, 8), R, dtype, false), sb = igemm_split((int)T, K, round_up(C, 8), R, dtype, true);
+    const int sa = igemm_split((int)T, HoWo, K, round_up(C, 8), R, dtype, false), sb = igemm_split((int)T, HoWo, K, round_up(C, 8), R, dtype, true);
     const int sp = sa > sb ? sa : sb;
     return sp > 1 ? align_up((size_t)sp * (size_t)K * (size_t)T * sizeof(float)) : 0;
 }
@@ -575,8 +576,9 @@ bool scale_ok(float v) { return v > 0.f && v < 3.0e38f && v == v; }
 size_t fp8_xq_bytes(int N, int C, int H, int W) { return align_up((size_t)N * H * W * (size_t)round_up(C, 16)); }
 size_t fp8_part_bytes(int N, int C, int H, int W, int K, int R, int stride) {
     const int pad = (R - 1) / 2;
-    const long long T = (long long)N * ((H + 2 * pad - R) / stride + 1) * ((W + 2 * pad - R) / stride + 1);
-    const int sp = igemm_split((int)T, K, round_up(C, 16), R, -1, false);
+    const int HoWo = ((H + 2 * pad - R) / stride + 1) * ((W + 2 * pad - R) / stride + 1);
+    const long long T = (long long)N * HoWo;
+    const int sp = igemm_split((int)T, HoWo, K, round_up(C, 16), R, -1, false);
     return sp > 1 ? align_up((size_t)sp * (size_t)K * (size_t)T * sizeof(float)) : 0;
 }
 }  // namespace

@@ -181,7 +181,7 @@ hipError_t launch_igemm_conv2d(const void* x, const void* Wr, const float* bias,
                                int N, int C, int H, int W, int K, int R, int st, int dt, bool nhwc,
                                void* workspace, size_t xh_bytes, int up, const PreOp* pre, const float* addvec, const void* residual,
                                hipStream_t s);
-int igemm_split(int T, int K, int Cp, int R, int dt, bool nhwc);   // number of partial products the path writes for a shape (dt < 0: 8-bit operands)
+int igemm_split(int T, int HoWo, int K, int Cp, int R, int dt, bool nhwc);   // number of partial products the path writes for a shape (dt < 0: 8-bit operands)
 hipError_t launch_igemm_fp8_filter_quant(const void* w, void* Wq, int K, int C, int R, int dt, float sw, hipStream_t s);
 hipError_t launch_igemm_fp8_conv2d(const void* x, const void* Wq, const float* bias, void* y,
                                    int N, int C, int H, int W, int K, int R, int st, int dt, bool nhwc,

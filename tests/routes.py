@@ -48,10 +48,11 @@ def pre_op(norm=False, up=False, C=1):
     return PreOp(ADDRESS if norm else None, ADDRESS, ADDRESS, 1, C, int(up))
 
 
-def igemm_tile(N, C, K, H, W, R, st, dtype, nhwc):
+def igemm_tile(N, C, K, H, W, R, st, dtype, nhwc, plain=True):
     """(block id, reduction ranges) of the 16x16-tile kernel: 0 = 64x64, 1 = 64x80, 2 = 128x128; id < 0: the kernels of conv_igemm.hip."""
-    f = _fn("_ZN4wino15igemm_tile_planEiiiiib", Pair, INT, INT, INT, INT, INT, BOOL)
-    p = f(N * _out(H, R, st) * _out(W, R, st), K, -(-C // 8) * 8, R, DT[dtype], nhwc)
+    f = _fn("_ZN4wino15igemm_tile_planEiiiiiibb", Pair, INT, INT, INT, INT, INT, INT, BOOL, BOOL)
+    pixels = _out(H, R, st) * _out(W, R, st)
+    p = f(N * pixels, pixels, K, -(-C // 8) * 8, R, DT[dtype], nhwc, plain)
     return p.a, p.b
 
 

@@ -11,7 +11,7 @@ import routes  # noqa: E402
 # direct path, channel counts that 256-wide blocks divide, one or more full rounds of 256x256 blocks: their kernel, up to the number of
 # stages (of 64 channels, per tap) from which smaller blocks are level
 @pytest.mark.parametrize("N,C,K,H,W,R,st,nhwc,wide", [
-    (1, 128, 512, 256, 256, 1, 1, True, True), (1, 512, 1024, 256, 256, 1, 1, True, True), (1, 128, 1024, 128, 128, 3, 1, True, True), (1, 256, 512, 512, 512, 3, 2, True, True),
+    (1, 128, 512, 256, 256, 1, 1, True, True), (1, 512, 1024, 256, 256, 1, 1, True, True), (1, 128, 1024, 128, 128, 3, 1, True, True), (1, 256, 512, 512, 512, 3, 2, True, True), (1, 256, 512, 240, 240, 3, 1, True, True),
     (1, 256, 256, 512, 512, 3, 1, True, True), (1, 256, 256, 512, 512, 1, 1, True, True), (1, 1024, 1024, 128, 128, 3, 1, True, False),
     (1, 256, 240, 512, 512, 3, 1, True, False), (1, 256, 264, 512, 512, 1, 1, True, False), (1, 256, 256, 240, 240, 3, 1, True, False), (1, 512, 512, 180, 180, 3, 1, True, False),
     (1, 1024, 768, 180, 180, 3, 1, True, False), (1, 128, 768, 180, 180, 1, 1, True, True),
@@ -20,6 +20,28 @@ import routes  # noqa: E402
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_direct_path_wide_blocks(N, C, K, H, W, R, st, nhwc, wide, dtype):
     assert (routes.igemm_tile(N, C, K, H, W, R, st, dtype, nhwc)[0] < 0) == wide
+    plan = routes.igemm_tile(N, C, K, H, W, R, st, dtype, nhwc, plain=False)           # a residual or a vector: never
+    assert plan[0] >= 0 and (not wide or plan[1] == 1)
+
+
+# ... NCHW images of an odd number of pixels, or of pairs: the older kernel where the 128x128 block would meet a short reduction
+@pytest.mark.parametrize("N,C,K,H,W,R,st,old", [
+    (1, 256, 256, 181, 181, 1, 1, True), (1, 128, 128, 301, 299, 1, 1, True), (2, 1856, 1184, 23, 57, 1, 1, True), (1, 64, 256, 251, 250, 3, 2, True),
+    (3, 64, 640, 33, 35, 1, 1, True), (1, 128, 384, 7, 215, 1, 1, True), (1, 256, 256, 181, 181, 3, 1, False), (2, 320, 320, 97, 121, 1, 1, False), (2, 320, 320, 97, 121, 3, 1, False), (1, 64, 256, 251, 250, 1, 1, False), (1, 256, 256, 180, 181, 1, 1, False),
+    (1, 512, 512, 99, 101, 3, 1, False), (1, 192, 320, 311, 201, 1, 1, False)])
+def test_direct_path_odd_images(N, C, K, H, W, R, st, old):
+    for dtype in ("f16", "bf16"):
+        assert (routes.igemm_tile(N, C, K, H, W, R, st, dtype, False)[0] < 0) == old
+        assert routes.igemm_tile(N, C, K, H, W, R, st, dtype, True)[0] >= 0 and routes.igemm_tile(N, C, K, H, W, R, st, dtype, False, plain=False)[0] >= 0
+
+
+def test_direct_path_blocks_of_short_reductions():
+    """64x64 where start and stores of the larger block outweigh its stages; two ranges from 16 stages on for tiny images; channel-last with
+    channels that are no multiple of four left to the older kernel."""
+    assert routes.igemm_tile(2, 256, 560, 144, 51, 1, 1, "f16", True) == (0, 1) and routes.igemm_tile(8, 128, 128, 76, 212, 1, 2, "f16", True)[0] == 0
+    assert routes.igemm_tile(2, 512, 512, 256, 256, 3, 1, "f16", False) == (2, 1) and routes.igemm_tile(2, 320, 320, 128, 128, 3, 1, "f16", True)[0] == 2
+    assert routes.igemm_tile(2, 128, 128, 17, 13, 3, 1, "f16", False)[1] == 2 and routes.igemm_tile(2, 64, 128, 17, 13, 3, 1, "f16", False)[1] == 1
+    assert routes.igemm_tile(8, 63, 799, 249, 7, 1, 1, "bf16", True)[0] < 0 and routes.igemm_tile(8, 63, 3, 249, 7, 1, 1, "bf16", True)[0] >= 0
 
 
 # one-kernel F(2x2): taken (True) or left to the paths that store V
