@@ -212,12 +212,15 @@ wino_fewc_f4_kernel(const float* __restrict__ x, const float* __restrict__ U, co
 // With two chunks of eight channels a wave's chain takes 12-13 us however small the call is, 20 element by element (NCHW rows that are no
 // whole 16-byte pieces, and upsampling); the chain's kernels back to back take less where there are few tiles and output channels (here / there,
 // NCHW: 16 -> 320 at 16x16 12.2 / 11.1, -> 8 at 64x64 12.5 / 11.6, -> 64 12.3 / 12.4, -> 320 13.4 / 19.5, -> 8 at 96x96 (N=2) 12.6 / 14.1;
-// at 78x43 -> 64 20.7 / 16.7, -> 320 21.8 / 22.8, at 128x125 -> 8 19.9 / 17.4, -> 64 21.0 / 22.3).
+// at 78x43 -> 64 20.7 / 16.7, -> 320 21.8 / 22.8, at 128x125 -> 8 19.9 / 17.4, -> 64 21.0 / 22.3).  Channel-last with a number of output
+// channels that is no multiple of four, stores are single words (4 -> 5 at 16x16 15.7 / 9.8, at 96x96 15.9 / 11.5).
 bool fewc_conv_ok(const Geom& g, int dt, bool nhwc, const PreOp* pre) {
     if (!(dt == DT_F32 && g.m == 4 && g.Cp <= 16 && !(pre && pre->stats))) return false;
     if ((size_t)g.C * g.H * g.W >= ((size_t)1 << 30) || (size_t)g.K * g.Cp >= ((size_t)1 << 28)) return false;       // lane offsets are 32-bit
     const bool element = !nhwc && (g.W % 4 != 0 || (pre && pre->up));
-    return g.Cp <= 8 || (long long)g.T * (g.K + 64LL) >= (element ? 81920 : 32768);
+    const long long size = (long long)g.T * (g.K + 64LL);
+    if (nhwc && g.K % 4 != 0) return size >= 131072;
+    return g.Cp <= 8 || size >= (element ? 81920 : 32768);
 }
 
 hipError_t launch_fewc_conv(const void* x, const void* U, const float* bias, void* y, const Geom& g, bool nhwc, const PreOp* pre,

@@ -84,7 +84,7 @@ def test_fp8_kernel(N, C, K, H, W, R, st, nhwc, taken):
 
 # few input channels, fp32 F(4x4): with more than eight channels only from some number of tiles times output channels on
 @pytest.mark.parametrize("N,C,K,H,W,nhwc,up,taken", [
-    (1, 4, 8, 16, 16, False, False, True), (1, 8, 3, 5, 7, True, True, True), (1, 9, 320, 16, 16, False, False, False), (1, 16, 8, 64, 64, True, False, False),
+    (1, 4, 8, 16, 16, False, False, True), (1, 8, 4, 5, 7, True, True, True), (1, 8, 3, 5, 7, False, True, True), (1, 4, 5, 96, 96, True, False, False), (2, 4, 5, 128, 128, True, False, True), (1, 9, 320, 16, 16, False, False, False), (1, 16, 8, 64, 64, True, False, False),
     (1, 16, 320, 64, 64, False, False, True), (1, 9, 64, 96, 96, True, False, True), (2, 9, 8, 96, 96, False, False, True), (1, 9, 8, 128, 125, False, False, False), (1, 16, 64, 78, 43, False, False, False), (1, 9, 320, 78, 43, False, False, True),
     (1, 16, 64, 78, 43, True, False, False), (1, 16, 64, 64, 64, False, True, False), (2, 16, 320, 64, 64, False, True, True), (1, 17, 320, 64, 64, False, False, False)])
 def test_few_channels(N, C, K, H, W, nhwc, up, taken):
