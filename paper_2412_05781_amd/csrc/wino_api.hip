@@ -94,7 +94,7 @@ int run_chain(const void* x, const wino_filter* w_t, const float* bias, void* y,
         return launch_fewc_conv(x, w_t->data, bias, y, g, nhwc, pre, post, s) == hipSuccess ? WINO_OK : WINO_ERR_HIP;
     // (a caller that asks for the fp16 product gets the chain that has one)
     if (!(half_product && w_t->variant == WINO_F2 && dt == WINO_F16)) {
-        const OnepassPlan plan = onepass_plan(x, g, dt, nhwc, fused_variant(w_t->variant), pre);
+        const OnepassPlan plan = onepass_plan(x, g, dt, nhwc, fused_variant(w_t->variant), pre, post && post->residual);
         if (plan.ns) return launch_onepass_conv(x, w_t->data, bias, y, g, dt, plan, pre, post, s) == hipSuccess ? WINO_OK : WINO_ERR_HIP;
     }
     if (launch_input_transform(x, V, g, dt, nhwc, pre, s) != hipSuccess) return WINO_ERR_HIP;

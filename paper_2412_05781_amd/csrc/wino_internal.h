@@ -139,7 +139,7 @@ hipError_t launch_fewc_conv(const void* x, const void* U, const float* bias, voi
 // All three steps in one kernel for F(2x2), two-byte storage types (wino_onepass.hip): sub-tiles per wave and how x is read (ns = 0: it
 // does not apply or does not pay), and the launch.  U as for the F(2x2) chain; no workspace.
 struct OnepassPlan { int ns, xm; };
-OnepassPlan onepass_plan(const void* x, const Geom& g, int dt, bool nhwc, bool fused_variant, const PreOp* pre);
+OnepassPlan onepass_plan(const void* x, const Geom& g, int dt, bool nhwc, bool fused_variant, const PreOp* pre, bool residual);
 hipError_t launch_onepass_conv(const void* x, const void* U, const float* bias, void* y, const Geom& g, int dt, const OnepassPlan& plan,
                                const PreOp* pre, const PostOp* post, hipStream_t s);
 

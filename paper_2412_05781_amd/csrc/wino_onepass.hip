@@ -489,46 +489,53 @@ static hipError_t launch_onepass_cfg(const void* x, const void* U, const float* 
     return hipGetLastError();
 }
 
-// Microseconds of the kernel with NS sub-tiles per wave, as measured (fp16 / bf16): workgroups come in rounds of 256; a chunk of 64
-// channels takes a time for pixels, transform and barriers plus one per sub-tile, more of both where SiLU competes for the vector unit; a
-// workgroup's start and end take 4 and the launch 3.  Element by element, the pixels of a chunk take 4.4 to 6 and those of the first, which
-// nothing hides, 9 more.  Predicted / measured: 320 -> 320 channels, N=2, 128x128, channel-last 67 / 70, NCHW with GroupNorm 88 / 86;
-// 512 at 128x128 NCHW with GroupNorm 116 / 118; element by element 128 -> 128 at 300x300 86 / 91, with GroupNorm 96 / 99, 320 -> 320 at
-// 52x78 (N=2) 53 / 57, with GroupNorm 61 / 63.
+// Microseconds of the kernel with NS sub-tiles per wave, fitted to 548 measured calls (64...1280 channels, 24x24...520x520, both layouts, with
+// and without GroupNorm and upsampling; off by 7 % channel-last, 10 % NCHW, 14 % element by element): workgroups come in rounds of 256; a
+// round takes start and end, and per chunk of 64 channels a time for pixels, transform and barriers plus one per sub-tile.
+struct OnepassTimes { double ends, pixels[2], subtile[2]; };             // [GroupNorm]
 static double onepass_us(const Geom& g, int xm, bool gn, int ns) {
-    static const double pixels[3][2] = {{2.0, 1.2}, {2.7, 2.1}, {4.4, 6.0}}, subtile[3][2] = {{0.74, 1.10}, {0.74, 1.12}, {0.74, 0.74}};     // [xm][gn]
+    static const OnepassTimes times[3] = {{2.9, {0.52, 1.81}, {1.05, 1.01}}, {2.3, {1.52, 2.15}, {1.12, 1.16}}, {7.8, {3.1, 3.4}, {1.48, 2.0}}};
     const long long wgs = (long long)g.N * ((g.th + 3) / 4) * ((g.tw + 7) / 8) * ((g.K + 32 * ns - 1) / (32 * ns));
-    return 3.0 + (double)((wgs + 255) / 256) * ((xm == XM_NCHW_ANY ? 13.0 : 4.0) + (g.C / 64) * (pixels[xm][gn] + subtile[xm][gn] * ns));
+    const OnepassTimes& t = times[xm];
+    return 3.0 + (double)((wgs + 255) / 256) * (t.ends + (g.C / 64) * (t.pixels[gn] + t.subtile[gn] * ns));
+}
+
+// ... and of the paths that store V, fitted the same way (12 % and 8 %).  Chain: V and M through memory and the products.  Fused variant: the
+// transform, then rounds of its blocks, each a serial chain of 16 positions; block shapes as fused_pick_shape() takes them.  It reads a
+// residual in 2.1 (NCHW) to 3.5 us per million outputs, this kernel in 0.5.
+static double stored_us(const Geom& g, bool ragged, bool gn, bool nhwc, bool residual, bool fused_variant) {
+    const double T = g.T, C = g.C;
+    if (!fused_variant) {
+        const double K = g.K < 128 ? 128.0 : (double)g.K;
+        return (11.5 + T * (1.18e-5 * C + 2.05e-5 * K + 2e-8 * C * K) + (gn ? 4.6e-6 * T * C : 0.0)) * (ragged ? 1.04 : 1.0);
+    }
+    auto blocks = [&](int bk, int bt) { return (double)((g.K + bk - 1) / bk) * (double)((g.T + bt - 1) / bt); };
+    auto rounds = [](double n) { const double most = (double)(((long long)n + 255) / 256), r = 0.3 * n / 256.0 + 0.7 * most; return r < 1.0 ? 1.0 : r; };
+    const double stages = 16.0 * (g.C / 64), b128 = blocks(128, 128), b64 = g.K < g.T ? blocks(128, 64) : blocks(64, 128), small = blocks(64, 64) / 512.0;
+    const double gemm = b128 >= 160 ? rounds(b128) * (21.8 + 0.55 * stages) : (b64 >= 200 ? rounds(b64) * (16.5 + 0.33 * stages) : (small < 1.0 ? 1.0 : small) * (15.7 + 0.235 * stages));
+    return 3.0 + T * C * 8.1e-6 * (ragged ? 1.38 : 1.0) + gemm + (gn ? 4.8e-6 * T * C : 0.0) +
+           (residual ? (nhwc ? 3.0e-6 : 1.7e-6) * g.N * g.H * (double)g.W * g.K : 0.0);
 }
 
 // Whether it applies and is taken, and how.  It applies to whole 128-byte reduction stages and whole 16-channel sub-tiles, and is taken
-// where it is faster than the paths that store V.  Those move V (and the three-kernel chain M) through memory: 8 us + T * (1.26e-5 C +
-// 2.1e-5 K + 2e-8 C K) us for the chain (N=2: 320 channels at 64x64 34 us, 640 at 64x64 70, 960 -> 320 at 64x64 61, 1280 at 32x32 57),
-// 6e-6 T C more with GroupNorm and a twelfth more element by element, for at least 128 output channels; 0.84 of that for the fused
-// variant, and 0.62 where its 128-wide blocks have no padding, but at least the serial chain of its 16 positions, 14 us + 0.075 C.  One
-// kernel / the other path (us; chain, and with (f) the fused variant): NCHW 320 channels at 128x128 80 / 111, with GroupNorm 92 / 128, (f) 92 / 103; at 64x64 30
-// / 35, 640 channels at 64x64 with GroupNorm 93 / 88, 256 at 256x256 with GroupNorm (f) 134 / 119; channel-last 320 at 64x64 25 / 34, with
-// GroupNorm (f) 36 / 51, 512 at 256x256 337 / 389; element by element 64 -> 128 at 250x250 47 / 62, (f) 46 / 33, 128 -> 128 at 300x300 93 / 121, (f) 91 / 80, 192 -> 96 at 500x300 (f) 164 / 198, 256 -> 256
-// at 250x250 with GroupNorm 226 / 204, (f) 227 / 126, 320 -> 320 at 52x78 (N=2) with GroupNorm 69 / 46.
-OnepassPlan onepass_plan(const void* x, const Geom& g, int dt, bool nhwc, bool fused_variant, const PreOp* pre) {
+// where it is faster than the paths that store V, by the times above: over the measured calls 0.5 % more than the better one each time.  One
+// kernel / the other path (us; chain, and with (f) the fused variant): NCHW 320 channels at 128x128 80 / 111, with GroupNorm 92 / 128, (f)
+// 92 / 103; at 64x64 30 / 35, 640 channels at 64x64 with GroupNorm 93 / 88, 512 at 256x256 with GroupNorm 487 / 433; channel-last 320 at
+// 64x64 25 / 34, with GroupNorm (f) 36 / 51, 512 at 256x256 337 / 389, 640 -> 320 at 96x96 110 / 87, 192 -> 320
+// at 128x312 with GroupNorm and residual (f) 83 / 119; element by element 64 -> 128 at 250x250
+// 47 / 62, (f) 46 / 33, 128 -> 128 at 300x300 93 / 121, (f) 91 / 80, 192 -> 96 at 500x300 (f) 164 / 198, 256 -> 256 at 250x250 with GroupNorm
+// 226 / 204, (f) 227 / 126, 320 -> 320 at 52x78 (N=2) with GroupNorm 69 / 46.
+OnepassPlan onepass_plan(const void* x, const Geom& g, int dt, bool nhwc, bool fused_variant, const PreOp* pre, bool residual) {
     const OnepassPlan none{0, 0};
     if (!(two_byte(dt) && dt != DT_I8 && g.m == 2 && g.C % 64 == 0 && g.K % 16 == 0)) return none;
     if ((size_t)g.C * g.H * g.W >= ((size_t)1 << 31)) return none;             // byte offsets inside an image are 32-bit
     if ((size_t)g.K * g.C * 2 >= ((size_t)1 << 31)) return none;               // byte offsets inside a position of U too
-    const bool gn = pre && pre->stats, rows = g.W % 8 == 0 && !(pre && pre->up) && (reinterpret_cast<uintptr_t>(x) & 15u) == 0;
+    const bool gn = pre && pre->stats, up = pre && pre->up, rows = g.W % 8 == 0 && !up && (reinterpret_cast<uintptr_t>(x) & 15u) == 0;
     const int xm = nhwc ? XM_NHWC : (rows ? XM_NCHW_ROWS : XM_NCHW_ANY);
     OnepassPlan plan{2, xm};
     for (int ns = 3; ns <= onepass_most(xm); ++ns)
         if (onepass_us(g, xm, gn, ns) < onepass_us(g, xm, gn, plan.ns)) plan.ns = ns;
-    const double K = g.K < 128 ? 128.0 : (double)g.K, C = (double)g.C, norm = gn ? 6e-6 * g.T * C : 0.0;
-    double other = 8.0 + (double)g.T * (1.26e-5 * C + 2.1e-5 * K + 2e-8 * C * K) + norm;
-    if (xm == XM_NCHW_ANY && !(pre && pre->up)) other *= 1.08;
-    if (fused_variant) {
-        const double chain = 14.0 + 0.075 * C + norm;
-        other *= g.K % 128 == 0 ? 0.62 : 0.84;
-        other = other > chain ? other : chain;
-    }
-    return onepass_us(g, xm, gn, plan.ns) < 0.95 * other ? plan : none;
+    return onepass_us(g, xm, gn, plan.ns) < 0.93 * stored_us(g, xm == XM_NCHW_ANY && !up, gn, nhwc, residual, fused_variant) ? plan : none;
 }
 
 template <typename E, int XM>

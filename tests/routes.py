@@ -56,11 +56,11 @@ def igemm_tile(N, C, K, H, W, R, st, dtype, nhwc, plain=True):
     return p.a, p.b
 
 
-def onepass(N, C, K, H, W, dtype, nhwc, fused_variant=False, norm=False, up=False, address=ADDRESS):
+def onepass(N, C, K, H, W, dtype, nhwc, fused_variant=False, norm=False, up=False, residual=False, address=ADDRESS):
     """(16-channel sub-tiles per wave, 0 channel-last / 1 rows of whole 16-byte pieces / 2 element by element) of the one-kernel F(2x2) path;
     0 sub-tiles: the paths that store V."""
-    f = _fn("_ZN4wino12onepass_planEPKvRKNS_4GeomEibbPKNS_5PreOpE", Pair, PTR, ctypes.POINTER(Geom), INT, BOOL, BOOL, ctypes.POINTER(PreOp))
-    p = f(address, ctypes.byref(winograd_geom(N, C, K, H, W, 2)), DT[dtype], nhwc, fused_variant, ctypes.byref(pre_op(norm, up, C)))
+    f = _fn("_ZN4wino12onepass_planEPKvRKNS_4GeomEibbPKNS_5PreOpEb", Pair, PTR, ctypes.POINTER(Geom), INT, BOOL, BOOL, ctypes.POINTER(PreOp), BOOL)
+    p = f(address, ctypes.byref(winograd_geom(N, C, K, H, W, 2)), DT[dtype], nhwc, fused_variant, ctypes.byref(pre_op(norm, up, C)), residual)
     return p.a, p.b
 
 

@@ -55,17 +55,18 @@ def test_direct_path_blocks_of_short_reductions():
     # whole pieces, channel-last
     (2, 640, 640, 64, 64, False, False, True, False, False), (1, 512, 512, 128, 128, False, False, True, False, False), (1, 512, 512, 256, 256, False, False, True, False, False),
     (1, 256, 256, 256, 256, False, True, True, False, False), (2, 320, 320, 64, 64, False, False, True, False, True), (2, 320, 320, 128, 128, False, True, True, False, True),
-    (1, 256, 256, 256, 256, True, True, True, False, True), (2, 320, 320, 64, 64, True, True, True, False, True), (1, 512, 256, 128, 128, True, True, True, False, True),
+    (1, 256, 256, 256, 256, True, False, True, False, True), (2, 320, 320, 64, 64, True, True, True, False, True), (1, 512, 256, 128, 128, True, True, True, False, True),
     (4, 320, 320, 64, 96, True, True, True, False, True), (1, 512, 512, 128, 128, False, True, False, False, False), (2, 192, 192, 104, 152, False, False, True, False, True), (2, 1280, 1280, 32, 32, True, False, False, False, False)])
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_one_kernel_f2(N, C, K, H, W, nhwc, fused, norm, up, taken, dtype):
     assert (routes.onepass(N, C, K, H, W, dtype, nhwc, fused, norm, up)[0] > 0) == taken
 
 
-def test_one_kernel_f2_does_not_apply():
+def test_one_kernel_f2_residual_and_bounds():
     for bad in (dict(C=120), dict(K=136), dict(dtype="f32")):
         assert routes.onepass(**{**dict(N=1, C=128, K=128, H=512, W=512, dtype="bf16", nhwc=True), **bad})[0] == 0
-    assert routes.onepass(1, 128, 128, 512, 512, "bf16", False) [1] == 1
+    assert routes.onepass(1, 192, 320, 128, 312, "bf16", True, True, True, residual=True)[0] > 0 and routes.onepass(1, 192, 320, 128, 312, "bf16", True, True, True)[0] == 0
+    assert routes.onepass(1, 128, 128, 512, 512, "bf16", False)[1] == 1
     assert routes.onepass(1, 128, 128, 512, 512, "bf16", False, address=routes.ADDRESS + 2)[1] == 2
 
 
