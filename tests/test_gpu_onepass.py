@@ -2,7 +2,7 @@
 
 Tolerances: those of F(2x2) for the storage type (fp16 5e-3 with the variant's band around 5e-4, bf16 8e-3 around 4e-3), and the
 element-wise bound of tests/parity_util.py.  The shapes are large enough for the library to take this path (about 130 blocks
-of 4 x 8 tiles and output channels) and sit at its edges: tile rows and columns off the block, odd images, one and several
+of 4 x 8 tiles and output channels; each test asks the rule for the kernel that it means) and sit at its edges: tile rows and columns off the block, odd images, one and several
 64-channel chunks, every number of 16-channel sub-tiles per wave, output channels off the block, rows that are and are not
 whole 16-byte pieces."""
 import os
@@ -18,6 +18,7 @@ from paper_2412_05781_amd import synth
 
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 import parity_util  # noqa: E402
+import routes  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -40,6 +41,7 @@ def test_onepass(case, fused, layout, dtype):
     N, C, K, H, W = case
     td = synth.TORCH_DTYPE[dtype]
     x, w, b = synth.make_inputs(N, C, K, H, W, dtype, seed=900 + sum(case))
+    assert routes.onepass(N, C, K, H, W, dtype, layout == B.WINO_NHWC, norm=fused, residual=fused)[0] > 0
     g = torch.Generator().manual_seed(sum(case))
     gamma = beta = addvec = residual = None
     if fused:
@@ -56,9 +58,40 @@ def test_onepass(case, fused, layout, dtype):
     parity_util.check(y, ref, TOL[dtype], 2, dtype, what=(case, fused, layout, dtype))
 
 
+# every number of sub-tiles per wave with two and three chunks of 64 channels, for rows that are read element by element (mode 2: off the
+# 16-byte piece, or upsampled), in whole pieces (1) and channel-last (0): the pixels of the next chunk are loaded and GroupNorm's
+# coefficients replaced during the products of this one, and the filter ring goes on over the end of a chunk
+@pytest.mark.parametrize("norm", [False, True])
+@pytest.mark.parametrize("variant,dtype", [(B.WINO_F2, "f16"), (B.WINO_F2, "bf16"), (B.WINO_FUSED_F2, "bf16")])
+@pytest.mark.parametrize("ns,mode,up,case", [
+    (2, 2, False, (2, 192, 16, 129, 58)), (2, 2, False, (1, 128, 32, 122, 102)), (2, 2, True, (1, 192, 16, 128, 120)),
+    (3, 2, False, (2, 192, 80, 122, 102)), (3, 2, True, (2, 128, 80, 64, 136)), (4, 2, False, (2, 192, 112, 122, 102)),
+    (4, 2, True, (2, 192, 112, 128, 120)), (4, 1, False, (1, 192, 320, 101, 72)), (5, 1, False, (1, 192, 400, 101, 72)),
+    (2, 0, False, (1, 192, 16, 97, 75)), (3, 0, False, (1, 192, 400, 66, 66)), (4, 0, False, (2, 128, 240, 66, 66)), (4, 0, False, (1, 192, 320, 101, 72)),
+    (5, 0, False, (2, 128, 320, 66, 66)), (5, 0, False, (1, 192, 400, 101, 72)), (5, 0, True, (2, 192, 320, 66, 66))])
+def test_onepass_chunks(ns, mode, up, case, variant, dtype, norm):
+    N, C, K, H, W = case
+    layout = B.WINO_NHWC if mode == 0 else B.WINO_NCHW
+    assert routes.onepass(N, C, K, H, W, dtype, mode == 0, variant == B.WINO_FUSED_F2, norm, up) == (ns, mode)
+    h, w_ = (H // 2, W // 2) if up else (H, W)
+    x, _, _ = synth.make_inputs(N, C, K, h, w_, dtype, seed=1300 + sum(case))
+    _, w, b = synth.make_inputs(1, C, K, 4, 4, dtype, seed=1400 + sum(case))
+    g = torch.Generator().manual_seed(sum(case))
+    gamma, beta = (1 + 0.2 * torch.randn(C, generator=g), 0.3 * torch.randn(C, generator=g)) if norm else (None, None)
+    perm = (lambda t: t.permute(0, 2, 3, 1).contiguous()) if layout == B.WINO_NHWC else (lambda t: t)
+    dev = lambda t: None if t is None else t.to(DEV)
+    y = B.conv2d_fused(perm(x).to(DEV), w.to(DEV), b.to(DEV), variant, layout, dev(gamma), dev(beta), 16, upsample=up)
+    torch.cuda.synchronize()
+    y = y.float().cpu()
+    y = (y.permute(0, 3, 1, 2) if layout == B.WINO_NHWC else y).numpy().astype(np.float64)
+    ref = fo.conv2d_fused(_np(x), _np(w), _np(b), _np(gamma), _np(beta), 16, upsample=up)
+    parity_util.check(y, ref, TOL[dtype], 2, dtype, what=(ns, mode, up, case, variant, dtype, norm), channels=C)
+
+
 @pytest.mark.parametrize("layout", [B.WINO_NCHW, B.WINO_NHWC])
 def test_onepass_upsampled(layout):
     N, C, K, h, w_ = 2, 64, 96, 36, 40
+    assert routes.onepass(N, C, K, 2 * h, 2 * w_, "bf16", layout == B.WINO_NHWC, up=True)[0] > 0
     x, w, b = synth.make_inputs(N, C, K, h, w_, "bf16", seed=78)
     up = x.repeat_interleave(2, 2).repeat_interleave(2, 3).contiguous()
     perm = (lambda t: t.permute(0, 2, 3, 1).contiguous()) if layout == B.WINO_NHWC else (lambda t: t)
