@@ -1,6 +1,9 @@
 """Parity of the implicit-GEMM convolution path (1x1, 3x3 stride 2, 3x3 stride 1) against the fp64 oracle:
 relative L2 <= 1e-5 for fp32 storage, <= 5e-3 for fp16 storage with fp32 accumulation (the path rounds only its
 output, so it sits far below that)."""
+import os
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -8,6 +11,9 @@ import torch
 import oracle
 from paper_2412_05781_amd import binding as B
 from paper_2412_05781_amd import synth
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+import routes  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -87,14 +93,19 @@ def test_igemm_split_reduction(dtype, shape, R, stride, layout):
     assert err <= (6e-4 if dtype == "f16" else 1e-5), (shape, R, stride, layout, dtype, err)
 
 
-# Cp a whole number of 64-channel stages (the 16x16-tile kernel): every block it has (64x64, 64x80, 128x128), tails in pixels and channels,
-# split reductions, outputs with 4k, 2k and an odd number of pixels, and the shapes left to the other kernels
+# Cp a whole number of 64-channel stages (the 16x16-tile kernel): each of its blocks (0: 64x64, 1: 64x80, 2: 128x128) with a single stage and
+# with several, tails in pixels and channels, split reductions, outputs with 4k, 2k and an odd number of pixels; where the layouts go
+# different ways, and shapes left to the other kernels (-1), in a pair (NCHW, channel-last)
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("layout", [B.WINO_NCHW, B.WINO_NHWC])
-@pytest.mark.parametrize("shape,R,stride", [((1, 64, 16, 5, 5), 1, 1), ((2, 128, 70, 9, 10), 3, 1), ((2, 192, 320, 64, 63), 1, 1), ((2, 320, 320, 64, 64), 1, 1),
-                                            ((1, 64, 130, 190, 131), 3, 2), ((1, 1280, 72, 9, 6), 3, 2), ((1, 640, 33, 7, 9), 1, 2),
-                                            ((1, 64, 256, 256, 257), 1, 1)])
-def test_igemm_tile_kernel(shape, R, stride, layout, dtype):
+@pytest.mark.parametrize("shape,R,stride,block", [((1, 64, 16, 5, 5), 1, 1, (-1, 0)), ((2, 128, 70, 9, 10), 3, 1, (0, 0)), ((2, 192, 320, 64, 63), 1, 1, (1, 1)),
+                                                  ((2, 320, 320, 64, 64), 1, 1, (1, 1)), ((1, 64, 130, 190, 131), 3, 2, (0, -1)), ((1, 1280, 72, 9, 6), 3, 2, (0, 0)),
+                                                  ((1, 640, 33, 7, 9), 1, 2, (0, 0)), ((1, 64, 256, 256, 257), 1, 1, (0, -1)),
+                                                  ((2, 64, 240, 128, 126), 1, 1, (2, 2)), ((2, 192, 320, 128, 126), 3, 1, (2, 2)), ((2, 128, 400, 129, 127), 3, 1, (2, 2)),
+                                                  ((1, 64, 200, 128, 125), 3, 1, (2, 2)), ((2, 320, 320, 64, 64), 3, 1, (1, 1)), ((1, 64, 72, 101, 99), 3, 1, (1, 1)), ((1, 192, 72, 101, 99), 3, 1, (0, 0))])
+def test_igemm_tile_kernel(shape, R, stride, block, layout, dtype):
+    nhwc = layout == B.WINO_NHWC
+    assert routes.igemm_tile(*shape, R, stride, dtype, nhwc)[0] == block[nhwc]
     N, C, K, H, W = shape
     x, w, b = _inputs(N, C, K, H, W, R, dtype, seed=8800 + sum(shape))
     ref = oracle.conv2d_general(_np(x), _np(w), _np(b), stride)
