@@ -70,12 +70,16 @@ def test_bf16_channel_last_and_stages(variant):
     assert oracle.rel_l2(_np(M.cpu()), np.einsum("bkc,btc->bkt", Uh, Vh)) <= 1e-6
 
 
-def test_bf16_auto_on_a_many_tile_layer_runs_the_fused_variant():
-    """4096 F(2x2) tiles: WINO_AUTO resolves to the fused variant for bf16; whole tensor and element-wise against the oracle."""
+@pytest.mark.parametrize("channels", [64, 72])
+def test_bf16_auto_on_a_many_tile_layer_runs_the_fused_variant(channels):
+    """4096 F(2x2) tiles: WINO_AUTO resolves to the fused variant for bf16 (which runs in one kernel with these channels and stores V with
+    72 of them); whole tensor and element-wise against the oracle."""
     import os, sys
     sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
     import parity_util as pu
-    N, C, K, H, W = 1, 64, 64, 128, 128
+    import routes
+    N, C, K, H, W = 1, channels, channels, 128, 128
+    assert (routes.onepass(N, C, K, H, W, "bf16", False, True)[0] > 0) == (channels == 64)
     assert B.wino_resolve_variant(N, C, H, W, K, B.WINO_BF16, B.WINO_AUTO) == B.WINO_FUSED_F2
     x, w, b = synth.make_inputs(N, C, K, H, W, "bf16", seed=10777)
     ref = oracle.conv2d_direct(_np(x), _np(w), _np(b))

@@ -166,8 +166,8 @@ FP16_BAND = {B.WINO_F2: (2.5e-4, 1.0e-3), B.WINO_F4: (1.5e-3, 4.5e-3), B.WINO_DI
 # Beside the variant the library picks for the layer (what bench.py times), the variants listed here are run on the
 # same oracle result: the fused variants everywhere (their block shapes differ from layer to layer; F(4x4) fused exists for the
 # two-byte types), the other tile size
-# on the largest workspaces (E4/F2: M alone is 2.1 GB, byte offsets pass 2^31) and the smallest images, the direct
-# variant on VAE- and UNet-sized layers.
+# on the largest and the smallest images, the direct variant on VAE- and UNet-sized layers.  F(2x2) of either kind runs in one kernel on many
+# of them (E4 and D1 among them); the paths that store V and M at that size are in test_f2_paths_that_store_v_at_full_size.
 EXTRA_VARIANTS = {
     "E4_vae": [B.WINO_F2, B.WINO_DIRECT], "C5_unet": [B.WINO_F4], "D1_sdxl": [B.WINO_F2], "E5_vae_out": [B.WINO_F2],
     "E2_vae": [B.WINO_DIRECT], "C6_unet": [B.WINO_DIRECT], "B_resblock": [B.WINO_F2, B.WINO_F4, B.WINO_DIRECT],
@@ -204,6 +204,24 @@ def test_every_layer_whole_tensor(name):
         else:
             assert 1e-8 <= err, "fp32 result suspiciously exact"
         del y
+
+
+# channel counts that the one-kernel F(2x2) path does not take (C off 64, K off 16): M of 2.1 GB with byte offsets past 2^31 in
+# the chain; the fused variant with many of its blocks, in both two-byte types (bf16: eight times fp16's unit, and so its band)
+@pytest.mark.parametrize("variant,dtype,shape", [(B.WINO_F2, "f16", (1, 120, 128, 1024, 1024)), (B.WINO_F2, "f16", (1, 64, 136, 1024, 1000)),
+                                                 (B.WINO_FUSED_F2, "f16", (1, 120, 128, 1024, 1024)), (B.WINO_FUSED_F2, "bf16", (2, 320, 328, 128, 128))])
+def test_f2_paths_that_store_v_at_full_size(variant, dtype, shape):
+    import parity_util as pu
+    import routes
+    N, C, K, H, W = shape
+    assert all(routes.onepass(*shape, dtype, nhwc, variant == B.WINO_FUSED_F2)[0] == 0 for nhwc in (False, True))
+    if variant == B.WINO_F2:
+        assert 16 * K * N * (H // 2) * (W // 2) * 4 >= 2 ** 31
+    x, w, b = synth.make_inputs(N, C, K, H, W, dtype, seed=4100 + sum(shape))
+    ref = oracle.conv2d_direct(_np(x), _np(w), _np(b))
+    err = pu.check(_run(x, w, b, variant), ref, 5e-3 if dtype == "f16" else 8e-3, 2, dtype, what=(variant, dtype, shape), channels=C)
+    lo, hi = FP16_BAND[B.WINO_F2] if dtype == "f16" else (8 * FP16_BAND[B.WINO_F2][0], 8 * FP16_BAND[B.WINO_F2][1])
+    assert lo <= err <= hi, err
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
