@@ -4,6 +4,9 @@ Two kinds of check: (1) against the MODEL of the quantised convolution - same qu
 GPU result differs only by fp32 accumulation and the output rounding, so the tolerance is that of the storage type of y;
 this also proves that the kernel's roundings to E4M3 are the model's.  (2) against the UNquantised fp64 convolution the
 error must sit in the band the model predicts (about 3.8e-2; tolerance of the path 6e-2)."""
+import os
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -13,6 +16,9 @@ from oracle import fp8_model as f8
 from oracle import fused_ops as fo
 from paper_2412_05781_amd import binding as B
 from paper_2412_05781_amd import synth
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+import routes  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -101,12 +107,17 @@ def test_fp8_fused_operators(dtype, layout):
 
 
 # the kernel for whole reductions: blocks of 256x256 with one and several stages, the last one partial, blocks that straddle two images,
-# planes that are and are not whole 16-byte pieces; blocks of 128x128 off the edge in both dimensions; additions at the end
+# planes that are and are not whole 16-byte pieces; blocks of 128x128 off the edge in both dimensions, images of an odd and an even number of
+# pixels, stride 1; additions at the end; with the layouts that the kernel takes (NCHW, channel-last), the others run the older one
 @pytest.mark.parametrize("layout", [B.WINO_NCHW, B.WINO_NHWC])
-@pytest.mark.parametrize("case", [(2, 272, 256, 180, 184, 1), (2, 80, 256, 181, 182, 1), (1, 384, 256, 255, 259, 1), (1, 112, 200, 24, 40, 3),
-                                  (2, 48, 136, 25, 40, 3), (3, 112, 72, 9, 11, 3)])
-def test_fp8_whole_reductions(case, layout):
+@pytest.mark.parametrize("case,taken", [((2, 272, 256, 180, 184, 1), (True, False)), ((2, 80, 256, 181, 182, 1), (True, False)),
+                                        ((1, 384, 256, 255, 259, 1), (True, False)), ((1, 112, 200, 24, 40, 3), (True, False)),
+                                        ((2, 48, 136, 25, 40, 3), (True, False)), ((3, 112, 72, 9, 11, 3), (False, False)),
+                                        ((1, 272, 136, 128, 129, 1), (True, True)), ((1, 128, 136, 128, 129, 3), (True, True)), ((2, 48, 330, 101, 99, 3), (True, True)),
+                                        ((1, 112, 260, 150, 121, 3), (True, True))])
+def test_fp8_whole_reductions(case, taken, layout):
     N, C, K, H, W, R = case
+    assert routes.fp8_tile(N, C, K, H, W, R, 1, "f16", layout == B.WINO_NHWC) == taken[layout == B.WINO_NHWC]
     x, w, b = _inputs(N, C, K, H, W, R, "f16", seed=400 + sum(case))
     g = torch.Generator().manual_seed(sum(case))
     addvec, residual = torch.randn(N, K, generator=g), torch.randn(N, K, H, W, generator=g).half()
