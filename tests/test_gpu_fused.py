@@ -168,8 +168,8 @@ def test_activation_windows(case, variant, dtype):
         y = B.conv2d_fused(x.to(DEV), w.to(DEV), b.to(DEV), variant, B.WINO_NCHW, None if ga is None else ga.to(DEV),
                            None if be is None else be.to(DEV), G)
         err = oracle.rel_l2(y.float().cpu().numpy(), ref)
-        # bf16 carries three bits less than fp16, F(4x4) near 2.5e-2
-        assert err <= (TOL[dtype] if dtype != "bf16" else 4e-2), (case, variant, dtype, gn, err)
+        # bf16 carries three bits less than fp16: F(4x4) near 2.5e-2, F(2x2) near 4e-3
+        assert err <= (TOL[dtype] if dtype != "bf16" else 8e-3 if variant == B.WINO_F2 else 4e-2), (case, variant, dtype, gn, err)
 
 
 def test_each_part_alone_and_in_place_residual():
