@@ -29,13 +29,6 @@ hipError_t launch_igemm_tile(const void* xh, const void* Wr, const float* bias, 
 // Shared by the kernels with two-byte outputs whose block rows are the contiguous dimension of y: four consecutive rows ra .. ra+3 of
 // column cb.  PIX_A: rows are pixels (NCHW y), else output channels (channel-last y; `planes`: an NCHW y with an odd number of pixels,
 // whose outputs are stored one by one).  Additions in fp32, one rounding.
-template <typename E> __device__ __forceinline__ uint32_t pack2(float a, float b) {
-    const E ea = from_f32<E>(a), eb = from_f32<E>(b);
-    return (uint32_t)*reinterpret_cast<const uint16_t*>(&ea) | ((uint32_t)*reinterpret_cast<const uint16_t*>(&eb) << 16);
-}
-template <typename E> __device__ __forceinline__ float lo16(uint32_t w) { const uint16_t h = (uint16_t)(w & 0xffffu); return to_f32<E>(*reinterpret_cast<const E*>(&h)); }
-template <typename E> __device__ __forceinline__ float hi16(uint32_t w) { const uint16_t h = (uint16_t)(w >> 16); return to_f32<E>(*reinterpret_cast<const E*>(&h)); }
-
 template <typename E, bool PIX_A>
 __device__ __forceinline__ void igemm_store4(f32x4_t v, int ra, int cb, E* __restrict__ y, const float* __restrict__ bias, const ConvGeom& g,
                                              const IgemmPost& post, int vec_ok, int planes) {

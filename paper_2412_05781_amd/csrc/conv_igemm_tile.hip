@@ -15,22 +15,6 @@
 
 namespace wino {
 
-namespace {
-
-template <typename E> struct Mma16;
-template <> struct Mma16<__half> {
-    static __device__ __forceinline__ void run(const u32x4_t& a, const u32x4_t& b, f32x4_t& c) {
-        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
-    }
-};
-template <> struct Mma16<bf16_t> {
-    static __device__ __forceinline__ void run(const u32x4_t& a, const u32x4_t& b, f32x4_t& c) {
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-    }
-};
-
-}  // namespace
-
 // BP pixels x BK output channels per workgroup, WP x WK waves.  PIX_A: pixels are the rows (NCHW y), else output channels (channel-last y).
 template <typename E, int BP, int BK, int WP, int WK, int NST, bool PIX_A>
 __global__ void __launch_bounds__(WP * WK * 64)

@@ -25,18 +25,6 @@ namespace wino {
 
 namespace {
 
-template <typename E> struct Mma16;
-template <> struct Mma16<__half> {
-    static __device__ __forceinline__ void run(const u32x4_t& a, const u32x4_t& b, f32x4_t& c) {
-        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
-    }
-};
-template <> struct Mma16<bf16_t> {
-    static __device__ __forceinline__ void run(const u32x4_t& a, const u32x4_t& b, f32x4_t& c) {
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-    }
-};
-
 // A^T of F(4x4,3x3): rows (1 1 1 1 1 0), (0 1 -1 2 -2 0), (0 1 1 4 4 0), (0 1 -1 8 -8 1); both arguments wave-uniform
 __device__ __forceinline__ float at4(int a, int x) {
     if (x == 0) return a == 0 ? 1.f : 0.f;
@@ -44,13 +32,6 @@ __device__ __forceinline__ float at4(int a, int x) {
     const float sign = (x & 1) ? 1.f : -1.f, mag = x <= 2 ? 1.f : 2.f;
     return a == 0 ? 1.f : (a == 1 ? sign * mag : (a == 2 ? mag * mag : sign * mag * mag * mag));
 }
-
-template <typename E> __device__ __forceinline__ uint32_t pack2(float a, float b) {
-    const E ea = from_f32<E>(a), eb = from_f32<E>(b);
-    return (uint32_t)*reinterpret_cast<const uint16_t*>(&ea) | ((uint32_t)*reinterpret_cast<const uint16_t*>(&eb) << 16);
-}
-template <typename E> __device__ __forceinline__ float lo16(uint32_t w) { const uint16_t h = (uint16_t)(w & 0xffffu); return to_f32<E>(*reinterpret_cast<const E*>(&h)); }
-template <typename E> __device__ __forceinline__ float hi16(uint32_t w) { const uint16_t h = (uint16_t)(w >> 16); return to_f32<E>(*reinterpret_cast<const E*>(&h)); }
 
 struct Fused4Geom { int N, K, H, W, th, tw, T; };
 

@@ -1,5 +1,5 @@
 // Device helpers shared by the kernels that feed the MFMA units from LDS: the 32x32 MFMA step per
-// storage type, the explicit vmcnt wait, and the global -> LDS transfer.
+// storage type, the 16x16 one, pairs of two-byte elements, the explicit vmcnt wait, and the global -> LDS transfer.
 #ifndef WINO_MMA_H
 #define WINO_MMA_H
 #include "wino_internal.h"
@@ -54,6 +54,27 @@ template <> struct Mma<float> {
         c = __builtin_amdgcn_mfma_f32_32x32x2f32(fa.w, fb.w, c, 0, 0, 0);
     }
 };
+
+// the 16x16 tile: one 16-byte chunk = 8 reduction elements, each quarter of the wave another one
+template <typename E> struct Mma16;
+template <> struct Mma16<__half> {
+    static __device__ __forceinline__ void run(const u32x4_t& a, const u32x4_t& b, f32x4_t& c) {
+        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
+    }
+};
+template <> struct Mma16<bf16_t> {
+    static __device__ __forceinline__ void run(const u32x4_t& a, const u32x4_t& b, f32x4_t& c) {
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+    }
+};
+
+// two 16-bit elements in one word, first element in the low half
+template <typename E> __device__ __forceinline__ uint32_t pack2(float a, float b) {
+    const E ea = from_f32<E>(a), eb = from_f32<E>(b);
+    return (uint32_t)*reinterpret_cast<const uint16_t*>(&ea) | ((uint32_t)*reinterpret_cast<const uint16_t*>(&eb) << 16);
+}
+template <typename E> __device__ __forceinline__ float lo16(uint32_t w) { const uint16_t h = (uint16_t)(w & 0xffffu); return to_f32<E>(*reinterpret_cast<const E*>(&h)); }
+template <typename E> __device__ __forceinline__ float hi16(uint32_t w) { const uint16_t h = (uint16_t)(w >> 16); return to_f32<E>(*reinterpret_cast<const E*>(&h)); }
 
 // 8-bit integer operands, exact int32 accumulation: one 16-byte chunk = 16 reduction elements per lane (32 per step)
 template <> struct Mma<i8_t> {

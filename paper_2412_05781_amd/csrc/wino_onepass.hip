@@ -27,30 +27,18 @@ namespace {
 
 struct OnepassGeom { int N, C, H, W, K, th, tw; };
 
-template <typename E> struct Mma16;
-template <> struct Mma16<__half> {
-    static __device__ __forceinline__ void run(const u32x4_t& a, const u32x4_t& b, f32x4_t& c) {
-        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
-    }
-};
-template <> struct Mma16<bf16_t> {
-    static __device__ __forceinline__ void run(const u32x4_t& a, const u32x4_t& b, f32x4_t& c) {
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-    }
-};
-
 typedef f32x4_t f32x4_word_t __attribute__((aligned(4)));           // bias and vector need only be aligned to their elements
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-// two elements in one word, rounded to nearest even; one instruction for bf16
-template <typename E> __device__ __forceinline__ uint32_t pack2(float a, float b);
-template <> __device__ __forceinline__ uint32_t pack2<__half>(float a, float b) { return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{a, b}), half2_t)); }
-template <> __device__ __forceinline__ uint32_t pack2<bf16_t>(float a, float b) { return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{a, b}), bf16x2_t)); }
-template <typename E> __device__ __forceinline__ float lo16(uint32_t w) { const uint16_t h = (uint16_t)(w & 0xffffu); return to_f32<E>(*reinterpret_cast<const E*>(&h)); }
-template <typename E> __device__ __forceinline__ float hi16(uint32_t w) { const uint16_t h = (uint16_t)(w >> 16); return to_f32<E>(*reinterpret_cast<const E*>(&h)); }
-template <> __device__ __forceinline__ float lo16<bf16_t>(uint32_t w) { return __uint_as_float(w << 16); }
-template <> __device__ __forceinline__ float hi16<bf16_t>(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+// two elements in one word, rounded to nearest even; one instruction for bf16 (pack2 of wino_mma.h rounds alike; its users' code is ordered otherwise with this form)
+template <typename E> __device__ __forceinline__ uint32_t convert2(float a, float b);
+template <> __device__ __forceinline__ uint32_t convert2<__half>(float a, float b) { return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{a, b}), half2_t)); }
+template <> __device__ __forceinline__ uint32_t convert2<bf16_t>(float a, float b) { return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{a, b}), bf16x2_t)); }
+template <typename E> __device__ __forceinline__ float low16(uint32_t w) { const uint16_t h = (uint16_t)(w & 0xffffu); return to_f32<E>(*reinterpret_cast<const E*>(&h)); }
+template <typename E> __device__ __forceinline__ float high16(uint32_t w) { const uint16_t h = (uint16_t)(w >> 16); return to_f32<E>(*reinterpret_cast<const E*>(&h)); }
+template <> __device__ __forceinline__ float low16<bf16_t>(uint32_t w) { return __uint_as_float(w << 16); }
+template <> __device__ __forceinline__ float high16<bf16_t>(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
 // LDS reads and writes issued so far have completed, then the workgroup barrier; transfers into LDS stay in flight
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -169,8 +157,8 @@ wino_onepass_f2_kernel(const E* __restrict__ x, const E* __restrict__ U, const f
         if constexpr (XM == XM_NHWC) {
             const int px = (tid + 512 * j) >> 3;
             const bool in = (xin >> j) & 1u;
-            float v[8] = {lo16<E>(xr[j].x), hi16<E>(xr[j].x), lo16<E>(xr[j].y), hi16<E>(xr[j].y),
-                          lo16<E>(xr[j].z), hi16<E>(xr[j].z), lo16<E>(xr[j].w), hi16<E>(xr[j].w)};
+            float v[8] = {low16<E>(xr[j].x), high16<E>(xr[j].x), low16<E>(xr[j].y), high16<E>(xr[j].y),
+                          low16<E>(xr[j].z), high16<E>(xr[j].z), low16<E>(xr[j].w), high16<E>(xr[j].w)};
             if (has_pre) {
                 float sc[8], sh[8];
                 *reinterpret_cast<float4*>(sc) = *reinterpret_cast<const float4*>(csc + (tid & 7) * 8);
@@ -200,7 +188,7 @@ wino_onepass_f2_kernel(const E* __restrict__ x, const E* __restrict__ U, const f
 #pragma unroll
             for (int u = 0; u < 4; ++u) w[u] = __builtin_amdgcn_update_dpp(w[u], w[u], 0xa5, 0xf, 0xf, true);      // quad_perm: lanes 1, 1, 2, 2
             const uint32_t w0 = pc & 1 ? w[2] : w[0], w1 = pc & 1 ? w[3] : w[1];
-            float v[5] = {lo16<E>(w0), hi16<E>(w0), lo16<E>(w1), hi16<E>(w1), lo16<E>(border)};
+            float v[5] = {low16<E>(w0), high16<E>(w0), low16<E>(w1), high16<E>(w1), low16<E>(border)};
             if (has_pre) {
                 const float sc = csc[cl], sh = csh[cl];
 #pragma unroll
@@ -246,10 +234,10 @@ wino_onepass_f2_kernel(const E* __restrict__ x, const E* __restrict__ U, const f
             for (int xi = 0; xi < 4; ++xi) {
                 const float2 d0 = tmp[xi][2 * u], d1 = tmp[xi][2 * u + 1], d2 = tmp[xi][(2 * u + 2) & 3], d3 = tmp[xi][(2 * u + 3) & 3];
                 uint32_t* p = reinterpret_cast<uint32_t*>(dst + xi * 4 * BT * 128);
-                p[0 * BT * 32] = pack2<E>(d0.x - d2.x, d0.y - d2.y);
-                p[1 * BT * 32] = pack2<E>(d1.x + d2.x, d1.y + d2.y);
-                p[2 * BT * 32] = pack2<E>(d2.x - d1.x, d2.y - d1.y);
-                p[3 * BT * 32] = pack2<E>(d1.x - d3.x, d1.y - d3.y);
+                p[0 * BT * 32] = convert2<E>(d0.x - d2.x, d0.y - d2.y);
+                p[1 * BT * 32] = convert2<E>(d1.x + d2.x, d1.y + d2.y);
+                p[2 * BT * 32] = convert2<E>(d2.x - d1.x, d2.y - d1.y);
+                p[3 * BT * 32] = convert2<E>(d1.x - d3.x, d1.y - d3.y);
             }
         };
         static_for<4>(column);
@@ -436,8 +424,8 @@ wino_onepass_f2_kernel(const E* __restrict__ x, const E* __restrict__ U, const f
                 auto put = [&](const float* v, size_t at) __attribute__((always_inline)) {
                     uint4 w = make_uint4(0u, 0u, 0u, 0u);
                     if (res) w = *reinterpret_cast<const uint4*>(res + at);
-                    w.x = pack2<E>(v[0] + lo16<E>(w.x), v[1] + hi16<E>(w.x)); w.y = pack2<E>(v[2] + lo16<E>(w.y), v[3] + hi16<E>(w.y));
-                    w.z = pack2<E>(v[4] + lo16<E>(w.z), v[5] + hi16<E>(w.z)); w.w = pack2<E>(v[6] + lo16<E>(w.w), v[7] + hi16<E>(w.w));
+                    w.x = convert2<E>(v[0] + low16<E>(w.x), v[1] + high16<E>(w.x)); w.y = convert2<E>(v[2] + low16<E>(w.y), v[3] + high16<E>(w.y));
+                    w.z = convert2<E>(v[4] + low16<E>(w.z), v[5] + high16<E>(w.z)); w.w = convert2<E>(v[6] + low16<E>(w.w), v[7] + high16<E>(w.w));
                     *reinterpret_cast<uint4*>(y + at) = w;
                 };
                 put(o0, o);
@@ -455,8 +443,8 @@ wino_onepass_f2_kernel(const E* __restrict__ x, const E* __restrict__ U, const f
                 if (row_ok) {                                                          // eight pixels, 16-byte aligned, inside the row
                     uint4 w = make_uint4(0u, 0u, 0u, 0u);
                     if (res) w = *reinterpret_cast<const uint4*>(res + o);
-                    w.x = pack2<E>(v0[0] + lo16<E>(w.x), v1[0] + hi16<E>(w.x)); w.y = pack2<E>(v0[1] + lo16<E>(w.y), v1[1] + hi16<E>(w.y));
-                    w.z = pack2<E>(v0[2] + lo16<E>(w.z), v1[2] + hi16<E>(w.z)); w.w = pack2<E>(v0[3] + lo16<E>(w.w), v1[3] + hi16<E>(w.w));
+                    w.x = convert2<E>(v0[0] + low16<E>(w.x), v1[0] + high16<E>(w.x)); w.y = convert2<E>(v0[1] + low16<E>(w.y), v1[1] + high16<E>(w.y));
+                    w.z = convert2<E>(v0[2] + low16<E>(w.z), v1[2] + high16<E>(w.z)); w.w = convert2<E>(v0[3] + low16<E>(w.w), v1[3] + high16<E>(w.w));
                     *reinterpret_cast<uint4*>(y + o) = w;
                 } else {
 #pragma unroll
