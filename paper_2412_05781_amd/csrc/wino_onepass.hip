@@ -488,20 +488,24 @@ static double onepass_us(const Geom& g, int xm, bool gn, int ns) {
     return 3.0 + (double)((wgs + 255) / 256) * (t.ends + (g.C / 64) * (t.pixels[gn] + t.subtile[gn] * ns));
 }
 
-// ... and of the paths that store V, fitted the same way (12 % and 8 %).  Chain: V and M through memory and the products.  Fused variant: the
-// transform, then rounds of its blocks, each a serial chain of 16 positions; block shapes as fused_pick_shape() takes them.  It reads a
-// residual in 2.1 (NCHW) to 3.5 us per million outputs, this kernel in 0.5.
+// ... and of the paths that store V, fitted the same way, with 200 more calls of up to 540 000 pixels (12 % and 8 %).  Chain: V and M through
+// memory, at more per byte where the two are larger than the 256 MB memory-side cache, and the products.  Fused variant: the transform, then
+// rounds of its blocks, each a serial chain of 16 positions; block shapes as fused_pick_shape() takes them.  Channel-last, V beyond 100 MB
+// costs it more (256 channels at 512x512 379 NCHW, 446 channel-last).  It reads a residual in 2.1 (NCHW) to 3.5 us per million outputs, this
+// kernel in 0.5.
 static double stored_us(const Geom& g, bool ragged, bool gn, bool nhwc, bool residual, bool fused_variant) {
-    const double T = g.T, C = g.C;
+    const double T = g.T, C = g.C, TC = T * C;
     if (!fused_variant) {
-        const double K = g.K < 128 ? 128.0 : (double)g.K;
-        return (11.5 + T * (1.18e-5 * C + 2.05e-5 * K + 2e-8 * C * K) + (gn ? 4.6e-6 * T * C : 0.0)) * (ragged ? 1.04 : 1.0);
+        const double K = g.K < 128 ? 128.0 : (double)g.K, far = T * (32.0 * C + 64.0 * K) - 219e6;
+        return (12.5 + T * (8.15e-6 * C + 1.76e-5 * K + 3.6e-8 * C * K) + (gn ? 3.3e-6 * TC : 0.0) + (far > 0.0 ? 7.7e-8 * far : 0.0)) *
+               (ragged ? 1.06 : 1.0);
     }
     auto blocks = [&](int bk, int bt) { return (double)((g.K + bk - 1) / bk) * (double)((g.T + bt - 1) / bt); };
     auto rounds = [](double n) { const double most = (double)(((long long)n + 255) / 256), r = 0.3 * n / 256.0 + 0.7 * most; return r < 1.0 ? 1.0 : r; };
     const double stages = 16.0 * (g.C / 64), b128 = blocks(128, 128), b64 = g.K < g.T ? blocks(128, 64) : blocks(64, 128), small = blocks(64, 64) / 512.0;
-    const double gemm = b128 >= 160 ? rounds(b128) * (21.8 + 0.55 * stages) : (b64 >= 200 ? rounds(b64) * (16.5 + 0.33 * stages) : (small < 1.0 ? 1.0 : small) * (15.7 + 0.235 * stages));
-    return 3.0 + T * C * 8.1e-6 * (ragged ? 1.38 : 1.0) + gemm + (gn ? 4.8e-6 * T * C : 0.0) +
+    const double gemm = b128 >= 160 ? rounds(b128) * (22.9 + 0.542 * stages) : (b64 >= 200 ? rounds(b64) * (16.8 + 0.332 * stages) : (small < 1.0 ? 1.0 : small) * (15.8 + 0.238 * stages));
+    const double last = nhwc ? 0.3e-6 * TC + (TC > 3.3e6 ? 5.2e-6 * (TC - 3.3e6) : 0.0) : 0.0;
+    return 3.0 + 7.8e-6 * TC * (ragged ? 1.44 : 1.0) + gemm + last + (gn ? (nhwc ? 3.65e-6 : 4.4e-6) * TC : 0.0) +
            (residual ? (nhwc ? 3.0e-6 : 1.7e-6) * g.N * g.H * (double)g.W * g.K : 0.0);
 }
 
@@ -509,7 +513,7 @@ static double stored_us(const Geom& g, bool ragged, bool gn, bool nhwc, bool res
 // where it is faster than the paths that store V, by the times above: over the measured calls 0.5 % more than the better one each time.  One
 // kernel / the other path (us; chain, and with (f) the fused variant): NCHW 320 channels at 128x128 80 / 111, with GroupNorm 92 / 128, (f)
 // 92 / 103; at 64x64 30 / 35, 640 channels at 64x64 with GroupNorm 93 / 88, 512 at 256x256 with GroupNorm 487 / 433; channel-last 320 at
-// 64x64 25 / 34, with GroupNorm (f) 36 / 51, 512 at 256x256 337 / 389, 640 -> 320 at 96x96 110 / 87, 192 -> 320
+// 64x64 25 / 34, with GroupNorm (f) 36 / 51, 512 at 256x256 337 / 389, 256 at 512x512 (f) 357 / 446, 640 -> 320 at 96x96 110 / 87, 192 -> 320
 // at 128x312 with GroupNorm and residual (f) 83 / 119; element by element 64 -> 128 at 250x250
 // 47 / 62, (f) 46 / 33, 128 -> 128 at 300x300 93 / 121, (f) 91 / 80, 192 -> 96 at 500x300 (f) 164 / 198, 256 -> 256 at 250x250 with GroupNorm
 // 226 / 204, (f) 227 / 126, 320 -> 320 at 52x78 (N=2) with GroupNorm 69 / 46.

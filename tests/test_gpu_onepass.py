@@ -64,9 +64,9 @@ def test_onepass(case, fused, layout, dtype):
 @pytest.mark.parametrize("norm", [False, True])
 @pytest.mark.parametrize("variant,dtype", [(B.WINO_F2, "f16"), (B.WINO_F2, "bf16"), (B.WINO_FUSED_F2, "bf16")])
 @pytest.mark.parametrize("ns,mode,up,case", [
-    (2, 2, False, (2, 192, 16, 129, 58)), (2, 2, False, (1, 128, 32, 122, 102)), (2, 2, True, (1, 192, 16, 128, 120)),
-    (3, 2, False, (2, 192, 80, 122, 102)), (3, 2, True, (2, 128, 80, 64, 136)), (4, 2, False, (2, 192, 112, 122, 102)),
-    (4, 2, True, (2, 192, 112, 128, 120)), (4, 1, False, (1, 192, 320, 101, 72)), (5, 1, False, (1, 192, 400, 101, 72)),
+    (2, 2, False, (1, 192, 16, 150, 130)), (2, 2, False, (1, 128, 48, 151, 131)), (2, 2, True, (1, 192, 16, 160, 120)), (3, 2, False, (2, 192, 80, 122, 102)),
+    (3, 2, True, (1, 128, 96, 160, 120)), (4, 2, False, (2, 192, 112, 122, 102)), (4, 2, False, (1, 128, 112, 180, 130)), (4, 2, True, (1, 128, 112, 200, 136)),
+    (4, 1, False, (1, 192, 320, 101, 72)), (5, 1, False, (1, 192, 400, 101, 72)),
     (2, 0, False, (1, 192, 16, 97, 75)), (3, 0, False, (1, 192, 400, 66, 66)), (4, 0, False, (2, 128, 240, 66, 66)), (4, 0, False, (1, 192, 320, 101, 72)),
     (5, 0, False, (2, 128, 320, 66, 66)), (5, 0, False, (1, 192, 400, 101, 72)), (5, 0, True, (2, 192, 320, 66, 66))])
 def test_onepass_chunks(ns, mode, up, case, variant, dtype, norm):

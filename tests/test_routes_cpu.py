@@ -56,7 +56,11 @@ def test_direct_path_blocks_of_short_reductions():
     (2, 640, 640, 64, 64, False, False, True, False, False), (1, 512, 512, 128, 128, False, False, True, False, False), (1, 512, 512, 256, 256, False, False, True, False, False),
     (1, 256, 256, 256, 256, False, True, True, False, False), (2, 320, 320, 64, 64, False, False, True, False, True), (2, 320, 320, 128, 128, False, True, True, False, True),
     (1, 256, 256, 256, 256, True, False, True, False, True), (2, 320, 320, 64, 64, True, True, True, False, True), (1, 512, 256, 128, 128, True, True, True, False, True),
-    (4, 320, 320, 64, 96, True, True, True, False, True), (1, 512, 512, 128, 128, False, True, False, False, False), (2, 192, 192, 104, 152, False, False, True, False, True), (2, 1280, 1280, 32, 32, True, False, False, False, False)])
+    (4, 320, 320, 64, 96, True, True, True, False, True), (1, 512, 512, 128, 128, False, True, False, False, False), (2, 192, 192, 104, 152, False, False, True, False, True), (2, 1280, 1280, 32, 32, True, False, False, False, False),
+    # large images
+    (1, 256, 256, 512, 512, True, True, False, False, True), (1, 256, 256, 512, 512, True, True, True, False, True), (1, 512, 256, 256, 256, True, True, False, False, True),
+    (1, 128, 352, 495, 744, True, True, False, False, True), (1, 640, 320, 256, 256, False, False, False, False, True), (1, 384, 384, 384, 384, False, False, False, False, True),
+    (1, 256, 256, 512, 512, False, True, False, False, False), (1, 512, 512, 256, 256, False, True, False, False, False), (1, 512, 512, 256, 256, True, True, True, False, False), (1, 256, 512, 512, 512, False, True, True, False, False)])
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_one_kernel_f2(N, C, K, H, W, nhwc, fused, norm, up, taken, dtype):
     assert (routes.onepass(N, C, K, H, W, dtype, nhwc, fused, norm, up)[0] > 0) == taken
