@@ -64,7 +64,11 @@ typedef enum wino_dtype { WINO_F32 = 0, WINO_F16 = 1, WINO_BF16 = 2 } wino_dtype
 
 /*
  * WINO_F2 / WINO_F4: Winograd F(2x2,3x3) / F(4x4,3x3), three kernels (activation
- * transform, batched MFMA GEMM, output transform).  WINO_AUTO: the library picks F2,
+ * transform, batched MFMA GEMM, output transform), or all three steps in one kernel where
+ * that is faster: F(2x2) with two-byte storage, C a multiple of 64 and K of 16, and F(4x4) in
+ * fp32 with at most 16 channels.  Same transforms and the same error; the sums over the channels
+ * are in another order, so results may differ in the last place from the three kernels' and
+ * between sizes.  WINO_AUTO: the library picks F2,
  * F4 or one of the fused variants per shape and storage type (wino_resolve_variant).  WINO_DIRECT: direct correlation; a filter prepared with it
  * (wino_filter_transform) makes wino_conv2d / wino_conv2d_ex run the implicit-GEMM
  * MFMA kernel described at the end of this header (no transformed tensors, output
@@ -76,7 +80,8 @@ typedef enum wino_dtype { WINO_F32 = 0, WINO_F16 = 1, WINO_BF16 = 2 } wino_dtype
  * (output channels x tiles) walks the 16 positions in turn, keeps one product block in the MFMA
  * accumulators and adds it at once, with its +-1 coefficients, into four output accumulators; the
  * product M is never stored (the paper's locality argument: dependent steps stay on chip).  Same U and
- * V as WINO_F2, same error (~5e-4 for fp16); workspace = V only.
+ * V as WINO_F2, same error (~5e-4 for fp16); workspace = V only.  Where the one-kernel F(2x2) above is
+ * faster, that runs here too.
  * WINO_FUSED_F4: the same for F(4x4,3x3), two-byte storage types only (WINO_ERR_DTYPE for fp32).  An output tile has 16 values,
  * so step (iii) is folded in one dimension at a time: four row sums per row of the transformed tile, added into the 16 output
  * accumulators when the row is complete.  Same U and V as WINO_F4, same error (~3e-3 for fp16); workspace = V only.  Meant for
@@ -169,8 +174,9 @@ int wino_conv2d_static(const void *x, const wino_filter *w_t, const float *bias,
                        int N, int C, int H, int W, int K, int layout, void *stream);
 
 /*
- * The three stages on their own (the same kernels wino_conv2d_ex chains), for
- * stage-by-stage checks and per-kernel measurement.  Layouts, `e` = dtype:
+ * The three stages on their own (the kernels wino_conv2d_ex chains where it does not run
+ * all three steps in one kernel, see WINO_F2), for stage-by-stage checks and per-kernel
+ * measurement.  Layouts, `e` = dtype:
  *   V[alpha^2][T][Cp]  e     step (i), activation: V[xi,nu,t,c] = (B^T d[c,t] B)[xi,nu],
  *                            d = alpha x alpha window of xhat at rows m*ti-1.., cols m*tj-1..;
  *                            entries with c >= C are written as zero
@@ -180,7 +186,7 @@ int wino_conv2d_static(const void *x, const wino_filter *w_t, const float *bias,
  * Channel-last (WINO_NHWC): the product is kept transposed, M[alpha^2][T][K], so that the channel
  * index stays contiguous from x to y.  wino_batched_gemm is symmetric in its two operands: called
  * as (V, U, M, T, C, K) it writes exactly that tensor, and wino_output_transform with
- * layout = WINO_NHWC reads it (and only it).  wino_conv2d_ex does the same internally.
+ * layout = WINO_NHWC reads it (and only it).  The chain of wino_conv2d_ex does the same internally.
  */
 int wino_input_transform(const void *x, void *V, int N, int C, int H, int W,
                          int dtype, int variant, int layout, void *stream);

@@ -239,8 +239,8 @@ static const TileShape kTiles[3] = {{64, 64, 0.27, 0.20, 1.3}, {64, 80, 0.35, 0.
 // 5 % longer, so a long reduction prefers the small blocks, and so does a last round that is not full.  Channel-last, us, here / there:
 // 1x1 at 256x256 128 -> 512 53 / 40, 512 -> 512 75 / 63, 1024 -> 1024 203 / 180; 3x3 128 -> 512 121 / 101, 512 -> 512 313 / 307; at 128x128
 // 1024 -> 1024 287 / 295; one and a half rounds (768 channels at 180x180) 1x1 128 in 39.7 / 36.5, 3x3 128 in 85 / 90, 1024 in 77 / 86 (1x1).
-// An image of an odd number of pixels, NCHW (see below), 1x1: 192 -> 320 at 311x201 82 / 75, 256 at 181x181 41 / 38; 1856 -> 1184 at 23x57 (N=2)
-// 45 / 40; but 3x3 256 at 181x181 72 / 74, 320 at 97x121 (N=2) 86 / 118.
+// An image of an odd number of pixels, NCHW (see below), 1x1: 192 -> 320 at 311x201 71 / 75 (with the 128x128 block 82), 256 at 181x181 41 / 38;
+// 1856 -> 1184 at 23x57 (N=2) 45 / 40; but 3x3 256 at 181x181 72 / 74, 320 at 97x121 (N=2) 86 / 118.
 // With a residual or a vector to add it loses: it reads them element by element (bf16 3x3, 256 -> 512 at 360x360: vector 355 / 378 NCHW, 338
 // / 355 channel-last, residual 407 / 524, 380 / 439).  The number of reduction ranges is one either way.
 // NCHW, where its stores are the narrower ones: 1x1 at 256x256 64 -> 512 52 / 48, 1024 -> 1024 261 / 246; 3x3 64 -> 512 89 / 81, 320 -> 512 234 / 233.
