@@ -175,9 +175,10 @@ int wino_resolve_variant(int N, int C, int H, int W, int K, int dtype, int varia
     // bfloat16 has 8 significant bits: F(4x4) would sit near 2.5e-2, F(2x2) near 4e-3
     if (dtype == WINO_BF16) pick = WINO_F2;
     // The fused variants (steps (ii) and (iii) in one kernel) where they measured faster with 2-byte storage.  F(2x2): against
-    // the F(2x2) chain from 4096 tiles on (128x128 images at batch 2 and everything larger: 0.6-0.9x the time).  F(4x4): against
-    // the F(4x4) chain from 4096 tiles on, with at most 512 channels and enough 64x64 blocks for two rounds of workgroups
-    // (512 channels at 256x256: 0.96x, 256 at 512x512: 0.85x, 128 at 1024x1024: 0.67x; with fewer tiles 1.2-2.2x slower).
+    // the F(2x2) chain from 4096 tiles on (128x128 images at batch 2 and everything larger: 0.6-0.9x the time; where F(2x2) in one kernel is
+    // the faster one, either variant runs that).  F(4x4): against the F(4x4) chain from 4096 tiles on, with at most 512 channels and
+    // enough 64x64 blocks for two rounds of workgroups (512 channels at 256x256: 0.97x, 256 at 512x512: 0.83x, 128 at 1024x1024:
+    // 0.66x; with fewer tiles 1.2-2.2x slower).  128 channels at 1024x1024 take 522, channel-last 400 us as F(2x2) in one kernel, 525 and 491 here.
     const Geom g2 = make_geom(N, C, H, W, K, 2);
     if (dtype != WINO_F32 && K >= 32) {
         if (pick == WINO_F2 && g2.T >= 4096) pick = WINO_FUSED_F2;
@@ -192,17 +193,18 @@ int wino_recommend_variant(int N, int C, int H, int W, int K, int dtype) {
     if (v < 0 || !igemm_dims_ok(N, C, H, W, K, 3, 1)) return v;
     // Measured on the VAE-sized layers: with few channels and many pixels the Winograd path is bound by the
     // traffic of V and M (about 27 bytes per output pixel and channel for F(4x4), 48 for F(2x2)), the direct
-    // path by its 18*C*K flops per pixel at 0.6-1.0 PFLOP/s.  256 channels at 512x512: direct 1.25x faster;
-    // 512 channels at 256x256: Winograd 1.18x faster.  The crossing is put at sqrt(C*K) = 320 against
-    // F(4x4) and 448 against F(2x2).
+    // path by its 18*C*K flops per pixel at 0.6-1.0 PFLOP/s.  256 channels at 512x512 as an F(4x4) chain 399 / 397 us (NCHW / NHWC),
+    // direct 396 / 342; 512 channels at 256x256 248 / 255 and 328 / 309.  The crossing is put at sqrt(C*K) = 320 against F(4x4) and 448
+    // against F(2x2), which was set when F(2x2) always stored V (256 channels at 512x512: 650-690 us, 354-384 now).
     // A handful of output channels on a large image (the VAE's 128 -> 3 at 1024 x 1024): the Winograd path would write and
     // re-read a transformed activation tensor far larger than x; the direct path has a one-pass kernel for it (fp16, at
     // least 512 tiles of 8 x 64 pixels; measured 130-160 us against 320-360 us for F(4x4))
     if (dtype == WINO_F16 && K <= 4 && C >= 16 && C % 16 == 0 && W % 8 == 0 &&
         (long long)N * ((H + 7) / 8) * ((W + 63) / 64) >= 512)
         return WINO_DIRECT;
-    // where WINO_AUTO takes the fused F(4x4) variant it is also ahead of the direct path (256 channels at 512x512: 342-350 us in
-    // either layout against 417 / 356 NCHW / NHWC; 128 at 1024x1024: 530 / 498 against 702 / 541; 512 at 256x256: 254 / 252 against 351 / 326)
+    // where WINO_AUTO takes the fused F(4x4) variant it is ahead of the direct path, but for 128 channels channel-last; the choice does not
+    // know the layout (NCHW / NHWC, us: 256 channels at 512x512 331 / 335 against 396 / 342; 128 at 1024x1024 522 / 490 against 547 / 460; 512
+    // at 256x256 219 / 222 against 328 / 309)
     if (v == WINO_FUSED_F4) return v;
     const long long pixels = (long long)N * H * W;
     const long long ck = (long long)C * K;
