@@ -300,19 +300,23 @@ static bool fp8_wide(const ConvGeom& g) { return g.K % 256 == 0 && (long long)((
 
 // Whole reductions and two-byte y.  Left to conv_igemm.hip: wide blocks with a channel-last y, where its sixteen waves measured 224 us
 // against 232 here (256 channels at 512x512), and images too small to give every compute unit a 128x128 block, where its 64x64 blocks are
-// faster.  In NCHW, where outputs leave through LDS here if the images are whole 16-byte pieces, half as many blocks are enough, and with no
-// more than a dozen stages, or where the last stage of a tap is a partial one, which its kernel fills through registers, any number (us, here
-// / there: channel-last 1x1 64 -> 128 at 32x32 11.3 / 8.5, 3x3 256 -> 256 at 64x64 23.7 / 18.1, 640 -> 640 at 64x64 40.9 / 38.3, but 256 ->
-// 256 at 128x128 27.9 / 34.5; NCHW 3x3 256 -> 256 at 64x64 20.1 / 18.2, 1280 -> 320 at 64x64 61.2 / 57.7, but 256 -> 256 at 96x96 22.0 / 24.5,
-// 64 -> 256 at 64x64 15.7 / 17.4, 320 -> 320 25.5 / 28.0, 1x1 1280 -> 128 15.9 / 16.6; at 15x12 128 -> 1024 11.3 / 9.7).  Everything else is
-// faster here (256 channels at 512x512 270 / 222, 512 at 256x256 187 / 151, 128 at 512x512 135 / 86, at 1024x1024 channel-last 456 / 353,
-// 192 -> 320 at 312x200 124 / 73).
+// faster; but not with so few output channels that its block is as empty as this one (us, here / there, channel-last: 1x1 64 -> 8 at 76x16
+// 6.5 / 8.7, 384 -> 8 at 76x72, N=4, 14.7 / 16.9, 3x3 16 -> 8 at 257x74 14.4 / 17.4, 1x1 48 -> 20 at 61x344 8.2 / 9.5; 112 -> 64 at 48x157
+// 10.8 / 9.0, and with 22 channels, stored one by one, 320 -> 22 at 141x120, stride 2, 14.6 / 12.3).
+// In NCHW, where outputs leave through LDS here if the images are whole 16-byte pieces, half as many blocks are enough, and with no
+// more than a dozen stages and more than 16 channels, or where the last stage of a tap is a partial one, which its kernel fills through
+// registers, any number (channel-last 1x1 64 -> 128 at 32x32 11.3 / 8.5, 3x3 256 -> 256 at 64x64 23.7 / 18.1, 640 -> 640 at 64x64 40.9 / 38.3,
+// but 256 -> 256 at 128x128 27.9 / 34.5; NCHW 3x3 256 -> 256 at 64x64 20.1 / 18.2, 1280 -> 320 at 64x64 61.2 / 57.7, but 256 -> 256 at 96x96
+// 22.0 / 24.5, 64 -> 256 at 64x64 15.7 / 17.4, 320 -> 320 25.5 / 28.0, 1x1 1280 -> 128 15.9 / 16.6; at 15x12 128 -> 1024 11.3 / 9.7; 3x3 128 ->
+// 8 at 91x152, stride 2, 16.1 / 14.0).  Everything else is faster here (256 channels at 512x512 270 / 222, 512 at 256x256 187 / 151, 128 at
+// 512x512 135 / 86, at 1024x1024 channel-last 456 / 353, 192 -> 320 at 312x200 124 / 73, 64 -> 16 at 118x131, N=8, 63 / 48, there / here).
 bool igemm_fp8_tile_ok(const ConvGeom& g, int dt, bool nhwc, int nsplit) {
     if (!two_byte(dt) || nsplit != 1 || (size_t)256 * g.Cp >= ((size_t)1 << 31)) return false;       // 32-bit lane offsets
     const long long blocks = (long long)((g.T + 127) / 128) * ((g.K + 127) / 128), outputs = (long long)g.T * g.K;
-    if (blocks >= 256 && (nhwc || outputs >= 136LL * 128 * 128)) return !(nhwc && fp8_wide(g));
-    if (nhwc || g.Ho * g.Wo % 8 != 0) return false;
-    return outputs >= 136LL * 128 * 128 || g.Cp % 128 != 0 || g.R * g.R * (g.Cp / 128) <= 12;
+    if (blocks >= 256) return !(nhwc && fp8_wide(g));
+    if (nhwc) return g.K <= 16 || (g.K <= 32 && g.K % 4 == 0);
+    if (g.Ho * g.Wo % 8 != 0) return false;
+    return outputs >= 136LL * 128 * 128 || g.Cp % 128 != 0 || (g.K > 16 && g.R * g.R * (g.Cp / 128) <= 12);
 }
 
 template <typename EO, bool PIX_A>

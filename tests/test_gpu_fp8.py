@@ -114,7 +114,7 @@ def test_fp8_fused_operators(dtype, layout):
                                         ((1, 384, 256, 255, 259, 1), (True, False)), ((1, 112, 200, 24, 40, 3), (True, False)),
                                         ((2, 48, 136, 25, 40, 3), (True, False)), ((3, 112, 72, 9, 11, 3), (False, False)),
                                         ((1, 272, 136, 128, 129, 1), (True, True)), ((1, 128, 136, 128, 129, 3), (True, True)), ((2, 48, 330, 101, 99, 3), (True, True)),
-                                        ((1, 112, 260, 150, 121, 3), (True, True))])
+                                        ((1, 112, 260, 150, 121, 3), (True, True)), ((2, 112, 7, 19, 23, 3), (False, True)), ((1, 144, 28, 9, 13, 1), (False, True)), ((3, 128, 1, 8, 16, 3), (False, True))])
 def test_fp8_whole_reductions(case, taken, layout):
     N, C, K, H, W, R = case
     assert routes.fp8_tile(N, C, K, H, W, R, 1, "f16", layout == B.WINO_NHWC) == taken[layout == B.WINO_NHWC]

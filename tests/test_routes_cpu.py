@@ -80,6 +80,9 @@ def test_one_kernel_f2_residual_and_bounds():
     (1, 256, 256, 128, 128, 3, 1, True, True), (1, 64, 512, 96, 96, 1, 1, True, True), (1, 128, 128, 1024, 1024, 3, 1, True, True), (1, 256, 256, 512, 512, 3, 1, True, False),
     (1, 256, 256, 64, 64, 3, 1, False, False), (1, 1280, 320, 64, 64, 3, 1, False, False), (1, 640, 128, 180, 180, 3, 1, False, True), (1, 256, 256, 96, 96, 3, 1, False, True), (1, 256, 64, 180, 180, 3, 1, False, False), (1, 640, 640, 64, 64, 3, 1, False, True), (1, 64, 256, 64, 64, 3, 1, False, True),
     (1, 1280, 128, 64, 64, 1, 1, False, True), (1, 320, 320, 64, 64, 3, 1, False, True), (1, 64, 512, 60, 49, 1, 2, False, False), (1, 64, 512, 60, 50, 1, 2, False, False), (1, 128, 1024, 15, 12, 1, 1, False, False), (1, 128, 1024, 16, 12, 1, 1, False, True),
+    # few output channels
+    (1, 64, 8, 76, 16, 1, 1, True, True), (1, 16, 1, 54, 6, 1, 1, True, True), (1, 48, 20, 61, 344, 1, 1, True, True), (1, 320, 22, 141, 120, 1, 2, True, False), (1, 112, 64, 48, 157, 1, 1, True, False),
+    (8, 64, 16, 118, 131, 3, 1, False, True), (4, 256, 16, 103, 128, 3, 1, False, True), (1, 128, 8, 91, 152, 3, 2, False, False), (1, 192, 8, 58, 71, 1, 1, False, False),
     (1, 256, 256, 128, 128, 3, 1, False, True), (1, 256, 256, 512, 512, 3, 1, False, True)])
 def test_fp8_kernel(N, C, K, H, W, R, st, nhwc, taken):
     for dtype in ("f16", "bf16"):
