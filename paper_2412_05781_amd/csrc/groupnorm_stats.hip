@@ -246,7 +246,7 @@ hipError_t launch_groupnorm_stats(const void* x, float* stats, int N, int C, int
         return hipGetLastError();
     }
     // channel-last with whole 16-byte channel octets, all of them within one workgroup's lanes; tensors of less than about 100 000 elements per
-    // image are faster group by group (64 channels at 8x8 4.9 us against 6.8, 1280 at 8x8 6.6 against 7.6, 128 at 32x32 8.2 against 7.2)
+    // image are faster group by group (64 channels at 8x8 4.9 us against 6.8, 1280 at 8x8 6.7 against 7.4, 128 at 32x32 8.1 against 7.2)
     constexpr int NT = 512;
     if (nhwc && (size_t)HW * C >= 98304 && C % (int)epc == 0 && C / (int)epc <= NT && x16) {
         // about 16 KB per workgroup and at most 256 per image: 32 slabs of pixels, then blocks of groups, of whole 16-byte pieces and at
