@@ -18,9 +18,11 @@ struct IgemmPost {
 };
 
 // The 16x16-tile kernel (conv_igemm_tile.hip): two-byte storage types, Cp a whole number of 128-byte stages.
-// Its choice of block and of the number of reduction ranges; id < 0: it does not apply or another block of conv_igemm.hip is better.
-// plain: nothing but a bias is added to the sums.
+// igemm_block_plan: its choice of block and of the number of reduction ranges, at most most_sp; id < 0: left to the kernels of conv_igemm.hip.
+// igemm_tile_plan: the number of ranges that a workspace is sized for (plain: nothing but a bias is added to the sums).
 struct IgemmTilePlan { int id, split; };
+IgemmTilePlan igemm_block_plan(int T, int K, int Cp, int R, int dt, bool nhwc, int most_sp);
+bool igemm_tile_fits(const ConvGeom& g);                               // the operands are small enough for the kernel's offsets
 int igemm_split_rule(int T, int K, int Cp, int R, int dt);             // ranges where the 16x16-tile kernel does not apply (conv_igemm.hip)
 IgemmTilePlan igemm_tile_plan(int T, int HoWo, int K, int Cp, int R, int dt, bool nhwc, bool plain);
 hipError_t launch_igemm_tile(const void* xh, const void* Wr, const float* bias, void* y, float* part, const IgemmTilePlan& plan,

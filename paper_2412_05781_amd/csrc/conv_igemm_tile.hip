@@ -1,10 +1,16 @@
 // Implicit-GEMM convolution, two-byte storage types: same operands and same staging as conv_igemm.hip (128-byte reduction stages,
-// global -> LDS transfers into a ring, XOR-swizzled chunks), but built from 16x16 MFMA tiles with four waves, blocks small enough that
-// two or three workgroups share a compute unit, and the fragments of the next step requested before the current one is multiplied.
+// global -> LDS transfers into a ring, XOR-swizzled chunks), but built from 16x16 MFMA tiles with eight waves, and the fragments of the next
+// step requested before the current one is multiplied.
 //
-// The layers of a UNet (1x1 shortcuts, stride 2, 8x8 ... 64x64 outputs) are bound by the latency of a stage - transfer, barrier, LDS
-// read, MFMA - and what hides it is another workgroup on the same unit, not a deeper ring (64x64 blocks with 2, 3, 4 and 9 slots: within
-// 3 %).  On large images the 128x128 block reaches 0.95 PFLOP/s (512 channels at 256x256 in 323 us).
+// The layers of a UNet (1x1 shortcuts, stride 2, 8x8 ... 64x64 outputs) have 2-8 us of stages between 4 us of start and stores, and a stage of
+// a few hundred clocks is as long as the instructions that a wave issues in it, one in four clocks or more.  So nothing is computed
+// per stage that can be computed once: a transfer is one buffer load with a fixed lane offset and a scalar that moves from stage to stage;
+// what lies outside the image has an offset beyond the descriptor's range and reads zeros, so a tap is a mask and a scalar; divisions are
+// multiplications prepared on the host; bias and addresses of the stores are found once.  Against pointers per transfer, tested taps and divisions
+// per store (64x64 block): 320 channels at 64x64 (N=2), stride 2, channel-last 17.7 -> 14.4 us; eight waves instead of four 14.0.
+// What is left of those 14.4: transfers alone 13.7, everything but the transfers 8.8, neither 4.2; the transfers run at 32 bytes per clock and
+// unit (60 where every workgroup reads the same block), and neither a deeper ring nor staggered starts move that.  512 channels at
+// 256x256, 3x3: 313 -> 306 us.
 //
 // Rows of the block are the dimension that is contiguous in y - output channels for a channel-last y, pixels for NCHW - because a lane
 // of a 16x16 accumulator holds four consecutive rows: they leave as one 8-byte store.  NCHW images with an odd number of
@@ -15,163 +21,239 @@
 
 namespace wino {
 
+namespace {
+
+// n / d for n < 2^31 as a multiplication, prepared on the host (Granlund and Montgomery, "Division by invariant integers using multiplication")
+struct FastDiv { uint32_t mul, shift; };
+FastDiv fast_div(uint32_t d) {
+    uint32_t l = 0;
+    while ((1u << l) < d) ++l;
+    return {(uint32_t)((((1ull << l) - d) << 32) / d + 1), l};
+}
+__device__ __forceinline__ uint32_t divide(uint32_t n, FastDiv f) { return (__umulhi(n, f.mul) + n) >> f.shift; }
+
+struct TileGeom {
+    FastDiv howo, wo, tiles, nsplit;       // divisions by Ho*Wo, Wo, the shorter tile dimension, the number of ranges
+    int tiles_k_fast;                      // the shorter one is that of the output channels
+    int total_blocks, blocks_per_xcd, nsplit_n, tiles_short;
+};
+
+typedef int rsrc_t __attribute__((ext_vector_type(4)));
+// Descriptor for buffer loads of at most 2 GB from `base` on.  A lane whose offset is kOutside lies beyond its range whatever scalar offset
+// is added, and reads zeros; every other lane's offset is inside the operand.
+constexpr uint32_t kOutside = 0x80000000u, kRange = 0x7fffffffu;
+__device__ __forceinline__ rsrc_t make_rsrc(const void* base) {
+    const uint64_t a = reinterpret_cast<uint64_t>(base);
+    rsrc_t r;
+    r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+    r[1] = __builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xffffu));
+    r[2] = (int)kRange;
+    r[3] = 0x00020000;
+    return r;
+}
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+// 1 KB to LDS: a wave-uniform descriptor and byte offset, a byte offset per lane; a lane outside the range writes zeros
+__device__ __forceinline__ void dma_buffer_1k(rsrc_t r, uint32_t lane_off, uint32_t off, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(lds_addr), "v"(lane_off), "s"(r), "s"(__builtin_amdgcn_readfirstlane(off)) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
+}  // namespace
+
 // BP pixels x BK output channels per workgroup, WP x WK waves.  PIX_A: pixels are the rows (NCHW y), else output channels (channel-last y).
 template <typename E, int BP, int BK, int WP, int WK, int NST, bool PIX_A>
 __global__ void __launch_bounds__(WP * WK * 64)
-conv_igemm_tile_kernel(const E* __restrict__ xh, const E* __restrict__ Wr, const E* __restrict__ zero_row, const float* __restrict__ bias,
-                       E* __restrict__ y, float* __restrict__ part, ConvGeom g, IgemmPost post, int tiles_p, int tiles_k,
-                       int total_blocks, int blocks_per_xcd, int nsplit, int vec_ok, int planes) {
+conv_igemm_tile_kernel(const E* __restrict__ xh, const E* __restrict__ Wr, const float* __restrict__ bias,
+                       E* __restrict__ y, float* __restrict__ part, ConvGeom g, IgemmPost post, TileGeom q, int vec_ok, int planes) {
     constexpr int RB = 128, CPR = RB / 16, BKE = RB / 2;  // stage: bytes, 16-byte chunks and reduction elements per row
-    constexpr int BM = PIX_A ? BP : BK, BN = PIX_A ? BK : BP, WGM = PIX_A ? WP : WK, WGN = PIX_A ? WK : WP;
-    constexpr int ROWS = BM + BN, NW = WP * WK;
-    constexpr int LOADS = ROWS / 8, LPW = (LOADS + NW - 1) / NW;       // 1 KB transfers (8 rows) per stage, and per wave
-    constexpr int WTM = BM / WGM, WTN = BN / WGN, FM = WTM / 16, FN = WTN / 16;
-    constexpr int STAGE_BYTES = ROWS * RB;
-    static_assert(WTM % 16 == 0 && WTN % 16 == 0 && LOADS >= NW, "tile shape");
+    constexpr int NW = WP * WK;
+    constexpr int PL = BP / 8 / NW, KLOADS = BK / 8, KL = (KLOADS + NW - 1) / NW, LPW = PL + KL;      // 1 KB transfers (8 rows) per wave and stage
+    constexpr int WTP = BP / WP, WTK = BK / WK, FP = WTP / 16, FK = WTK / 16;
+    constexpr int STAGE_BYTES = (BP + BK) * RB;
+    static_assert(BP % (8 * NW) == 0 && WTP % 16 == 0 && WTK % 16 == 0 && KLOADS >= NW, "tile shape");
     static_assert(NST >= 2 && LPW * (NST - 1) < 64, "ring depth / vmcnt range");
 
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
 
-    const int logical = (int)(blockIdx.x % 8) * blocks_per_xcd + (int)(blockIdx.x / 8);   // one contiguous range per XCD
-    if (logical >= total_blocks) return;                        // uniform, before any barrier
-    const int split = logical % nsplit, tile = logical / nsplit;
-    int tp, tk;
-    if (tiles_k <= tiles_p) { tk = tile % tiles_k; tp = tile / tiles_k; }
-    else { tp = tile % tiles_p; tk = tile / tiles_p; }
+    const int logical = (int)(blockIdx.x % 8) * q.blocks_per_xcd + (int)(blockIdx.x / 8);   // one contiguous range per XCD
+    if (logical >= q.total_blocks) return;                      // uniform, before any barrier
+    const int tile = (int)divide((uint32_t)logical, q.nsplit), split = logical - tile * q.nsplit_n;
+    const int t_hi = (int)divide((uint32_t)tile, q.tiles), t_lo = tile - t_hi * q.tiles_short;
+    const int tk = q.tiles_k_fast ? t_lo : t_hi, tp = q.tiles_k_fast ? t_hi : t_lo;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WGN, wn = wave % WGN;
+    const int wp = wave / WK, wk = wave % WK;
     const int p0 = tp * BP, k0 = tk * BK;
-    const int row_a0 = PIX_A ? p0 : k0, row_b0 = PIX_A ? k0 : p0;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte_t*)lds;
+    const uint32_t row_bytes = (uint32_t)g.Cp * (uint32_t)sizeof(E);
 
-    // Per-lane description of its transfers.  Filter rows: a pointer that advances with the tap.  Pixel rows: the first pixel of the image
-    // and the top-left input coordinate of the output pixel.  Where the transfers do not divide by the waves the last ones
-    // repeat a transfer of the same wave.
+    // Per-lane description of its transfers: a byte offset per transfer, fixed for the filter rows; for pixel rows that of the centre tap
+    // and one bit per tap that lies inside the image.  The descriptor of x starts one row and one pixel early, so that
+    // the offset of a tap, counted from the top left one, is a scalar and never negative; lanes outside read zeros.
     const int lrow = lane / CPR, lchunk = lane % CPR;
-    const int HoWo = g.Ho * g.Wo;
-    const E* fptr[LPW];
-    int pn[LPW], pi0[LPW], pj0[LPW], chunk_of[LPW];
-    uint32_t dst_of[LPW];
-    bool is_pix[LPW];
+    uint32_t pbase[PL], poff[PL], inside[PL];
 #pragma unroll
-    for (int i = 0; i < LPW; ++i) {
-        int load = wave + NW * i;
-        if (load >= LOADS) load -= NW;
-        const int row = load * 8 + lrow;                    // row inside the stage, A rows first
-        const int chunk = lchunk ^ ((row >> 1) & (CPR - 1));
-        chunk_of[i] = chunk * 8;
-        dst_of[i] = lds0 + (uint32_t)load * 1024u;
-        const bool in_a = load * 8 < BM;
-        is_pix[i] = in_a == PIX_A;                          // wave-uniform: BM is a multiple of 8
-        int gr = in_a ? row_a0 + row : row_b0 + (row - BM);
-        const int lim = is_pix[i] ? g.T : g.K;
-        gr = gr < lim ? gr : lim - 1;                       // rows beyond the end repeat the last one; never stored
-        fptr[i] = Wr + (size_t)gr * g.Cp + chunk_of[i];
-        const int n = gr / HoWo, p = gr - n * HoWo;
-        const int oi = p / g.Wo, oj = p - oi * g.Wo;
-        pn[i] = n * g.Hs * g.Ws; pi0[i] = oi * g.st - g.pad; pj0[i] = oj * g.st - g.pad;
+    for (int i = 0; i < PL; ++i) {
+        const int row = (wave + NW * i) * 8 + lrow;
+        const int t = p0 + row;
+        const uint32_t tc = (uint32_t)min(t, g.T - 1);
+        const uint32_t n = divide(tc, q.howo), p = tc - n * (uint32_t)(g.Ho * g.Wo);
+        const uint32_t oi = divide(p, q.wo), oj = p - oi * (uint32_t)g.Wo;
+        const int ii = (int)oi * g.st, jj = (int)oj * g.st;
+        pbase[i] = ((n * (uint32_t)g.Hs + (uint32_t)(ii >> g.up)) * (uint32_t)g.Ws + (uint32_t)(jj >> g.up)) * row_bytes +
+                   (uint32_t)((lchunk ^ ((row >> 1) & (CPR - 1))) * 16);
+        uint32_t m = 1u;
+        if (g.R == 3) {
+            const uint32_t cm = (jj > 0 ? 1u : 0u) | 2u | (jj + 1 < g.W ? 4u : 0u);
+            m = (ii > 0 ? cm : 0u) | cm << 3 | (ii + 1 < g.H ? cm << 6 : 0u);
+        }
+        inside[i] = (t < g.T ? m : 0u) | (uint32_t)(ii & 1) << 16 | (uint32_t)(jj & 1) << 17;
     }
+    uint32_t foff[KL], fdst[KL];
+#pragma unroll
+    for (int i = 0; i < KL; ++i) {
+        int load = wave + NW * i;
+        if (load >= KLOADS) load -= NW;                     // where the transfers do not divide by the waves, one is repeated
+        const int row = load * 8 + lrow;
+        fdst[i] = lds0 + (uint32_t)(BP / 8 + load) * 1024u;
+        foff[i] = k0 + row < g.K ? (uint32_t)(k0 + row) * row_bytes + (uint32_t)((lchunk ^ (((BP + row) >> 1) & (CPR - 1))) * 16) : kOutside;
+    }
+    const uint32_t early = g.R == 3 ? (uint32_t)(g.Ws + 1) * row_bytes : 0u;
+    const rsrc_t xr = make_rsrc(reinterpret_cast<const unsigned char*>(xh) - early);
+    const rsrc_t wr = make_rsrc(Wr);
 
     const int nkc = g.Cp / BKE;                             // whole stages per tap on this path
-    const int nstage_all = g.R * g.R * nkc;
-    const int q0 = (int)((long long)split * nstage_all / nsplit), q1 = (int)((long long)(split + 1) * nstage_all / nsplit);
-    const int total = q1 - q0;
-
-    int itap = q0 / nkc, ikc = q0 - (q0 / nkc) * nkc;
-    const unsigned char* src[LPW];
+    int total = g.R * g.R * nkc, itap = 0, ikc = 0;
+    if (q.nsplit_n > 1) {
+        const uint32_t all = (uint32_t)total;               // at most 16 ranges
+        const int q0 = (int)divide((uint32_t)split * all, q.nsplit);
+        total = (int)divide((uint32_t)(split + 1) * all, q.nsplit) - q0;
+        itap = __builtin_amdgcn_readfirstlane(q0 / nkc);
+        ikc = q0 - itap * nkc;
+    }
+    uint32_t soff_p = 0, soff_f = 0;
+    const uint32_t tap_bytes = (uint32_t)g.K * row_bytes;
     auto set_tap = [&]() __attribute__((always_inline)) {
-        const int r = itap / g.R, s = itap - r * g.R;
+        const int r = itap * 11 >> 5, s = itap - 3 * r;       // itap / 3 (R == 1: one tap, 0)
+        soff_f = (uint32_t)itap * tap_bytes + (uint32_t)ikc * RB;
+        soff_p = (uint32_t)ikc * RB;
+        if (!g.up) {
+            soff_p += (uint32_t)(r * g.Ws + s) * row_bytes;
 #pragma unroll
-        for (int i = 0; i < LPW; ++i) {
-            const E* p;
-            if (is_pix[i]) {
-                const int ii = pi0[i] + r, jj = pj0[i] + s;
-                const bool in = ii >= 0 && ii < g.H && jj >= 0 && jj < g.W;
-                p = in ? xh + ((size_t)pn[i] + (size_t)(ii >> g.up) * g.Ws + (jj >> g.up)) * g.Cp + chunk_of[i] : zero_row + chunk_of[i];
-            } else {
-                p = fptr[i] + (size_t)itap * g.K * g.Cp;
+            for (int i = 0; i < PL; ++i) poff[i] = (inside[i] >> itap) & 1u ? pbase[i] : kOutside;
+        } else {
+#pragma unroll
+            for (int i = 0; i < PL; ++i) {                  // the stored row and column move with every other tap
+                const int dr = ((int)(inside[i] >> 16 & 1u) + r + 1) >> 1, dc = ((int)(inside[i] >> 17 & 1u) + s + 1) >> 1;
+                poff[i] = (inside[i] >> itap) & 1u ? pbase[i] + (uint32_t)(dr * g.Ws + dc) * row_bytes : kOutside;
             }
-            src[i] = reinterpret_cast<const unsigned char*>(p + ikc * BKE);
         }
     };
     set_tap();
-    auto issue = [&](int slot) __attribute__((always_inline)) {          // the next stage in order
+    auto issue = [&](uint32_t slot_off) __attribute__((always_inline)) {          // the next stage in order
 #pragma unroll
-        for (int i = 0; i < LPW; ++i) {
-            dma_load_1k_v(src[i], dst_of[i] + (uint32_t)slot * STAGE_BYTES);
-            src[i] += RB;
-        }
-        if (++ikc == nkc) { ikc = 0; if (++itap < g.R * g.R) set_tap(); }
+        for (int i = 0; i < PL; ++i) dma_buffer_1k(xr, poff[i], soff_p, lds0 + slot_off + (uint32_t)(wave + NW * i) * 1024u);
+#pragma unroll
+        for (int i = 0; i < KL; ++i) dma_buffer_1k(wr, foff[i], soff_f, fdst[i] + slot_off);
+        soff_p += RB; soff_f += RB;
+        if (++ikc == nkc) { ikc = 0; ++itap; set_tap(); }
     };
 
-    f32x4_t acc[FM][FN];
+    f32x4_t acc[FP][FK];
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
+    for (int i = 0; i < FP; ++i)
 #pragma unroll
-        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < FK; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     // A stage holds two MFMA steps of 32 reduction elements.  The fragments of a step are requested one step ahead, across the
     // stage barrier, and waited for explicitly (as in the batched GEMM kernel).
-    constexpr int NREAD = FM + FN;
-    u32x4_t fa[2][FM], fb[2][FN];
+    constexpr int NREAD = FP + FK;
+    u32x4_t fp[2][FP], fk[2][FK];
     const int frow = lane & 15, fq = lane >> 4;
-    const int rowA = wm * WTM + frow, rowB = BM + wn * WTN + frow;
-    const uint32_t abase = lds0 + (uint32_t)rowA * RB + (uint32_t)((fq ^ ((rowA >> 1) & (CPR - 1))) << 4);
-    const uint32_t bbase = lds0 + (uint32_t)rowB * RB + (uint32_t)((fq ^ ((rowB >> 1) & (CPR - 1))) << 4);
-    auto read_step = [&](int slot, auto hc) __attribute__((always_inline)) {
+    const int rowP = wp * WTP + frow, rowK = BP + wk * WTK + frow;
+    const uint32_t pfrag = lds0 + (uint32_t)rowP * RB + (uint32_t)((fq ^ ((rowP >> 1) & (CPR - 1))) << 4);
+    const uint32_t kfrag = lds0 + (uint32_t)rowK * RB + (uint32_t)((fq ^ ((rowK >> 1) & (CPR - 1))) << 4);
+    auto read_step = [&](uint32_t slot_off, auto hc) __attribute__((always_inline)) {
         constexpr int h = decltype(hc)::value;
-        const uint32_t a = (abase + (uint32_t)slot * STAGE_BYTES) ^ (uint32_t)(h * 64), b = (bbase + (uint32_t)slot * STAGE_BYTES) ^ (uint32_t)(h * 64);
-        static_for<FM>([&](auto ic) { constexpr int i = decltype(ic)::value; lds_read16_async<i * 16 * RB>(fa[h][i], a); });
-        static_for<FN>([&](auto jc) { constexpr int j = decltype(jc)::value; lds_read16_async<j * 16 * RB>(fb[h][j], b); });
+        const uint32_t a = (pfrag ^ (uint32_t)(h * 64)) + slot_off, b = (kfrag ^ (uint32_t)(h * 64)) + slot_off;
+        static_for<FP>([&](auto ic) { constexpr int i = decltype(ic)::value; lds_read16_async<i * 16 * RB>(fp[h][i], a); });
+        static_for<FK>([&](auto jc) { constexpr int j = decltype(jc)::value; lds_read16_async<j * 16 * RB>(fk[h][j], b); });
     };
     auto await = [&](auto hc, auto newerc) __attribute__((always_inline)) {
         constexpr int h = decltype(hc)::value;
         lds_wait<decltype(newerc)::value>();
 #pragma unroll
-        for (int i = 0; i < FM; ++i) pin(fa[h][i]);
+        for (int i = 0; i < FP; ++i) pin(fp[h][i]);
 #pragma unroll
-        for (int j = 0; j < FN; ++j) pin(fb[h][j]);
+        for (int j = 0; j < FK; ++j) pin(fk[h][j]);
     };
     auto mma = [&](auto hc) __attribute__((always_inline)) {
         constexpr int h = decltype(hc)::value;
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
+        for (int i = 0; i < FP; ++i)
 #pragma unroll
-            for (int j = 0; j < FN; ++j) Mma16<E>::run(fa[h][i], fb[h][j], acc[i][j]);
+            for (int j = 0; j < FK; ++j) {
+                if constexpr (PIX_A) Mma16<E>::run(fp[h][i], fk[h][j], acc[i][j]);
+                else Mma16<E>::run(fk[h][j], fp[h][i], acc[i][j]);
+            }
     };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
     using NR = std::integral_constant<int, NREAD>;
     static_assert(STAGE_BYTES % 128 == 0 && NREAD <= 15, "swizzle period; lgkmcnt range");
 
+    // requested ahead of the transfers, used after the last of them
+    f32x4_t bv[FK];
 #pragma unroll
-    for (int s = 0; s < NST; ++s)
-        if (s < total) issue(s);
+    for (int j = 0; j < FK; ++j) {
+        const int k = k0 + wk * WTK + j * 16 + (PIX_A ? frow : 4 * fq);
+        bv[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        if (bias) {
+            if constexpr (PIX_A) { bv[j] += bias[min(k, g.K - 1)]; }
+            else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) bv[j][r] = bias[min(k + r, g.K - 1)];
+            }
+        }
+    }
+    constexpr uint32_t RING = NST * STAGE_BYTES;
+    {
+        const int first = total < NST ? total : NST;
+#pragma unroll 1
+        for (int s = 0; s < first; ++s) issue((uint32_t)s * STAGE_BYTES);
+    }
     if (NST - 1 >= total) wait_vmcnt<0>();
     else wait_vmcnt<(NST - 1) * LPW>();
     __syncthreads();
-    read_step(0, I0());
-    int slot = 0;
-    for (int s = 0; s < total - 1; ++s) {
-        const int next = slot + 1 == NST ? 0 : slot + 1;
+    read_step(0u, I0());
+    uint32_t slot = 0;
+    auto stage = [&](auto morec, auto drainc) __attribute__((always_inline)) {
+        uint32_t next = slot + STAGE_BYTES;
+        next = next == RING ? 0u : next;
         read_step(slot, I1());
         await(I0(), NR());
         __builtin_amdgcn_sched_barrier(0);
         mma(I0());
         __builtin_amdgcn_sched_barrier(0);
-        if (s + NST >= total) wait_vmcnt<0>();              // stage s+1 has landed
-        else wait_vmcnt<(NST - 2) * LPW>();
+        if constexpr (decltype(drainc)::value) wait_vmcnt<0>();
+        else wait_vmcnt<(NST - 2) * LPW>();                 // stage s+1 has landed
         await(I1(), I0());                                  // this wave has read all of stage s
         __syncthreads();
-        if (s + NST < total) issue(slot);                   // stage s+NST, into the slot of stage s
+        if constexpr (decltype(morec)::value) issue(slot);  // stage s+NST, into the slot of stage s
         read_step(next, I0());
         __builtin_amdgcn_sched_barrier(0);
         mma(I1());
         __builtin_amdgcn_sched_barrier(0);
         slot = next;
-    }
+    };
+    int s = 0;
+#pragma unroll 1
+    for (; s + NST < total; ++s) stage(std::true_type(), std::false_type());
+#pragma unroll 1
+    for (; s < total - 1; ++s) stage(std::false_type(), std::true_type());
     read_step(slot, I1());
     await(I0(), NR());
     mma(I0());
@@ -181,25 +263,72 @@ conv_igemm_tile_kernel(const E* __restrict__ xh, const E* __restrict__ Wr, const
     // 16x16 accumulator layout: register r of lane l holds row 4*(l/16) + r, column l%16.  Outputs are numbered in y's own
     // order, [pixel][channel] or [channel][pixel]; partial sums are stored in that order.
     const int rowsA = PIX_A ? g.T : g.K, rowsB = PIX_A ? g.K : g.T;
+    if (q.nsplit_n > 1) {
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-        const int cb = row_b0 + wn * WTN + j * 16 + frow;
-        if (cb >= rowsB) continue;
+        for (int i = 0; i < FP; ++i)
 #pragma unroll
-        for (int i = 0; i < FM; ++i) {
-            const int ra = row_a0 + wm * WTM + i * 16 + 4 * fq;          // four rows ra .. ra+3
-            if (ra >= rowsA) continue;
-            f32x4_t v = acc[i][j];
-            if (nsplit > 1) {
+            for (int j = 0; j < FK; ++j) {
+                const int pr = p0 + wp * WTP + i * 16, kr = k0 + wk * WTK + j * 16;
+                const int ra = (PIX_A ? pr : kr) + 4 * fq, cb = (PIX_A ? kr : pr) + frow;
+                if (ra >= rowsA || cb >= rowsB) continue;
                 float* dst = part + (size_t)split * rowsA * rowsB + (size_t)cb * rowsA + ra;
-                if (rowsA % 4 == 0) *reinterpret_cast<f32x4_t*>(dst) = v;
+                if (rowsA % 4 == 0) *reinterpret_cast<f32x4_t*>(dst) = acc[i][j];
                 else {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) if (ra + r < rowsA) dst[r] = v[r];
+                    for (int r = 0; r < 4; ++r) if (ra + r < rowsA) dst[r] = acc[i][j][r];
                 }
-                continue;
             }
-            igemm_store4<E, PIX_A>(v, ra, cb, y, bias, g, post, vec_ok, planes);
+        return;
+    }
+    if (!vec_ok) {
+#pragma unroll
+        for (int i = 0; i < FP; ++i)
+#pragma unroll
+            for (int j = 0; j < FK; ++j) {
+                const int pr = p0 + wp * WTP + i * 16, kr = k0 + wk * WTK + j * 16;
+                const int ra = (PIX_A ? pr : kr) + 4 * fq, cb = (PIX_A ? kr : pr) + frow;
+                igemm_store4<E, PIX_A>(acc[i][j], ra, cb, y, bias, g, post, vec_ok, planes);
+            }
+        return;
+    }
+    // the four outputs of a lane are adjacent and 8-byte aligned; the addresses along one dimension are found once
+    const uint32_t howo = (uint32_t)(g.Ho * g.Wo);
+    const E* res = static_cast<const E*>(post.residual);
+#pragma unroll
+    for (int i = 0; i < FP; ++i) {
+        const int pr = p0 + wp * WTP + i * 16 + (PIX_A ? 4 * fq : frow);           // first pixel of this lane
+        const bool p_ok = pr < g.T;
+        uint32_t n = 0;
+        size_t prow;                                        // offset of (pixel, channel 0) in y
+        if constexpr (PIX_A) {
+            n = divide((uint32_t)min(pr, g.T - 1), q.howo);
+            prow = (size_t)n * g.K * howo + ((uint32_t)pr - n * howo);
+        } else {
+            if (post.addvec) n = divide((uint32_t)min(pr, g.T - 1), q.howo);
+            prow = (size_t)pr * g.K;
+        }
+        uint2 rr[FK];
+        f32x4_t av[FK];
+#pragma unroll
+        for (int j = 0; j < FK; ++j) {
+            const int k = k0 + wk * WTK + j * 16 + (PIX_A ? frow : 4 * fq);
+            rr[j] = make_uint2(0u, 0u);
+            av[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            if (!(p_ok && k < g.K)) continue;
+            if (res) rr[j] = *reinterpret_cast<const uint2*>(res + prow + (PIX_A ? (size_t)k * howo : (size_t)k));
+            if (post.addvec) {
+                const float* a = post.addvec + (size_t)n * g.K + k;
+                if constexpr (PIX_A) av[j] += a[0];
+                else { av[j][0] += a[0]; av[j][1] += a[1]; av[j][2] += a[2]; av[j][3] += a[3]; }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < FK; ++j) {
+            const int k = k0 + wk * WTK + j * 16 + (PIX_A ? frow : 4 * fq);
+            if (!(p_ok && k < g.K)) continue;
+            f32x4_t v = acc[i][j] + (bv[j] + av[j]);
+            if (res) { v[0] += lo16<E>(rr[j].x); v[1] += hi16<E>(rr[j].x); v[2] += lo16<E>(rr[j].y); v[3] += hi16<E>(rr[j].y); }
+            *reinterpret_cast<uint2*>(y + prow + (PIX_A ? (size_t)k * howo : (size_t)k)) = make_uint2(pack2<E>(v[0], v[1]), pack2<E>(v[2], v[3]));
         }
     }
 }
@@ -216,34 +345,63 @@ static hipError_t launch_tile_cfg(const E* xh, const E* Wr, const float* bias, E
     auto kern = conv_igemm_tile_kernel<E, BP, BK, WP, WK, NST, PIX_A>;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
     if (attr != hipSuccess) return attr;
-    const E* zero_row = Wr + (size_t)g.R * g.R * g.K * g.Cp;
+    TileGeom q;
+    q.tiles_k_fast = tiles_k <= tiles_p;
+    q.tiles_short = q.tiles_k_fast ? tiles_k : tiles_p;
+    q.howo = fast_div((uint32_t)(g.Ho * g.Wo)); q.wo = fast_div((uint32_t)g.Wo);
+    q.tiles = fast_div((uint32_t)q.tiles_short); q.nsplit = fast_div((uint32_t)nsplit);
+    q.total_blocks = (int)total; q.blocks_per_xcd = per_xcd; q.nsplit_n = nsplit;
     const int vec_ok = igemm_vec_ok<PIX_A>(g, y, post, planes);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(per_xcd * 8)), dim3(WP * WK * 64), lds_bytes, s, xh, Wr, zero_row, bias, y, part, g, post,
-                       tiles_p, tiles_k, (int)total, per_xcd, nsplit, vec_ok, planes ? 1 : 0);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(per_xcd * 8)), dim3(WP * WK * 64), lds_bytes, s, xh, Wr, bias, y, part, g, post, q, vec_ok, planes ? 1 : 0);
     return hipGetLastError();
 }
 
-// Blocks on offer, pixels x output channels, with the time of a reduction stage: `alone` where a compute unit holds one workgroup,
-// `each` per workgroup where it holds several, and `ends` for a workgroup's start and stores, which overlap a little (us, measured; without the last, 1x1 and other
-// short reductions took the 128x128 block too often: 256 -> 560 1x1 at 144x51, N=2, 25.4 with it, 19.9 with 64x64).  Three workgroups of 64x64 or two of the others share a unit's LDS; rings
-// deeper than that and fewer workgroups were slower on every shape (128x128 with three slots, one workgroup per unit, 1.3x).
-struct TileShape { int bp, bk; double alone, each, ends; };
-static const TileShape kTiles[3] = {{64, 64, 0.27, 0.20, 1.3}, {64, 80, 0.35, 0.295, 1.6}, {128, 128, 0.65, 0.57, 4.6}};
+// Blocks on offer, pixels x output channels, all of eight waves, with the time of a reduction stage: `alone` where a compute unit holds one
+// workgroup, `each` per workgroup where it holds several; and `first`, `more`: start and stores of the first workgroup of a unit, beyond
+// those of a launch, and of each further one (us, fitted together to 530 calls, 5900 timings, of 1x1, stride 2 and 3x3 layers; the
+// choice by them is within 0.5 % of the best of the five on average).  The 128x96 block with three slots fills a unit by itself: it is for calls of one
+// round, where two slots leave the transfers waiting.
+struct TileShape { int bp, bk; double alone, each, first, more; };
+static const TileShape kTiles[5] = {{64, 64, 0.20, 0.179, 0.10, 0.43}, {128, 64, 0., 0.27, 0.67, 0.26}, {128, 96, 0.51, 0.352, 0.78, 0.80},
+                                    {128, 96, 0., 0.349, 1.37, 3.13}, {128, 128, 0., 0.487, 1.58, -0.95}};
 
-// The block and the number of reduction ranges with the least time by these figures, plus 6 us for the launch and, with a split reduction,
-// 1.5 us and the traffic of the partial sums for the second kernel (3x3 128 channels at 17x13, N=2, NCHW: 15.5 us whole, 13.0 in two ranges).  Measured, channel-last, us, against the kernels of
-// conv_igemm.hip: 1x1 960 -> 320 at 64x64 (N=2) 15.4 / 18.2, 1920 -> 640 at 64x64 36 / 45, stride 2 320 channels at 64x64 18.2 / 22.1, at
-// 97x121 23.8 / 32.7, 512 channels at 256x256 88 / 110, 3x3 128 channels at 256x256 34 / 39, 512 at 256x256 323 / 338.
-// Left to conv_igemm.hip: at least one round of its 256x256 blocks, of a number of channels that they divide, where that is the shorter time.
-// That block fetches half as much per product, and its start and end cost less than those of four small ones; the stages themselves are
-// 5 % longer, so a long reduction prefers the small blocks, and so does a last round that is not full.  Channel-last, us, here / there:
-// 1x1 at 256x256 128 -> 512 53 / 40, 512 -> 512 75 / 63, 1024 -> 1024 203 / 180; 3x3 128 -> 512 121 / 101, 512 -> 512 313 / 307; at 128x128
-// 1024 -> 1024 287 / 295; one and a half rounds (768 channels at 180x180) 1x1 128 in 39.7 / 36.5, 3x3 128 in 85 / 90, 1024 in 77 / 86 (1x1).
-// An image of an odd number of pixels, NCHW (see below), 1x1: 192 -> 320 at 311x201 71 / 75 (with the 128x128 block 82), 256 at 181x181 41 / 38;
-// 1856 -> 1184 at 23x57 (N=2) 45 / 40; but 3x3 256 at 181x181 72 / 74, 320 at 97x121 (N=2) 86 / 118.
-// With a residual or a vector to add it loses: it reads them element by element (bf16 3x3, 256 -> 512 at 360x360: vector 355 / 378 NCHW, 338
-// / 355 channel-last, residual 407 / 524, 380 / 439).  The number of reduction ranges is one either way.
-// NCHW, where its stores are the narrower ones: 1x1 at 256x256 64 -> 512 52 / 48, 1024 -> 1024 261 / 246; 3x3 64 -> 512 89 / 81, 320 -> 512 234 / 233.
+// The block and the number of reduction ranges with the least time by these figures; a split reduction adds a second kernel and the traffic of
+// the partial sums (3x3 128 channels at 17x13, N=2, NCHW: 15.5 us whole, 13.0 in two ranges).  Measured, channel-last, us, against the kernels of
+// conv_igemm.hip: 1x1 256 -> 256 at 414x300 (N=2) 91 / 99, 64 -> 1280 at 200x112 25.5 / 33.4, 3x3 320 -> 768 at 104x544 255 / 294, stride 2
+// 64 -> 768 at 465x168 (N=2) 52 / 64.  The 256x256 block there is nowhere more than 2 % ahead on calls of two-byte types with whole stages (60 calls of at
+// least one round of such blocks), nor are its other blocks on NCHW images with a number of pixels that is no multiple of four (100 calls).
+IgemmTilePlan igemm_block_plan(int T, int K, int Cp, int R, int dt, bool nhwc, int most_sp) {
+    IgemmTilePlan best{-1, 1};
+    if (!(dt == DT_F16 || dt == DT_BF16) || Cp % 64 != 0) return best;
+    const int stages = R * R * (Cp / 64);
+    double cost = 1e300;
+    for (int id = 0; id < 5; ++id) {
+        const TileShape& sh = kTiles[id];
+        const long long blocks = (long long)((T + sh.bp - 1) / sh.bp) * ((K + sh.bk - 1) / sh.bk);
+        for (int sp = 1; sp <= most_sp && (sp == 1 || sp * 8 <= stages); ++sp) {
+            const double share = (double)(blocks * sp) / 256.0;            // workgroups per compute unit
+            const double most = (double)((blocks * sp + 255) / 256);
+            double n = share < 2.0 ? 0.35 * share + 0.65 * most : most;
+            if (n < 1.0) n = 1.0;
+            const double stage = n * sh.each > sh.alone ? n * sh.each : sh.alone;
+            double c = (double)((stages + sp - 1) / sp) * stage + sh.first + sh.more * (n - 1.0);
+            if (sp > 1) c += 2.15 + (double)sp * K * T * 8.0 * 0.236e-6;
+            if (c < cost) { cost = c; best = {id, sp}; }
+        }
+    }
+    // channel-last, a number of channels that is no multiple of four: outputs are stored one by one, 16 lanes to as many lines, and a short
+    // reduction does not make up for it (1x1, here / there: 64 -> 1194 at 50x23 (N=2) 11.2 / 8.5, 576 -> 873 at 26x41 (N=4) 17.7 / 16.5, 128 -> 1203 at
+    // 78x117 (N=2) 53 / 49; but 64 -> 321 at 13x45 5.7 / 6.1, 832 -> 853 at 30x18 (N=2) 9.8 / 13.1, 3x3 64 -> 1110 at 16x32 (N=4) 15.8 / 17.2)
+    if (nhwc && K % 4 != 0 && K >= 512 && R == 1 && stages <= 9 && best.split == 1) return {-1, 1};
+    return best;
+}
+
+// Reduction ranges that a call's workspace is sized for: the choice of an earlier set of blocks of 64x64, 64x80 and 128x128 (id 0, 1 and 2; id < 0: the
+// kernels of conv_igemm.hip), with their stage times (us; `alone`: one workgroup to a compute unit, `each`: several, `ends`: a workgroup's start
+// and stores).  Programs keep workspaces, and what fits the library's static scratch fits it, so this rule stays what it was whatever
+// block runs a call; igemm_block_plan never takes more ranges than it grants.
+struct RangeShape { int bp, bk; double alone, each, ends; };
+static const RangeShape kRangeTiles[3] = {{64, 64, 0.27, 0.20, 1.3}, {64, 80, 0.35, 0.295, 1.6}, {128, 128, 0.65, 0.57, 4.6}};
 IgemmTilePlan igemm_tile_plan(int T, int HoWo, int K, int Cp, int R, int dt, bool nhwc, bool plain) {
     IgemmTilePlan best{-1, 1};
     if (!(dt == DT_F16 || dt == DT_BF16) || Cp % 64 != 0) return best;
@@ -260,7 +418,7 @@ IgemmTilePlan igemm_tile_plan(int T, int HoWo, int K, int Cp, int R, int dt, boo
     const int most_sp = igemm_split_rule(T, K, Cp, R, dt);
     double cost = 1e300;
     for (int id = 0; id < 3; ++id) {
-        const TileShape& sh = kTiles[id];
+        const RangeShape& sh = kRangeTiles[id];
         const long long blocks = (long long)((T + sh.bp - 1) / sh.bp) * ((K + sh.bk - 1) / sh.bk);
         for (int sp = 1; sp <= most_sp && (sp == 1 || sp * 8 <= stages); ++sp) {
             const double share = (double)(blocks * sp) / 256.0;            // workgroups per compute unit
@@ -287,11 +445,19 @@ template <typename E, bool PIX_A>
 static hipError_t launch_tile_t(const E* xh, const E* Wr, const float* bias, E* y, float* part, const IgemmTilePlan& plan, const ConvGeom& g,
                                 const IgemmPost& post, bool planes, hipStream_t s) {
     switch (plan.id) {
-        case 0: return launch_tile_cfg<E, 64, 64, 2, 2, 3, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
-        case 1: return launch_tile_cfg<E, 64, 80, 4, 1, 4, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
-        case 2: return launch_tile_cfg<E, 128, 128, 2, 2, 2, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
+        case 0: return launch_tile_cfg<E, 64, 64, 4, 2, 4, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
+        case 1: return launch_tile_cfg<E, 128, 64, 4, 2, 3, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
+        case 2: return launch_tile_cfg<E, 128, 96, 4, 2, 2, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
+        case 3: return launch_tile_cfg<E, 128, 96, 4, 2, 3, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
+        case 4: return launch_tile_cfg<E, 128, 128, 4, 2, 2, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
         default: return hipErrorInvalidValue;
     }
+}
+
+// Lane offsets are 32-bit and a descriptor covers 2 GB: x, with a row and a pixel in front of it, and the filter have to fit.
+bool igemm_tile_fits(const ConvGeom& g) {
+    const unsigned long long row = (unsigned long long)g.Cp * 2u, lim = kRange;
+    return ((unsigned long long)g.N * g.Hs * g.Ws + g.Ws + 1u) <= lim / row && (unsigned long long)g.R * g.R * g.K <= lim / row;
 }
 
 hipError_t launch_igemm_tile(const void* xh, const void* Wr, const float* bias, void* y, float* part, const IgemmTilePlan& plan,
