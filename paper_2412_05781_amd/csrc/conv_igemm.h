@@ -5,6 +5,37 @@
 
 namespace wino {
 
+// n / d for n < 2^31 as a multiplication, prepared on the host (Granlund and Montgomery, "Division by invariant integers using multiplication")
+struct FastDiv { uint32_t mul, shift; };
+inline FastDiv fast_div(uint32_t d) {
+    uint32_t l = 0;
+    while ((1u << l) < d) ++l;
+    return {(uint32_t)((((1ull << l) - d) << 32) / d + 1), l};
+}
+__device__ __forceinline__ uint32_t divide(uint32_t n, FastDiv f) { return (__umulhi(n, f.mul) + n) >> f.shift; }
+
+typedef int rsrc_t __attribute__((ext_vector_type(4)));
+// Descriptor for buffer loads of at most 2 GB from `base` on.  A lane whose offset is kOutside lies beyond its range whatever scalar offset
+// is added, and reads zeros; every other lane's offset is inside the operand.
+constexpr uint32_t kOutside = 0x80000000u, kRange = 0x7fffffffu;
+__device__ __forceinline__ rsrc_t make_rsrc(const void* base) {
+    const uint64_t a = reinterpret_cast<uint64_t>(base);
+    rsrc_t r;
+    r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+    r[1] = __builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xffffu));
+    r[2] = (int)kRange;
+    r[3] = 0x00020000;
+    return r;
+}
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+// 1 KB to LDS: a wave-uniform descriptor and byte offset, a byte offset per lane; a lane outside the range writes zeros
+__device__ __forceinline__ void dma_buffer_1k(rsrc_t r, uint32_t lane_off, uint32_t off, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(lds_addr), "v"(lane_off), "s"(r), "s"(__builtin_amdgcn_readfirstlane(off)) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
 struct ConvGeom {
     int N, C, Cp, H, W, K, R, st, pad, Ho, Wo, T;      // T = N*Ho*Wo output pixels
     int up, Hs, Ws;                                    // up = 1: x is stored at Hs x Ws = H/2 x W/2 and read upsampled
@@ -92,6 +123,10 @@ template <bool PIX_A, typename E> inline int igemm_vec_ok(const ConvGeom& g, con
 
 // The kernel for 8-bit operands (conv_igemm_fp8.hip), two-byte y: whether it applies, and the launch.
 bool igemm_fp8_tile_ok(const ConvGeom& g, int dt, bool nhwc, int nsplit);
+// ... and the one for 3x3, stride 1, which is asked first.
+bool igemm_fp8_rows_ok(const ConvGeom& g, int dt, int nsplit);
+hipError_t launch_igemm_fp8_rows(const void* xq, const void* Wq, const float* bias, void* y, const ConvGeom& g, const IgemmPost& post, int dt,
+                                 bool nhwc, hipStream_t s);
 hipError_t launch_igemm_fp8_tile(const void* xq, const void* Wq, const float* bias, void* y, const ConvGeom& g, const IgemmPost& post, int dt,
                                  bool nhwc, hipStream_t s);
 

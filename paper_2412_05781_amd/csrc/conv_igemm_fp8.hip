@@ -21,7 +21,74 @@ constexpr int NST = 2;                                   // ring slots (three wi
 
 // every LDS read of the wave has arrived (the caller's waits say so); the workgroup barrier
 __device__ __forceinline__ void block_barrier() { asm volatile("s_barrier" ::: "memory"); }
+
+struct RowsGeom {
+    FastDiv w, h, tiles;                   // divisions by W, H, the shorter tile dimension
+    int tiles_k_fast, tiles_short;         // the shorter one is that of the output channels
+    int total_blocks, blocks_per_xcd;
+};
 }  // namespace
+
+// The sums of a block, 32x32 tiles of 64-lane accumulators, scaled, added to and stored; every transfer into LDS has landed.
+template <typename EO, int BP, int BK, int WP, int WK, bool PIX_A, int LDS_BYTES, int FM, int FN>
+__device__ __forceinline__ void fp8_store(float16_t (&acc)[FM][FN], unsigned char* lds, const float* __restrict__ bias, EO* __restrict__ y,
+                                          const ConvGeom& g, const IgemmPost& post, int p0, int k0, int vec_ok, int planes) {
+    constexpr int BM = PIX_A ? BP : BK, BN = PIX_A ? BK : BP, WGN = PIX_A ? WK : WP, WTM = FM * 32, WTN = FN * 32, NW = WP * WK;
+    const int tid = threadIdx.x, lane = tid & 63, frow = lane & 31, fh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WGN, wn = wave % WGN;
+    const int row_a0 = PIX_A ? p0 : k0, row_b0 = PIX_A ? k0 : p0, HoWo = g.Ho * g.Wo;
+    // 32x32 accumulator layout: register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4, column l%32.
+    const int ra0 = row_a0 + wm * WTM + 4 * fh;
+    if constexpr (PIX_A) {
+        const int n0 = p0 / HoWo;
+        if (vec_ok > 1 && min(p0 + BP, g.T) <= (n0 + 1) * HoWo) {
+            // The planes of y are whole 16-byte pieces and the block lies in one image.  Stored from the accumulators, an instruction
+            // touches 32 lines with 16 bytes each; the block goes through the stages' LDS as [channel][pixel] in y's type, 16-byte
+            // pieces swizzled by the channel, and leaves as pieces of whole lines (256 channels at 512x512: 178 -> 162 us).  Channel-last
+            // the same made no difference.
+            constexpr int PIECES = BM / 8;                // 16-byte pieces per channel
+            static_assert(BM * BN * 2 <= LDS_BYTES, "the block fits the ring");
+            block_barrier();                              // every wave has read the last stage
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                const int cl = wn * WTN + j * 32 + frow, k = min(row_b0 + cl, g.K - 1);
+                const float bb = (bias ? bias[k] : 0.f) + (post.addvec ? post.addvec[(size_t)n0 * g.K + k] : 0.f);
+                const EO* ro = static_cast<const EO*>(post.residual) + ((size_t)n0 * g.K + k) * HoWo + (ra0 - n0 * HoWo);
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int d = i * 32 + 8 * q;
+                        float v[4];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) v[r] = acc[i][j][4 * q + r] * post.scale + bb;
+                        if (post.residual && ra0 + d < g.T && row_b0 + cl < g.K) {
+                            const uint2 w = *reinterpret_cast<const uint2*>(ro + d);
+                            v[0] += lo16<EO>(w.x); v[1] += hi16<EO>(w.x); v[2] += lo16<EO>(w.y); v[3] += hi16<EO>(w.y);
+                        }
+                        const int piece = (wm * WTM + d) / 8;
+                        *reinterpret_cast<uint2*>(lds + (cl * PIECES + (piece ^ (cl & (PIECES - 1)))) * 16 + fh * 8) =
+                            make_uint2(pack2<EO>(v[0], v[1]), pack2<EO>(v[2], v[3]));
+                    }
+            }
+            __syncthreads();
+            const int piece = tid % PIECES, t = row_a0 + 8 * piece;
+            if (t >= g.T) return;                         // no barrier follows
+            for (int cl = tid / PIECES; cl < BN && row_b0 + cl < g.K; cl += NW * 64 / PIECES)
+                *reinterpret_cast<uint4*>(y + ((size_t)n0 * g.K + row_b0 + cl) * HoWo + (t - n0 * HoWo)) =
+                    *reinterpret_cast<const uint4*>(lds + (cl * PIECES + (piece ^ (cl & (PIECES - 1)))) * 16);
+            return;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                igemm_store4<EO, PIX_A>(f32x4_t{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]},
+                                        ra0 + i * 32 + 8 * q, row_b0 + wn * WTN + j * 32 + frow, y, bias, g, post, vec_ok, planes);
+}
 
 // RAGGED: Cp is not a whole number of stages.
 // BP pixels x BK output channels per workgroup, WP x WK waves, two ring slots.  PIX_A: pixels are the rows (NCHW y), else channels.
@@ -212,58 +279,232 @@ conv_igemm_fp8_kernel(const uint8_t* __restrict__ xq, const uint8_t* __restrict_
     for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j) asm volatile("" : "+v"(acc[i][j]));    // the products stay in front of the branches of the epilogue
+    fp8_store<EO, BP, BK, WP, WK, PIX_A, NST * STAGE_BYTES>(acc, lds, bias, y, g, post, p0, k0, vec_ok, planes);
+}
 
-    // 32x32 accumulator layout: register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4, column l%32.
-    const int ra0 = row_a0 + wm * WTM + 4 * fh;
-    if constexpr (PIX_A) {
-        const int n0 = p0 / HoWo;
-        if (vec_ok > 1 && min(p0 + BP, g.T) <= (n0 + 1) * HoWo) {
-            // The planes of y are whole 16-byte pieces and the block lies in one image.  Stored from the accumulators, an instruction
-            // touches 32 lines with 16 bytes each; the block goes through the ring's LDS as [channel][pixel] in y's type, 16-byte
-            // pieces swizzled by the channel, and leaves as pieces of whole lines (256 channels at 512x512: 178 -> 162 us).  Channel-last
-            // the same made no difference.
-            constexpr int PIECES = BM / 8;                // 16-byte pieces per channel
-            static_assert(BM * BN * 2 <= NST * STAGE_BYTES, "the block fits the ring");
-            block_barrier();                              // every wave has read the last stage
+// 3x3, stride 1: the three taps of a filter row read the same pixels, one place apart.  So the pixels of a row of taps - BP of them and their two
+// neighbours, in the order of the image - are fetched once per 128 channels and a lane's fragments of tap s are rows s further on; a tap that
+// lies beyond the left or right edge reads a row of zeros instead (rows above and below the image arrive as zeros).  A stage, one tap, then
+// moves BK rows of the filter and a third of BP + 8 rows of pixels into LDS instead of BK + BP, and the pixels have three stages to arrive.
+template <typename EO, int BP, int BK, int WP, int WK, bool PIX_A, bool RAGGED>
+__global__ void __launch_bounds__(WP * WK * 64)
+conv_rows_fp8_kernel(const uint8_t* __restrict__ xq, const uint8_t* __restrict__ Wq, const float* __restrict__ bias, EO* __restrict__ y,
+                     ConvGeom g, IgemmPost post, RowsGeom q, int vec_ok, int planes) {
+    constexpr int RB = 128, CPR = RB / 16;                // stage bytes (= reduction elements) and 16-byte chunks per row
+    constexpr int BM = PIX_A ? BP : BK, BN = PIX_A ? BK : BP, WGM = PIX_A ? WP : WK, WGN = PIX_A ? WK : WP, NW = WP * WK;
+    constexpr int LPX = BP / 8 / NW, LPF = BK / 8 / NW;   // 1 KB transfers (8 rows) per wave: a row of taps' pixels (and one more), a tap's filter
+    constexpr int WTM = BM / WGM, WTN = BN / WGN, FM = WTM / 32, FN = WTN / 32, FPX = PIX_A ? FM : FN;
+    constexpr uint32_t PIX_BYTES = (BP + 8) * RB, FIL_BYTES = BK * RB, FIL0 = 2 * PIX_BYTES, ASIDE = FIL0 + 2 * FIL_BYTES, ZERO = ASIDE + 1024;
+    static_assert(WTM % 32 == 0 && WTN % 32 == 0 && BP % (8 * NW) == 0 && BK % (8 * NW) == 0 && (8 * NW) % 16 == 0, "tile shape");
+    constexpr int XBITS = 3 * LPX + LPF;
+    static_assert(XBITS + 3 <= 32, "mask bits");
+
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+
+    const int logical = (int)(blockIdx.x % 8) * q.blocks_per_xcd + (int)(blockIdx.x / 8);   // one contiguous range per XCD
+    if (logical >= q.total_blocks) return;                // uniform, before any barrier
+    const int t_hi = (int)divide((uint32_t)logical, q.tiles), t_lo = logical - t_hi * q.tiles_short;
+    const int tk = q.tiles_k_fast ? t_lo : t_hi, tp = q.tiles_k_fast ? t_hi : t_lo;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WGN, wn = wave % WGN;
+    const int p0 = tp * BP, k0 = tk * BK;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte_t*)lds, row_bytes = (uint32_t)g.Cp;
+    if (tid < 32) *reinterpret_cast<uint32_t*>(lds + ZERO + 4 * tid) = 0u;
+
+    // Transfers: LDS row j of the pixels is pixel p0 - 1 + j, one image row up or down with the row of taps; the descriptor starts one image
+    // row and one pixel early.  One lane offset per operand, the rest is scalar; a bit per transfer (and row of taps) says whether the lane's row exists.
+    const int lrow = wave * 8 + (lane >> 3);
+    const uint32_t chunk = (uint32_t)(((lane & 7) ^ ((lrow >> 1) & (CPR - 1))) * 16);     // 8 * NW rows further on the swizzle is the same
+    auto row_bits = [&](int t) __attribute__((always_inline)) {          // rows of taps that lie inside the image for pixel t
+        const uint32_t tc = (uint32_t)min(max(t, 0), g.T - 1), line = divide(tc, q.w), oi = line - divide(line, q.h) * (uint32_t)g.H;
+        return t >= 0 && t < g.T ? (oi > 0 ? 1u : 0u) | 2u | (oi + 1 < (uint32_t)g.H ? 4u : 0u) : 0u;
+    };
+    uint32_t live = 0;
 #pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                const int cl = wn * WTN + j * 32 + frow, k = min(row_b0 + cl, g.K - 1);
-                const float bb = (bias ? bias[k] : 0.f) + (post.addvec ? post.addvec[(size_t)n0 * g.K + k] : 0.f);
-                const EO* ro = static_cast<const EO*>(post.residual) + ((size_t)n0 * g.K + k) * HoWo + (ra0 - n0 * HoWo);
+    for (int i = 0; i < LPX; ++i) live |= row_bits(p0 - 1 + lrow + 8 * NW * i) << (3 * i);
 #pragma unroll
-                for (int i = 0; i < FM; ++i)
+    for (int i = 0; i < LPF; ++i) live |= (k0 + lrow + 8 * NW * i < g.K ? 1u : 0u) << (3 * LPX + i);
+    const uint32_t poff = (uint32_t)(p0 + lrow) * row_bytes + chunk, foff = (uint32_t)(k0 + lrow) * row_bytes + chunk;
+    // the last two pixels, by wave 0 (its lane offset again); the others write zeros aside, so that no branch parts a stage
+    live |= (wave == 0 && (lane >> 3) < 2 ? row_bits(p0 - 1 + BP + (lane >> 3)) : 0u) << XBITS;
+    const uint32_t xdst = lds0 + (wave == 0 ? (uint32_t)(BP * RB) : ASIDE), xstep = wave == 0 ? PIX_BYTES : 0u;
+    const uint32_t line_bytes = (uint32_t)g.W * row_bytes, step8 = (uint32_t)(8 * NW) * row_bytes;
+    const rsrc_t xr = make_rsrc(xq - line_bytes - row_bytes), wr = make_rsrc(Wq);
+    const uint32_t pdst = lds0 + (uint32_t)wave * 1024u, fdst = lds0 + FIL0 + (uint32_t)wave * 1024u;
+
+    const int nkc = (g.Cp + RB - 1) / RB, groups = 3 * nkc;              // rows of taps over all channel chunks, chunk by chunk
+    const uint32_t tail = row_bytes - (uint32_t)(nkc - 1) * RB;          // bytes of a row in the last chunk
+    const uint32_t tap_bytes = (uint32_t)g.K * row_bytes;
+    uint32_t pr = 0, pkc = 0, ftap = 0, fkc = 0;                         // next row of taps, next tap to fetch
+    // lanes of chunk kc that lie inside the operands: none beyond the last, and none of its bytes beyond Cp
+    const uint32_t whole = chunk < tail ? ~0u : 0u;
+    auto past = [&](uint32_t kc) __attribute__((always_inline)) {
+        const uint32_t inner = kc < (uint32_t)(nkc - 1) ? ~0u : 0u, any = kc < (uint32_t)nkc ? ~0u : 0u;
+        return RAGGED ? (whole | inner) & any : any;
+    };
+    auto issue_pixels = [&](uint32_t slot) __attribute__((always_inline)) {
+        const uint32_t gone = live & past(pkc);
+        uint32_t soff = pr * line_bytes + pkc * RB;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int d = i * 32 + 8 * q;
-                        float v[4];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) v[r] = acc[i][j][4 * q + r] * post.scale + bb;
-                        if (post.residual && ra0 + d < g.T && row_b0 + cl < g.K) {
-                            const uint2 w = *reinterpret_cast<const uint2*>(ro + d);
-                            v[0] += lo16<EO>(w.x); v[1] += hi16<EO>(w.x); v[2] += lo16<EO>(w.y); v[3] += hi16<EO>(w.y);
-                        }
-                        const int piece = (wm * WTM + d) / 8;
-                        *reinterpret_cast<uint2*>(lds + (cl * PIECES + (piece ^ (cl & (PIECES - 1)))) * 16 + fh * 8) =
-                            make_uint2(pack2<EO>(v[0], v[1]), pack2<EO>(v[2], v[3]));
-                    }
-            }
-            __syncthreads();
-            const int piece = tid % PIECES, t = row_a0 + 8 * piece;
-            if (t >= g.T) return;                         // no barrier follows
-            for (int cl = tid / PIECES; cl < BN && row_b0 + cl < g.K; cl += NW * 64 / PIECES)
-                *reinterpret_cast<uint4*>(y + ((size_t)n0 * g.K + row_b0 + cl) * HoWo + (t - n0 * HoWo)) =
-                    *reinterpret_cast<const uint4*>(lds + (cl * PIECES + (piece ^ (cl & (PIECES - 1)))) * 16);
-            return;
+        for (int i = 0; i < LPX; ++i) {
+            dma_buffer_1k(xr, gone >> (3 * i + pr) & 1u ? poff : kOutside, soff, pdst + slot * PIX_BYTES + (uint32_t)(8 * NW * i) * RB);
+            soff += step8;
         }
-    }
+        dma_buffer_1k(xr, gone >> (XBITS + pr) & 1u ? poff : kOutside, pr * line_bytes + pkc * RB + (uint32_t)BP * row_bytes, xdst + slot * xstep);
+        pr = pr == 2 ? 0u : pr + 1; pkc += pr == 0 ? 1u : 0u;
+    };
+    auto issue_filter = [&](uint32_t slot) __attribute__((always_inline)) {
+        const uint32_t gone = live & past(fkc);
+        uint32_t soff = ftap * tap_bytes + fkc * RB;
 #pragma unroll
-    for (int j = 0; j < FN; ++j)
+        for (int i = 0; i < LPF; ++i) {
+            dma_buffer_1k(wr, gone >> (3 * LPX + i) & 1u ? foff : kOutside, soff, fdst + slot * FIL_BYTES + (uint32_t)(8 * NW * i) * RB);
+            soff += step8;
+        }
+        ftap = ftap == 8 ? 0u : ftap + 1; fkc += ftap == 0 ? 1u : 0u;
+    };
+
+    float16_t acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    // Fragments as in the kernel above.  Pixel rows: an address per 32-pixel sub-tile, that of the row of zeros where the tap is
+    // beyond the edge; filter rows: one address.
+    u32x4_t fa[2][FM][2], fb[FN + 1][2];                  // [step][sub-tile][chunk]; fb[FN]: last column of step 1
+    const int frow = lane & 31, fh = lane >> 5;
+    const int prow = (PIX_A ? wm * WTM : wn * WTN) + frow, krow = (PIX_A ? wn * WTN : wm * WTM) + frow;
+    uint32_t edge = 0;                                    // bit 2i: left, 2i + 1: right
+#pragma unroll
+    for (int i = 0; i < FPX; ++i) {
+        const uint32_t t = (uint32_t)min(p0 + prow + 32 * i, g.T - 1), oj = t - divide(t, q.w) * (uint32_t)g.W;
+        edge |= (oj == 0 ? 1u : 0u) << (2 * i) | (oj + 1 == (uint32_t)g.W ? 2u : 0u) << (2 * i);
+    }
+    auto swz = [&](int row) __attribute__((always_inline)) { return (uint32_t)(((2 * fh) ^ ((row >> 1) & (CPR - 1))) << 4); };
+    const uint32_t pix_row[3] = {lds0 + (uint32_t)prow * RB + swz(prow), lds0 + (uint32_t)(prow + 1) * RB + swz(prow + 1), lds0 + (uint32_t)(prow + 2) * RB + swz(prow + 2)};
+    const uint32_t fil_row = lds0 + FIL0 + (uint32_t)krow * RB + swz(krow), zero_row = lds0 + ZERO;
+    uint32_t paddr[FPX], faddr;
+    auto locate = [&](auto sc, uint32_t pslot, uint32_t fslot) __attribute__((always_inline)) {         // fragment rows of tap s
+        constexpr int s = decltype(sc)::value;
+#pragma unroll
+        for (int i = 0; i < FPX; ++i) {
+            paddr[i] = pix_row[s] + pslot * PIX_BYTES + (uint32_t)(i * 32 * RB);
+            if constexpr (s != 1) paddr[i] = edge >> (2 * i + (s >> 1)) & 1u ? zero_row : paddr[i];
+        }
+        faddr = fil_row + fslot * FIL_BYTES;
+    };
+    auto read_row = [&](u32x4_t (&f)[2], auto px, auto ic, auto hc) __attribute__((always_inline)) {     // both chunks of a sub-tile, step h
+        constexpr int i = decltype(ic)::value, h = decltype(hc)::value;
+        if constexpr (decltype(px)::value) {
+            const uint32_t a = paddr[i] ^ (uint32_t)(64 * h);
+            lds_read16_async<0>(f[0], a);
+            lds_read16_async<0>(f[1], a ^ 16u);
+        } else {
+            const uint32_t a = faddr ^ (uint32_t)(64 * h);
+            lds_read16_async<i * 32 * RB>(f[0], a);
+            lds_read16_async<i * 32 * RB>(f[1], a ^ 16u);
+        }
+    };
+    using PA = std::integral_constant<bool, PIX_A>;
+    using PB = std::integral_constant<bool, !PIX_A>;
+    auto read_b = [&](auto hc, auto jc, auto rc) __attribute__((always_inline)) { read_row(fb[decltype(rc)::value], PB(), jc, hc); };
+    auto read_first = [&](auto hc) __attribute__((always_inline)) {       // rows and last column of step h
+        constexpr int h = decltype(hc)::value;
+        static_for<FM>([&](auto ic) { read_row(fa[h][decltype(ic)::value], PA(), ic, hc); });
+        read_b(hc, std::integral_constant<int, FN - 1>(), std::integral_constant<int, FN - 1 + h>());
+    };
+    auto pin_first = [&](auto hc) __attribute__((always_inline)) {
+        constexpr int h = decltype(hc)::value;
+#pragma unroll
+        for (int i = 0; i < FM; ++i) { pin(fa[h][i][0]); pin(fa[h][i][1]); }
+        pin(fb[FN - 1 + h][0]); pin(fb[FN - 1 + h][1]);
+    };
+    auto mma = [&](auto hc, auto jc) __attribute__((always_inline)) {
+        constexpr int h = decltype(hc)::value, j = decltype(jc)::value, r = j == FN - 1 ? FN - 1 + h : j;
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < FM; ++i)
+            Mma<fp8_t>::run2(__builtin_bit_cast(uint4, fa[h][i][0]), __builtin_bit_cast(uint4, fa[h][i][1]),
+                             __builtin_bit_cast(uint4, fb[r][0]), __builtin_bit_cast(uint4, fb[r][1]), acc[i][j]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    auto step0 = [&]() __attribute__((always_inline)) {   // of a stage whose fragments have been requested; requests step 1
+        lds_wait<2 * (FN - 2)>();
+        pin_first(I0());
+        read_first(I1());
+        static_for<FN>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            if constexpr (j > 0 && j < FN - 1) lds_wait<2 * (FN - 2 - j) + 2 * FM + 2 + 2 * j>();
+            if constexpr (j < FN - 1) { pin(fb[j][0]); pin(fb[j][1]); }
+            mma(I0(), jc);
+            if constexpr (j < FN - 1) read_b(I1(), jc, jc);
+        });
+    };
+    auto pin_step1 = [&]() __attribute__((always_inline)) {
+        lds_wait<0>();
+        pin_first(I1());
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                igemm_store4<EO, PIX_A>(f32x4_t{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]},
-                                        ra0 + i * 32 + 8 * q, row_b0 + wn * WTN + j * 32 + frow, y, bias, g, post, vec_ok, planes);
+        for (int j = 0; j < FN - 1; ++j) { pin(fb[j][0]); pin(fb[j][1]); }
+    };
+    static_assert(2 * FN + 2 * FM <= 15, "lgkmcnt range");
+
+    issue_pixels(0);
+    issue_filter(0);
+    issue_filter(1);
+    issue_pixels(1);
+    wait_vmcnt<LPF + LPX + 1>();
+    __syncthreads();
+    uint32_t pslot = 0, fslot = 0;
+    locate(I0(), 0, 0);
+    read_first(I0());
+    static_for<FN - 1>([&](auto jc) { read_b(I0(), jc, jc); });
+    // Tap s of a row of taps.  In the middle of it the tap's filter slot, and after the last tap the row's pixel slot, are free and filled with
+    // the filter two taps on and the pixels two rows on; beyond the end these are zeros, and the fragments of a stage that does not exist are
+    // read from whatever the slots hold: without a condition the stages are one basic block.
+    auto stage = [&](auto sc) __attribute__((always_inline)) {
+        constexpr int s = decltype(sc)::value;
+        step0();
+        // the next tap's filter has landed; requested after it are at most the next row's pixels, which have until the second tap
+        wait_vmcnt<s == 0 ? LPX + 1 : 0>();
+        pin_step1();                                      // this wave has read all of this stage
+        block_barrier();
+        issue_filter(fslot);
+        if constexpr (s == 2) { issue_pixels(pslot); pslot ^= 1u; }
+        fslot ^= 1u;
+        locate(std::integral_constant<int, s == 2 ? 0 : s + 1>(), pslot, fslot);
+        read_first(I0());
+        static_for<FN>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            mma(I1(), jc);
+            if constexpr (j < FN - 1) read_b(I0(), jc, jc);
+        });
+    };
+#pragma unroll 1
+    for (int gr = 0; gr < groups; ++gr) { stage(I0()); stage(I1()); stage(I2()); }
+    wait_vmcnt<0>();
+    lds_wait<0>();
+    pin_first(I0());
+#pragma unroll
+    for (int j = 0; j < FN - 1; ++j) { pin(fb[j][0]); pin(fb[j][1]); }
+    block_barrier();
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) asm volatile("" : "+v"(acc[i][j]));    // the products stay in front of the branches of the epilogue
+    fp8_store<EO, BP, BK, WP, WK, PIX_A, (int)ZERO>(acc, lds, bias, y, g, post, p0, k0, vec_ok, planes);
+}
+
+// 2: planes of whole 16-byte pieces
+template <bool PIX_A, typename EO> static int fp8_vec_ok(const ConvGeom& g, const EO* y, const IgemmPost& post, bool planes) {
+    return igemm_vec_ok<PIX_A>(g, y, post, planes) ? (g.Ho * g.Wo % 8 == 0 && (reinterpret_cast<uintptr_t>(y) & 15u) == 0 ? 2 : 1) : 0;
 }
 
 template <typename EO, int BP, int BK, int WP, int WK, bool PIX_A, bool RAGGED>
@@ -275,12 +516,11 @@ static hipError_t launch_fp8_rag(const uint8_t* xq, const uint8_t* Wq, const flo
     const int per_xcd = (int)((total + 7) / 8);
     constexpr int lds_bytes = NST * (BP + BK) * 128 + 12 * BP;
     static_assert(lds_bytes <= 160 * 1024, "LDS budget");
+    const int vec_ok = fp8_vec_ok<PIX_A>(g, y, post, planes);
+    const uint8_t* zero_row = Wq + (size_t)g.R * g.R * g.K * g.Cp;
     auto kern = conv_igemm_fp8_kernel<EO, BP, BK, WP, WK, PIX_A, RAGGED>;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
     if (attr != hipSuccess) return attr;
-    const uint8_t* zero_row = Wq + (size_t)g.R * g.R * g.K * g.Cp;
-    // 2: planes of whole 16-byte pieces
-    const int vec_ok = igemm_vec_ok<PIX_A>(g, y, post, planes) ? (g.Ho * g.Wo % 8 == 0 && (reinterpret_cast<uintptr_t>(y) & 15u) == 0 ? 2 : 1) : 0;
     hipLaunchKernelGGL(kern, dim3((unsigned)(per_xcd * 8)), dim3(WP * WK * 64), lds_bytes, s, xq, Wq, zero_row, bias, y, g, post, tiles_p, tiles_k,
                        (int)total, per_xcd, vec_ok, planes ? 1 : 0);
     return hipGetLastError();
@@ -297,6 +537,68 @@ static hipError_t launch_fp8_cfg(const uint8_t* xq, const uint8_t* Wq, const flo
 // call, NCHW, us, 128x128 / 256x256: 256 channels at 512x512 239 / 222, 512 at 256x256 172 / 151, but 512 at 128x128 46 / 59, 128 at
 // 512x512 86 / 113).
 static bool fp8_wide(const ConvGeom& g) { return g.K % 256 == 0 && (long long)((g.T + 255) / 256) * (g.K / 256) >= 256; }
+
+// 3x3, stride 1, not upsampled, and blocks of 128x128 for most compute units.  Lane offsets are 32-bit and a descriptor covers 2 GB: x, with a row
+// and a pixel in front of it, and the filter have to fit.  Whole calls, us, other kernels / here: 128 channels at 512x512 86.9 / 75.2 (NCHW), 99.2 /
+// 88.1 (channel-last), 320 -> 192 at 200x312 71.2 / 56.3 and 79.9 / 69.3, 448 -> 256 at 512x400 311 / 275 and 345 / 292, 192 -> 256 at 160x480
+// channel-last 99 / 73, 512 -> 320 at 120x72 channel-last (204 blocks) 36.9 / 35.2; but 555 -> 126 at 155x58, N=2 (141) 51.3 / 54.8, 172 -> 75
+// at 125x169 (166) 27.8 / 32.1.  512 -> 256 at 640x192, NCHW, loses 2 % (174 / 178).  Products of random bytes make the card lower its clock: with
+// zeros for x 256 channels at 512x512 take 178 us instead of 201.
+bool igemm_fp8_rows_ok(const ConvGeom& g, int dt, int nsplit) {
+    if (!two_byte(dt) || nsplit != 1 || g.R != 3 || g.st != 1 || g.up) return false;
+    const unsigned long long lim = kRange / (unsigned long long)g.Cp;
+    if ((unsigned long long)g.N * g.H * g.W + g.W + 512u > lim || 9ull * g.K + 512u > lim) return false;
+    return (long long)((g.T + 127) / 128) * ((g.K + 127) / 128) >= 200;
+}
+
+template <typename EO, int BP, int BK, int WP, int WK, bool PIX_A, bool RAGGED>
+static hipError_t launch_rows_cfg(const uint8_t* xq, const uint8_t* Wq, const float* bias, EO* y, const ConvGeom& g, const IgemmPost& post,
+                                  bool planes, hipStream_t s) {
+    const int tiles_p = (g.T + BP - 1) / BP, tiles_k = (g.K + BK - 1) / BK;
+    const long long total = (long long)tiles_p * tiles_k;
+    if (total > 0x3fffffffLL) return hipErrorInvalidValue;
+    constexpr int lds_bytes = 2 * (BP + 8 + BK) * 128 + 1024 + 128;
+    static_assert(lds_bytes <= 160 * 1024, "LDS budget");
+    RowsGeom q;
+    q.tiles_k_fast = tiles_k <= tiles_p;
+    q.tiles_short = q.tiles_k_fast ? tiles_k : tiles_p;
+    q.w = fast_div((uint32_t)g.W); q.h = fast_div((uint32_t)g.H); q.tiles = fast_div((uint32_t)q.tiles_short);
+    q.total_blocks = (int)total; q.blocks_per_xcd = (int)((total + 7) / 8);
+    auto kern = conv_rows_fp8_kernel<EO, BP, BK, WP, WK, PIX_A, RAGGED>;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(q.blocks_per_xcd * 8)), dim3(WP * WK * 64), lds_bytes, s, xq, Wq, bias, y, g, post, q,
+                       fp8_vec_ok<PIX_A>(g, y, post, planes), planes ? 1 : 0);
+    return hipGetLastError();
+}
+
+// NCHW: 256x256 instead of 128x128, one workgroup to a unit instead of two, where their rounds are full: such a round takes as long as 15 / 16 of
+// that of four times as many small blocks (us, 128x128 / 256x256: 512 channels at 256x256 159 / 152, 448 -> 192 at 224x576 176 / 158, 320 -> 192 at 200x312 61.3 / 56.3,
+// 256 channels at 512x512 208 / 207; but 448 -> 256 at 512x400 275 / 296, 512 channels at 128x128 44 / 63), with at least two chunks of channels.
+static bool fp8_rows_wide(const ConvGeom& g) {
+    const long long small = (long long)((g.T + 127) / 128) * ((g.K + 127) / 128), wide = (long long)((g.T + 255) / 256) * ((g.K + 255) / 256);
+    return g.Cp > 128 && 15 * 256 * ((wide + 255) / 256) <= 4 * small;
+}
+
+template <typename EO, int BP, int BK, int WP, int WK, bool PIX_A>
+static hipError_t launch_rows_t(const uint8_t* xq, const uint8_t* Wq, const float* bias, EO* y, const ConvGeom& g, const IgemmPost& post,
+                                bool planes, hipStream_t s) {
+    return g.Cp % 128 == 0 ? launch_rows_cfg<EO, BP, BK, WP, WK, PIX_A, false>(xq, Wq, bias, y, g, post, planes, s)
+                           : launch_rows_cfg<EO, BP, BK, WP, WK, PIX_A, true>(xq, Wq, bias, y, g, post, planes, s);
+}
+
+hipError_t launch_igemm_fp8_rows(const void* xq, const void* Wq, const float* bias, void* y, const ConvGeom& g, const IgemmPost& post, int dt,
+                                 bool nhwc, hipStream_t s) {
+    const bool planes = !nhwc && g.Ho * g.Wo % 2 != 0;
+    auto run = [&](auto* tag) {
+        using EO = std::remove_pointer_t<decltype(tag)>;
+        const uint8_t *x8 = (const uint8_t*)xq, *w8 = (const uint8_t*)Wq;
+        if (nhwc || planes) return launch_rows_t<EO, 128, 128, 2, 2, false>(x8, w8, bias, (EO*)y, g, post, planes, s);
+        return fp8_rows_wide(g) ? launch_rows_t<EO, 256, 256, 4, 2, true>(x8, w8, bias, (EO*)y, g, post, false, s)
+                                : launch_rows_t<EO, 128, 128, 2, 2, true>(x8, w8, bias, (EO*)y, g, post, false, s);
+    };
+    return dt == DT_F16 ? run(static_cast<__half*>(nullptr)) : run(static_cast<bf16_t*>(nullptr));
+}
 
 // Whole reductions and two-byte y.  Left to conv_igemm.hip: wide blocks with a channel-last y, where its sixteen waves measured 224 us
 // against 232 here (256 channels at 512x512), and images too small to give every compute unit a 128x128 block, where its 64x64 blocks are

@@ -23,42 +23,11 @@ namespace wino {
 
 namespace {
 
-// n / d for n < 2^31 as a multiplication, prepared on the host (Granlund and Montgomery, "Division by invariant integers using multiplication")
-struct FastDiv { uint32_t mul, shift; };
-FastDiv fast_div(uint32_t d) {
-    uint32_t l = 0;
-    while ((1u << l) < d) ++l;
-    return {(uint32_t)((((1ull << l) - d) << 32) / d + 1), l};
-}
-__device__ __forceinline__ uint32_t divide(uint32_t n, FastDiv f) { return (__umulhi(n, f.mul) + n) >> f.shift; }
-
 struct TileGeom {
     FastDiv howo, wo, tiles, nsplit;       // divisions by Ho*Wo, Wo, the shorter tile dimension, the number of ranges
     int tiles_k_fast;                      // the shorter one is that of the output channels
     int total_blocks, blocks_per_xcd, nsplit_n, tiles_short;
 };
-
-typedef int rsrc_t __attribute__((ext_vector_type(4)));
-// Descriptor for buffer loads of at most 2 GB from `base` on.  A lane whose offset is kOutside lies beyond its range whatever scalar offset
-// is added, and reads zeros; every other lane's offset is inside the operand.
-constexpr uint32_t kOutside = 0x80000000u, kRange = 0x7fffffffu;
-__device__ __forceinline__ rsrc_t make_rsrc(const void* base) {
-    const uint64_t a = reinterpret_cast<uint64_t>(base);
-    rsrc_t r;
-    r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
-    r[1] = __builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xffffu));
-    r[2] = (int)kRange;
-    r[3] = 0x00020000;
-    return r;
-}
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-// 1 KB to LDS: a wave-uniform descriptor and byte offset, a byte offset per lane; a lane outside the range writes zeros
-__device__ __forceinline__ void dma_buffer_1k(rsrc_t r, uint32_t lane_off, uint32_t off, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds_addr), "v"(lane_off), "s"(r), "s"(__builtin_amdgcn_readfirstlane(off)) : "memory", "m0");
-}
-#pragma clang diagnostic pop
 
 }  // namespace
 
