@@ -5,15 +5,6 @@
 
 namespace wino {
 
-// n / d for n < 2^31 as a multiplication, prepared on the host (Granlund and Montgomery, "Division by invariant integers using multiplication")
-struct FastDiv { uint32_t mul, shift; };
-inline FastDiv fast_div(uint32_t d) {
-    uint32_t l = 0;
-    while ((1u << l) < d) ++l;
-    return {(uint32_t)((((1ull << l) - d) << 32) / d + 1), l};
-}
-__device__ __forceinline__ uint32_t divide(uint32_t n, FastDiv f) { return (__umulhi(n, f.mul) + n) >> f.shift; }
-
 typedef int rsrc_t __attribute__((ext_vector_type(4)));
 // Descriptor for buffer loads of at most 2 GB from `base` on.  A lane whose offset is kOutside lies beyond its range whatever scalar offset
 // is added, and reads zeros; every other lane's offset is inside the operand.

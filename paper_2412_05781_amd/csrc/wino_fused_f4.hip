@@ -6,9 +6,9 @@
 //   - a wave owns a 16 x 32 piece (two 16x16 MFMA tiles, v_mfma_f32_16x16x32: four accumulator registers per tile), and
 //   - step (iii) is taken one dimension at a time.  Positions run xi-major; while nu runs over a row of the
 //     transformed tile the product is folded into four row sums  Z[b] += A^T[b][nu] * M[xi,nu]; at the end of the row
-//     Y[a][b] += A^T[a][xi] * Z[b].  That is 22 accumulator sets of 8 registers (16 outputs, 4 row sums, and the product twice:
-//     the two MFMA steps of a stage alternate between two accumulators), all in vector registers, and 180 multiply-adds per
-//     accumulator register instead of 324.
+//     Y[a][b] += A^T[a][xi] * Z[b].  That is 21 accumulator sets of 8 registers (16 outputs, 4 row sums, the product), all in vector
+//     registers, and 180 multiply-adds per accumulator register instead of 324.  They are not hidden: without them 128 channels at 1024x1024
+//     take 413 us instead of 457 (a second set for the product, added in front of each, 8 more).
 // The price of the small wave tile is traffic: 3 KB of LDS fragments per 32 reduction elements and wave, and a block of
 // at most 64 x 64 per compute unit (the register file holds no more accumulators of this kind), so every byte of U and V is
 // fetched into LDS by T/64 and K/64 workgroups.  That fill traffic bounds the kernel; it pays on large images with at
@@ -33,7 +33,7 @@ __device__ __forceinline__ float at4(int a, int x) {
     return a == 0 ? 1.f : (a == 1 ? sign * mag : (a == 2 ? mag * mag : sign * mag * mag * mag));
 }
 
-struct Fused4Geom { int N, K, H, W, th, tw, T; };
+struct Fused4Geom { int N, K, H, W, th, tw, T; FastDiv dth, dtw; };
 
 __device__ const uint4 zero_chunk = {0u, 0u, 0u, 0u};     // source of the chunks beyond Cp
 
@@ -126,11 +126,10 @@ wino_fused_f4_kernel(const E* __restrict__ Aop, const E* __restrict__ Bop, const
     };
 
     // accumulators of the wave's two 16x16 tiles: the product of the current position, the four row sums, the 16 outputs
-    f32x4_t accM[2][2], accZ[4][2], accY[4][4][2];
+    f32x4_t accM[2], accZ[4][2], accY[4][4][2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-        accM[0][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        accM[1][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        accM[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
             accZ[b][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -170,8 +169,8 @@ wino_fused_f4_kernel(const E* __restrict__ Aop, const E* __restrict__ Bop, const
         constexpr int set = decltype(setc)::value;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            Mma16<E>::run(fa[set][h], fb[set][h][0], accM[h][0]);
-            Mma16<E>::run(fa[set][h], fb[set][h][1], accM[h][1]);
+            Mma16<E>::run(fa[set][h], fb[set][h][0], accM[0]);
+            Mma16<E>::run(fa[set][h], fb[set][h][1], accM[1]);
         }
     };
     using I0 = std::integral_constant<int, 0>;
@@ -198,11 +197,11 @@ wino_fused_f4_kernel(const E* __restrict__ Aop, const E* __restrict__ Bop, const
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) accZ[b][j][r] = fmaf(c, accM[0][j][r] + accM[1][j][r], accZ[b][j][r]);
+                    for (int r = 0; r < 4; ++r) accZ[b][j][r] = fmaf(c, accM[j][r], accZ[b][j][r]);
             }
         }
 #pragma unroll
-        for (int j = 0; j < 2; ++j) { accM[0][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; accM[1][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
+        for (int j = 0; j < 2; ++j) accM[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         if (++nu < 6) return;
         nu = 0;
 #pragma unroll
@@ -264,30 +263,40 @@ wino_fused_f4_kernel(const E* __restrict__ Aop, const E* __restrict__ Bop, const
     // 16x16 accumulator layout: register r of lane l holds row 4*(l/16) + r, column l%16 of the tile
     const int H = g.H, W = g.W, K = g.K;
     const E* res = static_cast<const E*>(post.residual);
+    // tile t (clamped): image, first output row and column
+    auto locate = [&](int t, int& n, int& i0, int& j0) __attribute__((always_inline)) {
+        const uint32_t tc = (uint32_t)min(t, g.T - 1), q = divide(tc, g.dtw);
+        n = (int)divide(q, g.dth);
+        j0 = 4 * (int)(tc - q * (uint32_t)g.tw);
+        i0 = 4 * ((int)q - n * g.th);
+    };
     if constexpr (ROWS_K) {
         // columns are tiles: a lane owns one tile per column tile, its four registers run over output channels; the four
         // pixels of an output row of the tile are stored together, neighbouring lanes hold neighbouring tiles of a tile row
+        const int k0 = row0 + wm * 16 + 4 * frag_q;
+        float bk[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) bk[r] = bias ? bias[min(k0 + r, K - 1)] : 0.f;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            int t = col0 + wn * 32 + j * 16 + frag_row;
-            const bool t_ok = t < g.T;
-            t = t_ok ? t : g.T - 1;
-            const int tj = t % g.tw; const int q = t / g.tw;
-            const int ti = q % g.th, n = q / g.th;
-            const int i0 = 4 * ti, j0 = 4 * tj;
+            const int t = col0 + wn * 32 + j * 16 + frag_row;
+            int n, i0, j0;
+            locate(t, n, i0, j0);
+            float bb[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) bb[r] = bk[r] + (post.addvec ? post.addvec[(size_t)n * K + min(k0 + r, K - 1)] : 0.f);
+            if (t >= g.T) continue;
+            const size_t off = (((size_t)n * K + k0) * H + i0) * W + j0;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int k = row0 + wm * 16 + 4 * frag_q + r;
-                if (!(k < K && t_ok)) continue;
-                const float bb = (bias ? bias[k] : 0.f) + (post.addvec ? post.addvec[(size_t)n * K + k] : 0.f);
-                const size_t off = (((size_t)n * K + k) * H + i0) * W + j0;
+                if (k0 + r >= K) continue;
 #pragma unroll
                 for (int a = 0; a < 4; ++a) {
                     if (i0 + a >= H) continue;
-                    const size_t o = off + (size_t)a * W;
+                    const size_t o = off + ((size_t)r * H + a) * W;
                     float v[4];
 #pragma unroll
-                    for (int b = 0; b < 4; ++b) v[b] = accY[a][b][j][r] + bb;
+                    for (int b = 0; b < 4; ++b) v[b] = accY[a][b][j][r] + bb[r];
                     if (vec_ok) {
                         if (res) {
                             const uint2 rr = *reinterpret_cast<const uint2*>(res + o);
@@ -305,54 +314,57 @@ wino_fused_f4_kernel(const E* __restrict__ Aop, const E* __restrict__ Bop, const
     } else {
         // Columns are output channels, which are contiguous in a channel-last y - but a lane holds one channel and a 16x16
         // tile only 16 of them, so stores straight from the accumulators would be 32-byte pieces.  The block goes through LDS
-        // instead (the ring is free by now): for each output row a of the tile, every wave parks its values for the four
-        // pixels (a, b) as storage-type elements at [b][tile][channel], and the workgroup then writes them out as 16-byte
-        // pieces, eight lanes to a 128-byte line.  Bias, vector and residual are added before the one rounding, as everywhere.
-        constexpr int PSTRIDE = BN * 2 + 16;              // bytes per (pixel, tile) row in LDS; the pad spreads the rows over the banks
-        constexpr int PIECES = BN / 8;                    // 16-byte pieces per row
+        // instead (the ring is free by now): for each output row a of the tile, every wave parks its sums for the four pixels
+        // (a, b) at [b][tile][channel], and a thread then takes eight channels of one tile, always the same, finds its place in y once, adds
+        // bias, vector and residual before the one rounding, as everywhere, and writes 16-byte pieces, eight lanes to a 128-byte line.  (With
+        // the tile's place found for every value parked and every piece stored, the end of a block took 15 us, and a sixth of that now:
+        // 128 channels at 1024x1024, eight rounds of blocks, 488 -> 457 us a call.)
+        constexpr int PSTRIDE = BN * 4 + 16;              // bytes per (pixel, tile) row in LDS; the pad spreads the rows over the banks
+        constexpr int PIECES = BN / 8;                    // pieces of eight channels per row
         static_assert(4 * BM * PSTRIDE <= NST * STAGE_BYTES, "the parked rows fit the ring's LDS");
-        const bool rows16 = (K % 8 == 0);                 // a pixel's channel vector starts on a 16-byte boundary
+        static_assert(BM * PIECES == NW * 64, "a thread keeps its tile and piece");
+        const int piece = tid % PIECES, tl = tid / PIECES, t = row0 + tl, k0 = col0 + piece * 8;
+        int n, i0, j0;
+        locate(t, n, i0, j0);
+        float bb[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int k = min(k0 + e, K - 1);
+            bb[e] = (bias ? bias[k] : 0.f) + (post.addvec ? post.addvec[(size_t)n * K + k] : 0.f);
+        }
+        const bool whole = K % 8 == 0 && k0 + 8 <= K;     // a pixel's channel vector starts on a 16-byte boundary
+        const size_t base = (((size_t)n * H + i0) * W + j0) * K + k0;
+        unsigned char* park = lds + (size_t)(wm * 16 + 4 * frag_q) * PSTRIDE + (size_t)(wn * 32 + frag_row) * 4;
+        const unsigned char* take = lds + (size_t)tl * PSTRIDE + (size_t)piece * 32;
 #pragma unroll
         for (int a = 0; a < 4; ++a) {                     // unrolled: the accumulators are registers, a must be a constant
             __syncthreads();                              // nobody reads the ring (or the previous rows) any more
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int kl = wn * 32 + j * 16 + frag_row, k = col0 + kl;
-                const bool k_ok = k < K;
-                const float bk = (bias && k_ok) ? bias[k] : 0.f;
+            for (int b = 0; b < 4; ++b)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int tl = wm * 16 + 4 * frag_q + r, t = row0 + tl;
-                    const bool ok = t < g.T && k_ok;
-                    const int tc = t < g.T ? t : g.T - 1;
-                    const int tj = tc % g.tw; const int q = tc / g.tw;
-                    const int ti = q % g.th, n = q / g.th;
-                    const float bb = bk + ((post.addvec && ok) ? post.addvec[(size_t)n * K + k] : 0.f);
-                    const int ii = 4 * ti + a;
+                for (int j = 0; j < 2; ++j)
 #pragma unroll
-                    for (int b = 0; b < 4; ++b) {
-                        const int jj = 4 * tj + b;
-                        float v = accY[a][b][j][r] + bb;
-                        if (res && ok && ii < H && jj < W) v += to_f32<E>(res[(((size_t)n * H + ii) * W + jj) * K + k]);
-                        *reinterpret_cast<E*>(lds + (size_t)(b * BM + tl) * PSTRIDE + (size_t)kl * 2) = from_f32<E>(v);
-                    }
-                }
-            }
+                    for (int r = 0; r < 4; ++r)
+                        *reinterpret_cast<float*>(park + (b * BM + r) * PSTRIDE + j * 64) = accY[a][b][j][r];
             __syncthreads();
-            for (int idx = tid; idx < 4 * BM * PIECES; idx += NW * 64) {
-                const int piece = idx % PIECES, tl = (idx / PIECES) % BM, b = idx / (PIECES * BM);
-                const int t = row0 + tl, k0 = col0 + piece * 8;
-                if (t >= g.T || k0 >= K) continue;
-                const int tj = t % g.tw; const int q = t / g.tw;
-                const int ti = q % g.th, n = q / g.th;
-                const int ii = 4 * ti + a, jj = 4 * tj + b;
-                if (ii >= H || jj >= W) continue;
-                const unsigned char* src = lds + (size_t)(b * BM + tl) * PSTRIDE + (size_t)piece * 16;
-                E* dst = y + (((size_t)n * H + ii) * W + jj) * K + k0;
-                if (rows16 && k0 + 8 <= K) {
-                    *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
+            if (t >= g.T || k0 >= K || i0 + a >= H) continue;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                if (j0 + b >= W) continue;
+                const size_t o = base + ((size_t)a * W + b) * K;
+                const f32x4_t lo = *reinterpret_cast<const f32x4_t*>(take + b * BM * PSTRIDE), hi = *reinterpret_cast<const f32x4_t*>(take + b * BM * PSTRIDE + 16);
+                float v[8] = {lo[0] + bb[0], lo[1] + bb[1], lo[2] + bb[2], lo[3] + bb[3], hi[0] + bb[4], hi[1] + bb[5], hi[2] + bb[6], hi[3] + bb[7]};
+                if (whole) {
+                    if (res) {
+                        const uint4 w = *reinterpret_cast<const uint4*>(res + o);
+                        v[0] += lo16<E>(w.x); v[1] += hi16<E>(w.x); v[2] += lo16<E>(w.y); v[3] += hi16<E>(w.y);
+                        v[4] += lo16<E>(w.z); v[5] += hi16<E>(w.z); v[6] += lo16<E>(w.w); v[7] += hi16<E>(w.w);
+                    }
+                    *reinterpret_cast<uint4*>(y + o) = make_uint4(pack2<E>(v[0], v[1]), pack2<E>(v[2], v[3]), pack2<E>(v[4], v[5]), pack2<E>(v[6], v[7]));
                 } else {
-                    for (int e = 0; e < 8 && k0 + e < K; ++e) dst[e] = reinterpret_cast<const E*>(src)[e];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if (k0 + e < K) y[o + e] = from_f32<E>(v[e] + (res ? to_f32<E>(res[o + e]) : 0.f));
                 }
             }
         }
@@ -374,7 +386,7 @@ static hipError_t launch_fused4_cfg(const void* Aop, const void* Bop, int rowsA,
     auto kern = wino_fused_f4_kernel<E, NST, WGM, WGN, ROWS_K, RAGGED>;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
     if (attr != hipSuccess) return attr;
-    Fused4Geom fg{g.N, g.K, g.H, g.W, g.th, g.tw, g.T};
+    Fused4Geom fg{g.N, g.K, g.H, g.W, g.th, g.tw, g.T, fast_div((uint32_t)g.th), fast_div((uint32_t)g.tw)};
     // four-pixel stores of a tile's output row need W % 4 == 0 (the group then never straddles the row end) and 8-byte alignment
     const int vec_ok = (g.W % 4 == 0) && ((reinterpret_cast<uintptr_t>(y) & 7u) == 0) && ((reinterpret_cast<uintptr_t>(post.residual) & 7u) == 0);
     hipLaunchKernelGGL(kern, dim3((unsigned)(per_xcd * 8)), dim3(WGM * WGN * 64), lds_bytes, s,

@@ -31,6 +31,15 @@ inline Geom make_geom(int N, int C, int H, int W, int K, int m) {
     return g;
 }
 
+// n / d for n < 2^31 as a multiplication, prepared on the host (Granlund and Montgomery, "Division by invariant integers using multiplication")
+struct FastDiv { uint32_t mul, shift; };
+inline FastDiv fast_div(uint32_t d) {
+    uint32_t l = 0;
+    while ((1u << l) < d) ++l;
+    return {(uint32_t)((((1ull << l) - d) << 32) / d + 1), l};
+}
+__device__ __forceinline__ uint32_t divide(uint32_t n, FastDiv f) { return (__umulhi(n, f.mul) + n) >> f.shift; }
+
 // Storage types (values of wino_dtype).  `with_dtype` calls f with a null pointer of the element
 // type, so that a generic lambda can name it:  using E = std::remove_pointer_t<decltype(tag)>.
 typedef __hip_bfloat16 bf16_t;
