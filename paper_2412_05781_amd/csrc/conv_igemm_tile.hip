@@ -325,7 +325,7 @@ static hipError_t launch_tile_cfg(const E* xh, const E* Wr, const float* bias, E
     return hipGetLastError();
 }
 
-// Blocks on offer, pixels x output channels, all of eight waves, with the time of a reduction stage: `alone` where a compute unit holds one
+// Blocks on offer, pixels x output channels, of eight waves (but for a sixth, see below), with the time of a reduction stage: `alone` where a compute unit holds one
 // workgroup, `each` per workgroup where it holds several; and `first`, `more`: start and stores of the first workgroup of a unit, beyond
 // those of a launch, and of each further one (us, fitted together to 530 calls, 5900 timings, of 1x1, stride 2 and 3x3 layers; the
 // choice by them is within 0.5 % of the best of the five on average).  The 128x96 block with three slots fills a unit by itself: it is for calls of one
@@ -358,6 +358,12 @@ IgemmTilePlan igemm_block_plan(int T, int K, int Cp, int R, int dt, bool nhwc, i
             if (c < cost) { cost = c; best = {id, sp}; }
         }
     }
+    // One column of blocks.  Up to 32 output channels a block of 64x32 with four waves has no empty half (us, 128x64 / 64x64 / 64x32, channel-last: 256 ->
+    // 24 at 485x194 33.2 / 38.9 / 28.7, 384 -> 18 at 569x166 68.5 / 56.5 / 45.5, 128 -> 32 at 400x400 30.0 / 39.8 / 27.5, 128 -> 16 at 64x64 8.5 / 6.6 /
+    // 6.2); up to 64 a long reduction prefers the smaller block, whose workgroups hide each other's transfers (512 -> 48 at 256x256, 72
+    // stages, 74.8 / 53.1; 256 -> 64 at 300x300, 36 stages, 38.3 / 45.0)
+    if (best.split == 1 && K <= 32) best.id = 5;
+    else if (best.split == 1 && K <= 64 && stages >= 54) best.id = 0;
     // channel-last, a number of channels that is no multiple of four: outputs are stored one by one, 16 lanes to as many lines, and a short
     // reduction does not make up for it (1x1, here / there: 64 -> 1194 at 50x23 (N=2) 11.2 / 8.5, 576 -> 873 at 26x41 (N=4) 17.7 / 16.5, 128 -> 1203 at
     // 78x117 (N=2) 53 / 49; but 64 -> 321 at 13x45 5.7 / 6.1, 832 -> 853 at 30x18 (N=2) 9.8 / 13.1, 3x3 64 -> 1110 at 16x32 (N=4) 15.8 / 17.2)
@@ -419,6 +425,7 @@ static hipError_t launch_tile_t(const E* xh, const E* Wr, const float* bias, E* 
         case 2: return launch_tile_cfg<E, 128, 96, 4, 2, 2, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
         case 3: return launch_tile_cfg<E, 128, 96, 4, 2, 3, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
         case 4: return launch_tile_cfg<E, 128, 128, 4, 2, 2, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
+        case 5: return launch_tile_cfg<E, 64, 32, 2, 2, 4, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
         default: return hipErrorInvalidValue;
     }
 }
