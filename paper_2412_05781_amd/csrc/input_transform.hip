@@ -54,7 +54,11 @@ template <typename E> __device__ __forceinline__ float unpack(uint32_t w, int h)
     return to_f32<E>(*reinterpret_cast<const E*>(&e));
 }
 
-template <int M, typename E, int CB, int TJ, bool PRE>
+// two neighbouring two-byte elements at an address of any element
+struct __attribute__((packed, aligned(2))) pair_t { uint32_t w; };
+
+// PAIRS: two-byte types and stored rows of at least two elements: the patch is fetched in pairs of columns.
+template <int M, typename E, int CB, int TJ, bool PRE, bool PAIRS>
 __global__ void __launch_bounds__(256)
 input_transform_nchw_kernel(const E* __restrict__ x, E* __restrict__ V,
                             int N, int C, int H, int W, int th, int tw, int T, int Cp, int strips_per_row, PreOp pre) {
@@ -86,13 +90,43 @@ input_transform_nchw_kernel(const E* __restrict__ x, E* __restrict__ V,
     // consecutive lanes walk along W.  Loads are issued from clamped addresses and masked: all of a lane's are in flight together.
     // (Element by element over [channel][row][column], each index divided out and tested: 20.2 us against 11.9 for 640 channels, N=2,
     // 52x78 upsampled.)
+    const int Hs = H >> pre.up, Ws = W >> pre.up;
+    const size_t img = (size_t)Hs * Ws;
+    if constexpr (PAIRS) {
+        // The window's first column is odd, so a pair of columns is a pair of neighbours in x whether that is read upsampled or not.  At the
+        // ends of a row the pair one place further in is fetched and shifted.  (A whole call of 640 channels, N=2, 52x78 upsampled, single
+        // elements / pairs: 55.9 / 54.5 us; 960 at 34x50 upsampled 33.6 / 32.7.)
+        constexpr int PWW = PW / 2, RAWW = A * PWW, G = 256 / RAWW, LOADS = (CB + G - 1) / G;
+        const int rem = tid % RAWW, cg = tid / RAWW;
+        const int pr = row0 + rem / PWW, pq = col0 + 2 * (rem % PWW);
+        const int s0 = pq >> pre.up, sc = min(max(s0, 0), Ws - 2);
+        const int left = s0 < sc ? 16 : 0, right = s0 > sc ? 16 : 0;
+        const uint32_t in = pr >= 0 && pr < H ? (pq >= 0 && pq < W ? 0xffffu : 0u) | (pq + 1 >= 0 && pq + 1 < W ? 0xffff0000u : 0u) : 0u;
+        // 32-bit lane offsets from the slab's first pixel: the slab spans less than 2 GB
+        const unsigned char* xp = reinterpret_cast<const unsigned char*>(x + ((size_t)n * C + c0) * img);
+        const uint32_t plane = (uint32_t)img * 2u, last = (uint32_t)min(CB - 1, C - 1 - c0);
+        const uint32_t pix = ((uint32_t)(min(max(pr, 0), H - 1) >> pre.up) * (uint32_t)Ws + (uint32_t)sc) * 2u;
+        const uint32_t most = pix + last * plane;         // channels beyond the last repeat it, and are staged as zeros
+        uint32_t off = pix + (uint32_t)cg * plane, v[LOADS];
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            v[i] = reinterpret_cast<const pair_t*>(xp + min(off, most))->w;
+            off += (uint32_t)G * plane;
+        }
+        if (cg < G) {
+            uint32_t* dst = patch + cg * CSW + rem;
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i) {
+                const uint32_t w = v[i] << left >> right & in;
+                if (CB % G == 0 || cg + G * i < CB) dst[G * i * CSW] = (uint32_t)(cg + G * i) <= last ? w : 0u;
+            }
+        }
+    } else {
     constexpr int G = 256 / RAW;                         // channels in hand at a time
     constexpr int LOADS = (CB + G - 1) / G;
-    const int Hs = H >> pre.up, Ws = W >> pre.up;
     const int rem = tid % RAW, cg = tid / RAW;
     const int pr = row0 + rem / PW, pq = col0 + rem % PW;
     const bool in = pr >= 0 && pr < H && pq >= 0 && pq < W;
-    const size_t img = (size_t)Hs * Ws;
     const E* xp = x + ((size_t)n * C + c0) * img + (size_t)(min(max(pr, 0), H - 1) >> pre.up) * Ws + (min(max(pq, 0), W - 1) >> pre.up);
     E v[LOADS];
 #pragma unroll
@@ -101,6 +135,7 @@ input_transform_nchw_kernel(const E* __restrict__ x, E* __restrict__ V,
     for (int i = 0; i < LOADS; ++i) {
         const int ch = cg + G * i;
         if (cg < G && ch < CB) reinterpret_cast<E*>(patch + ch * CSW)[rem] = in && c0 + ch < C ? v[i] : from_f32<E>(0.f);
+    }
     }
     __syncthreads();
 
@@ -519,10 +554,19 @@ static hipError_t launch_it_cfg(const void* x, void* V, const Geom& g, const Pre
         else     hipLaunchKernelGGL((input_transform_nchw_vec_kernel<M, E, CB, TJ, false>), dim3((unsigned)(per_xcd * 8)), block, 0, s,
                                     (const E*)x, (E*)V, g.N, g.C, g.H, g.W, g.th, g.tw, g.T, g.Cp, strips, (int)total, per_xcd, po);
     } else {
-        if (gn) hipLaunchKernelGGL((input_transform_nchw_kernel<M, E, CB, TJ, true>), grid, block, 0, s,
-                                    (const E*)x, (E*)V, g.N, g.C, g.H, g.W, g.th, g.tw, g.T, g.Cp, strips, po);
-        else     hipLaunchKernelGGL((input_transform_nchw_kernel<M, E, CB, TJ, false>), grid, block, 0, s,
-                                    (const E*)x, (E*)V, g.N, g.C, g.H, g.W, g.th, g.tw, g.T, g.Cp, strips, po);
+        const auto run = [&](auto kern) {
+            hipLaunchKernelGGL(kern, grid, block, 0, s, (const E*)x, (E*)V, g.N, g.C, g.H, g.W, g.th, g.tw, g.T, g.Cp, strips, po);
+        };
+        if constexpr (sizeof(E) == 2) {
+            // (lane offsets of the pairs, of up to CB + 6 channels: 32-bit)
+            if (g.W >> po.up >= 2 && (size_t)(CB + 6) * (g.H >> po.up) * (g.W >> po.up) * sizeof(E) < ((size_t)1 << 31)) {
+                if (gn) run(input_transform_nchw_kernel<M, E, CB, TJ, true, true>);
+                else run(input_transform_nchw_kernel<M, E, CB, TJ, false, true>);
+                return hipGetLastError();
+            }
+        }
+        if (gn) run(input_transform_nchw_kernel<M, E, CB, TJ, true, false>);
+        else run(input_transform_nchw_kernel<M, E, CB, TJ, false, false>);
     }
     return hipGetLastError();
 }
