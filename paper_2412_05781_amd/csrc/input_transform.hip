@@ -83,8 +83,8 @@ input_transform_nchw_kernel(const E* __restrict__ x, E* __restrict__ V,
 
     const int cc = tid & 63;
     const int c = c0 + cc;
-    PreLane pl = {0.f, 0.f, false};
-    if (PRE) pl = pre_lane(pre, n, c, C);
+    PreRaw raw = {0.f, 0.f, 0.f, 0.f};                    // requested here, with the pixels
+    if (PRE) raw = pre_request(pre, n, c, C);
 
     // ---- stage the patch: a lane owns one patch position and walks the channels, so its address and its bounds test are found once;
     // consecutive lanes walk along W.  Loads are issued from clamped addresses and masked: all of a lane's are in flight together.
@@ -140,6 +140,8 @@ input_transform_nchw_kernel(const E* __restrict__ x, E* __restrict__ V,
     __syncthreads();
 
     // ---- transform: lane = channel, one tile per wave per iteration ----------------------
+    PreLane pl = {0.f, 0.f, false};
+    if (PRE) pl = pre_finish(raw, c, C);
     if (c >= Cp) return;                                 // no barrier follows
     const size_t plane = (size_t)T * Cp;
     for (int tl = __builtin_amdgcn_readfirstlane(tid >> 6); tl < TJ; tl += 4) {
@@ -170,7 +172,7 @@ input_transform_nchw_kernel(const E* __restrict__ x, E* __restrict__ V,
 // fetched as 16-byte chunks, all loads of a lane issued before the first LDS write, so one global
 // round trip covers the whole patch.  Patch columns run from m*tj0 - EPC to m*(tj0+TJ) + EPC
 // (EPC = elements per chunk); a chunk is either wholly inside the image or wholly outside (zero).
-template <int M, typename E, int CB, int TJ, bool PRE>
+template <int M, typename E, int CB, int TJ, bool PRE, int UP>
 __global__ void __launch_bounds__(256)
 input_transform_nchw_vec_kernel(const E* __restrict__ x, E* __restrict__ V,
                                 int N, int C, int H, int W, int th, int tw, int T, int Cp, int strips_per_row,
@@ -199,35 +201,41 @@ input_transform_nchw_vec_kernel(const E* __restrict__ x, E* __restrict__ V,
     static_assert(CB == 64, "lane = channel");
     const int cc = tid & 63;                              // of the transform
     const int c = c0 + cc;
-    PreLane pl = {0.f, 0.f, false};                       // requested here, with the pixels
-    if (PRE) pl = pre_lane(pre, n, c, C);
+    PreRaw raw = {0.f, 0.f, 0.f, 0.f};                    // requested here, with the pixels
+    if (PRE) raw = pre_request(pre, n, c, C);
 
     // 32-bit lane offsets against wave-uniform 64-bit bases keep the address arithmetic off the
     // vector ALU (the transform itself is only ~200 operations per tile and channel).
-    const int Hs = H >> pre.up, Ws = W >> pre.up;         // the stored image (half size when it is read upsampled)
+    const int Hs = H >> UP, Ws = W >> UP;                 // the stored image (half size when it is read upsampled)
     const unsigned char* xb = reinterpret_cast<const unsigned char*>(x + ((size_t)n * C + c0) * Hs * Ws);
-    // a lane owns one (channel, chunk column) and walks the alpha patch rows: one add per load
+    // A lane owns one (channel, chunk column) and walks the alpha patch rows.  Loads come from clamped addresses and what lies outside is
+    // cleared afterwards: none sits in a branch, where an upsampled row would be waited for before the next one is requested.
     constexpr int ITEMS = CB * NCH;
     constexpr int PASSES = (ITEMS + 255) / 256;
     uint4 reg[PASSES][A];
 #pragma unroll
     for (int ps = 0; ps < PASSES; ++ps) {
-        const int item = tid + ps * 256;
-        const int cc = item / NCH, ch = item - cc * NCH;
-        const int col = col0 + ch * EPC;
-        const bool ok = item < ITEMS && (c0 + cc) < C && col >= 0 && col + EPC <= W;
-        const unsigned off0 = (unsigned)(((cc * H + row0) * W + col) * (int)sizeof(E));   // may wrap for row0 = -1; only used when the row is valid
+        const int item = min(tid + ps * 256, ITEMS - 1);
+        const int cc = min(item / NCH, C - 1 - c0), col = min(max(col0 + item % NCH * EPC, 0), W - EPC);
+        const unsigned lane0 = (unsigned)((cc * Hs * Ws + (col >> UP)) * (int)sizeof(E));
 #pragma unroll
         for (int a = 0; a < A; ++a) {
-            const int r = row0 + a;
-            reg[ps][a] = make_uint4(0, 0, 0, 0);
-            if (ok && r >= 0 && r < H) {
-                if (pre.up)   // 8 source bytes under the 16-byte chunk, every element twice
-                    reg[ps][a] = dup_elements<E>(*reinterpret_cast<const uint2*>(
-                        xb + (unsigned)(((cc * Hs + (r >> 1)) * Ws + (col >> 1)) * (int)sizeof(E))));
-                else
-                    reg[ps][a] = *reinterpret_cast<const uint4*>(xb + (off0 + (unsigned)(a * W * (int)sizeof(E))));
-            }
+            const unsigned off = lane0 + (unsigned)((min(max(row0 + a, 0), H - 1) >> UP) * Ws * (int)sizeof(E));
+            if constexpr (UP) {                           // 8 source bytes under the 16-byte chunk
+                const uint2 h = *reinterpret_cast<const uint2*>(xb + off);
+                reg[ps][a].x = h.x; reg[ps][a].y = h.y;
+            } else reg[ps][a] = *reinterpret_cast<const uint4*>(xb + off);
+        }
+    }
+#pragma unroll
+    for (int ps = 0; ps < PASSES; ++ps) {
+        const int item = tid + ps * 256, cc = item / NCH, col = col0 + (item - cc * NCH) * EPC;
+        const bool ok = c0 + cc < C && col >= 0 && col + EPC <= W;
+#pragma unroll
+        for (int a = 0; a < A; ++a) {
+            if constexpr (UP) reg[ps][a] = dup_elements<E>(make_uint2(reg[ps][a].x, reg[ps][a].y));        // every element twice
+            const uint32_t m = ok && row0 + a >= 0 && row0 + a < H ? ~0u : 0u;
+            reg[ps][a].x &= m; reg[ps][a].y &= m; reg[ps][a].z &= m; reg[ps][a].w &= m;
         }
     }
 #pragma unroll
@@ -249,6 +257,8 @@ input_transform_nchw_vec_kernel(const E* __restrict__ x, E* __restrict__ V,
     const size_t plane = (size_t)T * Cp;
     constexpr int EPW = 4 / (int)sizeof(E);
     constexpr int W0 = EPC - EPW, NWD = (A - 1 + EPW - 1) / EPW + 1;       // first word of tile 0's window (its last element), words per row
+    PreLane pl = {0.f, 0.f, false};
+    if (PRE) pl = pre_finish(raw, c, C);
     if (c >= Cp) return;                                  // no barrier follows
     for (int tl = __builtin_amdgcn_readfirstlane(tid >> 6); tl < TJ; tl += 4) {
         const int tj = tj0 + tl;
@@ -355,14 +365,16 @@ input_transform_nchw_slide_kernel(const E* __restrict__ x, E* __restrict__ V,
     const size_t plane_bytes = (size_t)T * Cp * sizeof(E);
     const uint32_t* pch = patch + cc * CSW;
     const unsigned coff = (unsigned)c * (unsigned)sizeof(E);
-    PreLane pl = {0.f, 0.f, false};
-    if (PRE) pl = pre_lane(pre, n, c, C);
+    PreRaw raw = {0.f, 0.f, 0.f, 0.f};                    // requested here, with the pixels
+    if (PRE) raw = pre_request(pre, n, c, C);
 
     fetch(s0 - 1);
     stash(s0 - 1);
     fetch(s0);
     stash(s0);
     __syncthreads();
+    PreLane pl = {0.f, 0.f, false};
+    if (PRE) pl = pre_finish(raw, c, C);
     for (int s = s0; s < s1; ++s) {
         if (s + 1 < s1) fetch(s + 1);                     // in flight while this step is transformed
         // the wave's tiles, neighbours (wave-uniform); moved inside the row as a group, the duplicates write identical values
@@ -422,9 +434,9 @@ input_transform_nhwc_kernel(const E* __restrict__ x, E* __restrict__ V,
     const int ti = q % th;
     const int n = q / th;
     const bool live = c < C;                                   // CPT divides C on this path
-    PreLane pl[CPT];
+    PreRaw raw[CPT];
 #pragma unroll
-    for (int u = 0; u < CPT; ++u) { pl[u].sc = 0.f; pl[u].sh = 0.f; pl[u].on = false; if (PRE) pl[u] = pre_lane(pre, n, c + u, C); }
+    for (int u = 0; u < CPT; ++u) { raw[u] = PreRaw{0.f, 0.f, 0.f, 0.f}; if (PRE) raw[u] = pre_request(pre, n, c + u, C); }
     // Every load is issued unconditionally from a clamped (always valid) address and the loaded
     // bits are ANDed with an all-ones / all-zeros mask, so that the alpha^2 loads of a lane are all
     // in flight together.  The masks pass through an empty asm statement: seen as a select on the
@@ -440,7 +452,8 @@ input_transform_nhwc_kernel(const E* __restrict__ x, E* __restrict__ V,
         asm("" : "+v"(rmask[a]));
         asm("" : "+v"(cmask[a]));
     }
-    float d[CPT][A][A];
+    union word_t { uint32_t w; E e[4 / sizeof(E)]; };
+    word_t v[A][A];
 #pragma unroll
     for (int a = 0; a < A; ++a) {
         const int r = M * ti - 1 + a;
@@ -449,19 +462,27 @@ input_transform_nhwc_kernel(const E* __restrict__ x, E* __restrict__ V,
         for (int b = 0; b < A; ++b) {
             const int col = M * tj - 1 + b;
             const E* p = xr + (size_t)(min(max(col, 0), W - 1) >> us) * C;
+            if constexpr (CPT == 2) v[a][b].w = *reinterpret_cast<const uint32_t*>(p);
+            else if constexpr (sizeof(E) == 4) v[a][b].w = *reinterpret_cast<const uint32_t*>(p);
+            else v[a][b].w = *reinterpret_cast<const uint16_t*>(p);
+        }
+    }
+    PreLane pl[CPT];
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) { pl[u] = PreLane{0.f, 0.f, false}; if (PRE) pl[u] = pre_finish(raw[u], c + u, C); }
+    float d[CPT][A][A];
+#pragma unroll
+    for (int a = 0; a < A; ++a)
+#pragma unroll
+        for (int b = 0; b < A; ++b) {
             const uint32_t msk = rmask[a] & cmask[b];
-            union { uint32_t w; E e[4 / sizeof(E)]; } v;
-            if constexpr (CPT == 2) v.w = *reinterpret_cast<const uint32_t*>(p);
-            else if constexpr (sizeof(E) == 4) v.w = *reinterpret_cast<const uint32_t*>(p);
-            else v.w = *reinterpret_cast<const uint16_t*>(p);
-            v.w &= msk;
+            v[a][b].w &= msk;
 #pragma unroll
             for (int u = 0; u < CPT; ++u) {
-                d[u][a][b] = to_f32<E>(v.e[u]);
+                d[u][a][b] = to_f32<E>(v[a][b].e[u]);
                 if (PRE) d[u][a][b] = pre_apply_as<E>(d[u][a][b], pl[u], msk != 0u);
             }
         }
-    }
     float o[CPT][A][A];
 #pragma unroll
     for (int u = 0; u < CPT; ++u) {
@@ -549,10 +570,13 @@ static hipError_t launch_it_cfg(const void* x, void* V, const Geom& g, const Pre
         const long long total = (long long)grid.x * grid.y;
         if (total > 0x3fffffffLL) return hipErrorInvalidValue;
         const int per_xcd = (int)((total + 7) / 8);
-        if (gn) hipLaunchKernelGGL((input_transform_nchw_vec_kernel<M, E, CB, TJ, true>), dim3((unsigned)(per_xcd * 8)), block, 0, s,
-                                    (const E*)x, (E*)V, g.N, g.C, g.H, g.W, g.th, g.tw, g.T, g.Cp, strips, (int)total, per_xcd, po);
-        else     hipLaunchKernelGGL((input_transform_nchw_vec_kernel<M, E, CB, TJ, false>), dim3((unsigned)(per_xcd * 8)), block, 0, s,
-                                    (const E*)x, (E*)V, g.N, g.C, g.H, g.W, g.th, g.tw, g.T, g.Cp, strips, (int)total, per_xcd, po);
+        const auto run = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3((unsigned)(per_xcd * 8)), block, 0, s, (const E*)x, (E*)V, g.N, g.C, g.H, g.W, g.th, g.tw, g.T, g.Cp, strips,
+                               (int)total, per_xcd, po);
+        };
+        if (po.up) { if (gn) run(input_transform_nchw_vec_kernel<M, E, CB, TJ, true, 1>); else run(input_transform_nchw_vec_kernel<M, E, CB, TJ, false, 1>); }
+        else if (gn) run(input_transform_nchw_vec_kernel<M, E, CB, TJ, true, 0>);
+        else run(input_transform_nchw_vec_kernel<M, E, CB, TJ, false, 0>);
     } else {
         const auto run = [&](auto kern) {
             hipLaunchKernelGGL(kern, grid, block, 0, s, (const E*)x, (E*)V, g.N, g.C, g.H, g.W, g.th, g.tw, g.T, g.Cp, strips, po);

@@ -114,6 +114,20 @@ __device__ __forceinline__ PreLane pre_lane(const PreOp& pre, int n, int c, int 
     }
     return l;
 }
+// The same in two halves, so that the loads can be in flight together with those of the pixels (waited for in front of them they cost a kernel a
+// round trip to memory): from a clamped channel, finished where the constants are first used.
+struct PreRaw { float mean, rstd, gamma, beta; };
+__device__ __forceinline__ PreRaw pre_request(const PreOp& pre, int n, int c, int C) {
+    const int cc = c < C ? c : C - 1;
+    const float* st = pre.stats + ((size_t)n * pre.groups + cc / pre.cpg) * 2;
+    return PreRaw{st[0], st[1], pre.gamma[cc], pre.beta[cc]};
+}
+__device__ __forceinline__ PreLane pre_finish(const PreRaw& q, int c, int C) {
+    PreLane l; l.on = c < C;
+    const float sc = q.gamma * q.rstd, sh = q.beta - q.mean * sc;
+    l.sc = l.on ? sc : 0.f; l.sh = l.on ? sh : 0.f;
+    return l;
+}
 __device__ __forceinline__ float pre_apply(float x, const PreLane& l, bool in_image) {
     if (!(l.on && in_image)) return 0.f;
     const float v = fmaf(x, l.sc, l.sh);
