@@ -430,10 +430,13 @@ static hipError_t launch_tile_t(const E* xh, const E* Wr, const float* bias, E* 
     }
 }
 
-// Lane offsets are 32-bit and a descriptor covers 2 GB: x, with a row and a pixel in front of it, and the filter have to fit.
+// Lane offsets are 32-bit and a descriptor covers 2 GB: x, with a row and a pixel in front of it, and the filter have to fit; so has the scalar
+// offset by itself, two rows, two pixels and the channels of one, which is more than x where that is a single row: beyond the range it
+// would not be sure that lanes at kOutside fail the test against what is left of it.
 bool igemm_tile_fits(const ConvGeom& g) {
-    const unsigned long long row = (unsigned long long)g.Cp * 2u, lim = kRange;
-    return ((unsigned long long)g.N * g.Hs * g.Ws + g.Ws + 1u) <= lim / row && (unsigned long long)g.R * g.R * g.K <= lim / row;
+    const unsigned long long row = (unsigned long long)g.Cp * 2u, lim = kRange, ws = (unsigned long long)g.Ws;
+    const unsigned long long operand = (unsigned long long)g.N * g.Hs * ws + ws + 1u, scalar = 2u * ws + 3u;
+    return (operand > scalar ? operand : scalar) <= lim / row && (unsigned long long)g.R * g.R * g.K <= lim / row;
 }
 
 hipError_t launch_igemm_tile(const void* xh, const void* Wr, const float* bias, void* y, float* part, const IgemmTilePlan& plan,

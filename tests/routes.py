@@ -48,6 +48,23 @@ def pre_op(norm=False, up=False, C=1):
     return PreOp(ADDRESS if norm else None, ADDRESS, ADDRESS, 1, C, int(up))
 
 
+def conv_geom(N, C, K, H, W, R=3, st=1, up=0, align=8):
+    Ho, Wo = _out(H, R, st), _out(W, R, st)
+    return ConvGeom(N, C, -(-C // align) * align, H, W, K, R, st, (R - 1) // 2, Ho, Wo, N * Ho * Wo, up, H >> up, W >> up)
+
+
+def tile_fits(*geom, **kw):
+    """Whether the operands of a two-byte direct call lie within the 16x16-tile kernel's offsets."""
+    f = _fn("_ZN4wino15igemm_tile_fitsERKNS_8ConvGeomE", BOOL, ctypes.POINTER(ConvGeom))
+    return f(ctypes.byref(conv_geom(*geom, **kw)))
+
+
+def fp8_rows(N, C, K, H, W, dtype, nsplit=1, **kw):
+    """Whether the 8-bit kernel that fetches the pixels of a filter row once takes a call."""
+    f = _fn("_ZN4wino17igemm_fp8_rows_okERKNS_8ConvGeomEii", BOOL, ctypes.POINTER(ConvGeom), INT, INT)
+    return f(ctypes.byref(conv_geom(N, C, K, H, W, align=16, **kw)), DT[dtype], nsplit)
+
+
 def igemm_tile(N, C, K, H, W, R, st, dtype, nhwc, plain=True):
     """(block id, reduction ranges) of the 16x16-tile kernel: 0 = 64x64, 1 = 64x80, 2 = 128x128; id < 0: the kernels of conv_igemm.hip."""
     f = _fn("_ZN4wino15igemm_tile_planEiiiiiibb", Pair, INT, INT, INT, INT, INT, INT, BOOL, BOOL)

@@ -44,6 +44,31 @@ def test_direct_path_blocks_of_short_reductions():
     assert routes.igemm_tile(8, 63, 799, 249, 7, 1, 1, "bf16", True)[0] < 0 and routes.igemm_tile(8, 63, 3, 249, 7, 1, 1, "bf16", True)[0] >= 0
 
 
+# Buffer offsets of the direct kernels: what a lane reads, and the scalar that is added for all lanes, also to the offset 2^31 of a lane that
+# must read zeros, have to stay within the descriptor's 2^31 - 1 bytes.  The widest admitted image of each form, a single row among them.
+@pytest.mark.parametrize("C,e,fits", [(64, 2, "tile"), (192, 2, "tile"), (1280, 2, "tile"), (64, 1, "rows"), (160, 1, "rows")])
+@pytest.mark.parametrize("N,H,up,R", [(1, 1, 0, 3), (1, 2, 0, 3), (2, 1, 0, 3), (3, 5, 0, 3), (1, 2, 1, 3), (1, 1, 0, 1)])
+def test_buffer_offsets_stay_in_range(C, e, fits, N, H, up, R):
+    if fits == "rows" and (up or R == 1):
+        pytest.skip("3x3 at full size only")
+    ok = (lambda W: routes.tile_fits(N, C, 8, H, W, R=R, up=up)) if fits == "tile" else (lambda W: routes.fp8_rows(N, C, 8, H, W, "f16"))
+    lo, hi = 2 ** 15, 2 ** 31 // (N * H)                # admitted, refused; widths that can be read upsampled are even
+    assert ok(lo)
+    while hi - lo > 2:
+        mid = (lo + hi) // 4 * 2
+        lo, hi = (mid, hi) if ok(mid) else (lo, mid)
+    for W in (lo, lo + 1):
+        if not ok(W) or (up and W % 2):
+            continue
+        row, stored = C * e, W >> up
+        lanes = (N * (H >> up) * stored + stored + 1) * row
+        scalar = (0 if up or R == 1 else 2 * stored + 2) * row + row - 128 * (e == 2)
+        if fits == "rows":                              # a block of up to 256 pixels and its neighbours beyond the last one
+            lanes, scalar = lanes + 258 * row, scalar + 256 * row
+        assert lanes <= 2 ** 31 - 1 and scalar <= 2 ** 31 - 1, (W, lanes, scalar)
+    assert lo * N * H * C * e > 2 ** 29                  # and no more is given away than a single row needs
+
+
 # one-kernel F(2x2): taken (True) or left to the paths that store V
 @pytest.mark.parametrize("N,C,K,H,W,nhwc,fused,norm,up,taken", [
     # element by element: rows of no whole 16-byte pieces, and upsampling
