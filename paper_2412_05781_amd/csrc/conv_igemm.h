@@ -43,7 +43,8 @@ struct IgemmPost {
 // igemm_block_plan: its choice of block and of the number of reduction ranges, at most most_sp; id < 0: left to the kernels of conv_igemm.hip.
 // igemm_tile_plan: the number of ranges that a workspace is sized for (plain: nothing but a bias is added to the sums).
 struct IgemmTilePlan { int id, split; };
-IgemmTilePlan igemm_block_plan(int T, int K, int Cp, int R, int dt, bool nhwc, int most_sp);
+IgemmTilePlan igemm_block_plan(int T, int HoWo, int K, int Cp, int R, int dt, bool nhwc, int most_sp);
+double igemm_block_time(int id, int T, int HoWo, int K, int Cp, int R, bool nhwc, int split);      // the times it compares
 bool igemm_tile_fits(const ConvGeom& g);                               // the operands are small enough for the kernel's offsets
 int igemm_split_rule(int T, int K, int Cp, int R, int dt);             // ranges where the 16x16-tile kernel does not apply (conv_igemm.hip)
 IgemmTilePlan igemm_tile_plan(int T, int HoWo, int K, int Cp, int R, int dt, bool nhwc, bool plain);

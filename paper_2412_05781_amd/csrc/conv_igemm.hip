@@ -533,7 +533,7 @@ static hipError_t igemm_conv_t(const void* x, const void* Wr, const float* bias,
     }
     // the workspace holds the partial sums of the larger of the two layouts' numbers of ranges
     const int other = igemm_split(g.T, g.Ho * g.Wo, g.K, g.Cp, g.R, dt, !nhwc);
-    const IgemmTilePlan plan = igemm_block_plan(g.T, g.K, g.Cp, g.R, dt, nhwc, nsplit > other ? nsplit : other);
+    const IgemmTilePlan plan = igemm_block_plan(g.T, g.Ho * g.Wo, g.K, g.Cp, g.R, dt, nhwc, nsplit > other ? nsplit : other);
     if (plan.id >= 0 && igemm_tile_fits(g)) {
         const hipError_t e = launch_igemm_tile(xh, Wr, bias, y, part, plan, g, post, dt, nhwc, s);
         return e == hipSuccess && plan.split > 1 ? launch_igemm_reduce<E>(part, bias, (E*)y, plan.split, g, post, nhwc, s) : e;

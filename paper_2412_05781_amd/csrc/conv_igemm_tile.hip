@@ -325,49 +325,75 @@ static hipError_t launch_tile_cfg(const E* xh, const E* Wr, const float* bias, E
     return hipGetLastError();
 }
 
-// Blocks on offer, pixels x output channels, of eight waves (but for a sixth, see below), with the time of a reduction stage: `alone` where a compute unit holds one
-// workgroup, `each` per workgroup where it holds several; and `first`, `more`: start and stores of the first workgroup of a unit, beyond
-// those of a launch, and of each further one (us, fitted together to 530 calls, 5900 timings, of 1x1, stride 2 and 3x3 layers; the
-// choice by them is within 0.5 % of the best of the five on average).  The 128x96 block with three slots fills a unit by itself: it is for calls of one
+// Blocks on offer, pixels x output channels, of eight waves (but for 64x32 and 64x80, of four), and the two of conv_igemm.hip that are compared with
+// them where outputs are stored one by one, with the time of a reduction stage: `alone` where a compute unit holds one workgroup, `each` per
+// workgroup where it holds several; `first`, `more`: start and stores of the first workgroup of a unit, beyond those of a launch, and of each further
+// one; and what 4096 outputs cost beyond that where they are no 8-byte pieces of y: single elements of a channel-last y, pairs and single
+// elements of an NCHW y (us, fitted together to 2800 calls with up to eight blocks and ten numbers of ranges each, 31000 timings: 1x1, stride 2 and 3x3, 1 to 280
+// stages, 8 to 1400 output channels, 40 to 1.5 million pixels, both layouts.  Every figure is a time, so a call's time grows with its pixels; it is within 12 % of the
+// measured one, and the choice within 0.5 % of the best on average).  The 128x96 block with three slots fills a unit by itself: it is for calls of one
 // round, where two slots leave the transfers waiting.
-struct TileShape { int bp, bk; double alone, each, first, more; };
-static const TileShape kTiles[5] = {{64, 64, 0.20, 0.179, 0.10, 0.43}, {128, 64, 0., 0.27, 0.67, 0.26}, {128, 96, 0.51, 0.352, 0.78, 0.80},
-                                    {128, 96, 0., 0.349, 1.37, 3.13}, {128, 128, 0., 0.487, 1.58, -0.95}};
+struct TileShape { int bp, bk; double alone, each, first, more, elem, pair, planes; };
+constexpr int kTileBlocks = 7;
+static const TileShape kTiles[kTileBlocks + 2] = {
+    {64, 64, 0.15, 0.212, 0.32, 1.22, 1.10, 0.51, 0.53}, {128, 64, 0.20, 0.294, 1.45, 1.39, 1.35, 0.73, 0.82},
+    {128, 96, 0.534, 0.414, 1.73, 1.92, 1.45, 0.69, 0.89}, {128, 96, 0.30, 0.417, 1.99, 5.56, 1.56, 0.73, 0.91},
+    {128, 128, 0.30, 0.504, 3.77, 1.85, 1.45, 0.73, 0.79}, {64, 32, 0.181, 0.145, 0.01, 0.62, 2.10, 0.83, 0.72},
+    {64, 80, 0.265, 0.28, 1.53, 2.06, 1.52, 0.85, 1.34},
+    {64, 64, 0.419, 0.122, 3.28, 0.02, 0.02, 0., 0.}, {128, 128, 0.30, 0.48, 5.02, 1.55, 1.17, 0., 0.}};
 
-// The block and the number of reduction ranges with the least time by these figures; a split reduction adds a second kernel and the traffic of
-// the partial sums (3x3 128 channels at 17x13, N=2, NCHW: 15.5 us whole, 13.0 in two ranges).  Measured, channel-last, us, against the kernels of
-// conv_igemm.hip: 1x1 256 -> 256 at 414x300 (N=2) 91 / 99, 64 -> 1280 at 200x112 25.5 / 33.4, 3x3 320 -> 768 at 104x544 255 / 294, stride 2
-// 64 -> 768 at 465x168 (N=2) 52 / 64.  The 256x256 block there is nowhere more than 2 % ahead on calls of two-byte types with whole stages (60 calls of at
-// least one round of such blocks), nor are its other blocks on NCHW images with a number of pixels that is no multiple of four (100 calls).
-IgemmTilePlan igemm_block_plan(int T, int K, int Cp, int R, int dt, bool nhwc, int most_sp) {
+// Time of a call by these figures, less what all its blocks share; split: reduction ranges, whose second kernel and partial sums it includes.
+double igemm_block_time(int id, int T, int HoWo, int K, int Cp, int R, bool nhwc, int split) {
+    const TileShape& sh = kTiles[id];
+    const int stages = R * R * (Cp / 64);
+    const long long blocks = (long long)((T + sh.bp - 1) / sh.bp) * ((K + sh.bk - 1) / sh.bk) * split;
+    const double share = (double)blocks / 256.0, most = (double)((blocks + 255) / 256);                 // workgroups per compute unit
+    double n = share < 2.0 ? 0.51 * share + 0.49 * most : most;
+    if (n < 1.0) n = 1.0;
+    const double stage = n * sh.each > sh.alone ? n * sh.each : sh.alone;
+    double c = (double)((stages + split - 1) / split) * stage + sh.first + sh.more * (n - 1.0);
+    if (split > 1) return c + 2.31 + (double)split * K * T * 8.0 * 0.295e-6;
+    const double store = nhwc ? (K % 4 == 0 ? 0. : sh.elem) : (HoWo % 4 == 0 ? 0. : HoWo % 2 == 0 ? sh.pair : sh.planes);
+    return c + n * store * (sh.bp * sh.bk / 4096.0);
+}
+
+// The block and the number of reduction ranges with the least time; a split reduction adds a second kernel and the traffic of the partial
+// sums (3x3 128 channels at 17x13, N=2, NCHW: 15.5 us whole, 13.0 in two ranges).  The 64x32 block is for up to 64 channels, 64x80 for more and up to 400, where
+// it was measured: it is ahead on long reductions in one round (us, the other blocks / 64x80: 832 -> 68 at 311x185, stride 2, 47.7 / 39.3, 1088 -> 80 at
+// 183x319, stride 2, NCHW 176 / 159, 1600 -> 144 at 57x55 (N=2) 67.2 / 62.5).  Short reductions on large images, which a block with empty columns used to
+// take (us, channel-last, 128x128 / now): 1x1 64 -> 64 at 999x1014 86.1 / 68.9, 64 -> 48 at 400x453 14.8 / 12.2, 128 -> 56 at 645x659 43.3 / 37.8, 64 -> 160 at
+// 568x625 (N=2) 128 / 112, 192 -> 192 at 121x177 (N=2) NCHW 43.4 / 37.6.  Against the kernels of conv_igemm.hip: 1x1 256 -> 256 at 414x300 (N=2) 91 / 99, 64 ->
+// 1280 at 200x112 25.5 / 33.4, 3x3 320 -> 768 at 104x544 255 / 294, stride 2 64 -> 768 at 465x168 (N=2) 52 / 64.
+IgemmTilePlan igemm_block_plan(int T, int HoWo, int K, int Cp, int R, int dt, bool nhwc, int most_sp) {
     IgemmTilePlan best{-1, 1};
     if (!(dt == DT_F16 || dt == DT_BF16) || Cp % 64 != 0) return best;
     const int stages = R * R * (Cp / 64);
+    const auto blocks = [&](int bp, int bk) { return (long long)((T + bp - 1) / bp) * ((K + bk - 1) / bk); };
+    // 1x1, NCHW, images that are no multiple of four pixels, full rounds of that file's 256x256 block: its 32x32 tiles store runs of 64 bytes here,
+    // sixteen lanes of this kernel 32 (us, 128x128 here / 256x256 there: odd 640 -> 512 at 415x473 525 / 434, 64 -> 512 at 343x473 135 / 119, 512 -> 512 at
+    // 305x199 127 / 123; pairs 64 -> 256 at 829x778 308 / 274, 320 -> 256 at 578x515 335 / 312, 128 -> 768 at 353x358 162 / 163; but less than one and a half rounds, pairs
+    // less than three and a half, or the last one short: 384 -> 768 at 157x189 64 / 72, 640 -> 512 at 233x302 163 / 181; 3x3 128 -> 768 at 221x333 189 / 218)
+    if (!nhwc && R == 1 && HoWo % 4 != 0 && K % 256 == 0) {
+        const double share = (double)blocks(256, 256) / 256.0;
+        if (share >= (HoWo % 2 != 0 ? 1.5 : 3.5) && share >= 0.7 * (double)((blocks(256, 256) + 255) / 256)) return best;
+    }
     double cost = 1e300;
-    for (int id = 0; id < 5; ++id) {
-        const TileShape& sh = kTiles[id];
-        const long long blocks = (long long)((T + sh.bp - 1) / sh.bp) * ((K + sh.bk - 1) / sh.bk);
+    for (int id = 0; id < kTileBlocks; ++id) {
+        if ((id == 5 && K > 64) || (id == 6 && (K <= 64 || K > 400))) continue;
         for (int sp = 1; sp <= most_sp && (sp == 1 || sp * 8 <= stages); ++sp) {
-            const double share = (double)(blocks * sp) / 256.0;            // workgroups per compute unit
-            const double most = (double)((blocks * sp + 255) / 256);
-            double n = share < 2.0 ? 0.35 * share + 0.65 * most : most;
-            if (n < 1.0) n = 1.0;
-            const double stage = n * sh.each > sh.alone ? n * sh.each : sh.alone;
-            double c = (double)((stages + sp - 1) / sp) * stage + sh.first + sh.more * (n - 1.0);
-            if (sp > 1) c += 2.15 + (double)sp * K * T * 8.0 * 0.236e-6;
+            const double c = igemm_block_time(id, T, HoWo, K, Cp, R, nhwc, sp);
             if (c < cost) { cost = c; best = {id, sp}; }
         }
     }
-    // One column of blocks.  Up to 32 output channels a block of 64x32 with four waves has no empty half (us, 128x64 / 64x64 / 64x32, channel-last: 256 ->
-    // 24 at 485x194 33.2 / 38.9 / 28.7, 384 -> 18 at 569x166 68.5 / 56.5 / 45.5, 128 -> 32 at 400x400 30.0 / 39.8 / 27.5, 128 -> 16 at 64x64 8.5 / 6.6 /
-    // 6.2); up to 64 a long reduction prefers the smaller block, whose workgroups hide each other's transfers (512 -> 48 at 256x256, 72
-    // stages, 74.8 / 53.1; 256 -> 64 at 300x300, 36 stages, 38.3 / 45.0)
-    if (best.split == 1 && K <= 32) best.id = 5;
-    else if (best.split == 1 && K <= 64 && stages >= 54) best.id = 0;
-    // channel-last, a number of channels that is no multiple of four: outputs are stored one by one, 16 lanes to as many lines, and a short
-    // reduction does not make up for it (1x1, here / there: 64 -> 1194 at 50x23 (N=2) 11.2 / 8.5, 576 -> 873 at 26x41 (N=4) 17.7 / 16.5, 128 -> 1203 at
-    // 78x117 (N=2) 53 / 49; but 64 -> 321 at 13x45 5.7 / 6.1, 832 -> 853 at 30x18 (N=2) 9.8 / 13.1, 3x3 64 -> 1110 at 16x32 (N=4) 15.8 / 17.2)
-    if (nhwc && K % 4 != 0 && K >= 512 && R == 1 && stages <= 9 && best.split == 1) return {-1, 1};
+    // one column of blocks: a long reduction prefers the smaller block, whose three workgroups to a unit hide each other's transfers (us, 128x64 / 64x64,
+    // channel-last: 3x3 384 -> 48 at 315x249, 54 stages, 62.2 / 52.6, 512 -> 64 at 330x354 132 / 118, 704 -> 60 at 252x295 136 / 105; but 320 -> 62, 45
+    // stages, 1.18 times, 256 -> 49, 36 stages, 1.16 times)
+    if (best.id == 1 && best.split == 1 && K <= 64 && stages >= 54) best.id = 0;
+    // 1x1, channel-last, a number of channels that is no multiple of four: outputs are stored one by one, 16 lanes to as many lines, where the
+    // other file's 32x32 tiles make runs of 64 bytes (us, here / there: 64 -> 243 at 544x392 117 / 99, 128 -> 1379 at 22x24 (N=4) 11.4 / 8.6, 256 -> 118 at 187x154
+    // 13.4 / 11.5, 640 -> 319 at 274x190 (N=4) 247 / 241; but 64 -> 130 at 159x192 14.0 / 16.2, 192 -> 306 21.1 / 31.1, 64 -> 126 at 5313 pixels 5.2 / 6.0)
+    if (nhwc && R == 1 && K % 4 != 0 && K > 64 && best.split == 1 &&
+        igemm_block_time(kTileBlocks + (blocks(128, 128) >= 256 ? 1 : 0), T, HoWo, K, Cp, R, nhwc, 1) < cost) return {-1, 1};
     return best;
 }
 
@@ -426,6 +452,7 @@ static hipError_t launch_tile_t(const E* xh, const E* Wr, const float* bias, E* 
         case 3: return launch_tile_cfg<E, 128, 96, 4, 2, 3, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
         case 4: return launch_tile_cfg<E, 128, 128, 4, 2, 2, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
         case 5: return launch_tile_cfg<E, 64, 32, 2, 2, 4, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
+        case 6: return launch_tile_cfg<E, 64, 80, 4, 1, 4, PIX_A>(xh, Wr, bias, y, part, plan.split, g, post, planes, s);
         default: return hipErrorInvalidValue;
     }
 }

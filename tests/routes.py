@@ -59,6 +59,32 @@ def tile_fits(*geom, **kw):
     return f(ctypes.byref(conv_geom(*geom, **kw)))
 
 
+def igemm_split(N, C, K, H, W, R, st, dtype, nhwc):
+    """Reduction ranges that the workspace of a direct call is sized for, in this layout."""
+    f = _fn("_ZN4wino11igemm_splitEiiiiiib", INT, INT, INT, INT, INT, INT, INT, BOOL)
+    pixels = _out(H, R, st) * _out(W, R, st)
+    return f(N * pixels, pixels, K, -(-C // 8) * 8, R, DT[dtype], nhwc)
+
+
+def block_plan(N, C, K, H, W, R, st, dtype, nhwc):
+    """(block, reduction ranges) of a direct call on the 16x16-tile kernel: 0 = 64x64, 1 = 128x64, 2 and 3 = 128x96 with two and three slots, 4 = 128x128,
+    5 = 64x32, 6 = 64x80 (pixels x output channels); block < 0: the kernels of conv_igemm.hip."""
+    f = _fn("_ZN4wino16igemm_block_planEiiiiiibi", Pair, INT, INT, INT, INT, INT, INT, BOOL, INT)
+    pixels = _out(H, R, st) * _out(W, R, st)
+    most = max(igemm_split(N, C, K, H, W, R, st, dtype, layout) for layout in (False, True))
+    p = f(N * pixels, pixels, K, -(-C // 8) * 8, R, DT[dtype], nhwc, most)
+    return p.a, p.b
+
+
+BLOCKS = [(64, 64), (128, 64), (128, 96), (128, 96), (128, 128), (64, 32), (64, 80)]
+
+
+def block_time(block, pixels, pixels_per_image, K, C, R, nhwc, ranges=1):
+    """Time in us by which block_plan compares its choices."""
+    f = _fn("_ZN4wino16igemm_block_timeEiiiiiibi", ctypes.c_double, INT, INT, INT, INT, INT, INT, BOOL, INT)
+    return f(block, pixels, pixels_per_image, K, C, R, nhwc, ranges)
+
+
 def fp8_rows(N, C, K, H, W, dtype, nsplit=1, **kw):
     """Whether the 8-bit kernel that fetches the pixels of a filter row once takes a call."""
     f = _fn("_ZN4wino17igemm_fp8_rows_okERKNS_8ConvGeomEii", BOOL, ctypes.POINTER(ConvGeom), INT, INT)

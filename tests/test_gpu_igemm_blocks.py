@@ -1,5 +1,4 @@
 """The blocks of the 16x16-tile direct kernel at the edges of their range, against the fp64 oracle, element by element."""
-import ctypes
 import os
 import sys
 
@@ -19,22 +18,13 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def block_plan(N, C, K, H, W, R, st, dtype, nhwc):
-    """(block, reduction ranges) of a call: 0 = 64x64, 1 = 128x64, 2 and 3 = 128x96 with two and three slots, 4 = 128x128, 5 = 64x32."""
-    split = routes._fn("_ZN4wino11igemm_splitEiiiiiib", ctypes.c_int, *[ctypes.c_int] * 6, ctypes.c_bool)
-    plan = routes._fn("_ZN4wino16igemm_block_planEiiiiibi", routes.Pair, *[ctypes.c_int] * 5, ctypes.c_bool, ctypes.c_int)
-    pixels, Cp = routes._out(H, R, st) * routes._out(W, R, st), -(-C // 8) * 8
-    most = max(split(N * pixels, pixels, K, Cp, R, routes.DT[dtype], layout) for layout in (False, True))
-    p = plan(N * pixels, K, Cp, R, routes.DT[dtype], nhwc, most)
-    return p.a, p.b
-
-
 # one stage and several (fewer than the ring has slots, and more), tails in pixels and channels, images of one pixel, row and column (taps
 # outside on both sides), channels and pixels that are no multiple of four, split reductions
-CASES = [((1, 64, 16, 1, 1), 3, 1, 5), ((1, 64, 8, 1, 7), 3, 2, 5), ((1, 128, 24, 130, 127), 3, 1, 5), ((2, 192, 32, 33, 20), 1, 1, 5), ((1, 384, 64, 131, 130), 3, 1, 0), ((1, 128, 70, 9, 1), 3, 1, 0), ((2, 192, 33, 7, 9), 1, 2, 0), ((1, 1280, 72, 9, 6), 3, 2, 0),
-         ((2, 192, 320, 64, 63), 1, 1, 1), ((1, 64, 190, 130, 127), 3, 1, 1), ((1, 128, 130, 190, 131), 3, 2, 1),
+CASES = [((1, 64, 16, 1, 1), 3, 1, 5), ((1, 64, 8, 1, 7), 3, 2, 5), ((1, 128, 24, 130, 127), 3, 1, 5), ((2, 192, 32, 33, 20), 1, 1, 5), ((1, 384, 64, 131, 130), 3, 1, 0), ((1, 128, 70, 9, 1), 3, 1, 0), ((2, 192, 33, 7, 9), 1, 2, 5), ((1, 1280, 40, 9, 6), 3, 2, 5), ((2, 192, 70, 7, 9), 1, 2, 0), ((1, 1280, 72, 9, 6), 3, 2, 0),
+         ((2, 128, 192, 97, 95), 1, 1, 1), ((1, 192, 64, 300, 299), 1, 1, 1), ((1, 64, 190, 130, 127), 3, 1, 1), ((1, 704, 144, 57, 54), 3, 1, 1), ((2, 192, 320, 64, 63), 1, 1, 3),
          ((2, 64, 96, 128, 128), 1, 1, 2), ((1, 128, 500, 70, 121), 3, 1, 2), ((2, 64, 264, 65, 63), 3, 1, 3), ((1, 64, 130, 257, 254), 3, 2, 3),
-         ((2, 64, 240, 128, 126), 1, 1, 4), ((2, 192, 330, 128, 126), 3, 1, 4)]
+         ((2, 64, 240, 128, 126), 1, 1, 4), ((2, 192, 330, 128, 126), 3, 1, 4),
+         ((2, 64, 66, 181, 179), 3, 2, 6), ((1, 128, 130, 190, 131), 3, 2, 6), ((1, 832, 68, 95, 61), 3, 1, 6)]
 
 
 def _check(y, ref, layout, dtype):
@@ -61,7 +51,7 @@ def _np(t):
 @pytest.mark.parametrize("shape,R,stride,block", CASES)
 def test_block(shape, R, stride, block, layout, dtype):
     N, C, K, H, W = shape
-    assert block_plan(*shape, R, stride, dtype, layout == B.WINO_NHWC)[0] == block
+    assert routes.block_plan(*shape, R, stride, dtype, layout == B.WINO_NHWC)[0] == block
     x, w, b = _inputs(*shape, R, dtype, 9100 + sum(shape))
     ref = oracle.conv2d_general(_np(x), _np(w), _np(b), stride)
     xd = (x.permute(0, 2, 3, 1).contiguous() if layout == B.WINO_NHWC else x).to(DEV)

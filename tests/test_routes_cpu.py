@@ -44,6 +44,41 @@ def test_direct_path_blocks_of_short_reductions():
     assert routes.igemm_tile(8, 63, 799, 249, 7, 1, 1, "bf16", True)[0] < 0 and routes.igemm_tile(8, 63, 3, 249, 7, 1, 1, "bf16", True)[0] >= 0
 
 
+# Times by which the direct path's blocks are compared: times, so positive, and longer for more pixels, more channels and more stages; a block of which
+# half the columns are empty is not credited for them.
+@pytest.mark.parametrize("nhwc", [False, True])
+@pytest.mark.parametrize("C,R", [(64, 1), (128, 1), (192, 1), (640, 1), (64, 3), (512, 3)])
+@pytest.mark.parametrize("K", [16, 40, 64, 130, 192, 512, 999])
+def test_block_times_are_times(K, C, R, nhwc):
+    pixels = [64, 1000, 5000, 2 ** 14, 40000, 2 ** 16, 2 ** 18, 2 ** 20, 2 ** 24]
+    for block in range(len(routes.BLOCKS)):
+        t = [routes.block_time(block, T, T, K, C, R, nhwc) for T in pixels]
+        assert t[0] > 0 and all(a <= b for a, b in zip(t, t[1:])), (block, t)
+        assert t[-1] > 40 * t[5] and routes.block_time(block, 2 ** 18, 2 ** 18, 3 * K, C, R, nhwc) >= t[6]
+        assert routes.block_time(block, 2 ** 18, 2 ** 18, K, C + 64, R, nhwc) > t[6]
+        assert all(routes.block_time(block, 256, 256, K, C, R, nhwc, ranges) > 0 for ranges in (2, 16))
+
+
+# ... and the block itself, 1x1 on large images: none with half of its columns empty, and 96 columns where they fit
+@pytest.mark.parametrize("H,W", [(512, 512), (1024, 1024), (999, 1014), (400, 453)])
+@pytest.mark.parametrize("C", [64, 128, 192])
+@pytest.mark.parametrize("K", [33, 40, 48, 56, 64])
+def test_direct_path_blocks_of_few_columns(K, C, H, W):
+    for nhwc in (False, True):
+        block, ranges = routes.block_plan(1, C, K, H, W, 1, 1, "f16", nhwc)
+        assert routes.BLOCKS[block][1] == 64 and ranges == 1, (block, nhwc)
+
+
+def test_direct_path_blocks_that_fit():
+    assert all(routes.block_plan(1, C, 192, 512, 512, 1, 1, "f16", nhwc)[0] == 2 for C in (64, 128) for nhwc in (False, True))
+    assert routes.block_plan(2, 64, 160, 568, 625, 1, 1, "f16", True)[0] == 2 and routes.block_plan(1, 832, 68, 311, 185, 3, 2, "f16", True) == (6, 1)
+    # elements of a channel-last y, and NCHW images of an odd number of pixels with full rounds: conv_igemm.hip; without, here
+    for N, C, K, H, W, nhwc, here in [(1, 64, 243, 544, 392, True, False), (4, 128, 1379, 22, 24, True, False), (1, 256, 118, 187, 154, True, False), (1, 64, 130, 159, 192, True, True),
+                                      (1, 64, 126, 69, 77, True, True), (1, 64, 244, 544, 392, True, True), (1, 640, 512, 415, 473, False, False), (1, 64, 256, 829, 778, False, False),
+                                      (1, 384, 768, 157, 189, False, True), (1, 640, 512, 233, 302, False, True), (1, 640, 512, 416, 473, False, True)]:
+        assert (routes.block_plan(N, C, K, H, W, 1, 1, "bf16", nhwc)[0] >= 0) == here, (C, K)
+
+
 # Buffer offsets of the direct kernels: what a lane reads, and the scalar that is added for all lanes, also to the offset 2^31 of a lane that
 # must read zeros, have to stay within the descriptor's 2^31 - 1 bytes.  The widest admitted image of each form, a single row among them.
 @pytest.mark.parametrize("C,e,fits", [(64, 2, "tile"), (192, 2, "tile"), (1280, 2, "tile"), (64, 1, "rows"), (160, 1, "rows")])
