@@ -115,8 +115,9 @@ template <bool PIX_A, typename E> inline int igemm_vec_ok(const ConvGeom& g, con
 
 // The kernel for 8-bit operands (conv_igemm_fp8.hip), two-byte y: whether it applies, and the launch.
 bool igemm_fp8_tile_ok(const ConvGeom& g, int dt, bool nhwc, int nsplit);
-// ... and the one for 3x3, stride 1, which is asked first.
-bool igemm_fp8_rows_ok(const ConvGeom& g, int dt, int nsplit);
+// ... and the one for 3x3, stride 1, which is asked first, and whether its NCHW blocks are 256x256.
+bool igemm_fp8_rows_ok(const ConvGeom& g, int dt, bool nhwc, int nsplit);
+bool igemm_fp8_rows_wide(const ConvGeom& g);
 hipError_t launch_igemm_fp8_rows(const void* xq, const void* Wq, const float* bias, void* y, const ConvGeom& g, const IgemmPost& post, int dt,
                                  bool nhwc, hipStream_t s);
 hipError_t launch_igemm_fp8_tile(const void* xq, const void* Wq, const float* bias, void* y, const ConvGeom& g, const IgemmPost& post, int dt,

@@ -789,7 +789,7 @@ hipError_t launch_igemm_fp8_conv2d(const void* x, const void* Wq, const float* b
         const int nsplit = igemm_split(g.T, g.Ho * g.Wo, g.K, g.Cp, g.R, -1, nhwc);
         float* part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + xq_bytes);
         const fp8_t* xq = static_cast<const fp8_t*>(workspace);
-        if (igemm_fp8_rows_ok(g, dt, nsplit)) return launch_igemm_fp8_rows(xq, Wq, bias, y, g, post, dt, nhwc, s);
+        if (igemm_fp8_rows_ok(g, dt, nhwc, nsplit)) return launch_igemm_fp8_rows(xq, Wq, bias, y, g, post, dt, nhwc, s);
         if (igemm_fp8_tile_ok(g, dt, nhwc, nsplit)) return launch_igemm_fp8_tile(xq, Wq, bias, y, g, post, dt, nhwc, s);
         return nhwc ? launch_igemm_t<fp8_t, EO, true>(xq, (const fp8_t*)Wq, bias, (EO*)y, part, nsplit, g, post, s)
                     : launch_igemm_t<fp8_t, EO, false>(xq, (const fp8_t*)Wq, bias, (EO*)y, part, nsplit, g, post, s);

@@ -538,17 +538,43 @@ static hipError_t launch_fp8_cfg(const uint8_t* xq, const uint8_t* Wq, const flo
 // 512x512 86 / 113).
 static bool fp8_wide(const ConvGeom& g) { return g.K % 256 == 0 && (long long)((g.T + 255) / 256) * (g.K / 256) >= 256; }
 
-// 3x3, stride 1, not upsampled, and blocks of 128x128 for most compute units.  Lane offsets are 32-bit and a descriptor covers 2 GB: x, with a row
-// and a pixel in front of it, and the filter have to fit.  Whole calls, us, other kernels / here: 128 channels at 512x512 86.9 / 75.2 (NCHW), 99.2 /
-// 88.1 (channel-last), 320 -> 192 at 200x312 71.2 / 56.3 and 79.9 / 69.3, 448 -> 256 at 512x400 311 / 275 and 345 / 292, 192 -> 256 at 160x480
-// channel-last 99 / 73, 512 -> 320 at 120x72 channel-last (204 blocks) 36.9 / 35.2; but 555 -> 126 at 155x58, N=2 (141) 51.3 / 54.8, 172 -> 75
-// at 125x169 (166) 27.8 / 32.1.  512 -> 256 at 640x192, NCHW, loses 2 % (174 / 178).  Products of random bytes make the card lower its clock: with
-// zeros for x 256 channels at 512x512 take 178 us instead of 201.
-bool igemm_fp8_rows_ok(const ConvGeom& g, int dt, int nsplit) {
+// How full the rounds of 256x256 blocks are, one to a compute unit, in 128x128 quarters that are not empty; and the share from which on NCHW images of
+// an even number of pixels take them.  Such a round takes as long as 15 / 16 of that of four times as many small blocks, and less in long
+// reductions with several columns of blocks or with a partial last chunk of channels (us, 128x128 / 256x256 and how full: 704 -> 512 at 349x144 197 / 185, 0.77,
+// 704 -> 768 at 316x128 217 / 190, 0.93, 448 -> 768 at 83x672 204 / 191, 0.85, 448 -> 256 at 224x520 165 / 151, 0.89; but 448 -> 512 at 122x400 122 / 130,
+// 0.75, 358 -> 512 at 386x199 226 / 252, 0.78).
+static double fp8_round_fill(const ConvGeom& g) {
+    const long long small = (long long)((g.T + 127) / 128) * ((g.K + 127) / 128), wide = (long long)((g.T + 255) / 256) * ((g.K + 255) / 256);
+    return (double)small / (1024.0 * (double)((wide + 255) / 256));
+}
+static bool fp8_round_full(const ConvGeom& g) {
+    const bool early = fp8_wide(g) && g.Cp > 256 && (g.K >= 512 || g.Cp % 128 != 0);
+    return fp8_round_fill(g) >= (!early ? 0.9375 : g.Cp > 512 ? 0.75 : 0.84);
+}
+
+// 3x3, stride 1, not upsampled, and blocks of 128x128 for most compute units, or for all of them where outputs leave one by one: channels of a
+// channel-last y, or fewer than 96 of an NCHW image of an odd number of pixels.  Lane offsets are 32-bit and a descriptor covers 2 GB: x, with a
+// row and a pixel in front of it, and the filter have to fit.  Whole calls, us, other kernels / here: 128 channels at 512x512 86.9 / 75.2 (NCHW), 99.2 /
+// 88.1 (channel-last), 320 -> 192 at 200x312 71.2 / 56.3 and 79.9 / 69.3, 192 -> 256 at 160x480 channel-last 99 / 73, 512 -> 320 at 120x72 channel-last
+// (204 blocks) 36.9 / 35.2; but 555 -> 126 at 155x58, N=2 (141) 51.3 / 54.8, 172 -> 75 at 125x169 (166) 27.8 / 32.1.  Channel-last, one by one: 256 -> 58 at
+// 253x104 (206) 23.3 / 32.4, 47 -> 150 at 76x205 (244) 20.4 / 26.7, 192 -> 222 at 220x60 (208) 29.1 / 33.5, but 192 -> 93 at 82x466 (299) 45.0 /
+// 41.2, 320 -> 219 at 182x102 (292) 53.1 / 48.6; NCHW 62 -> 64 at 149x87, N=2 (203) 23.7 / 25.5, but 273 -> 253 at 71x181 (202) 41.3 / 38.0.
+// Left to the 256x256 blocks of the kernel above: NCHW, full rounds of them, two columns or more, three whole chunks of channels or more, where the
+// pixels of the taps are a small part of what it waits for (us, there / 256x256 here / 128x128 here: 512 -> 512 at 256x256 155 / 157 / 160, at 192x320
+// 145 / 146 / 153, 1024 -> 512 at 256x256 278 / 285 / 295, 768 -> 512 at 141x232 112 / 115 / 121, 640 -> 768 at 156x224 158 / 166 / 163; but with one
+// column 512 -> 256 at 512x512 358 / 357 / 361, 640 -> 256 at 286x352 194 / 191 / 184, with two chunks 256 -> 256 at 512x512 207 / 201 / 197, with a partial
+// chunk 448 -> 768 at 566x72 141 / 133 / 149).  Channel-last, one full round, or two with several columns: those of conv_igemm.hip (256 channels at 256x256
+// 59.4 / 60.8, 512 at 192x320 163 / 167, at 256x256 169 / 171; but 640 -> 256 at 512x256 242 / 232, in three rounds 512 at 384x256 248.8 / 248.2).  Over 1196
+// calls of 180 blocks and more: 0.876 times the other kernels' time, four calls 1 to 2 % slower than there.
+bool igemm_fp8_rows_ok(const ConvGeom& g, int dt, bool nhwc, int nsplit) {
     if (!two_byte(dt) || nsplit != 1 || g.R != 3 || g.st != 1 || g.up) return false;
     const unsigned long long lim = kRange / (unsigned long long)g.Cp;
     if ((unsigned long long)g.N * g.H * g.W + g.W + 512u > lim || 9ull * g.K + 512u > lim) return false;
-    return (long long)((g.T + 127) / 128) * ((g.K + 127) / 128) >= 200;
+    const long long blocks = (long long)((g.T + 127) / 128) * ((g.K + 127) / 128);
+    const bool planes = !nhwc && g.Ho * g.Wo % 2 != 0, whole = g.Cp % 128 == 0;
+    if (blocks < (g.K > 32 && (planes ? g.K <= 96 : nhwc && g.K % 4 != 0) ? 256 : 200)) return false;
+    if (nhwc) return !(whole && g.Cp > 128 && fp8_wide(g) && (long long)((g.T + 255) / 256) * (g.K / 256) <= (g.K >= 512 ? 512 : 256) && fp8_round_fill(g) >= 0.88);
+    return planes || !(whole && g.K >= 512 && g.Cp > 256 && fp8_wide(g) && fp8_round_full(g));
 }
 
 template <typename EO, int BP, int BK, int WP, int WK, bool PIX_A, bool RAGGED>
@@ -572,13 +598,10 @@ static hipError_t launch_rows_cfg(const uint8_t* xq, const uint8_t* Wq, const fl
     return hipGetLastError();
 }
 
-// NCHW: 256x256 instead of 128x128, one workgroup to a unit instead of two, where their rounds are full: such a round takes as long as 15 / 16 of
-// that of four times as many small blocks (us, 128x128 / 256x256: 512 channels at 256x256 159 / 152, 448 -> 192 at 224x576 176 / 158, 320 -> 192 at 200x312 61.3 / 56.3,
-// 256 channels at 512x512 208 / 207; but 448 -> 256 at 512x400 275 / 296, 512 channels at 128x128 44 / 63), with at least two chunks of channels.
-static bool fp8_rows_wide(const ConvGeom& g) {
-    const long long small = (long long)((g.T + 127) / 128) * ((g.K + 127) / 128), wide = (long long)((g.T + 255) / 256) * ((g.K + 255) / 256);
-    return g.Cp > 128 && 15 * 256 * ((wide + 255) / 256) <= 4 * small;
-}
+// NCHW: 256x256 instead of 128x128, one workgroup to a unit instead of two, where their rounds are full (us, 128x128 / 256x256: 448 -> 192 at 224x576 176 / 158,
+// 320 -> 192 at 200x312 61.3 / 56.3, 448 -> 768 at 566x72 149 / 133; but 448 -> 256 at 512x400 275 / 296, 512 channels at 128x128 45 / 65), with at least
+// two chunks of channels.
+bool igemm_fp8_rows_wide(const ConvGeom& g) { return g.Cp > 128 && fp8_round_full(g); }
 
 template <typename EO, int BP, int BK, int WP, int WK, bool PIX_A>
 static hipError_t launch_rows_t(const uint8_t* xq, const uint8_t* Wq, const float* bias, EO* y, const ConvGeom& g, const IgemmPost& post,
@@ -594,7 +617,7 @@ hipError_t launch_igemm_fp8_rows(const void* xq, const void* Wq, const float* bi
         using EO = std::remove_pointer_t<decltype(tag)>;
         const uint8_t *x8 = (const uint8_t*)xq, *w8 = (const uint8_t*)Wq;
         if (nhwc || planes) return launch_rows_t<EO, 128, 128, 2, 2, false>(x8, w8, bias, (EO*)y, g, post, planes, s);
-        return fp8_rows_wide(g) ? launch_rows_t<EO, 256, 256, 4, 2, true>(x8, w8, bias, (EO*)y, g, post, false, s)
+        return igemm_fp8_rows_wide(g) ? launch_rows_t<EO, 256, 256, 4, 2, true>(x8, w8, bias, (EO*)y, g, post, false, s)
                                 : launch_rows_t<EO, 128, 128, 2, 2, true>(x8, w8, bias, (EO*)y, g, post, false, s);
     };
     return dt == DT_F16 ? run(static_cast<__half*>(nullptr)) : run(static_cast<bf16_t*>(nullptr));

@@ -85,10 +85,13 @@ def block_time(block, pixels, pixels_per_image, K, C, R, nhwc, ranges=1):
     return f(block, pixels, pixels_per_image, K, C, R, nhwc, ranges)
 
 
-def fp8_rows(N, C, K, H, W, dtype, nsplit=1, **kw):
-    """Whether the 8-bit kernel that fetches the pixels of a filter row once takes a call."""
-    f = _fn("_ZN4wino17igemm_fp8_rows_okERKNS_8ConvGeomEii", BOOL, ctypes.POINTER(ConvGeom), INT, INT)
-    return f(ctypes.byref(conv_geom(N, C, K, H, W, align=16, **kw)), DT[dtype], nsplit)
+def fp8_rows(N, C, K, H, W, dtype, nhwc, nsplit=1, **kw):
+    """Whether the 8-bit kernel that fetches the pixels of a filter row once takes a call, and whether its NCHW blocks are 256x256 (128x128 otherwise)."""
+    g = conv_geom(N, C, K, H, W, align=16, **kw)
+    f = _fn("_ZN4wino17igemm_fp8_rows_okERKNS_8ConvGeomEibi", BOOL, ctypes.POINTER(ConvGeom), INT, BOOL, INT)
+    wide = _fn("_ZN4wino19igemm_fp8_rows_wideERKNS_8ConvGeomE", BOOL, ctypes.POINTER(ConvGeom))
+    taken = f(ctypes.byref(g), DT[dtype], nhwc, nsplit)
+    return taken, taken and not nhwc and H * W % 2 == 0 and wide(ctypes.byref(g))
 
 
 def igemm_tile(N, C, K, H, W, R, st, dtype, nhwc, plain=True):

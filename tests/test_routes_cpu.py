@@ -86,7 +86,7 @@ def test_direct_path_blocks_that_fit():
 def test_buffer_offsets_stay_in_range(C, e, fits, N, H, up, R):
     if fits == "rows" and (up or R == 1):
         pytest.skip("3x3 at full size only")
-    ok = (lambda W: routes.tile_fits(N, C, 8, H, W, R=R, up=up)) if fits == "tile" else (lambda W: routes.fp8_rows(N, C, 8, H, W, "f16"))
+    ok = (lambda W: routes.tile_fits(N, C, 8, H, W, R=R, up=up)) if fits == "tile" else (lambda W: routes.fp8_rows(N, C, 8, H, W, "f16", True)[0])
     lo, hi = 2 ** 15, 2 ** 31 // (N * H)                # admitted, refused; widths that can be read upsampled are even
     assert ok(lo)
     while hi - lo > 2:
@@ -148,6 +148,25 @@ def test_fp8_kernel(N, C, K, H, W, R, st, nhwc, taken):
     for dtype in ("f16", "bf16"):
         assert routes.fp8_tile(N, C, K, H, W, R, st, dtype, nhwc) == taken
     assert not routes.fp8_tile(N, C, K, H, W, R, st, "f32", nhwc) and not routes.fp8_tile(N, C, K, H, W, R, st, "f16", nhwc, nsplit=2)
+
+
+# ... 3x3 at stride 1: the kernel that fetches the pixels of a filter row once, with 128x128 ("rows") or 256x256 blocks ("wide"), or the others ("")
+@pytest.mark.parametrize("N,C,K,H,W,nhwc,kernel", [
+    (1, 128, 128, 512, 512, False, "rows"), (1, 128, 128, 512, 512, True, "rows"), (1, 512, 320, 120, 72, True, "rows"), (2, 62, 192, 58, 106, True, ""), (1, 72, 256, 84, 160, True, "rows"), (2, 555, 126, 155, 58, False, ""),
+    # outputs one by one: channels of a channel-last y, an odd number of pixels
+    (1, 256, 58, 253, 104, True, ""), (1, 47, 150, 76, 205, True, ""), (1, 192, 222, 220, 60, True, ""), (1, 192, 93, 300, 128, True, "rows"), (1, 75, 23, 300, 104, True, "rows"),
+    (1, 62, 64, 299, 87, False, ""), (1, 62, 64, 299, 115, False, "rows"), (2, 62, 64, 149, 87, False, ""), (1, 273, 253, 71, 181, False, "rows"),
+    # full rounds of 256x256 blocks
+    (1, 512, 512, 256, 256, False, ""), (1, 512, 512, 192, 320, False, ""), (1, 1024, 512, 256, 256, False, ""), (1, 768, 512, 141, 232, False, ""), (1, 640, 768, 156, 224, False, ""),
+    (1, 512, 256, 512, 512, False, "wide"), (1, 640, 256, 286, 352, False, "rows"), (1, 256, 256, 512, 512, False, "wide"), (1, 448, 768, 566, 72, False, "wide"), (1, 704, 512, 349, 144, False, "wide"),
+    (1, 512, 512, 128, 128, False, "rows"), (1, 512, 512, 320, 320, False, "rows"), (1, 448, 256, 512, 400, False, "rows"), (1, 448, 192, 224, 576, False, "wide"), (1, 512, 512, 257, 255, False, "rows"),
+    (1, 256, 256, 256, 256, True, ""), (1, 512, 512, 256, 256, True, ""), (1, 512, 512, 192, 320, True, ""), (1, 512, 512, 384, 256, True, "rows"), (1, 256, 256, 512, 512, True, "rows"), (1, 320, 512, 256, 256, True, "rows"), (1, 640, 256, 512, 256, True, "rows"), (1, 448, 256, 224, 520, False, "wide")])
+def test_fp8_rows_kernel(N, C, K, H, W, nhwc, kernel):
+    for dtype in ("f16", "bf16"):
+        taken, wide = routes.fp8_rows(N, C, K, H, W, dtype, nhwc)
+        assert ("wide" if wide else "rows" if taken else "") == kernel
+        assert not routes.fp8_rows(N, C, K, H, W, dtype, nhwc, nsplit=2)[0] and not routes.fp8_rows(N, C, K, H, W, dtype, nhwc, st=2)[0]
+    assert not routes.fp8_rows(N, C, K, H, W, "f32", nhwc)[0]
 
 
 # few input channels, fp32 F(4x4): with more than eight channels only from some number of tiles times output channels on
