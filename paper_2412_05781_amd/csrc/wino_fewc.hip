@@ -13,9 +13,10 @@
 // one 16-byte load per row in NCHW, and takes the two border columns from its neighbours' registers; the four waves share the
 // window's rows through LDS, and the filter block comes in as 1 KB transfers.
 // Bound by latency on small images - the chain from load to store, 320 workgroups on 256 units for 4 -> 320 at 64x64 - and by writing y and the
-// number of workgroups that a unit holds (three, by registers) on large ones.  One wave for all 36 positions had 1100 instructions and 72 MFMAs
-// in a row (us, NCHW / channel-last, before -> now: 4 -> 320 at 64x64 10.0 / 11.6 -> 7.6 / 9.6, N=2 at 128x128 29.1 / 42.0 -> 25.9 / 33.4, at 47x91 18.6 /
-// 11.5 -> 11.2 / 9.7, 16 -> 320 at 64x64 13.6 / 17.1 -> 10.5 / 14.1; without the bound on registers, two workgroups to a unit, 32 at N=2, 128x128).
+// number of workgroups that a unit holds on large ones: four, by registers (128, which is why the channels are transformed one after the other) and by LDS;
+// with three, calls of more than three and up to four to a unit took a second round (us: 16 -> 448 at 41x208 19.7 -> 14.7, 4 -> 160 at 66x360 13.0 -> 10.2, 4 -> 560
+// at 282x9, N=2, channel-last 15.5 -> 12.5).  One wave for all 36 positions had 1100 instructions and 72 MFMAs in a row (us, NCHW / channel-last, before -> now: 4 -> 320 at
+// 64x64 9.6 / 11.4 -> 7.3 / 9.3, N=2 at 128x128 27.6 / 40.6 -> 21.4 / 29.3, at 47x91 18.2 / 11.5 -> 10.8 / 9.4, 16 -> 320 at 64x64 13.2 / 16.7 -> 10.0 / 13.6).
 #include "wino_internal.h"
 #include "wino_mma.h"
 #include "wino_transforms.h"
@@ -34,13 +35,14 @@ __device__ __forceinline__ uint32_t from_right(uint32_t edge, uint32_t v) { retu
 
 // NHWC: x and y channel-last.  ROWVEC: x NCHW, not upsampled, rows of whole 16-byte pieces: the four owned columns are one load.
 template <bool NHWC, bool ROWVEC>
-__global__ void __launch_bounds__(256, 3)
+__global__ void __launch_bounds__(256, 4)
 wino_fewc_f4_kernel(const float* __restrict__ x, const float* __restrict__ U, const float* __restrict__ bias, float* __restrict__ y,
                     FewcGeom g, int tiles_t, int vec_ok, int up, PostOp post) {
     // of each wave: the filter block of a chunk, [position][channel][8], and in its place the row sums, [row][b][lane]
     __shared__ __attribute__((aligned(1024))) f32x4_t part[3][2 * 4 * 64];
     __shared__ uint4 xs[2][6][64];                                          // windows, [channel][row][lane]: the four owned columns
     __shared__ uint32_t es[2][6][64];                                       // ... and the border column of the outer lanes
+    static_assert(4 * (sizeof(part) + sizeof(xs) + sizeof(es)) <= 160 * 1024, "four workgroups to a unit");
     const int lane = threadIdx.x & 63, i = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int kb = (int)(blockIdx.x / (unsigned)tiles_t) * 16, tb = (int)(blockIdx.x % (unsigned)tiles_t) * 16;
@@ -126,10 +128,10 @@ wino_fewc_f4_kernel(const float* __restrict__ x, const float* __restrict__ U, co
         load_rows(c0);
         __syncthreads();
         if (wave == 3) continue;
-        float v[2][2][6];                                   // [channel][row xi0 / xi1][nu]
+        // channel by channel: the twelve values of one are gone before those of the next are made (registers for four workgroups to a unit)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            float d[6][6], tmp[2][6];
+            float d[6][6], tmp[2][6], v[2][6];              // v: [row xi0 / xi1][nu]
 #pragma unroll
             for (int a = 0; a < 6; ++a) {
                 const uint4 o = xs[j][a][lane];
@@ -151,15 +153,12 @@ wino_fewc_f4_kernel(const float* __restrict__ x, const float* __restrict__ U, co
                     tmp[1][b] = P - Q;
                 }
             }
-            bt_1d<4>(tmp[0], v[j][0]);
-            bt_1d<4>(tmp[1], v[j][1]);
-        }
-        wait_vmcnt<0>();                                    // the wave's filter has landed (its own transfers: no barrier)
+            bt_1d<4>(tmp[0], v[0]);
+            bt_1d<4>(tmp[1], v[1]);
+            if (j == 0) wait_vmcnt<0>();                    // the wave's filter has landed (its own transfers: no barrier)
 #pragma unroll
-        for (int p = 0; p < 12; ++p) {
-            const float2 u = *reinterpret_cast<const float2*>(uw + p * 128 + i * 8 + q * 2);
-            acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(u.x, v[0][p / 6][p % 6], acc[p], 0, 0, 0);
-            acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(u.y, v[1][p / 6][p % 6], acc[p], 0, 0, 0);
+            for (int p = 0; p < 12; ++p)
+                acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(uw[p * 128 + i * 8 + q * 2 + j], v[p / 6][p % 6], acc[p], 0, 0, 0);
         }
         lds_wait<0>();                                      // every read of the block has returned
     }
@@ -237,7 +236,7 @@ wino_fewc_f4_kernel(const float* __restrict__ x, const float* __restrict__ U, co
 }
 
 // fp32 storage, F(4x4), at most 16 (padded) input channels and no GroupNorm on the way in.  Against the three-kernel chain (us, NCHW / channel-last):
-// 4 -> 320 at 64x64 7.6 / 9.6 against 21.4 / 20.7, N=2 at 128x128 26 / 33 against 61 / 59; 16 -> 320 at 64x64 10.5 / 14.1 against 20.6 / 20.4.
+// 4 -> 320 at 64x64 7.3 / 9.3 against 21.4 / 20.7, N=2 at 128x128 21 / 29 against 61 / 59; 16 -> 320 at 64x64 10.0 / 13.6 against 20.6 / 20.4.
 // Where two chunks of eight channels are left to the chain the line was drawn with one wave to a block, whose serial chain took 12-13 us
 // however small the call was, 20 element by element (that kernel / the chain, NCHW: 16 -> 320 at 16x16 12.2 / 11.1, -> 8 at 64x64 12.5 / 11.6, ->
 // 64 12.3 / 12.4; at 78x43 -> 64 20.7 / 16.7, -> 320 21.8 / 22.8; channel-last with a number of output channels that is no multiple of four,

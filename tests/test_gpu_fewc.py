@@ -27,11 +27,11 @@ def _np(t):
 
 # tile counts around the 16 of a wave, rows of tiles shorter and longer than 16, sizes off the tile edge, channels around
 # the chunk of 8 and the limit of 16 (17 runs the chain), output channels off 16 and off 4; with the layouts that the one-kernel
-# path takes (NCHW, channel-last), the others run the chain
+# path takes (NCHW, channel-last), the others run the chain; the last has four workgroups to a compute unit
 CASES = [((1, 4, 320, 64, 64), (True, True)), ((2, 9, 33, 5, 7), (False, False)), ((1, 1, 1, 1, 1), (True, False)), ((3, 16, 18, 4, 60), (False, False)),
          ((1, 8, 16, 68, 68), (True, True)), ((2, 15, 21, 9, 66), (False, False)), ((1, 17, 16, 8, 64), (False, False)), ((1, 5, 20, 6, 130), (True, True)),
          ((2, 7, 21, 9, 66), (True, False)), ((3, 8, 20, 4, 60), (True, True)), ((1, 6, 4, 3, 2), (True, True)), ((2, 9, 164, 90, 95), (True, True)), ((2, 16, 136, 66, 124), (True, True)),
-         ((2, 15, 277, 70, 131), (True, True)), ((1, 5, 33, 258, 130), (True, True))]
+         ((2, 15, 277, 70, 131), (True, True)), ((1, 5, 33, 258, 130), (True, True)), ((1, 16, 224, 251, 64), (True, True))]
 
 
 @pytest.mark.parametrize("layout", [B.WINO_NCHW, B.WINO_NHWC])
