@@ -358,7 +358,7 @@ double igemm_block_time(int id, int T, int HoWo, int K, int Cp, int R, bool nhwc
 }
 
 // The block and the number of reduction ranges with the least time; a split reduction adds a second kernel and the traffic of the partial
-// sums (3x3 128 channels at 17x13, N=2, NCHW: 15.5 us whole, 13.0 in two ranges).  The 64x32 block is for up to 64 channels, 64x80 for more and up to 400, where
+// sums (stride 2, 1088 -> 23 at 16x17, NCHW: 36.0 us whole, 14.0 in eight ranges).  The 64x32 block is for up to 64 channels, 64x80 for more and up to 400, where
 // it was measured: it is ahead on long reductions in one round (us, the other blocks / 64x80: 832 -> 68 at 311x185, stride 2, 47.7 / 39.3, 1088 -> 80 at
 // 183x319, stride 2, NCHW 176 / 159, 1600 -> 144 at 57x55 (N=2) 67.2 / 62.5).  Short reductions on large images, which a block with empty columns used to
 // take (us, channel-last, 128x128 / now): 1x1 64 -> 64 at 999x1014 86.1 / 68.9, 64 -> 48 at 400x453 14.8 / 12.2, 128 -> 56 at 645x659 43.3 / 37.8, 64 -> 160 at
@@ -369,13 +369,20 @@ IgemmTilePlan igemm_block_plan(int T, int HoWo, int K, int Cp, int R, int dt, bo
     if (!(dt == DT_F16 || dt == DT_BF16) || Cp % 64 != 0) return best;
     const int stages = R * R * (Cp / 64);
     const auto blocks = [&](int bp, int bk) { return (long long)((T + bp - 1) / bp) * ((K + bk - 1) / bk); };
-    // 1x1, NCHW, images that are no multiple of four pixels, full rounds of that file's 256x256 block: its 32x32 tiles store runs of 64 bytes here,
-    // sixteen lanes of this kernel 32 (us, 128x128 here / 256x256 there: odd 640 -> 512 at 415x473 525 / 434, 64 -> 512 at 343x473 135 / 119, 512 -> 512 at
-    // 305x199 127 / 123; pairs 64 -> 256 at 829x778 308 / 274, 320 -> 256 at 578x515 335 / 312, 128 -> 768 at 353x358 162 / 163; but less than one and a half rounds, pairs
-    // less than three and a half, or the last one short: 384 -> 768 at 157x189 64 / 72, 640 -> 512 at 233x302 163 / 181; 3x3 128 -> 768 at 221x333 189 / 218)
-    if (!nhwc && R == 1 && HoWo % 4 != 0 && K % 256 == 0) {
-        const double share = (double)blocks(256, 256) / 256.0;
-        if (share >= (HoWo % 2 != 0 ? 1.5 : 3.5) && share >= 0.7 * (double)((blocks(256, 256) + 255) / 256)) return best;
+    // 1x1, full rounds of that file's 256x256 block, which moves half as much into LDS per product (us, 128x128 here / 256x256 there).  From seven
+    // stages on: channel-last 512 -> 512 at 512x512 252 / 242, 1280 -> 512 at 296x432 245 / 218, 640 -> 256 at 664x456 191 / 181,
+    // 896 -> 256 at 704x160 94.9 / 87.6, 640 -> 1024 at 408x232 214 / 201; NCHW 512 ->
+    // 512 at 512x512 413 / 383, 832 -> 512 at 272x600 375 / 332, 896 -> 1024 at 256x576 574 / 498; but fewer stages (256 -> 256 at 496x592 105 / 118), a
+    // last round that is not full (640 -> 768 at 128x752 155 / 166) and, NCHW, few rounds (512 -> 512 at 256x256 84 / 95, 512 -> 1024 at 256x256 142 / 157; channel-last
+    // 66.8 / 64.9 and 125.6 / 123.3).  NCHW images that are no multiple of four pixels, of any number of stages: its 32x32 tiles store runs of 64
+    // bytes, sixteen lanes of this kernel 32 (odd 640 -> 512 at 415x473 525 / 434, 64 -> 512 at 343x473 135 / 119, 512 -> 512 at 305x199 127 / 123; pairs 64 -> 256 at
+    // 829x778 308 / 274, 320 -> 256 at 578x515 335 / 312, 128 -> 768 at 353x358 162 / 163; but 384 -> 768 at 157x189 64 / 72, 640 -> 512 at 233x302 163 /
+    // 181).  3x3 it loses: 128 -> 768 at 221x333 189 / 218, and 260 calls of whole pieces.
+    if (R == 1 && K % 256 == 0) {
+        const bool ragged = !nhwc && HoWo % 4 != 0, few = K <= 512;
+        const double share = (double)blocks(256, 256) / 256.0, fill = share / (double)((blocks(256, 256) + 255) / 256);
+        const double least = ragged ? (HoWo % 2 != 0 ? 1.5 : 3.5) : nhwc ? 1.5 : few ? 2.5 : 6.5;
+        if (share >= least && (ragged || stages >= 7) && fill >= (ragged ? 0.7 : nhwc && K == 256 ? 0.86 : few ? 0.91 : 0.96)) return best;
     }
     double cost = 1e300;
     for (int id = 0; id < kTileBlocks; ++id) {

@@ -72,10 +72,11 @@ def test_direct_path_blocks_of_few_columns(K, C, H, W):
 def test_direct_path_blocks_that_fit():
     assert all(routes.block_plan(1, C, 192, 512, 512, 1, 1, "f16", nhwc)[0] == 2 for C in (64, 128) for nhwc in (False, True))
     assert routes.block_plan(2, 64, 160, 568, 625, 1, 1, "f16", True)[0] == 2 and routes.block_plan(1, 832, 68, 311, 185, 3, 2, "f16", True) == (6, 1)
-    # elements of a channel-last y, and NCHW images of an odd number of pixels with full rounds: conv_igemm.hip; without, here
+    # elements of a channel-last y, and full rounds of 256x256 blocks in long 1x1 reductions or on NCHW images of an odd number of pixels: conv_igemm.hip; without, here
     for N, C, K, H, W, nhwc, here in [(1, 64, 243, 544, 392, True, False), (4, 128, 1379, 22, 24, True, False), (1, 256, 118, 187, 154, True, False), (1, 64, 130, 159, 192, True, True),
                                       (1, 64, 126, 69, 77, True, True), (1, 64, 244, 544, 392, True, True), (1, 640, 512, 415, 473, False, False), (1, 64, 256, 829, 778, False, False),
-                                      (1, 384, 768, 157, 189, False, True), (1, 640, 512, 233, 302, False, True), (1, 640, 512, 416, 473, False, True)]:
+                                      (1, 384, 768, 157, 189, False, True), (1, 640, 512, 233, 302, False, True), (1, 384, 512, 416, 473, False, True), (1, 512, 512, 512, 512, True, False), (1, 512, 512, 512, 512, False, False),
+                                      (1, 512, 512, 256, 256, False, True), (1, 512, 1024, 256, 256, True, False), (1, 384, 256, 512, 512, True, True), (1, 640, 768, 128, 752, True, True), (1, 512, 516, 512, 512, True, True)]:
         assert (routes.block_plan(N, C, K, H, W, 1, 1, "bf16", nhwc)[0] >= 0) == here, (C, K)
 
 
