@@ -41,13 +41,16 @@ struct IgemmPost {
 
 // The 16x16-tile kernel (conv_igemm_tile.hip): two-byte storage types, Cp a whole number of 128-byte stages.
 // igemm_block_plan: its choice of block and of the number of reduction ranges, at most most_sp; id < 0: left to the kernels of conv_igemm.hip.
-// igemm_tile_plan: the number of ranges that a workspace is sized for (plain: nothing but a bias is added to the sums).
+// igemm_tile_ranges: the number of ranges that a workspace is sized for, 0: igemm_split_rule says.
 struct IgemmTilePlan { int id, split; };
 IgemmTilePlan igemm_block_plan(int T, int HoWo, int K, int Cp, int R, int dt, bool nhwc, int most_sp);
 double igemm_block_time(int id, int T, int HoWo, int K, int Cp, int R, bool nhwc, int split);      // the times it compares
 bool igemm_tile_fits(const ConvGeom& g);                               // the operands are small enough for the kernel's offsets
 int igemm_split_rule(int T, int K, int Cp, int R, int dt);             // ranges where the 16x16-tile kernel does not apply (conv_igemm.hip)
-IgemmTilePlan igemm_tile_plan(int T, int HoWo, int K, int Cp, int R, int dt, bool nhwc, bool plain);
+int igemm_tile_ranges(int T, int HoWo, int K, int Cp, int R, int dt, bool nhwc);
+// The blocks of conv_igemm.hip, pixels x output channels.
+struct IgemmShape { int tp, tk; };
+IgemmShape igemm_shape(int T, int K);
 hipError_t launch_igemm_tile(const void* xh, const void* Wr, const float* bias, void* y, float* part, const IgemmTilePlan& plan,
                              const ConvGeom& g, const IgemmPost& post, int dt, bool nhwc, hipStream_t s);
 

@@ -435,11 +435,11 @@ static hipError_t launch_igemm_cfg(const E* xh, const E* Wr, const float* bias, 
 
 // Block shape as (pixels x output channels).  The stage is bound by what a compute unit can pull from L2
 // into LDS (26-37 bytes per clock measured), so the block with the fewest operand bytes per flop that
-// still fills the chip wins: 256x256 (16 waves; 1.0 PFLOP/s on 512 channels at 256x256) when K is a
-// multiple of 256, 256x128 (8 waves) when K is a multiple of 128, each while >= 256 blocks remain;
-// then 128x128 while >= 256 blocks remain, else 64x64.
-struct IgemmShape { int tp, tk; };
-static IgemmShape igemm_shape(int T, int K) {
+// still fills the chip wins: 256x256 (16 waves) when K is a multiple of 256, 256x128 (8 waves) when K is a
+// multiple of 128, each while >= 256 blocks remain; then 128x128 while >= 256 blocks remain, else 64x64.
+// Two-byte calls with whole stages come here only for full rounds of 256x256 blocks in 1x1 reductions and for
+// outputs that are stored one by one (igemm_block_plan).
+IgemmShape igemm_shape(int T, int K) {
     static const IgemmShape menu[5] = {{128, 128}, {64, 64}, {256, 256}, {256, 128}, {128, 256}};
     auto blocks = [&](int tp, int tk) { return (long long)((T + tp - 1) / tp) * ((K + tk - 1) / tk); };
     if (K % 256 == 0 && blocks(256, 256) >= 256) return menu[2];
@@ -470,8 +470,8 @@ int igemm_split_rule(int T, int K, int Cp, int R, int dt) {
 }
 int igemm_split(int T, int HoWo, int K, int Cp, int R, int dt, bool nhwc) {
     if (dt >= 0) {
-        const IgemmTilePlan plan = igemm_tile_plan(T, HoWo, K, Cp, R, dt, nhwc, true);
-        if (plan.id >= 0) return plan.split;
+        const int ranges = igemm_tile_ranges(T, HoWo, K, Cp, R, dt, nhwc);
+        if (ranges > 0) return ranges;
     }
     return igemm_split_rule(T, K, Cp, R, dt);
 }

@@ -404,26 +404,24 @@ IgemmTilePlan igemm_block_plan(int T, int HoWo, int K, int Cp, int R, int dt, bo
     return best;
 }
 
-// Reduction ranges that a call's workspace is sized for: the choice of an earlier set of blocks of 64x64, 64x80 and 128x128 (id 0, 1 and 2; id < 0: the
-// kernels of conv_igemm.hip), with their stage times (us; `alone`: one workgroup to a compute unit, `each`: several, `ends`: a workgroup's start
-// and stores).  Programs keep workspaces, and what fits the library's static scratch fits it, so this rule stays what it was whatever
-// block runs a call; igemm_block_plan never takes more ranges than it grants.
+// Reduction ranges that a call's workspace is sized for; 0: igemm_split_rule says.  The choice of an earlier set of blocks, 64x64, 64x80 and 128x128, with their
+// stage times (us; `alone`: one workgroup to a compute unit, `each`: several, `ends`: a workgroup's start and stores).  Programs keep workspaces,
+// and what fits the library's static scratch fits it, so this rule stays what it was whatever block runs a call; igemm_block_plan
+// never takes more ranges than it grants.
 struct RangeShape { int bp, bk; double alone, each, ends; };
 static const RangeShape kRangeTiles[3] = {{64, 64, 0.27, 0.20, 1.3}, {64, 80, 0.35, 0.295, 1.6}, {128, 128, 0.65, 0.57, 4.6}};
-IgemmTilePlan igemm_tile_plan(int T, int HoWo, int K, int Cp, int R, int dt, bool nhwc, bool plain) {
-    IgemmTilePlan best{-1, 1};
-    if (!(dt == DT_F16 || dt == DT_BF16) || Cp % 64 != 0) return best;
+int igemm_tile_ranges(int T, int HoWo, int K, int Cp, int R, int dt, bool nhwc) {
+    if (!(dt == DT_F16 || dt == DT_BF16) || Cp % 64 != 0) return 0;
     const int stages = R * R * (Cp / 64);
     const long long wide_blocks = (long long)((T + 255) / 256) * (K / 256);
-    if (plain && K % 256 == 0 && wide_blocks >= 256) {      // one of them, or one of its 128x128 quarters, to a compute unit (us)
+    if (K % 256 == 0 && wide_blocks >= 256) {               // a round of the 256x256 block of conv_igemm.hip, or of its 128x128 quarters (us)
         const double share = (double)wide_blocks / 256.0, rounds = 0.4 * share + 0.6 * (double)((wide_blocks + 255) / 256);
         const long long small = (long long)((T + 127) / 128) * (K / 128);
         const double quarters = 0.5 * ((double)small / 256.0 + (double)((small + 255) / 256));
-        if (rounds * (15.5 + 1.9 * stages) <= quarters * (nhwc ? 6.3 + 0.4425 * stages : 5.0 + 0.4525 * stages)) return best;
+        if (rounds * (15.5 + 1.9 * stages) <= quarters * (nhwc ? 6.3 + 0.4425 * stages : 5.0 + 0.4525 * stages)) return 0;
     }
-    // never more ranges than the other kernel takes: the workspace of a call, and with it what fits the library's static scratch, stays
-    // what it is there
-    const int most_sp = igemm_split_rule(T, K, Cp, R, dt);
+    const int most_sp = igemm_split_rule(T, K, Cp, R, dt);  // never more ranges than the other kernel takes
+    int best = 0, ranges = 1;
     double cost = 1e300;
     for (int id = 0; id < 3; ++id) {
         const RangeShape& sh = kRangeTiles[id];
@@ -434,19 +432,17 @@ IgemmTilePlan igemm_tile_plan(int T, int HoWo, int K, int Cp, int R, int dt, boo
             const double stage = n * sh.each > sh.alone ? n * sh.each : sh.alone;
             double c = 6.0 + (double)((stages + sp - 1) / sp) * stage + (n > 1.0 ? 0.3 + 0.7 * n : 1.0) * sh.ends;
             if (sp > 1) c += 1.5 + (double)sp * K * T * 8.0 / 3e6;
-            if (c < cost) { cost = c; best = {id, sp}; }
+            if (c < cost) { cost = c; best = id; ranges = sp; }
         }
     }
-    // NCHW images that are no multiple of four pixels are stored one by one or in pairs, 16 lanes to 32 bytes, where the other kernel's
-    // 32x32 tiles make runs of 64; with a short reduction that costs more than the stages gain, most of all with the 128x128 block
-    if (plain && !nhwc && HoWo % 4 != 0) {
+    // outputs stored one by one or in pairs, where that set left short reductions and the 128x128 block to the other kernel
+    if (!nhwc && HoWo % 4 != 0) {
         const long long blocks2 = (long long)((T + 127) / 128) * ((K + 127) / 128);
-        if (HoWo % 2 != 0 && stages <= 2) return {-1, 1};
-        if (best.id == 2 && ((blocks2 < 256 && stages <= 32) || (HoWo % 2 != 0 && stages <= 8))) return {-1, 1};
+        if (HoWo % 2 != 0 && stages <= 2) return 0;
+        if (best == 2 && ((blocks2 < 256 && stages <= 32) || (HoWo % 2 != 0 && stages <= 8))) return 0;
     }
-    // channel-last, a number of channels that is no multiple of four: 16 lanes to as many lines (63 -> 799 1x1 at 249x7, N=8, 54 / 33)
-    if (nhwc && K % 4 != 0 && K >= 64 && best.split == 1) return {-1, 1};
-    return best;
+    if (nhwc && K % 4 != 0 && K >= 64 && ranges == 1) return 0;
+    return ranges;
 }
 
 template <typename E, bool PIX_A>

@@ -94,11 +94,9 @@ def fp8_rows(N, C, K, H, W, dtype, nhwc, nsplit=1, **kw):
     return taken, taken and not nhwc and H * W % 2 == 0 and wide(ctypes.byref(g))
 
 
-def igemm_tile(N, C, K, H, W, R, st, dtype, nhwc, plain=True):
-    """(block id, reduction ranges) of the 16x16-tile kernel: 0 = 64x64, 1 = 64x80, 2 = 128x128; id < 0: the kernels of conv_igemm.hip."""
-    f = _fn("_ZN4wino15igemm_tile_planEiiiiiibb", Pair, INT, INT, INT, INT, INT, INT, BOOL, BOOL)
-    pixels = _out(H, R, st) * _out(W, R, st)
-    p = f(N * pixels, pixels, K, -(-C // 8) * 8, R, DT[dtype], nhwc, plain)
+def igemm_shape(pixels, K):
+    """Block (pixels, output channels) of conv_igemm.hip."""
+    p = _fn("_ZN4wino11igemm_shapeEii", Pair, INT, INT)(pixels, K)
     return p.a, p.b
 
 

@@ -1,6 +1,7 @@
 """Parity of the implicit-GEMM convolution path (1x1, 3x3 stride 2, 3x3 stride 1) against the fp64 oracle:
 relative L2 <= 1e-5 for fp32 storage, <= 5e-3 for fp16 storage with fp32 accumulation (the path rounds only its
 output, so it sits far below that)."""
+import functools
 import os
 import sys
 
@@ -93,22 +94,29 @@ def test_igemm_split_reduction(dtype, shape, R, stride, layout):
     assert err <= (6e-4 if dtype == "f16" else 1e-5), (shape, R, stride, layout, dtype, err)
 
 
-# Cp a whole number of 64-channel stages (the 16x16-tile kernel): each of its blocks (0: 64x64, 1: 64x80, 2: 128x128) with a single stage and
-# with several, tails in pixels and channels, split reductions, outputs with 4k, 2k and an odd number of pixels; where the layouts go
-# different ways, and shapes left to the other kernels (-1), in a pair (NCHW, channel-last)
+@functools.lru_cache(maxsize=2)                     # both layouts, either type
+def _with_reference(shape, R, stride, dtype):
+    x, w, b = _inputs(*shape, R, dtype, seed=8800 + sum(shape))
+    return x, w, b, oracle.conv2d_general(_np(x), _np(w), _np(b), stride)
+
+
+# Cp a whole number of 64-channel stages (the 16x16-tile kernel): its blocks (0: 64x64, 1: 128x64, 3: 128x96 with three slots, 4: 128x128, 5: 64x32, 6: 64x80)
+# with a single stage and with several, tails in pixels and channels, split reductions, outputs with 4k, 2k and an odd number of pixels; where the
+# layouts go different ways, and calls left to the other kernels (-1), in a pair (NCHW, channel-last)
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("layout", [B.WINO_NCHW, B.WINO_NHWC])
-@pytest.mark.parametrize("shape,R,stride,block", [((1, 64, 16, 5, 5), 1, 1, (-1, 0)), ((2, 128, 70, 9, 10), 3, 1, (0, 0)), ((2, 192, 320, 64, 63), 1, 1, (1, 1)),
-                                                  ((2, 320, 320, 64, 64), 1, 1, (1, 1)), ((1, 64, 130, 190, 131), 3, 2, (0, -1)), ((1, 1280, 72, 9, 6), 3, 2, (0, 0)),
-                                                  ((1, 640, 33, 7, 9), 1, 2, (0, 0)), ((1, 64, 256, 256, 257), 1, 1, (0, -1)),
-                                                  ((2, 64, 240, 128, 126), 1, 1, (2, 2)), ((2, 192, 320, 128, 126), 3, 1, (2, 2)), ((2, 128, 400, 129, 127), 3, 1, (2, 2)),
-                                                  ((1, 64, 200, 128, 125), 3, 1, (2, 2)), ((2, 320, 320, 64, 64), 3, 1, (1, 1)), ((1, 64, 72, 101, 99), 3, 1, (1, 1)), ((1, 192, 72, 101, 99), 3, 1, (0, 0))])
+@pytest.mark.parametrize("shape,R,stride,block", [((1, 64, 16, 5, 5), 1, 1, (5, 5)), ((2, 128, 70, 9, 10), 3, 1, (0, 0)), ((2, 192, 320, 64, 63), 1, 1, (3, 3)),
+                                                  ((2, 320, 320, 64, 64), 1, 1, (3, 3)), ((1, 64, 130, 190, 131), 3, 2, (0, 0)), ((1, 1280, 72, 9, 6), 3, 2, (0, 0)),
+                                                  ((1, 640, 33, 7, 9), 1, 2, (5, 5)), ((1, 64, 256, 256, 257), 1, 1, (4, 4)),
+                                                  ((2, 64, 240, 128, 126), 1, 1, (4, 4)), ((2, 192, 320, 128, 126), 3, 1, (1, 1)), ((2, 128, 400, 129, 127), 3, 1, (4, 4)),
+                                                  ((1, 64, 200, 128, 125), 3, 1, (1, 1)), ((2, 320, 320, 64, 64), 3, 1, (3, 3)), ((1, 64, 72, 101, 99), 3, 1, (0, 6)), ((1, 192, 72, 101, 99), 3, 1, (6, 6)),
+                                                  # channel-last and stored one by one: 64x64 and 128x128 blocks of 32x32 tiles
+                                                  ((2, 64, 423, 64, 45), 1, 1, (2, -1)), ((1, 128, 321, 154, 120), 1, 1, (4, -1)),
+                                                  # full rounds of 256x256 blocks: an odd number of pixels, pairs, whole pieces
+                                                  ((1, 64, 512, 245, 203), 1, 1, (-1, 4)), ((1, 64, 1024, 310, 187), 1, 1, (-1, 4)), ((1, 448, 512, 250, 246), 1, 1, (4, -1))])
 def test_igemm_tile_kernel(shape, R, stride, block, layout, dtype):
-    nhwc = layout == B.WINO_NHWC
-    assert routes.igemm_tile(*shape, R, stride, dtype, nhwc)[0] == block[nhwc]
-    N, C, K, H, W = shape
-    x, w, b = _inputs(N, C, K, H, W, R, dtype, seed=8800 + sum(shape))
-    ref = oracle.conv2d_general(_np(x), _np(w), _np(b), stride)
+    assert routes.block_plan(*shape, R, stride, dtype, layout == B.WINO_NHWC)[0] == block[layout == B.WINO_NHWC]
+    x, w, b, ref = _with_reference(shape, R, stride, dtype)
     xd = (x.permute(0, 2, 3, 1).contiguous() if layout == B.WINO_NHWC else x).to(DEV)
     y = B.conv2d_igemm(xd, w.to(DEV), b.to(DEV), stride, layout)
     torch.cuda.synchronize()
@@ -117,6 +125,21 @@ def test_igemm_tile_kernel(shape, R, stride, block, layout, dtype):
     # only the output is rounded: element-wise half a unit in the last place, plus fp32 sums of up to 11520 products
     half_ulp = 2.0 ** -11 if dtype == "f16" else 2.0 ** -8
     assert np.all(np.abs(y - ref) <= 1.001 * half_ulp * np.abs(ref) + 3e-5), np.abs(y - ref).max()
+
+
+# two-byte types, stages that are not whole: the 256-wide blocks of conv_igemm.hip, with the tails of a last block
+@pytest.mark.parametrize("layout", [B.WINO_NCHW, B.WINO_NHWC])
+@pytest.mark.parametrize("shape,block", [((1, 24, 256, 257, 256), (256, 256)), ((1, 40, 128, 256, 257), (256, 128))])
+def test_igemm_wide_blocks(shape, block, layout):
+    N, C, K, H, W = shape
+    assert routes.igemm_shape(N * H * W, K) == block and routes.block_plan(*shape, 3, 1, "f16", layout == B.WINO_NHWC)[0] < 0
+    x, w, b = _inputs(N, C, K, H, W, 3, "f16", seed=8900 + sum(shape))
+    ref = oracle.conv2d_general(_np(x), _np(w), _np(b), 1)
+    y = B.conv2d_igemm((x.permute(0, 2, 3, 1).contiguous() if layout == B.WINO_NHWC else x).to(DEV), w.to(DEV), b.to(DEV), 1, layout)
+    torch.cuda.synchronize()
+    y = y.float().cpu()
+    y = (y.permute(0, 3, 1, 2) if layout == B.WINO_NHWC else y).numpy().astype(np.float64)
+    assert np.all(np.abs(y - ref) <= 1.001 * 2.0 ** -11 * np.abs(ref) + 3e-5), np.abs(y - ref).max()
 
 
 def test_igemm_matches_winograd_and_direct_kernels():

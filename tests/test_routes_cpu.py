@@ -8,40 +8,35 @@ sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 import routes  # noqa: E402
 
 
-# direct path, channel counts that 256-wide blocks divide, one or more full rounds of 256x256 blocks: their kernel, up to the number of
-# stages (of 64 channels, per tap) from which smaller blocks are level
-@pytest.mark.parametrize("N,C,K,H,W,R,st,nhwc,wide", [
-    (1, 128, 512, 256, 256, 1, 1, True, True), (1, 512, 1024, 256, 256, 1, 1, True, True), (1, 128, 1024, 128, 128, 3, 1, True, True), (1, 256, 512, 512, 512, 3, 2, True, True), (1, 256, 512, 240, 240, 3, 1, True, True),
-    (1, 256, 256, 512, 512, 3, 1, True, True), (1, 256, 256, 512, 512, 1, 1, True, True), (1, 1024, 1024, 128, 128, 3, 1, True, False),
-    (1, 256, 240, 512, 512, 3, 1, True, False), (1, 256, 264, 512, 512, 1, 1, True, False), (1, 256, 256, 240, 240, 3, 1, True, False), (1, 512, 512, 180, 180, 3, 1, True, False),
-    (1, 1024, 768, 180, 180, 3, 1, True, False), (1, 128, 768, 180, 180, 1, 1, True, True),
-    (1, 64, 256, 256, 256, 3, 1, False, True), (1, 64, 1024, 180, 180, 3, 1, False, True), (1, 320, 1024, 256, 256, 1, 1, False, True), (1, 1024, 512, 256, 256, 1, 1, False, True),
-    (1, 1024, 1024, 128, 128, 3, 1, False, False), (1, 64, 512, 180, 180, 3, 1, False, False), (1, 320, 320, 256, 256, 1, 1, False, False)])
+# direct path, two-byte types and whole stages: the block, channel-last and NCHW alike, at sizes where the blocks were timed against each other
+@pytest.mark.parametrize("N,C,K,H,W,R,st,block", [
+    (1, 128, 512, 256, 256, 1, 1, 4), (1, 256, 512, 512, 512, 3, 2, 4), (1, 256, 512, 240, 240, 3, 1, 4), (1, 256, 256, 512, 512, 3, 1, 4), (1, 256, 240, 512, 512, 3, 1, 4),
+    (1, 512, 512, 256, 256, 3, 1, 4), (1, 128, 128, 1024, 1024, 3, 1, 4), (2, 128, 400, 129, 127, 3, 1, 4), (1, 512, 512, 128, 128, 3, 1, 4), (1, 64, 512, 180, 180, 3, 1, 4),
+    (1, 256, 264, 512, 512, 1, 1, 2), (1, 512, 512, 99, 101, 3, 1, 2), (2, 256, 560, 144, 51, 1, 1, 2), (2, 640, 640, 64, 64, 3, 1, 2), (2, 1280, 640, 64, 64, 1, 1, 2),
+    (2, 320, 320, 64, 64, 3, 1, 3), (2, 320, 320, 64, 64, 1, 1, 3), (2, 960, 320, 64, 64, 1, 1, 3),
+    (2, 1856, 1184, 23, 57, 1, 1, 1), (1, 64, 256, 251, 250, 3, 2, 1), (2, 320, 320, 97, 121, 3, 1, 1), (2, 320, 320, 97, 121, 1, 1, 1), (8, 128, 128, 76, 212, 1, 2, 1),
+    (2, 320, 320, 64, 64, 3, 2, 0), (1, 384, 48, 315, 249, 3, 1, 0), (1, 512, 64, 330, 354, 3, 1, 0), (1, 128, 384, 7, 215, 1, 1, 0), (1, 64, 16, 5, 5, 1, 1, 5), (1, 128, 24, 130, 127, 3, 1, 5)])
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
-def test_direct_path_wide_blocks(N, C, K, H, W, R, st, nhwc, wide, dtype):
-    assert (routes.igemm_tile(N, C, K, H, W, R, st, dtype, nhwc)[0] < 0) == wide
-    plan = routes.igemm_tile(N, C, K, H, W, R, st, dtype, nhwc, plain=False)           # a residual or a vector: never
-    assert plan[0] >= 0 and (not wide or plan[1] == 1)
+def test_direct_path_blocks(N, C, K, H, W, R, st, block, dtype):
+    for nhwc in (False, True):
+        assert routes.block_plan(N, C, K, H, W, R, st, dtype, nhwc) == (block, 1)
+        assert routes.block_plan(N, C, K, H, W, R, st, "f32", nhwc)[0] < 0 and routes.block_plan(N, C - 8, K, H, W, R, st, dtype, nhwc)[0] < (0 if C % 64 == 0 else 6)
 
 
-# ... NCHW images of an odd number of pixels, or of pairs: the older kernel where the 128x128 block would meet a short reduction
-@pytest.mark.parametrize("N,C,K,H,W,R,st,old", [
-    (1, 256, 256, 181, 181, 1, 1, True), (1, 128, 128, 301, 299, 1, 1, True), (2, 1856, 1184, 23, 57, 1, 1, True), (1, 64, 256, 251, 250, 3, 2, True),
-    (3, 64, 640, 33, 35, 1, 1, True), (1, 128, 384, 7, 215, 1, 1, True), (1, 256, 256, 181, 181, 3, 1, False), (2, 320, 320, 97, 121, 1, 1, False), (2, 320, 320, 97, 121, 3, 1, False), (1, 64, 256, 251, 250, 1, 1, False), (1, 256, 256, 180, 181, 1, 1, False),
-    (1, 512, 512, 99, 101, 3, 1, False), (1, 192, 320, 311, 201, 1, 1, False)])
-def test_direct_path_odd_images(N, C, K, H, W, R, st, old):
+# few pixels and a long reduction: ranges, never more than the workspace of either layout holds
+@pytest.mark.parametrize("N,C,K,H,W,R,st,ranges", [(2, 640, 640, 32, 32, 3, 2, 3), (2, 1280, 1280, 16, 16, 3, 2, 6), (1, 1280, 72, 9, 6, 3, 2, 15), (2, 128, 128, 17, 13, 3, 1, 2), (2, 64, 128, 17, 13, 3, 1, 1)])
+def test_direct_path_workspace_ranges(N, C, K, H, W, R, st, ranges):
     for dtype in ("f16", "bf16"):
-        assert (routes.igemm_tile(N, C, K, H, W, R, st, dtype, False)[0] < 0) == old
-        assert routes.igemm_tile(N, C, K, H, W, R, st, dtype, True)[0] >= 0 and routes.igemm_tile(N, C, K, H, W, R, st, dtype, False, plain=False)[0] >= 0
+        assert max(routes.igemm_split(N, C, K, H, W, R, st, dtype, nhwc) for nhwc in (False, True)) == ranges
+        assert all(1 <= routes.block_plan(N, C, K, H, W, R, st, dtype, nhwc)[1] <= ranges for nhwc in (False, True))
 
 
-def test_direct_path_blocks_of_short_reductions():
-    """64x64 where start and stores of the larger block outweigh its stages; two ranges from 16 stages on for tiny images; channel-last with
-    channels that are no multiple of four left to the older kernel."""
-    assert routes.igemm_tile(2, 256, 560, 144, 51, 1, 1, "f16", True) == (0, 1) and routes.igemm_tile(8, 128, 128, 76, 212, 1, 2, "f16", True)[0] == 0
-    assert routes.igemm_tile(2, 512, 512, 256, 256, 3, 1, "f16", False) == (2, 1) and routes.igemm_tile(2, 320, 320, 128, 128, 3, 1, "f16", True)[0] == 2
-    assert routes.igemm_tile(2, 128, 128, 17, 13, 3, 1, "f16", False)[1] == 2 and routes.igemm_tile(2, 64, 128, 17, 13, 3, 1, "f16", False)[1] == 1
-    assert routes.igemm_tile(8, 63, 799, 249, 7, 1, 1, "bf16", True)[0] < 0 and routes.igemm_tile(8, 63, 3, 249, 7, 1, 1, "bf16", True)[0] >= 0
+# the blocks of conv_igemm.hip: what does not come in whole stages, and what is left to them
+@pytest.mark.parametrize("N,C,K,H,W,R,st,shape", [(1, 24, 256, 256, 256, 3, 1, (256, 256)), (1, 24, 128, 256, 256, 3, 1, (256, 128)), (1, 24, 72, 256, 256, 3, 1, (128, 128)), (1, 24, 72, 64, 64, 3, 1, (64, 64)),
+                                                 (1, 512, 512, 512, 512, 1, 1, (256, 256))])
+def test_direct_path_blocks_of_the_other_kernel(N, C, K, H, W, R, st, shape):
+    assert routes.igemm_shape(N * H * W, K) == shape
+    assert all(routes.block_plan(N, C, K, H, W, R, st, dtype, nhwc)[0] < 0 for dtype in ("f16", "bf16") for nhwc in (False, True))
 
 
 # Times by which the direct path's blocks are compared: times, so positive, and longer for more pixels, more channels and more stages; a block of which
