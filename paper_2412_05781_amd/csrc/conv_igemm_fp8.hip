@@ -5,7 +5,7 @@
 // and multiplies them when the last has arrived; here the fragments of a step are requested one step ahead, across the barrier, and the
 // stage after next is requested in the middle of a stage.  The 256x256 block has eight waves of 64x128 instead of sixteen of 64x64: LDS
 // feeds a 64x64 piece at exactly the rate at which it is multiplied, and the transfers into LDS come on top; a 64x128 piece needs 3/4
-// of that.  256 channels at 512x512: 208 -> 162 us (1.9 PFLOP/s), four rounds of workgroups of 18 stages.  About 30 us of it are start and
+// of that.  256 channels at 512x512, a call that the kernel for 3x3 further down takes now: 208 -> 162 us (1.9 PFLOP/s), four rounds of workgroups of 18 stages.  About 30 us of it are start and
 // stores, which one workgroup to a unit does not overlap (1x1: 41 us with one stage, 10 more for each further one of the four rounds), the
 // rest 1.8 us a stage; a further stage of a long reduction costs 1.4 (1024 channels: 288 stages in 501 us).  Its products alone take 0.85.
 //
@@ -286,6 +286,8 @@ conv_igemm_fp8_kernel(const uint8_t* __restrict__ xq, const uint8_t* __restrict_
 // neighbours, in the order of the image - are fetched once per 128 channels and a lane's fragments of tap s are rows s further on; a tap that
 // lies beyond the left or right edge reads a row of zeros instead (rows above and below the image arrive as zeros).  A stage, one tap, then
 // moves BK rows of the filter and a third of BP + 8 rows of pixels into LDS instead of BK + BP, and the pixels have three stages to arrive.
+// The 256x256 block gains little by that: 256 channels at 512x512, in turn in one run, us with random bytes / with zeros for x (which leave the clock
+// higher): the kernel above 162.7 / 146.1, here 161.6 / 148.1, 128x128 blocks 157.2 / 137.9; its products alone would take 62.
 template <typename EO, int BP, int BK, int WP, int WK, bool PIX_A, bool RAGGED>
 __global__ void __launch_bounds__(WP * WK * 64)
 conv_rows_fp8_kernel(const uint8_t* __restrict__ xq, const uint8_t* __restrict__ Wq, const float* __restrict__ bias, EO* __restrict__ y,
@@ -534,7 +536,7 @@ static hipError_t launch_fp8_cfg(const uint8_t* xq, const uint8_t* Wq, const flo
 }
 
 // Blocks: 256x256 where there is a round of them and K is a whole number, else 128x128 with two workgroups to a compute unit (a whole
-// call, NCHW, us, 128x128 / 256x256: 256 channels at 512x512 239 / 222, 512 at 256x256 172 / 151, but 512 at 128x128 46 / 59, 128 at
+// call of 3x3, also of those that the kernel above takes now, NCHW, us, 128x128 / 256x256: 256 channels at 512x512 239 / 222, 512 at 256x256 172 / 151, but 512 at 128x128 46 / 59, 128 at
 // 512x512 86 / 113).
 static bool fp8_wide(const ConvGeom& g) { return g.K % 256 == 0 && (long long)((g.T + 255) / 256) * (g.K / 256) >= 256; }
 
@@ -633,7 +635,7 @@ hipError_t launch_igemm_fp8_rows(const void* xq, const void* Wq, const float* bi
 // registers, any number (channel-last 1x1 64 -> 128 at 32x32 11.3 / 8.5, 3x3 256 -> 256 at 64x64 23.7 / 18.1, 640 -> 640 at 64x64 40.9 / 38.3,
 // but 256 -> 256 at 128x128 27.9 / 34.5; NCHW 3x3 256 -> 256 at 64x64 20.1 / 18.2, 1280 -> 320 at 64x64 61.2 / 57.7, but 256 -> 256 at 96x96
 // 22.0 / 24.5, 64 -> 256 at 64x64 15.7 / 17.4, 320 -> 320 25.5 / 28.0, 1x1 1280 -> 128 15.9 / 16.6; at 15x12 128 -> 1024 11.3 / 9.7; 3x3 128 ->
-// 8 at 91x152, stride 2, 16.1 / 14.0).  Everything else is faster here (256 channels at 512x512 270 / 222, 512 at 256x256 187 / 151, 128 at
+// 8 at 91x152, stride 2, 16.1 / 14.0).  Everything else is faster here (measured on 3x3 calls, most of which igemm_fp8_rows_ok takes first now: 256 channels at 512x512 270 / 222, 512 at 256x256 187 / 151, 128 at
 // 512x512 135 / 86, at 1024x1024 channel-last 456 / 353, 192 -> 320 at 312x200 124 / 73, 64 -> 16 at 118x131, N=8, 63 / 48, there / here).
 bool igemm_fp8_tile_ok(const ConvGeom& g, int dt, bool nhwc, int nsplit) {
     if (!two_byte(dt) || nsplit != 1 || (size_t)256 * g.Cp >= ((size_t)1 << 31)) return false;       // 32-bit lane offsets

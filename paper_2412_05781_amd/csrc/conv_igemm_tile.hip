@@ -115,7 +115,7 @@ conv_igemm_tile_kernel(const E* __restrict__ xh, const E* __restrict__ Wr, const
             for (int i = 0; i < PL; ++i) poff[i] = (inside[i] >> itap) & 1u ? pbase[i] : kOutside;
         } else {
 #pragma unroll
-            for (int i = 0; i < PL; ++i) {                  // the stored row and column move with every other tap
+            for (int i = 0; i < PL; ++i) {                  // the stored row and column move with every other tap (3x3: nothing else is read upsampled)
                 const int dr = ((int)(inside[i] >> 16 & 1u) + r + 1) >> 1, dc = ((int)(inside[i] >> 17 & 1u) + s + 1) >> 1;
                 poff[i] = (inside[i] >> itap) & 1u ? pbase[i] + (uint32_t)(dr * g.Ws + dc) * row_bytes : kOutside;
             }

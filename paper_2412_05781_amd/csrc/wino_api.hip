@@ -177,8 +177,8 @@ int wino_resolve_variant(int N, int C, int H, int W, int K, int dtype, int varia
     // The fused variants (steps (ii) and (iii) in one kernel) where they measured faster with 2-byte storage.  F(2x2): against
     // the F(2x2) chain from 4096 tiles on (128x128 images at batch 2 and everything larger: 0.6-0.9x the time; where F(2x2) in one kernel is
     // the faster one, either variant runs that).  F(4x4): against the F(4x4) chain from 4096 tiles on, with at most 512 channels and
-    // enough 64x64 blocks for two rounds of workgroups (512 channels at 256x256: 0.97x, 256 at 512x512: 0.83x, 128 at 1024x1024:
-    // 0.66x; with fewer tiles 1.2-2.2x slower).  128 channels at 1024x1024 take 522, channel-last 400 us as F(2x2) in one kernel, 525 and 491 here.
+    // enough 64x64 blocks for two rounds of workgroups (512 channels at 256x256: 0.93x, 256 at 512x512: 0.82x, 128 at 1024x1024:
+    // 0.65x; with fewer tiles 1.04-2.1x slower).  128 channels at 1024x1024 take 524, channel-last 394 us as F(2x2) in one kernel, 515 and 483 here.
     const Geom g2 = make_geom(N, C, H, W, K, 2);
     if (dtype != WINO_F32 && K >= 32) {
         if (pick == WINO_F2 && g2.T >= 4096) pick = WINO_FUSED_F2;
@@ -193,18 +193,18 @@ int wino_recommend_variant(int N, int C, int H, int W, int K, int dtype) {
     if (v < 0 || !igemm_dims_ok(N, C, H, W, K, 3, 1)) return v;
     // Measured on the VAE-sized layers: with few channels and many pixels the Winograd path is bound by the
     // traffic of V and M (about 27 bytes per output pixel and channel for F(4x4), 48 for F(2x2)), the direct
-    // path by its 18*C*K flops per pixel at 0.6-1.0 PFLOP/s.  256 channels at 512x512 as an F(4x4) chain 399 / 397 us (NCHW / NHWC),
-    // direct 396 / 342; 512 channels at 256x256 248 / 255 and 328 / 309.  The crossing is put at sqrt(C*K) = 320 against F(4x4) and 448
-    // against F(2x2), which was set when F(2x2) always stored V (256 channels at 512x512: 650-690 us, 354-384 now).
+    // path by its 18*C*K flops per pixel at 0.6-1.0 PFLOP/s.  256 channels at 512x512 as an F(4x4) chain 399 / 403 us (NCHW / NHWC),
+    // direct 356 / 312; 512 channels at 256x256 257 / 256 and 319 / 295.  The crossing was put at sqrt(C*K) = 320 against F(4x4) and 448
+    // against F(2x2) when the direct path took 396 / 342 and 328 / 309 there and F(2x2) always stored V (256 channels at 512x512: 650-690 us, 360-434
+    // now), and has not been drawn again.
     // A handful of output channels on a large image (the VAE's 128 -> 3 at 1024 x 1024): the Winograd path would write and
     // re-read a transformed activation tensor far larger than x; the direct path has a one-pass kernel for it (fp16, at
     // least 512 tiles of 8 x 64 pixels; measured 130-160 us against 320-360 us for F(4x4))
     if (dtype == WINO_F16 && K <= 4 && C >= 16 && C % 16 == 0 && W % 8 == 0 &&
         (long long)N * ((H + 7) / 8) * ((W + 63) / 64) >= 512)
         return WINO_DIRECT;
-    // where WINO_AUTO takes the fused F(4x4) variant it is ahead of the direct path, but for 128 channels channel-last; the choice does not
-    // know the layout (NCHW / NHWC, us: 256 channels at 512x512 331 / 335 against 396 / 342; 128 at 1024x1024 522 / 490 against 547 / 460; 512
-    // at 256x256 219 / 222 against 328 / 309)
+    // where WINO_AUTO takes the fused F(4x4) variant (NCHW / NHWC, us, against the direct path: 512 at 256x256 226 / 224 against 319 / 295, 256 channels
+    // at 512x512 331 / 320 against 356 / 312, 128 at 1024x1024 516 / 473 against 493 / 359, where the direct path took 547 / 460 when this was chosen)
     if (v == WINO_FUSED_F4) return v;
     const long long pixels = (long long)N * H * W;
     const long long ck = (long long)C * K;
